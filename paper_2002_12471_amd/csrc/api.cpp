@@ -33,6 +33,14 @@ struct lmosem_ctx {
     // the path table (or near-field band), sensitivities and primary weights
     // are built at the first call that needs them (binned work does not)
     bool paths_ready = false;
+    // sub-iterations through directional flux (every exact-path context whose
+    // node counts, tables and workspace fit; the others run term by term)
+    bool flux = false, flux_fits = false;
+    FluxModel fg{};
+    FluxTables ft{};
+    std::vector<int> flux_order;   // the flux order's support indices
+    float *fws = nullptr;          // workspace of one realisation
+    size_t fws_floats = 0;
     // HIP graphs: one captured iteration per prepared set, replayed on an
     // internal stream ordered after the caller's stream by events
     bool graphs = true;
@@ -69,6 +77,16 @@ struct lmosem_evset {
     int use_graph = -1;       // autotuned choice (1 replay graphs, 0 launch directly), -1 = context setting
     float *col = nullptr;     // surrogate: per-sub-iteration event column features [max_rows][4] + ranks [max_rows][2]
     uint16_t *X = nullptr;    // surrogate: network inputs [pair_cap][8], bf16
+    bool flux = false;        // iterates through directional flux unless its rows are cached
+    bool tuned = false;       // autotuned; a later row cache tunes its own kernels too
+    float *fws = nullptr;     // flux workspace of the set (null: the context's)
+    size_t fws_floats = 0;
+    // per subset the angle list and the first row of each (realisation, angle)
+    // slot: [angles][first rows][first blocks][first slot of each subset] on the
+    // device, rows and blocks on the host too
+    int *lists = nullptr;
+    std::vector<int> list_off, slot_off, n_list, slot_rows, slot_blk;
+    int lists_rows = 0, lists_blk = 0;   // where rows and blocks begin in lists
     size_t pb_chunks = 0;     // chunk rows allocated in pb
     size_t pmean_groups = 0;  // pixel groups allocated in pmean
     int64_t bytes = 0;        // device bytes held by the set (counted in its context's set_bytes)
@@ -174,6 +192,7 @@ void free_set(lmosem_evset *s) {
     hipFree(s->s.crange); hipFree(s->s.rrange);
     hipFree(s->H); hipFree(s->Hc); hipFree(s->pmean); hipFree(s->mean); hipFree(s->inv); hipFree(s->pb); hipFree(s->f);
     hipFree(s->ll); hipFree(s->col); hipFree(s->X); hipFree(s->s.ang);
+    hipFree(s->s.fev); hipFree(s->s.fblk); hipFree(s->lists); hipFree(s->fws);
     delete s;
 }
 
@@ -187,29 +206,37 @@ int64_t set_device_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
     const int64_t n_chunks = std::max<int64_t>(v.chunk_off.empty() ? 1 : v.chunk_off.back(), 1);
     int64_t b = 20 * n + (int64_t)sizeof(Tile) * n_tiles + (int64_t)sizeof(Chunk) * n_chunks +
                 8 * (int64_t)g.n_subsets * (v.n_real + 1);
-    b += 4 * rows * g.n_qpad + 4 * rows * std::max<int64_t>((int64_t)s->pmean_groups, forward_groups(g)) + 8 * rows + 4 * chunks * g.n_qpad +
-         4 * (int64_t)v.n_real * g.n_qpad + 8 * (int64_t)v.n_real;
+    b += 8 * rows + 4 * (int64_t)v.n_real * g.n_qpad + 8 * (int64_t)v.n_real;
+    if (s->H) b += 4 * rows * g.n_qpad;
+    if (s->pmean) b += 4 * rows * std::max<int64_t>((int64_t)s->pmean_groups, forward_groups(g));
+    if (s->pb) b += 4 * chunks * g.n_qpad;
+    if (s->flux)
+        b += (int64_t)sizeof(FluxEvent) * n + 4 * (int64_t)s->fws_floats +
+             (int64_t)sizeof(FluxBlock) * (s->slot_blk.empty() ? 0 : s->slot_blk.back()) +
+             4 * (int64_t)(2 * s->slot_rows.size() + g.n_angles + s->n_list.size());
     if (c->surrogate) b += 24 * rows + 8 * 2 * kPairCap;
     if (s->Hc) b += 4 * n * g.n_qpad;
     return b;
 }
 
 // (Re)allocate the per-set workspace for the current tile plan.
-lmosem_status alloc_workspace(lmosem_ctx *c, lmosem_evset *s) {
+lmosem_status alloc_workspace(lmosem_ctx *c, lmosem_evset *s, bool for_rows = false) {
     const Geo g = set_geo(c, s);
     size_t rows = std::max(s->s.max_rows, 1), groups = forward_groups(g);
     size_t chunks = std::max(s->s.max_chunks, 1);
     hipError_t e;
+    // a flux set works without rows until they are cached (then in the cache)
+    const bool direct = !s->flux || for_rows;
 #define AL(p, bytes) do { if (!(p)) { e = hipMalloc(&(p), (bytes)); if (e != hipSuccess) return alloc_err(c, "workspace", e); } } while (0)
-    AL(s->H, sizeof(float) * rows * g.n_qpad);
+    if (direct) AL(s->H, sizeof(float) * rows * g.n_qpad);
     if (s->pmean && s->pmean_groups < groups) { hipFree(s->pmean); s->pmean = nullptr; }
     if (!s->pmean) s->pmean_groups = groups;
-    AL(s->pmean, sizeof(float) * rows * groups);
+    if (direct) AL(s->pmean, sizeof(float) * rows * groups);
     AL(s->mean, sizeof(float) * rows);
     AL(s->inv, sizeof(float) * rows);
     if (s->pb && s->pb_chunks < chunks) { hipFree(s->pb); s->pb = nullptr; }
     if (!s->pb) s->pb_chunks = chunks;
-    AL(s->pb, sizeof(float) * chunks * g.n_qpad);
+    if (direct) AL(s->pb, sizeof(float) * chunks * g.n_qpad);
     AL(s->f, sizeof(float) * (size_t)s->s.n_real * g.n_qpad);
     AL(s->ll, sizeof(double) * s->s.n_real);
     if (c->surrogate) {
@@ -232,8 +259,83 @@ std::string cap_msg(const lmosem_ctx *c, const char *what, int64_t more) {
            " device bytes, above its cap of " + std::to_string(c->mem_cap) + " (lmosem_set_memory_cap)";
 }
 
+// Whether a sub-iteration of so many terms runs faster through the flux
+// stages than term by term (8.6e12 terms/s and about 20 us of launches): the
+// stages' own time hardly depends on the events; measured 110 us on a support
+// of 156 pixels, 235 us on 1436, 880 us on 5736.  Without scatter they always
+// do (the term-by-term kernels visit every path end all the same).
+bool flux_pays(const Geo &g, int64_t terms) {
+    const double kpix = 1e-3 * g.n_p;
+    return !g.scatter || 20.0 + terms / 8.6e6 > 90.0 + 60.0 * kpix * sqrt(kpix);
+}
+
+// The angle lists, slots and event records of a flux set: all angles of each
+// subset, or (one given subset) the angles that have events; and the set's own
+// workspace, for sets that are kept or hold several realisations: what a whole
+// sub-iteration needs, as far as that takes no more than its system rows would.
+lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool kept) {
+    const Geo &g = c->g;
+    EvSet &v = s->s;
+    std::vector<int> angles;
+    s->list_off.assign(g.n_subsets, 0);
+    s->slot_off.assign(g.n_subsets, 0);
+    s->n_list.assign(g.n_subsets, 0);
+    s->slot_rows.clear();
+    s->slot_blk.clear();
+    int max_slots = 1, max_list = 1, row = 0, blk = 0;
+    for (int i = 0; i < g.n_subsets; ++i) {
+        s->list_off[i] = (int)angles.size();
+        s->slot_off[i] = (int)s->slot_rows.size();
+        if (force_subset >= 0 && i != force_subset) continue;
+        for (int a = 0; a < g.n_angles; ++a)
+            if (force_subset >= 0 ? v.counts[(size_t)i * v.n_real * g.n_angles + a] > 0 : a % g.n_subsets == i)
+                angles.push_back(a);
+        if ((int)angles.size() == s->list_off[i]) angles.push_back(0);   // no events: one angle, nothing in it
+        const int k = s->n_list[i] = (int)angles.size() - s->list_off[i];
+        max_list = std::max(max_list, k);
+        max_slots = std::max(max_slots, k * v.n_real);
+        for (int r = 0; r < v.n_real; ++r)
+            for (int l = 0; l < k; ++l) {
+                const int c = v.counts[((size_t)i * v.n_real + r) * g.n_angles + angles[s->list_off[i] + l]];
+                s->slot_rows.push_back(row);
+                s->slot_blk.push_back(blk);
+                row += c;
+                blk += (c + 63) / 64;
+            }
+    }
+    const int n_slots = (int)s->slot_rows.size(), na = (int)angles.size();
+    s->slot_rows.push_back(row);
+    s->slot_blk.push_back(blk);
+    s->lists_rows = na;
+    s->lists_blk = na + n_slots + 1;
+    std::vector<int> up(angles);
+    up.insert(up.end(), s->slot_rows.begin(), s->slot_rows.end());
+    up.insert(up.end(), s->slot_blk.begin(), s->slot_blk.end());
+    up.insert(up.end(), s->slot_off.begin(), s->slot_off.end());
+    hipError_t e = hipMalloc(&s->lists, sizeof(int) * up.size());
+    if (e == hipSuccess) e = hipMalloc(&v.fev, sizeof(FluxEvent) * (size_t)std::max<int64_t>(v.n, 1));
+    if (e == hipSuccess) e = hipMalloc(&v.fblk, sizeof(FluxBlock) * (size_t)std::max(blk, 1));
+    if (e == hipSuccess) e = hipMemcpyAsync(s->lists, up.data(), sizeof(int) * up.size(), hipMemcpyHostToDevice, c->st);
+    if (e == hipSuccess)
+        e = flux_events(g, c->fg, 0, blk, 0, s->lists + s->lists_rows, s->lists + s->lists_blk, n_slots,
+                        force_subset >= 0 ? nullptr : s->lists + s->lists_blk + n_slots + 1, v.ang, v.u, v.e, c->t, v.fev,
+                        v.fblk, c->st);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->st);
+    if (e != hipSuccess) return alloc_err(c, "event records", e);
+    if (!kept && v.n_real == 1) return LMOSEM_OK;
+    const size_t budget = (size_t)std::max(v.max_rows, 1) * g.n_qpad;
+    const size_t need = flux_ws_floats(g, c->fg, v.n_real, max_slots);
+    if (need > budget && budget <= c->fws_floats) return LMOSEM_OK;
+    const size_t floats = std::min(need, budget);
+    if (flux_group(g, c->fg, floats, v.n_real, max_list) < 1) return LMOSEM_OK;
+    e = hipMalloc(&s->fws, sizeof(float) * floats);
+    if (e != hipSuccess) return alloc_err(c, "workspace", e);
+    s->fws_floats = floats;
+    return LMOSEM_OK;
+}
+
 lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batch *batch, int force_subset,
-                       lmosem_evset **out) {
+                       lmosem_evset **out, bool kept = false) {
     lmosem_status st = LMOSEM_OK;
     if (c->surrogate && !c->net) return set_err(c, LMOSEM_ESTATE, "scatter_model 2 needs a network (lmosem_set_surrogate)");
     if (!check_events(c, ev, st)) return st;
@@ -257,7 +359,9 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
         free_set(s);
         return e == hipErrorOutOfMemory ? set_err(c, LMOSEM_ENOMEM, why) : set_err(c, LMOSEM_EDEVICE, why);
     }
-    lmosem_status ws = alloc_workspace(c, s);
+    s->flux = c->flux && flux_pays(c->g, *std::max_element(s->s.terms_sub.begin(), s->s.terms_sub.end()));
+    lmosem_status ws = s->flux ? plan_flux(c, s, force_subset, kept) : LMOSEM_OK;
+    if (ws == LMOSEM_OK) ws = alloc_workspace(c, s);
     if (ws != LMOSEM_OK) { free_set(s); return ws; }
     if (over_cap(c, 0)) {
         const std::string msg = cap_msg(c, "the event set", 0);
@@ -318,6 +422,37 @@ hipError_t drain_timing(lmosem_ctx *c) {
     return e;
 }
 
+// The flux stages of subset i: means alone, means and backprojection with
+// the update by sens, or (weights in s->inv) the backprojection alone.  first:
+// nothing of this set ran in the workspace just before.
+hipError_t flux_subset(lmosem_ctx *c, lmosem_evset *s, int i, bool first, bool means, bool adjoint, const float *sens,
+                       bool want_ll, hipStream_t st) {
+    const EvSet &v = s->s;
+    FluxRun p{};
+    p.g = &c->g; p.fg = &c->fg; p.ft = &c->ft; p.t = &c->t;
+    p.ws = s->fws ? s->fws : c->fws;
+    p.ws_floats = s->fws ? s->fws_floats : c->fws_floats;
+    p.alist = s->lists + s->list_off[i];
+    p.n_list = s->n_list[i];
+    p.n_real = v.n_real;
+    p.slot_rows = s->slot_rows.data() + s->slot_off[i];
+    p.blk_host = s->slot_blk.data() + s->slot_off[i];
+    p.blk_beg = s->lists + s->lists_blk + s->slot_off[i];
+    p.ev = v.fev;
+    p.blk = v.fblk;
+    p.row_base = v.row_off[i];
+    p.means = means;
+    p.box = first;
+    p.f = s->f; p.mean = s->mean; p.inv = s->inv;
+    p.skipped = c->skipped_dev;
+    p.sens = sens;
+    p.want_ll = want_ll;
+    p.rrange = v.rrange + (size_t)i * (v.n_real + 1);
+    p.ll = s->ll;
+    p.st = st;
+    return flux_run(p, adjoint, [&](int kind, const std::function<hipError_t()> &launch) { return timed(c, kind, launch, st); });
+}
+
 // System rows and partial means of subset i: exact forward projection, or
 // exact primaries plus the network's scatter term.
 hipError_t forward_rows(lmosem_ctx *c, lmosem_evset *s, int i, float *H, hipStream_t st) {
@@ -349,13 +484,14 @@ int mean_groups(const lmosem_ctx *c, const lmosem_evset *s) { return c->surrogat
 // One sub-iteration of Eq. 7 on all realisations of a prepared set: the
 // system rows are computed (and kept when the set caches them) or, once
 // cached, read back for the means.
-hipError_t subiteration(lmosem_ctx *c, lmosem_evset *s, int i, bool want_ll, hipStream_t st) {
+hipError_t subiteration(lmosem_ctx *c, lmosem_evset *s, int i, bool first, bool want_ll, hipStream_t st) {
     const Geo &g = c->g;
     const EvSet &v = s->s;
     const int rows = v.row_off[i + 1] - v.row_off[i];
     const int n_tiles = v.tile_off[i + 1] - v.tile_off[i];
     const int n_chunks = v.chunk_off[i + 1] - v.chunk_off[i];
     const bool cached = s->Hc && s->rows_valid;
+    if (s->flux && !s->Hc) return flux_subset(c, s, i, first, true, true, c->t.sens + (size_t)i * g.n_qpad, want_ll, st);
     const int groups = cached ? 1 : mean_groups(c, s);
     float *H = s->Hc ? s->Hc + (size_t)v.row_off[i] * g.n_qpad : s->H;
     const float *sens = c->t.sens + (size_t)i * g.n_qpad;
@@ -417,7 +553,7 @@ hipError_t capture_iteration(lmosem_ctx *c, lmosem_evset *s, bool want_ll) {
     if ((e = hipStreamBeginCapture(c->gst, hipStreamCaptureModeThreadLocal)) != hipSuccess) return e;
     hipError_t body = hipSuccess;
     if (want_ll) body = launch_fill_d(s->ll, s->s.n_real, 0.0, c->gst);
-    for (int i = 0; i < c->g.n_subsets && body == hipSuccess; ++i) body = subiteration(c, s, i, want_ll, c->gst);
+    for (int i = 0; i < c->g.n_subsets && body == hipSuccess; ++i) body = subiteration(c, s, i, i == 0, want_ll, c->gst);
     e = hipStreamEndCapture(c->gst, &graph);
     if (body != hipSuccess) { if (graph) hipGraphDestroy(graph); return body; }
     if (e != hipSuccess) return e;
@@ -440,7 +576,7 @@ hipError_t one_iteration(lmosem_ctx *c, lmosem_evset *s, bool want_ll) {
     if (!graph || c->timing) {
         if (want_ll && (e = launch_fill_d(s->ll, s->s.n_real, 0.0, c->st)) != hipSuccess) return e;
         for (int i = 0; i < c->g.n_subsets; ++i)
-            if ((e = subiteration(c, s, i, want_ll, c->st)) != hipSuccess) return e;
+            if ((e = subiteration(c, s, i, i == 0, want_ll, c->st)) != hipSuccess) return e;
     } else {
         const int k = (want_ll ? 1 : 0) + (cached ? 2 : 0);
         if (!s->exec[k] && (e = capture_iteration(c, s, want_ll)) != hipSuccess) return e;
@@ -511,6 +647,28 @@ lmosem_status ensure_paths(lmosem_ctx *c) {
         return set_err(c, LMOSEM_ENOMEM, msg);
     }
     c->table_bytes += bytes;
+    // the flux stages' tables and workspace; without room for them (in memory
+    // or under the cap) the context runs term by term
+    if (c->flux_fits) {
+        int64_t fb = 0;
+        hipError_t fe = build_flux(c->g, c->fg, c->flux_order, c->t, c->ft, c->st, fb);
+        if (fe == hipSuccess) {
+            // one realisation and a chunk of angles
+            c->fws_floats = flux_ws_floats(g, c->fg, 1, flux_angles(g, c->fg, g.n_angles));
+            fb += (int64_t)(sizeof(float) * c->fws_floats);
+            fe = over_cap(c, fb) ? hipErrorOutOfMemory : hipMalloc(&c->fws, sizeof(float) * c->fws_floats);
+        }
+        if (fe != hipSuccess && fe != hipErrorOutOfMemory) return dev_err(c, "flux tables", fe);
+        if (fe == hipSuccess) {
+            c->flux = true;
+            c->table_bytes += fb;
+        } else {
+            (void)hipGetLastError();
+            free_flux(c->ft);
+            c->fws = nullptr;
+            c->fws_floats = 0;
+        }
+    }
     c->table_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     c->paths_ready = true;
     return LMOSEM_OK;
@@ -591,6 +749,7 @@ lmosem_status lmosem_create_emission(const lmosem_config *cfg, const float *mu_d
     g.e_c = std::round(0.5 * (g.win_lo + g.win_hi) * 64.0) / 64.0;
     g.c2 = 1.0 / (2.0 * g.sig_e * g.sig_e * log(2.0));
     g.acq_time = cfg->acq_time;
+    c->flux_fits = !c->surrogate && flux_geometry(g, p_pix, c->fg, c->flux_order);
 
     std::vector<double> cs(2 * g.n_angles);
     for (int a = 0; a < g.n_angles; ++a) {
@@ -640,6 +799,7 @@ void lmosem_destroy(lmosem_ctx *c) {
     hipFree(c->t.T); hipFree(c->t.sens); hipFree(c->t.sens_all); hipFree(c->t.Ldet); hipFree(c->t.Lback);
     hipFree(c->t.prim); hipFree(c->t.band); hipFree(c->t.band_lo); hipFree(c->t.Ld); hipFree(c->t.Bt);
     hipFree(c->t.D_sorted); hipFree(c->bad_dev); hipFree(c->skipped_dev);
+    free_flux(c->ft); hipFree(c->fws);
     delete c;
 }
 
@@ -658,7 +818,7 @@ lmosem_status lmosem_events_load(lmosem_ctx *c, const lmosem_events *ev, const l
     PATHS(c);
     if (!out) return set_err(c, LMOSEM_EINVAL, "null output");
     *out = nullptr;
-    return load_set(c, ev, batch, -1, out);
+    return load_set(c, ev, batch, -1, out, true);
 }
 
 void lmosem_events_free(lmosem_evset *s) { free_set(s); }
@@ -729,7 +889,7 @@ lmosem_status lmosem_subset_update(lmosem_ctx *c, int32_t subset, const lmosem_e
     if (st != LMOSEM_OK) return st;
     const Geo &g = c->g;
     hipError_t e = launch_gather_image(g, c->t, image_dev, 1, 0, s->f, 0, c->st);
-    if (e == hipSuccess) e = subiteration(c, s, subset, false, c->st);
+    if (e == hipSuccess) e = subiteration(c, s, subset, true, false, c->st);
     if (e == hipSuccess) { c->terms += s->s.terms_sub[subset]; c->useful += s->s.useful_sub[subset]; }
     if (e == hipSuccess && event_mean_dev)
         e = launch_scatter_rows(s->mean, s->s.orig + s->s.row_off[subset],
@@ -751,8 +911,12 @@ lmosem_status lmosem_forward(lmosem_ctx *c, const lmosem_events *ev, const float
     const EvSet &v = s->s;
     const int rows = v.row_off[1];
     hipError_t e = launch_gather_image(g, c->t, image_dev, 1, 0, s->f, 0, c->st);
-    if (e == hipSuccess) e = forward_rows(c, s, 0, s->H, c->st);
-    if (e == hipSuccess) e = launch_mean(s->pmean, mean_groups(c, s), rows, s->mean, s->inv, c->skipped_dev, c->st);
+    if (s->flux) {
+        if (e == hipSuccess) e = flux_subset(c, s, 0, true, true, false, nullptr, false, c->st);
+    } else {
+        if (e == hipSuccess) e = forward_rows(c, s, 0, s->H, c->st);
+        if (e == hipSuccess) e = launch_mean(s->pmean, mean_groups(c, s), rows, s->mean, s->inv, c->skipped_dev, c->st);
+    }
     if (e == hipSuccess) e = launch_scatter_rows(s->mean, v.orig, rows, mean_dev, c->st);
     if (e == hipSuccess) e = hipStreamSynchronize(c->st);
     if (e == hipSuccess) { c->terms += v.terms_sub[0]; c->useful += v.useful_sub[0]; }
@@ -780,7 +944,12 @@ lmosem_status lmosem_forward_noalloc(lmosem_ctx *c, const lmosem_events *ev, con
     lmosem_status st = LMOSEM_OK;
     if (!check_events(c, ev, st)) return st;
     int64_t terms = 0, useful = 0;
-    e = forward_noalloc(c->g, c->t, *ev, c->ev_tile, image_dev, event_mean_dev, c->skipped_dev, c->st, terms, useful);
+    FluxRun fr{};
+    fr.g = &c->g; fr.fg = &c->fg; fr.ft = &c->ft; fr.t = &c->t;
+    fr.ws = c->fws;
+    fr.ws_floats = c->fws_floats;
+    e = forward_noalloc(c->g, c->t, *ev, c->ev_tile, image_dev, event_mean_dev, c->skipped_dev, c->st, terms, useful,
+                        c->flux ? &fr : nullptr);
     if (e != hipSuccess) return dev_err(c, "forward (no allocation)", e);
     c->terms += terms;
     c->useful += useful;
@@ -799,10 +968,14 @@ lmosem_status lmosem_backproject(lmosem_ctx *c, const lmosem_events *ev, const f
     const EvSet &v = s->s;
     const int rows = v.row_off[1];
     hipError_t e = launch_fill(s->f, (size_t)g.n_qpad, 0.0f, c->st);
-    if (e == hipSuccess) e = forward_rows(c, s, 0, s->H, c->st);
     if (e == hipSuccess) e = launch_gather_rows(weights_dev, v.orig, rows, s->inv, c->st);
-    if (e == hipSuccess) e = launch_backproject(g, v.chunks, v.chunk_off[1], s->H, s->inv, s->pb, c->st);
-    if (e == hipSuccess) e = launch_sum_real(g, v.crange, 1, s->pb, s->f, c->st);
+    if (s->flux) {
+        if (e == hipSuccess) e = flux_subset(c, s, 0, true, false, true, nullptr, false, c->st);
+    } else {
+        if (e == hipSuccess) e = forward_rows(c, s, 0, s->H, c->st);
+        if (e == hipSuccess) e = launch_backproject(g, v.chunks, v.chunk_off[1], s->H, s->inv, s->pb, c->st);
+        if (e == hipSuccess) e = launch_sum_real(g, v.crange, 1, s->pb, s->f, c->st);
+    }
     if (e == hipSuccess) e = launch_scatter_image(g, c->t, s->f, 1, image_dev, c->st);
     if (e == hipSuccess) e = hipStreamSynchronize(c->st);
     if (e == hipSuccess) { c->terms += v.terms_sub[0]; c->useful += v.useful_sub[0]; }
@@ -1146,6 +1319,17 @@ lmosem_status lmosem_cache_rows(lmosem_ctx *c, lmosem_evset *s, int32_t enable) 
     c->set_bytes -= s->bytes;
     s->bytes = set_device_bytes(c, s);
     c->set_bytes += s->bytes;
+    if (s->flux) {
+        // the rows' own kernels: their partial sums, and (for a set that was
+        // autotuned) their plan
+        lmosem_status ws = alloc_workspace(c, s, true);
+        if (ws == LMOSEM_OK && s->tuned) ws = lmosem_autotune(c, s, nullptr, nullptr, nullptr);
+        if (ws != LMOSEM_OK) {   // the set stays usable without the cache
+            hipFree(s->Hc);
+            s->Hc = nullptr;
+            return ws;
+        }
+    }
     // zero padding columns (the learned-scatter rows never write them)
     e = launch_fill(s->Hc, n, 0.0f, c->st);
     return e == hipSuccess ? LMOSEM_OK : dev_err(c, "row cache", e);
@@ -1159,9 +1343,9 @@ std::string tune_key(const lmosem_ctx *c, const lmosem_evset *s) {
     int lg = 0;
     while ((1 << (lg + 1)) <= std::max(1, s->s.max_rows)) ++lg;
     char buf[160];
-    snprintf(buf, sizeof buf, "np=%d nq=%d na=%d ns=%d real=%d rows2^%d", c->g.n_p, c->g.n_q, c->g.n_angles,
+    snprintf(buf, sizeof buf, "np=%d nq=%d na=%d ns=%d real=%d rows2^%d%s", c->g.n_p, c->g.n_q, c->g.n_angles,
              c->g.n_subsets,
-             s->s.n_real, lg);
+             s->s.n_real, lg, s->flux && !s->Hc ? " flux" : "");
     return buf;
 }
 
@@ -1232,15 +1416,19 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
     const Geo &g = c->g;
     EvSet &v = s->s;
     std::string why, key = tune_key(c, s);
+    s->tuned = true;
+    // a flux set without a row cache has nothing to tune but the replay
+    const bool direct = !s->flux || s->Hc;
     // tune the computing path; a row cache is refilled by the next iteration
-    float *hc = s->Hc;
-    s->Hc = nullptr;
-    s->rows_valid = false;
     struct Restore {
         lmosem_evset *s;
         float *hc;
-        ~Restore() { s->Hc = hc; s->rows_valid = false; drop_graphs(s); }
-    } restore{s, hc};
+        bool flux;
+        ~Restore() { s->Hc = hc; s->flux = flux; s->rows_valid = false; drop_graphs(s); }
+    } restore{s, s->Hc, s->flux};
+    s->Hc = nullptr;
+    s->rows_valid = false;
+    s->flux = s->flux && !direct;
     int best_ev = v.ev_tile, best_ch = v.chunk_rows, best_graph = -1, best_waves = v.fwd_waves;
     float fwd_ms = 0.0f;   // the fastest forward launch of the largest subset
     hipError_t e = hipSuccess;
@@ -1268,7 +1456,7 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
         float best = 3.4e38f;
         std::vector<float> cand_ms;
         float sweep_ms = 0.0f;
-        for (int sweep = 0; sweep < 2 && !c->surrogate && e == hipSuccess; ++sweep) {
+        for (int sweep = 0; sweep < 2 && !c->surrogate && direct && e == hipSuccess; ++sweep) {
             if (sweep == 1 && sweep_ms >= 300.0f) break;
             size_t ci = 0;
             for (int ev : {8, 16, 32}) {
@@ -1294,11 +1482,11 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
                 }
             }
         }
-        if (!c->surrogate) v.fwd_waves = best_waves;
+        if (!c->surrogate && direct) v.fwd_waves = best_waves;
         fwd_ms = best < 3.4e38f ? best : 0.0f;
         best = 3.4e38f;
         for (int ch : {64, 128, 256, 512, 1024, 2048, 4096}) {
-            if (e != hipSuccess) break;
+            if (e != hipSuccess || !direct) break;
             if ((e = plan_tiles(g, c->t, v, best_ev, ch, c->st, why)) != hipSuccess) break;
             lmosem_status ws = alloc_workspace(c, s);
             if (ws != LMOSEM_OK) return ws;

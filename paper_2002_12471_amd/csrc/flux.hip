@@ -1,0 +1,1209 @@
+// Sub-iterations through directional flux: the per-event means (denominator
+// of Eq. 8) and the backprojection (numerator of Eq. 7) of the exact model
+// without a term per (event, emission pixel, path end).
+//
+// The scatter part of the model is, for event j of angle a,
+//     sum_s K(u_j - u_s) sum_q f_q B(q, s) g_as(phi_qs; E_j),
+//     g_as(phi; E) = Psi(c)/Psi_bar e^(-rho(c) L_a(s)) G(E; E'(c)),  c = cos(phi - theta_a),
+// with phi_qs the direction of flight from q to s: for one scatter point
+// everything behind B depends on the emission pixel only through phi_qs, and
+// g is smooth in phi and in E.  So the sums are taken in stages,
+//     I_s(n)    = sum_q f_q B(q, s) l_n(phi_qs)               directional flux (k_flux_spread)
+//     S_as(k)   = sum_n I_s(n) g_as(phi_n; E_k)               spectra (k_flux_spectra)
+//     mean_j    = sum_s K_js (P_as g0_j + sum_k l_k(E_j) S_as(k))   (k_flux_means)
+// and the adjoint runs the same stages backwards (k_flux_adjoint: events to
+// energy nodes, k_flux_fields: energy nodes to directions, k_flux_gather:
+// directions to emission pixels).  l_n and l_k are eight-point interpolation
+// weights on equispaced directions phi_n and energies E_k.  The primary path
+// (P_as = f_s e^(-L_a(s)), energy factor g0_j) is carried exactly.
+//
+// The interpolated functions are Gaussians of the energy difference, so in a
+// node's neighbourhood they run like exponentials e^(b x); the weights are
+// exact for eight exponents b at Chebyshev points of the range met (and not
+// for powers of x, whose remainder grows far out in the tails): for the
+// energies after dividing out a Gaussian about the middle of the end
+// energies, which leaves pure exponentials.  With the node spacings of
+// flux_geometry one path's relative error is at most 4.5e-7 in energy at
+// any distance from its end energy, and in direction 1e-7 within three
+// widths of the energy response, 2e-6 within six, 5e-5 within eight
+// (evaluated over the whole range of directions and energies, 90-175 keV),
+// alternating in sign from path to path.
+//
+// Work per sub-iteration: n_p^2 pair visits (twice), angles x n_p x N x K
+// multiply-adds on the matrix cores (twice), and eight multiply-adds per
+// (event, path end) (twice), where the direct form evaluates an exponential
+// per (event, path end, emission pixel).
+#include <hip/hip_runtime.h>
+#include <hipcub/device/device_scan.hpp>
+#include <math.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "lmosem_int.h"
+#include "paths.h"
+
+namespace lmo {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kSec = 12;    // direction nodes per sector (one wave's share of a pixel block's pairs)
+constexpr int kTap = 8;     // interpolation points
+constexpr int kStrip = 16;  // columns of a strip of the flux order
+
+// interpolation weights at offset t (in node spacings, [0, 1) from the fourth
+// node), exact for the fit's eight exponentials
+__device__ __forceinline__ void fit_weights(const FluxFit &fit, double t, double (&w)[kTap]) {
+    double x[kTap];
+#pragma unroll
+    for (int m = 0; m < kTap; ++m) x[m] = exp(fit.b[m] * t);
+#pragma unroll
+    for (int i = 0; i < kTap; ++i) {
+        w[i] = 0.0;
+#pragma unroll
+        for (int m = 0; m < kTap; ++m) w[i] = fma(fit.v[i][m], x[m], w[i]);
+    }
+}
+
+// workgroups are dealt to the 8 XCDs round-robin: the item that gives each
+// XCD one contiguous run
+__device__ __forceinline__ int xcd_logical(int p, int n) {
+    const int x = p % 8, m = n / 8, rem = n % 8;
+    return x * m + min(x, rem) + p / 8;
+}
+
+__device__ __forceinline__ int wrap(int n, int N) { return n < 0 ? n + N : (n >= N ? n - N : n); }
+
+// ---------------------------------------------------------------- tables (once per attenuation map)
+
+// node position (in node spacings, [0, N)) of the direction of offset (di, dj)
+__device__ inline double node_pos(int di, int dj, int N) {
+    double t = atan2((double)dj, (double)di) * (N / (2.0 * M_PI));
+    if (t < 0.0) t += N;
+    return t >= N ? 0.0 : t;
+}
+
+// the box offsets whose direction lies in node interval n, in index order:
+// one block per interval
+__global__ __launch_bounds__(256) void k_flux_offsets(int W, int Hh, int N, int cap, int *__restrict__ cnt,
+                                                      int2 *__restrict__ off) {
+    __shared__ int wsum[4];
+    const int n = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w2 = 2 * W - 1, total = w2 * (2 * Hh - 1);
+    int have = 0;
+    for (int i0 = 0; i0 < total; i0 += 256) {
+        const int i = i0 + threadIdx.x;
+        const int di = i % w2 - (W - 1), dj = i / w2 - (Hh - 1);
+        const bool in = i < total && (di || dj) && (int)node_pos(di, dj, N) == n;
+        const unsigned long long m = __ballot(in);
+        if (lane == 0) wsum[wave] = __popcll(m);
+        __syncthreads();
+        int at = have + __popcll(m & ((1ull << lane) - 1));
+        for (int w = 0; w < wave; ++w) at += wsum[w];
+        if (in && at < cap) off[(size_t)n * cap + at] = make_int2(di, dj);
+        have += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) cnt[n] = min(have, cap);
+}
+
+// Per pixel block (64 pixels of the flux order, one per lane) and node
+// interval: the offsets that lead at least one of its pixels to another
+// support pixel.  FILL = 0 counts them; FILL = 1 writes their records (box
+// offset and the interpolation weights of their direction) and, per lane, the
+// symmetric part of the pair factor, B(q, s) / mu(s) = pixel_cm^2 e^(-l) / (2 pi r)
+// (0 where the lane's pixel has no partner), rounded from FP64.
+template <int FILL>
+__global__ __launch_bounds__(64) void k_flux_pairs(Geo g, FluxGeo fg, FluxFit fit, const int *__restrict__ sup,
+                                                   const int *__restrict__ p_pix, const int *__restrict__ q_of_pix,
+                                                   const float *__restrict__ mu, const double *__restrict__ Bt,
+                                                   const int *__restrict__ cnt, const int2 *__restrict__ off, int cap,
+                                                   int *__restrict__ beg, int *__restrict__ rec_off,
+                                                   float *__restrict__ rec_w, float *__restrict__ sym) {
+    const int n = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
+    const int x = b * 64 + lane < g.n_p ? sup[b * 64 + lane] : -1;
+    const int px = x >= 0 ? p_pix[x] : -1;
+    const int xi = px >= 0 ? px % g.nx : -1, xj = px >= 0 ? px / g.nx : -1;
+    int at = FILL ? beg[b * fg.N + n] : 0;
+    for (int k = 0; k < cnt[n]; ++k) {
+        const int2 d = off[(size_t)n * cap + k];
+        const int yi = xi + d.x, yj = xj + d.y;
+        const bool in = px >= 0 && yi >= 0 && yi < g.nx && yj >= 0 && yj < g.ny;
+        const int y = in ? q_of_pix[yj * g.nx + yi] : -1;
+        // a pair without an emission pixel carries nothing
+        const bool use = y >= 0 && (x < g.n_q || y < g.n_q);
+        if (__ballot(use) == 0) continue;
+        if (FILL) {
+            double v = 0.0;
+            if (use)
+                v = y < g.n_q ? Bt[(size_t)x * g.n_p + y] / (double)mu[px]
+                              : Bt[(size_t)y * g.n_p + x] / (double)mu[p_pix[y]];
+            sym[(size_t)at * 64 + lane] = (float)v;
+            if (lane == 0) {
+                rec_off[at] = d.y * fg.W + d.x;
+                double w[kTap];
+                fit_weights(fit, node_pos(d.x, d.y, fg.N) - n, w);
+#pragma unroll
+                for (int i = 0; i < kTap; ++i) rec_w[(size_t)at * kTap + i] = (float)w[i];
+            }
+        }
+        ++at;
+    }
+    if (!FILL && lane == 0) beg[b * fg.N + n] = at;
+}
+
+// per (angle, direction node): Psi/Psi_bar, -rho log2 e, and the energy
+// response at every energy node; one block per angle and 16 directions
+__global__ __launch_bounds__(256) void k_flux_angles(Geo g, FluxGeo fg, const double *__restrict__ cs,
+                                                     float *__restrict__ psi, float *__restrict__ rho,
+                                                     float *__restrict__ G) {
+    __shared__ double ep_s[16];
+    const int a = blockIdx.y, n0 = blockIdx.x * 16;
+    if (threadIdx.x < 16) {
+        const int n = n0 + threadIdx.x;
+        const double ph = 2.0 * M_PI * n / fg.N;
+        const double c = cos(ph) * cs[2 * a] + sin(ph) * cs[2 * a + 1];
+        const double t = 1.0 + g.kappa * (1.0 - c), P = 1.0 / t, ep = g.e0 * P;
+        psi[(size_t)a * fg.N + n] = (float)(P * P * (P + t - 1.0 + c * c) / g.psi_bar);
+        rho[(size_t)a * fg.N + n] = (float)(-kn_total(ep) / g.sigma_kn_e0 * 1.4426950408889634);
+        ep_s[threadIdx.x] = ep;
+    }
+    __syncthreads();
+    const double norm = 1.0 / (sqrt(2.0 * M_PI) * g.sig_e);
+    for (int i = threadIdx.x; i < 16 * fg.K; i += 256) {
+        const int n = i / fg.K, k = i - n * fg.K;
+        const double e = fg.e_lo + (k - 3) * fg.h - ep_s[n];
+        G[((size_t)a * fg.N + n0 + n) * fg.K + k] = (float)(norm * exp2(-g.c2 * e * e));
+    }
+}
+
+// tables of the flux order (strips of kStrip columns, so that a block of 64
+// pixels is compact in both directions): support index, box index, mu; per
+// angle rank, primary weight and attenuation, and the order's index by rank
+__global__ void k_flux_support(Geo g, FluxGeo fg, const int *__restrict__ sup, const int *__restrict__ p_pix,
+                               const float *__restrict__ mu, int *__restrict__ pos, int *__restrict__ box,
+                               float *__restrict__ mu_s) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= g.n_p) return;
+    const int pix = p_pix[sup[x]];
+    pos[sup[x]] = x;
+    box[x] = (pix / g.nx - fg.y0) * fg.W + (pix % g.nx - fg.x0);
+    mu_s[x] = mu[pix];
+}
+
+__global__ void k_flux_ranks(Geo g, const int *__restrict__ pos, const int *__restrict__ s_sorted,
+                             const double *__restrict__ Ld, int *__restrict__ rank_of, int *__restrict__ x_of,
+                             float *__restrict__ pw, float *__restrict__ pwr, float *__restrict__ Lx) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= g.n_angles * g.n_p) return;
+    const int a = i / g.n_p, s = s_sorted[i], x = pos[s];
+    const size_t o = (size_t)a * g.n_p;
+    const double L = Ld[o + s];
+    const float w = (float)exp(-L);
+    x_of[i] = x;
+    pwr[i] = w;
+    rank_of[o + x] = i - (int)o;
+    pw[o + x] = w;
+    Lx[o + x] = (float)L;
+}
+
+// ---------------------------------------------------------------- forward stages
+
+// the estimate on the support's bounding box (0 off the emission set)
+__global__ void k_flux_box(Geo g, FluxGeo fg, FluxTables ft, const float *__restrict__ f, float *__restrict__ fbox) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x, r = blockIdx.y;
+    if (x >= g.n_p) return;
+    const int q = ft.sup[x];
+    fbox[(size_t)r * fg.nb + ft.box[x]] = q < g.n_q ? f[(size_t)r * g.n_qpad + q] : 0.0f;
+}
+
+// I_s(n): one workgroup per (block of 64 scatter points, sector of kSec node
+// intervals), each of its four waves a quarter of the sector.  Every lane
+// visits the same offset, so its direction's weights and nodes are scalars
+// and the eight sums of the current interval's nodes sit in registers, moving
+// on by one node per interval; the pair factors stream in as written, one per
+// lane.  The waves' nodes overlap and are added in LDS; a sector touches
+// kSec + 7 nodes, so even and odd sectors write two separate copies (24 nodes
+// each, the rest zero) that the next stage adds.
+constexpr int kWaveSec = kSec / 4;             // intervals of one wave
+constexpr int kWaveNodes = kWaveSec + kTap - 1;
+constexpr int kBatch = 8;                      // pairs loaded ahead
+
+__global__ __launch_bounds__(256) void k_flux_spread(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ beg_all,
+                                                     const int *__restrict__ rec_off, const float *__restrict__ rec_w,
+                                                     const float *__restrict__ sym, const float *__restrict__ fbox,
+                                                     float *__restrict__ I) {
+    __shared__ float part[4][kWaveNodes][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int sec = blockIdx.y, b = blockIdx.x, r = blockIdx.z;
+    const int s = b * 64 + lane;
+    const int lin = s < g.n_p ? ft.box[s] : 0;
+    const float *__restrict__ fr = fbox + (size_t)r * fg.nb;
+    const unsigned top = (unsigned)fg.nb - 1;
+    float acc[kTap];
+#pragma unroll
+    for (int i = 0; i < kTap; ++i) acc[i] = 0.0f;
+    const int *beg = beg_all + b * fg.N + sec * kSec + wave * kWaveSec;
+    const int e1 = beg[kWaveSec];
+    int k = 0, next = beg[1];
+    for (int e = beg[0]; e < e1; e += kBatch) {
+        float v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int eu = min(e + u, e1 - 1);
+            const float y = sym[(size_t)eu * 64 + lane];
+            const unsigned at = min((unsigned)(lin + rec_off[eu]), top);
+            const float fy = fr[at];
+            v[u] = y != 0.0f ? y * fy : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (e + u < e1) {
+                while (e + u >= next) {   // the lowest node is complete: on to the next interval
+                    part[wave][k][lane] = acc[0];
+#pragma unroll
+                    for (int i = 0; i + 1 < kTap; ++i) acc[i] = acc[i + 1];
+                    acc[kTap - 1] = 0.0f;
+                    ++k;
+                    next = beg[k + 1];
+                }
+#pragma unroll
+                for (int i = 0; i < kTap; ++i) acc[i] = fmaf(rec_w[(size_t)(e + u) * kTap + i], v[u], acc[i]);
+            }
+        }
+    }
+    for (; k < kWaveSec; ++k) {
+        part[wave][k][lane] = acc[0];
+#pragma unroll
+        for (int i = 0; i + 1 < kTap; ++i) acc[i] = acc[i + 1];
+        acc[kTap - 1] = 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i + 1 < kTap; ++i) part[wave][kWaveSec + i][lane] = acc[i];
+    __syncthreads();
+    // directions of flight q -> s are opposite to the offsets s -> q
+    const int n0 = sec * kSec - 3 + fg.N / 2;
+    const float m = s < g.n_p ? ft.mu_s[s] : 0.0f;
+    float *out = I + ((size_t)(r * 2 + (sec & 1)) * fg.N) * fg.np64 + s;
+    for (int j = wave; j < 2 * kSec; j += 4) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const int l = j - w * kWaveSec;
+            if (l >= 0 && l < kWaveNodes) t += part[w][l][lane];
+        }
+        out[(size_t)wrap(n0 + j, fg.N) * fg.np64] = m * t;
+    }
+}
+
+// S_as(k) and P_as of a chunk of (realisation, angle) slots, in rank order:
+// C[s][k] = sum_n A[s][n] G_a[n][k] on v_mfma_f32_16x16x4_f32 with
+// A = I psi e^(-rho L) formed in the operand registers.  One workgroup: 32
+// scatter points x up to 96 energy nodes, its four waves a quarter of the
+// directions each, added in LDS (small problems would otherwise be one long
+// chain of loads per wave).
+constexpr int kSpecTiles = 6;   // 16-node tiles of one workgroup
+
+__global__ __launch_bounds__(256) void k_flux_spectra(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ alist,
+                                                      int n_list, int slot0, const float *__restrict__ I,
+                                                      const float *__restrict__ f, float *__restrict__ S,
+                                                      float *__restrict__ SP) {
+    __shared__ f32x4 red[4][2 * kSpecTiles][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int c = lane & 15, q = lane >> 4;
+    const int s0 = blockIdx.x * 32, ls = blockIdx.y, slot = slot0 + ls;
+    const int r = slot / n_list, a = alist[slot - r * n_list];
+    const int kb = blockIdx.z * 16 * kSpecTiles, n_kt = min(kSpecTiles, (fg.K - kb) / 16);
+    const int *rank = ft.rank_of + (size_t)a * g.n_p;
+    if (blockIdx.z == 0 && threadIdx.x < 32) {
+        const int s = s0 + threadIdx.x;
+        if (s < g.n_p) {
+            const int p = ft.sup[s];
+            SP[(size_t)ls * g.n_p + rank[s]] = p < g.n_q ? f[(size_t)r * g.n_qpad + p] * ft.pw[(size_t)a * g.n_p + s] : 0.0f;
+        }
+    }
+    const float *I0 = I + (size_t)r * 2 * fg.N * fg.np64 + s0 + c, *I1 = I0 + (size_t)fg.N * fg.np64;
+    const float *psi = ft.psi + (size_t)a * fg.N, *rho = ft.rho + (size_t)a * fg.N;
+    const float *G = ft.G + (size_t)a * fg.N * fg.K + kb + c;
+    float L[2];
+    f32x4 acc[2][kSpecTiles];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        L[t] = ft.Lx[(size_t)a * g.n_p + min(s0 + 16 * t + c, g.n_p - 1)];
+#pragma unroll
+        for (int kt = 0; kt < kSpecTiles; ++kt) acc[t][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int nq = fg.N / 4;
+#pragma unroll 3
+    for (int n = wave * nq + q; n < (wave + 1) * nq; n += 4) {
+        const float ps = psi[n], rh = rho[n];
+        float gv[kSpecTiles];
+#pragma unroll
+        for (int kt = 0; kt < kSpecTiles; ++kt) gv[kt] = kt < n_kt ? G[(size_t)n * fg.K + 16 * kt] : 0.0f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const size_t at = (size_t)n * fg.np64 + 16 * t;   // np64 covers whole groups of 32
+            const float av = (I0[at] + I1[at]) * ps * __builtin_amdgcn_exp2f(rh * L[t]);
+#pragma unroll
+            for (int kt = 0; kt < kSpecTiles; ++kt)
+                if (kt < n_kt) acc[t][kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, gv[kt], acc[t][kt], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int kt = 0; kt < kSpecTiles; ++kt) red[wave][t * kSpecTiles + kt][lane] = acc[t][kt];
+    __syncthreads();
+    for (int i = wave; i < 2 * kSpecTiles; i += 4) {
+        const int t = i / kSpecTiles, kt = i - t * kSpecTiles;
+        if (kt >= n_kt) continue;
+        const f32x4 v = (red[0][i][lane] + red[1][i][lane]) + (red[2][i][lane] + red[3][i][lane]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int s = s0 + 16 * t + 4 * q + j;
+            if (s < g.n_p) S[((size_t)ls * g.n_p + rank[s]) * fg.K + kb + 16 * kt + c] = v[j];
+        }
+    }
+}
+
+// position response (times Z_K): offset in FP64, response in FP32, as the
+// term-by-term kernel evaluates it
+__device__ __forceinline__ float response(double d, float inv2s2, float edge) {
+    const float x = (float)d;
+    return fmaxf(__expf(-x * x * inv2s2) - edge, 0.0f);
+}
+
+// Event means on the matrix cores.  Events come in blocks of 64 neighbours in
+// position, ordered by energy within a block; a wave takes 16 of them:
+// V[j][k] = sum_s K_js S_as(k) over the ends that any of them reaches and the
+// 16-node tiles that their eight nodes touch, then mean_j = sum_k l_k(E_j) V[j][k].
+// The responses are the A operand, formed in registers (one per event and
+// end); 16 events share each read of the spectra.  The energy order keeps a
+// wave's nodes to two or three tiles.
+constexpr int kMaxTiles = kFluxMaxK / 16;
+
+template <int TILES>
+__global__ __launch_bounds__(256) void k_flux_means(Geo g, FluxGeo fg, const FluxEvent *__restrict__ ev,
+                                                    const FluxBlock *__restrict__ blk,
+                                                    const double *__restrict__ us_sorted,
+                                                    const int *__restrict__ alist, int n_list, int slot_base, int slot0,
+                                                    int row0, int row_base, const float *__restrict__ S,
+                                                    const float *__restrict__ SP, float *__restrict__ mean,
+                                                    float *__restrict__ inv, unsigned long long *__restrict__ skipped) {
+    __shared__ float w_s[4][16][kTap];
+    __shared__ int et_s[4][16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int c = lane & 15, q = lane >> 4;
+    const FluxBlock bk = blk[blockIdx.x];
+    const int i = wave * 16 + c;   // this lane's event in the block
+    const bool on = i < bk.n;
+    if (wave * 16 >= bk.n) return;
+    const int slot = bk.slot - slot_base, ls = slot - slot0, r = slot / n_list;
+    const size_t ao = (size_t)alist[slot - r * n_list] * g.n_p;
+    const double *us = us_sorted + ao;
+    FluxEvent e = ev[bk.row + min(i, bk.n - 1) - row0];
+    if (q == 0) {
+#pragma unroll
+        for (int t = 0; t < kTap; ++t) w_s[wave][c][t] = on ? e.w[t] : 0.0f;
+        et_s[wave][c] = e.et;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+    __builtin_amdgcn_wave_barrier();
+    // the wave's ranks and tiles
+    int r0 = e.r0, r1 = e.r1, t0 = e.et >> 4, t1 = (e.et + kTap - 1) >> 4;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        r0 = min(r0, __shfl_xor(r0, o, 64));
+        r1 = max(r1, __shfl_xor(r1, o, 64));
+        t0 = min(t0, __shfl_xor(t0, o, 64));
+        t1 = max(t1, __shfl_xor(t1, o, 64));
+    }
+    r0 = __builtin_amdgcn_readfirstlane(r0);
+    r1 = __builtin_amdgcn_readfirstlane(r1);
+    t0 = __builtin_amdgcn_readfirstlane(t0);
+    t1 = __builtin_amdgcn_readfirstlane(t1);
+    const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
+    const float edge = expf(-4.5f);
+    const float *Sr = S + (size_t)ls * g.n_p * fg.K, *Pr = SP + (size_t)ls * g.n_p;
+    float total[4] = {0.f, 0.f, 0.f, 0.f};   // of events 4 q + v, this lane's nodes
+    float prim = 0.0f;
+    // up to TILES tiles at a time
+    for (int tb = t0; tb <= t1; tb += TILES) {
+        const int nt = min(TILES, t1 + 1 - tb);
+        f32x4 acc[TILES];
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int k = r0; k < r1; k += 4) {
+            const int kr = min(k + q, r1 - 1);
+            float kv = response(e.u - us[kr], inv2s2, edge);
+            kv = k + q < r1 ? kv : 0.0f;
+            if (tb == t0) prim = fmaf(kv, Pr[kr], prim);
+            const float *row = Sr + (size_t)kr * fg.K + 16 * tb + c;
+#pragma unroll
+            for (int t = 0; t < TILES; ++t)
+                if (t < nt) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, row[16 * t], acc[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < TILES; ++t)
+            if (t < nt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int d = 16 * (tb + t) + c - et_s[wave][4 * q + v];
+                    const float w = (unsigned)d < kTap ? w_s[wave][4 * q + v][d & 7] : 0.0f;
+                    total[v] = fmaf(w, acc[t][v], total[v]);
+                }
+    }
+    prim += __shfl_xor(prim, 16, 64);
+    prim += __shfl_xor(prim, 32, 64);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) total[v] += __shfl_xor(total[v], o, 64);
+    // event c sits in lane group c / 4, element c % 4
+    float s = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const float x = __shfl(total[v], (c >> 2) * 16, 64);
+        s = (c & 3) == v ? x : s;
+    }
+    int dead = 0;
+    if (q == 0 && on) {
+        s = (s + prim * e.g0) * fg.inv_zk;
+        const int j = e.row - row_base;
+        mean[j] = s;
+        dead = !(s > 1e-30f);
+        inv[j] = dead ? 0.0f : 1.0f / s;
+    }
+    const unsigned long long m = __ballot(dead);
+    if (lane == 0 && m) atomicAdd(skipped, (unsigned long long)__popcll(m));
+}
+
+// primary paths only: LPE lanes per event, the primary weights formed here
+template <int LPE>
+__global__ __launch_bounds__(256) void k_flux_means_primary(Geo g, FluxGeo fg, FluxTables ft,
+                                                            const FluxEvent *__restrict__ ev,
+                                                            const double *__restrict__ us_sorted,
+                                                            const int *__restrict__ s_sorted,
+                                                            const int *__restrict__ alist, int n_list, int slot_base,
+                                                            int j0, int j1, int row0, int row_base,
+                                                            const float *__restrict__ f, float *__restrict__ mean,
+                                                            float *__restrict__ inv,
+                                                            unsigned long long *__restrict__ skipped) {
+    const int sub = threadIdx.x % LPE;
+    const int i = j0 + (blockIdx.x * 256 + threadIdx.x) / LPE;
+    int dead = 0;
+    if (i < j1) {
+        const FluxEvent e = ev[i - row0];
+        const int slot = e.slot - slot_base, r = slot / n_list;
+        const size_t ao = (size_t)alist[slot - r * n_list] * g.n_p;
+        const double *us = us_sorted + ao;
+        const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
+        const float edge = expf(-4.5f);
+        const float *fr = f + (size_t)r * g.n_qpad;
+        float s = 0.0f;
+#pragma unroll 4
+        for (int k = e.r0 + sub; k < e.r1; k += LPE) {
+            const int p = s_sorted[ao + k];
+            const float h = p < g.n_q ? fr[p] * ft.pwr[ao + k] : 0.0f;
+            s = fmaf(response(e.u - us[k], inv2s2, edge), h, s);
+        }
+#pragma unroll
+        for (int o = LPE / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (sub == 0) {
+            s *= e.g0 * fg.inv_zk;
+            const int j = e.row - row_base;
+            mean[j] = s;
+            dead = !(s > 1e-30f);
+            inv[j] = dead ? 0.0f : 1.0f / s;
+        }
+    }
+    const unsigned long long m = __ballot(dead);
+    if ((threadIdx.x & 63) == 0 && m) atomicAdd(skipped, (unsigned long long)__popcll(m));
+}
+
+// ---------------------------------------------------------------- adjoint stages
+
+// first block in [lo, hi) whose last position is past v (FIRST: whose first
+// position is at or past v), by 64-way steps: every lane of the wave takes
+// part and gets the same answer
+template <bool FIRST>
+__device__ __forceinline__ int wave_search(const FluxBlock *blk, int lo, int hi, double v, int lane) {
+    while (hi > lo) {
+        const int step = (hi - lo + 63) / 64, at = min(lo + lane * step + step - 1, hi - 1);
+        const unsigned long long m = __ballot(FIRST ? blk[at].u0 >= v : blk[at].u1 > v);
+        if (m == 0) return hi;
+        const int k = __ffsll((unsigned long long)m) - 1;
+        hi = min(lo + k * step + step - 1, hi - 1);   // this one is past v; the answer is at most here
+        lo = lo + k * step;
+        if (step == 1) return hi;
+    }
+    return lo;
+}
+
+// R_as(k) = sum_j w_j K_js l_k(E_j) (and the primary's R0 = sum_j w_j K_js g0_j)
+// of 16 path ends of one slot on the matrix cores: one wave walks the event
+// blocks that reach any of its ends, four events per product (A: responses of
+// 16 ends to four events; B: the events' interpolation weights spread over a
+// 16-node tile).  The events' energy order within a block keeps four events'
+// nodes to one or two tiles; the others are skipped.  Every sum has one owner
+// and a fixed order.  Rows are written in flux order.
+template <int TILES>
+__global__ __launch_bounds__(64) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTables ft, const FluxEvent *__restrict__ ev,
+                                                     const FluxBlock *__restrict__ blk,
+                                                     const double *__restrict__ us_sorted,
+                                                     const int *__restrict__ alist, const int *__restrict__ blk_beg,
+                                                     int n_list, int slot0, int row_base,
+                                                     const float *__restrict__ wgt, float *__restrict__ R,
+                                                     float *__restrict__ R0) {
+    __shared__ __align__(16) float w_s[64][kTap];   // weight times interpolation weights
+    __shared__ float p_s[64];                       // weight times the primary's energy response
+    __shared__ int et_s[64];
+    __shared__ double u_s[64];
+    const int lane = threadIdx.x, c = lane & 15, q = lane >> 4;
+    const int ls = blockIdx.y, slot = slot0 + ls;
+    const int r = slot / n_list, a = alist[slot - r * n_list];
+    const double *us = us_sorted + (size_t)a * g.n_p;
+    const int *x_of = ft.x_of + (size_t)a * g.n_p;
+    const int k0 = blockIdx.x * 16, rank = min(k0 + c, g.n_p - 1);
+    const double my_u = us[rank], reach = 3.0 * g.sig_u;
+    const int b0 = wave_search<false>(blk, blk_beg[slot], blk_beg[slot + 1], us[k0] - reach, lane);
+    const int b1 = wave_search<true>(blk, b0, blk_beg[slot + 1], us[min(k0 + 15, g.n_p - 1)] + reach, lane);
+    const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
+    const float edge = expf(-4.5f);
+    f32x4 acc[TILES > 0 ? TILES : 1];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float r0 = 0.0f;
+    for (int b = b0; b < b1; ++b) {
+        const FluxBlock bk = blk[b];
+        __syncthreads();
+        {
+            const FluxEvent e = ev[bk.row + min(lane, bk.n - 1)];
+            const float y = lane < bk.n ? wgt[e.row - row_base] * fg.inv_zk : 0.0f;
+            u_s[lane] = e.u;
+            p_s[lane] = y * e.g0;
+            if (TILES > 0) {
+#pragma unroll
+                for (int i = 0; i < kTap; ++i) w_s[lane][i] = y * e.w[i];
+                et_s[lane] = e.et;
+            }
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (int i = 0; i < bk.n; i += 4) {
+            const float kv = response(u_s[i + q] - my_u, inv2s2, edge);
+            r0 = fmaf(kv, p_s[i + q], r0);
+            if (TILES > 0) {
+                const int et = et_s[i + q];
+                // energies ascend: the four events' first and last tiles
+                const int t0 = __builtin_amdgcn_readfirstlane(et_s[i]) >> 4;
+                const int t1 = (__builtin_amdgcn_readfirstlane(et_s[i + 3]) + kTap - 1) >> 4;
+#pragma unroll
+                for (int t = 0; t < TILES; ++t)
+                    if (t >= t0 && t <= t1) {
+                        const int d = 16 * t + c - et;
+                        const float w = (unsigned)d < kTap ? w_s[i + q][d & 7] : 0.0f;
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, w, acc[t], 0, 0, 0);
+                    }
+            }
+        }
+    }
+    r0 += __shfl_xor(r0, 16, 64);
+    r0 += __shfl_xor(r0, 32, 64);
+    if (lane < 16 && k0 + c < g.n_p) R0[(size_t)ls * g.n_p + x_of[k0 + c]] = r0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int k = k0 + 4 * q + v;
+        if (TILES == 0 || k >= g.n_p) continue;
+        float *row = R + ((size_t)ls * g.n_p + x_of[k]) * fg.K + c;
+#pragma unroll
+        for (int t = 0; t < TILES; ++t)
+            if (16 * t < fg.K) row[16 * t] = acc[t][v];
+    }
+}
+
+// T_s(n) = mu(s) sum_a psi_a(n) e^(-rho_a(n) L_a(s)) sum_k G_a[n][k] R_as(k),
+// over the chunk's angles of one realisation (added to the stored field from
+// the second chunk on), and the primary paths' share of the backprojection.
+// One workgroup: 32 directions x 32 scatter points, its four waves every
+// fourth angle each, added in LDS; the energy sum on the matrix cores with
+// both operands read as float4 along k (lane group q takes k = 16 i + 4 q + v
+// in step v).  Rows of T run from direction -3 to N + 4, so that the next
+// stage reads eight neighbours without wrapping.
+__global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ alist,
+                                                     int n_list, int slot0, int n_slots, const float *__restrict__ R,
+                                                     const float *__restrict__ R0, float *__restrict__ T,
+                                                     float *__restrict__ pb) {
+    __shared__ f32x4 red[4][4][64];   // [wave][direction tile * 2 + point tile]
+    __shared__ float red0[4][32];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int c = lane & 15, q = lane >> 4;
+    const int n0 = blockIdx.y * 32, s0 = blockIdx.x * 32;
+    const int s[2] = {min(s0 + c, g.n_p - 1), min(s0 + 16 + c, g.n_p - 1)};
+    const int r = slot0 / n_list + blockIdx.z;
+    const int a_lo = max(0, slot0 - r * n_list), a_hi = min(n_list, slot0 + n_slots - r * n_list);
+    const bool two = n0 + 16 < fg.N;   // N is a multiple of 16
+    f32x4 tot[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) tot[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float prim[2] = {0.0f, 0.0f};
+    for (int ai = a_lo + wave; ai < a_hi; ai += 4) {
+        const int a = alist[ai], ls = r * n_list + ai - slot0;
+        const float *R1 = R + ((size_t)ls * g.n_p + s[0]) * fg.K + 4 * q, *R2 = R + ((size_t)ls * g.n_p + s[1]) * fg.K + 4 * q;
+        const float *G1 = ft.G + ((size_t)a * fg.N + n0 + c) * fg.K + 4 * q, *G2 = two ? G1 + (size_t)16 * fg.K : G1;
+        float L[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            L[u] = ft.Lx[(size_t)a * g.n_p + s[u]];
+            if (blockIdx.y == 0) prim[u] = fmaf(ft.pw[(size_t)a * g.n_p + s[u]], R0[(size_t)ls * g.n_p + s[u]], prim[u]);
+        }
+        f32x4 acc[2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 5
+        for (int k = 0; k < fg.K; k += 16) {
+            const f32x4 r1 = *reinterpret_cast<const f32x4 *>(R1 + k), r2 = *reinterpret_cast<const f32x4 *>(R2 + k);
+            const f32x4 g1 = *reinterpret_cast<const f32x4 *>(G1 + k), g2 = *reinterpret_cast<const f32x4 *>(G2 + k);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(g1[v], r1[v], acc[0][0], 0, 0, 0);
+                acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(g1[v], r2[v], acc[0][1], 0, 0, 0);
+                acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(g2[v], r1[v], acc[1][0], 0, 0, 0);
+                acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(g2[v], r2[v], acc[1][1], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (t == 1 && !two) continue;
+            const f32x4 ps = *reinterpret_cast<const f32x4 *>(ft.psi + (size_t)a * fg.N + n0 + 16 * t + 4 * q);
+            const f32x4 rh = *reinterpret_cast<const f32x4 *>(ft.rho + (size_t)a * fg.N + n0 + 16 * t + 4 * q);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    tot[t][u][v] = fmaf(acc[t][u][v], ps[v] * __builtin_amdgcn_exp2f(rh[v] * L[u]), tot[t][u][v]);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) red[wave][2 * t + u][lane] = tot[t][u];
+    if (q == 0) {
+        red0[wave][c] = prim[0];
+        red0[wave][16 + c] = prim[1];
+    }
+    __syncthreads();
+    const bool first = a_lo == 0;
+    if (blockIdx.y == 0 && threadIdx.x < 32 && s0 + threadIdx.x < g.n_p) {
+        const int i = threadIdx.x, p = ft.sup[s0 + i];
+        if (p < g.n_q) {
+            float *o = pb + (size_t)r * (fg.N / kSec + 1) * g.n_qpad + p;
+            const float v = (red0[0][i] + red0[1][i]) + (red0[2][i] + red0[3][i]);
+            *o = first ? v : *o + v;
+        }
+    }
+    // wave w finishes direction tile w / 2, point tile w % 2
+    const int t = wave >> 1, x = s0 + 16 * (wave & 1) + c;
+    if ((t == 1 && !two) || x >= g.n_p) return;
+    const f32x4 v = (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
+    const float m = ft.mu_s[x];
+    float *Tr = T + (size_t)r * (fg.N + kTap - 1) * fg.nb + ft.box[x];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = n0 + 16 * t + 4 * q + i;
+        float *o = Tr + (size_t)(n + 3) * fg.nb;
+        const float y = first ? m * v[i] : fmaf(m, v[i], *o);
+        *o = y;
+        if (n < 4) o[(size_t)fg.N * fg.nb] = y;
+        if (n >= fg.N - 3) o[-(ptrdiff_t)fg.N * fg.nb] = y;
+    }
+}
+
+// b_q: one workgroup per (block of 64 emission pixels, sector), as
+// k_flux_spread with the sums the other way round: the field's eight nodes
+// around each offset's direction, read along the pixels.  Each XCD takes a
+// run of sectors, so that its L2 holds the few rows of the field they read.
+__global__ __launch_bounds__(256) void k_flux_gather(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ beg_all,
+                                                     const int *__restrict__ rec_off, const float *__restrict__ rec_w,
+                                                     const float *__restrict__ sym, const float *__restrict__ T,
+                                                     float *__restrict__ pb) {
+    __shared__ float part[4][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n_sec = fg.N / kSec;
+    const int item = xcd_logical(blockIdx.x, gridDim.x);
+    const int sec = item / fg.n_blk, b = item - sec * fg.n_blk, r = blockIdx.y;
+    const int x = b * 64 + lane;
+    const int lin = x < g.n_p ? ft.box[x] : 0;
+    const unsigned top = (unsigned)fg.nb - 1;
+    const size_t nb = fg.nb;
+    float acc = 0.0f;
+    const int *beg = beg_all + b * fg.N + sec * kSec + wave * kWaveSec;
+    const float *__restrict__ Tk = T + ((size_t)r * (fg.N + kTap - 1) + sec * kSec + wave * kWaveSec) * nb;
+#pragma unroll 1
+    for (int k = 0; k < kWaveSec; ++k, Tk += nb) {
+        const int e0 = beg[k], e1 = beg[k + 1];
+#pragma unroll 4
+        for (int e = e0; e < e1; ++e) {
+            const float y = sym[(size_t)e * 64 + lane];
+            const unsigned at = min((unsigned)(lin + rec_off[e]), top);
+            float v = 0.0f;
+#pragma unroll
+            for (int i = 0; i < kTap; ++i) v = fmaf(rec_w[(size_t)e * kTap + i], Tk[i * nb + at], v);
+            acc = y != 0.0f ? fmaf(y, v, acc) : acc;
+        }
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && x < g.n_p) {
+        const int p = ft.sup[x];
+        if (p < g.n_q)
+            pb[((size_t)r * (n_sec + 1) + 1 + sec) * g.n_qpad + p] =
+                (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    }
+}
+
+// the primary paths' backprojection without scatter: per angle chunk of one
+// realisation (added to the stored row from the second chunk on)
+__global__ __launch_bounds__(256) void k_flux_primary_back(Geo g, FluxTables ft, const int *__restrict__ alist,
+                                                           int n_list, int slot0, int n_slots,
+                                                           const float *__restrict__ R0, float *__restrict__ pb) {
+    __shared__ float part[4][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, x = blockIdx.x * 64 + lane;
+    const int r = slot0 / n_list + blockIdx.y;
+    const int a_lo = max(0, slot0 - r * n_list), a_hi = min(n_list, slot0 + n_slots - r * n_list);
+    float s = 0.0f;
+    if (x < g.n_p)
+#pragma unroll 4
+        for (int ai = a_lo + wave; ai < a_hi; ai += 4)
+            s = fmaf(ft.pw[(size_t)alist[ai] * g.n_p + x], R0[(size_t)(r * n_list + ai - slot0) * g.n_p + x], s);
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave || x >= g.n_p) return;
+    const int p = ft.sup[x];
+    if (p >= g.n_q) return;
+    float *o = pb + (size_t)r * g.n_qpad + p;
+    const float v = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    *o = a_lo == 0 ? v : *o + v;
+}
+
+// f <- f b / sens with b the sum of the realisation's partial rows (the
+// primary's first), and the box copy of the new estimate; BACK: b itself
+template <bool BACK>
+__global__ void k_flux_update(Geo g, FluxGeo fg, FluxTables ft, int rows, const float *__restrict__ pb,
+                              const float *__restrict__ sens, float *__restrict__ f, float *__restrict__ fbox) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x, r = blockIdx.y;
+    if (x >= g.n_p) return;
+    const int q = ft.sup[x];
+    if (q >= g.n_q) return;
+    const float *p = pb + (size_t)r * rows * g.n_qpad + q;
+    float b = 0.0f;
+    for (int k0 = 0; k0 < rows; k0 += 14) {
+        float v[14];
+#pragma unroll
+        for (int k = 0; k < 14; ++k) v[k] = k0 + k < rows ? p[(size_t)(k0 + k) * g.n_qpad] : 0.0f;
+#pragma unroll
+        for (int k = 0; k < 14; ++k) b += v[k];
+    }
+    float *fp = f + (size_t)r * g.n_qpad + q;
+    if (BACK) {
+        *fp = b;
+        return;
+    }
+    const float s = sens[q];
+    float v = *fp;
+    if (s > 0.0f) v = (v * b) / s;
+    *fp = v;
+    if (fg.N) fbox[(size_t)r * fg.nb + ft.box[x]] = v;
+}
+
+// the event records of the stages above, from the sorted events: one wave per
+// block of 64 neighbours of one slot, their records ordered by energy node.
+// blk_beg [slots + 1]: first block of each slot over all subsets' slots,
+// slot_row their first rows; base[i] is the first slot of subset i (null: one
+// list).  Blocks [b0, b0 + gridDim) go to ev[row - row0].
+__global__ __launch_bounds__(64) void k_flux_events(Geo g, FluxGeo fg, FluxFit fit, int b0, int row0,
+                                                    const int *__restrict__ slot_row, const int *__restrict__ blk_beg,
+                                                    int n_slots, const int *__restrict__ base,
+                                                    const int *__restrict__ ang, const float *__restrict__ su,
+                                                    const float *__restrict__ se, const double *__restrict__ us_sorted,
+                                                    FluxEvent *__restrict__ ev, FluxBlock *__restrict__ blk) {
+    __shared__ int key[64];
+    const int b = b0 + blockIdx.x, lane = threadIdx.x;
+    int lo = 0, hi = n_slots;   // the last slot whose blocks begin at or before b
+    while (hi - lo > 1) { const int m = (lo + hi) >> 1; if (blk_beg[m] <= b) lo = m; else hi = m; }
+    const int first = slot_row[lo] + 64 * (b - blk_beg[lo]);
+    const int n = min(64, slot_row[lo + 1] - first);
+    const int row = first + min(lane, n - 1);
+    FluxEvent e;
+    const int a = ang[row];
+    e.slot = lo - (base ? base[a % g.n_subsets] : 0);
+    e.row = row;
+    e.u = ((double)su[row] - 0.5 * g.n_bins) * g.bin_cm;
+    const double en = (double)se[row] + g.e_c;
+    // the node interval of the energy and the weights of its eight nodes
+    const double t = (en - fg.e_lo) / fg.h;
+    e.et = min(max((int)t, 0), max(fg.K - 8, 0));
+    if (fg.N) {
+        double w[kTap];
+        fit_weights(fit, t - e.et, w);
+        const double y = en - fg.e_mid;
+#pragma unroll
+        for (int i = 0; i < kTap; ++i) {
+            const double yi = fg.e_lo + (e.et + i - 3) * fg.h - fg.e_mid;
+            e.w[i] = (float)(w[i] * exp2(g.c2 * (yi * yi - y * y)));
+        }
+    }
+    const double d0 = en - g.e0;
+    e.g0 = (float)(exp2(-g.c2 * d0 * d0) / (sqrt(2.0 * M_PI) * g.sig_e));
+    const double *us = us_sorted + (size_t)a * g.n_p;
+    const double reach = 3.0 * g.sig_u;
+    int l = 0, h = g.n_p;     // first rank with us > u - reach
+    while (l < h) { const int m = (l + h) >> 1; if (us[m] > e.u - reach) h = m; else l = m + 1; }
+    e.r0 = l;
+    h = g.n_p;                // first rank with us >= u + reach
+    while (l < h) { const int m = (l + h) >> 1; if (us[m] >= e.u + reach) h = m; else l = m + 1; }
+    e.r1 = l;
+    key[lane] = e.et;
+    __syncthreads();
+    int at = 0;
+    for (int i = 0; i < n; ++i) at += key[i] < e.et || (key[i] == e.et && i < lane);
+    if (lane < n) ev[first + at - row0] = e;
+    const double u0 = __shfl(e.u, 0, 64), u1 = __shfl(e.u, n - 1, 64);
+    if (lane == 0) blk[b] = FluxBlock{u0, u1, e.slot, first, n, 0};
+}
+
+// ---------------------------------------------------------------- host side
+// weights exact for exponents at the Chebyshev points of [-b, b] (per node
+// spacing): the inverse of their values at the nodes -3 .. 4, in extended
+// precision
+static void fit_exponentials(double b, FluxFit &fit) {
+    b = std::max(b, 0.4);   // (closer exponents would lose digits, and gain nothing)
+    long double A[kTap][2 * kTap];
+    for (int m = 0; m < kTap; ++m) {
+        fit.b[m] = b * cos((2 * m + 1) * M_PI / (2 * kTap));
+        for (int i = 0; i < kTap; ++i) {
+            A[m][i] = expl((long double)fit.b[m] * (i - 3));
+            A[m][kTap + i] = m == i;
+        }
+    }
+    for (int k = 0; k < kTap; ++k) {
+        int p = k;
+        for (int j = k + 1; j < kTap; ++j)
+            if (fabsl(A[j][k]) > fabsl(A[p][k])) p = j;
+        for (int i = 0; i < 2 * kTap; ++i) std::swap(A[k][i], A[p][i]);
+        const long double d = A[k][k];
+        for (int i = 0; i < 2 * kTap; ++i) A[k][i] /= d;
+        for (int j = 0; j < kTap; ++j) {
+            if (j == k) continue;
+            const long double f = A[j][k];
+            for (int i = 0; i < 2 * kTap; ++i) A[j][i] -= f * A[k][i];
+        }
+    }
+    for (int i = 0; i < kTap; ++i)
+        for (int m = 0; m < kTap; ++m) fit.v[i][m] = (double)A[i][kTap + m];
+}
+
+bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order) {
+    int x0 = g.nx, x1 = -1, y0 = g.ny, y1 = -1;
+    for (int pix : p_pix) {
+        const int i = pix % g.nx, j = pix / g.nx;
+        x0 = std::min(x0, i); x1 = std::max(x1, i);
+        y0 = std::min(y0, j); y1 = std::max(y1, j);
+    }
+    fg.x0 = x0; fg.y0 = y0; fg.W = x1 - x0 + 1; fg.Hh = y1 - y0 + 1;
+    fg.nb = fg.W * fg.Hh;
+    // the flux order: strips of kStrip columns, row by row within a strip
+    std::vector<int> at((size_t)fg.nb, -1);
+    for (int p = 0; p < g.n_p; ++p) at[(size_t)(p_pix[p] / g.nx - y0) * fg.W + (p_pix[p] % g.nx - x0)] = p;
+    order.clear();
+    for (int i0 = 0; i0 < fg.W; i0 += kStrip)
+        for (int j = 0; j < fg.Hh; ++j)
+            for (int i = i0; i < std::min(fg.W, i0 + kStrip); ++i)
+                if (at[(size_t)j * fg.W + i] >= 0) order.push_back(at[(size_t)j * fg.W + i]);
+    fg.n_blk = (g.n_p + 63) / 64;
+    fg.np64 = fg.n_blk * 64;
+    fg.inv_zk = (float)(1.0 / g.zk);
+    fg.e_lo = g.win_lo;
+    fg.N = fg.K = 0;
+    fg.h = 1.0;
+    if (!g.scatter) return true;
+    // the steepest logarithmic slope over directions and window energies
+    auto end_energy = [&](double ph) { return g.e0 / (1.0 + g.kappa * (1.0 - cos(ph))); };
+    double slope = 0.0;
+    for (int i = 0; i < 2048; ++i) {
+        const double ph = M_PI * i / 2048, ep = end_energy(ph);
+        const double far = std::max(fabs(g.win_lo - ep), fabs(g.win_hi - ep));
+        slope = std::max(slope, far * ep * ep * g.kappa * sin(ph) / g.e0);
+    }
+    slope /= g.sig_e * g.sig_e;
+    // direction nodes: slope x spacing at most 0.79, a multiple of 48 (whole
+    // matrix tiles, an even number of sectors)
+    const double n = std::max(2.0 * M_PI * slope / 0.79, 48.0);
+    // energy nodes: largest exponent x spacing at most 0.70, eight nodes more
+    // than intervals, a multiple of 16
+    fg.e_mid = 0.5 * (g.e0 + end_energy(M_PI));
+    const double b_e = 0.5 * (g.e0 - end_energy(M_PI)) / (g.sig_e * g.sig_e);
+    const double k = (g.win_hi - g.win_lo) * b_e / 0.70 + 8.0;
+    if (!(n <= kFluxMaxN) || !(k <= kFluxMaxK)) return false;
+    fg.N = (int)ceil(n / 48.0) * 48;
+    fg.K = std::max(32, (int)ceil(k / 16.0) * 16);
+    fg.h = (g.win_hi - g.win_lo) / (fg.K - 8);
+    // (the directions' exponents fill 0.6 of the range: the near tails,
+    // which carry the sums, at some cost in the far ones)
+    fit_exponentials(0.6 * slope * 2.0 * M_PI / fg.N, fg.direction);
+    fit_exponentials(b_e * fg.h, fg.energy);
+    return (int64_t)g.n_angles * fg.N * fg.K <= kFluxMaxG;
+}
+
+void free_flux(FluxTables &ft) {
+    for (void *p : {(void *)ft.sup, (void *)ft.box, (void *)ft.mu_s, (void *)ft.rank_of, (void *)ft.x_of, (void *)ft.pw,
+                    (void *)ft.pwr, (void *)ft.Lx, (void *)ft.beg, (void *)ft.rec_off, (void *)ft.rec_w, (void *)ft.sym,
+                    (void *)ft.G, (void *)ft.psi, (void *)ft.rho})
+        hipFree(p);
+    ft = FluxTables{};
+}
+
+hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> &order, const Tables &t, FluxTables &ft,
+                      hipStream_t st, int64_t &bytes) {
+    const FluxGeo &fg = fm;
+    hipError_t e = hipSuccess;
+    int *cnt = nullptr, *pos = nullptr;
+    int2 *off = nullptr;
+    void *tmp = nullptr;
+    int64_t held = 0;
+    auto done = [&](hipError_t err) {
+        hipFree(cnt); hipFree(off); hipFree(tmp); hipFree(pos);
+        if (err != hipSuccess) { hipStreamSynchronize(st); free_flux(ft); }
+        else bytes += held;
+        return err;
+    };
+    auto al = [&](auto &p, size_t n) {
+        held += (int64_t)(n * sizeof(*p));
+        return e = hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(*p));
+    };
+    const size_t na_np = (size_t)g.n_angles * g.n_p;
+    if (al(ft.sup, g.n_p) || al(ft.box, g.n_p) || al(ft.mu_s, g.n_p) || al(ft.rank_of, na_np) || al(ft.x_of, na_np) ||
+        al(ft.pw, na_np) || al(ft.pwr, na_np) || al(ft.Lx, na_np))
+        return done(e);
+    if ((e = hipMalloc(&pos, sizeof(int) * g.n_p)) != hipSuccess) return done(e);
+    if ((e = hipMemcpyAsync(ft.sup, order.data(), sizeof(int) * g.n_p, hipMemcpyHostToDevice, st)) != hipSuccess) return done(e);
+    hipLaunchKernelGGL(k_flux_support, dim3((g.n_p + 255) / 256), dim3(256), 0, st, g, fg, ft.sup, t.p_pix, t.mu, pos,
+                       ft.box, ft.mu_s);
+    hipLaunchKernelGGL(k_flux_ranks, dim3((unsigned)((na_np + 255) / 256)), dim3(256), 0, st, g, pos, t.s_sorted, t.Ld,
+                       ft.rank_of, ft.x_of, ft.pw, ft.pwr, ft.Lx);
+    if ((e = hipGetLastError()) != hipSuccess) return done(e);
+    if (!g.scatter) return done(hipStreamSynchronize(st));
+    const size_t an = (size_t)g.n_angles * fg.N;
+    if (al(ft.psi, an) || al(ft.rho, an) || al(ft.G, an * fg.K)) return done(e);
+    hipLaunchKernelGGL(k_flux_angles, dim3(fg.N / 16, g.n_angles), dim3(256), 0, st, g, fg, t.cs, ft.psi, ft.rho, ft.G);
+    if ((e = hipGetLastError()) != hipSuccess) return done(e);
+    // offsets of one direction interval: the lattice points of a sector of
+    // the box's diagonal, with room for the lattice lines along it
+    const double diag = sqrt((double)fg.W * fg.W + (double)fg.Hh * fg.Hh);
+    const int cap = (int)std::min(0.5 * diag * diag * 2.0 * M_PI / fg.N + 4.0 * diag + 64.0,
+                                  4.0 * (double)fg.W * fg.Hh);
+    const int nbin = fg.n_blk * fg.N;
+    size_t tmp_bytes = 0;
+    if ((e = hipMalloc(&cnt, sizeof(int) * fg.N)) != hipSuccess) return done(e);
+    if ((e = hipMalloc(&off, sizeof(int2) * (size_t)fg.N * cap)) != hipSuccess) return done(e);
+    if (al(ft.beg, (size_t)nbin + 1)) return done(e);
+    if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, ft.beg, ft.beg, nbin + 1, st)) != hipSuccess) return done(e);
+    if ((e = hipMalloc(&tmp, tmp_bytes)) != hipSuccess) return done(e);
+    hipLaunchKernelGGL(k_flux_offsets, dim3(fg.N), dim3(256), 0, st, fg.W, fg.Hh, fg.N, cap, cnt, off);
+    const dim3 grid(fg.N, fg.n_blk);
+    const int *q_of_pix = t.p_pix + g.n_p;
+    hipLaunchKernelGGL(k_flux_pairs<0>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
+                       cap, ft.beg, (int *)nullptr, (float *)nullptr, (float *)nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return done(e);
+    if ((e = launch_fill(reinterpret_cast<float *>(ft.beg + nbin), 1, 0.0f, st)) != hipSuccess) return done(e);
+    if ((e = hipcub::DeviceScan::ExclusiveSum(tmp, tmp_bytes, ft.beg, ft.beg, nbin + 1, st)) != hipSuccess) return done(e);
+    int total = 0;
+    if ((e = hipMemcpyAsync(&total, ft.beg + nbin, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return done(e);
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return done(e);
+    if (al(ft.rec_off, total) || al(ft.rec_w, (size_t)total * kTap) || al(ft.sym, (size_t)total * 64)) return done(e);
+    hipLaunchKernelGGL(k_flux_pairs<1>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
+                       cap, ft.beg, ft.rec_off, ft.rec_w, ft.sym);
+    if ((e = hipGetLastError()) != hipSuccess) return done(e);
+    return done(hipStreamSynchronize(st));
+}
+
+static size_t up64(size_t n) { return (n + 63) & ~size_t(63); }
+int flux_rows(const FluxGeo &fg) { return fg.N / kSec + 1; }
+static size_t per_real(const Geo &g, const FluxGeo &fg) {
+    return up64(fg.N ? fg.nb : 0) + up64((size_t)2 * fg.N * fg.np64) + up64(fg.N ? (size_t)(fg.N + kTap - 1) * fg.nb : 0) +
+           up64((size_t)flux_rows(fg) * g.n_qpad);
+}
+static size_t per_slot(const Geo &g, const FluxGeo &fg) { return (size_t)g.n_p * (fg.K + 1); }
+
+// Angles of one realisation that run together: all of the list, or as many
+// as have spectra of 32 MB (a function of the geometry alone, so that a
+// realisation's sums are the same in any batch and workspace).
+int flux_angles(const Geo &g, const FluxGeo &fg, int n_list) {
+    return (int)std::min<size_t>(n_list, std::max<size_t>(1, (size_t(8) << 20) / per_slot(g, fg)));
+}
+
+size_t flux_ws_floats(const Geo &g, const FluxGeo &fg, int n_real, int n_slots) {
+    return n_real * per_real(g, fg) + (size_t)n_slots * per_slot(g, fg);
+}
+
+// realisations whose fields fit a workspace beside one chunk of angles (0: none)
+int flux_group(const Geo &g, const FluxGeo &fg, size_t floats, int n_real, int n_list) {
+    const size_t one = flux_angles(g, fg, n_list) * per_slot(g, fg);
+    return (int)std::min<size_t>(n_real, (floats > one ? floats - one : 0) / per_real(g, fg));
+}
+
+// event records of blocks [b0, b1) of a set, at ev[row - row0]
+hipError_t flux_events(const Geo &g, const FluxModel &fg, int b0, int b1, int row0, const int *slot_row,
+                       const int *blk_beg, int n_slots, const int *base, const int *ang, const float *su,
+                       const float *se, const Tables &t, FluxEvent *ev, FluxBlock *blk, hipStream_t st) {
+    if (b1 <= b0) return hipSuccess;
+    hipLaunchKernelGGL(k_flux_events, dim3(b1 - b0), dim3(64), 0, st, g, (const FluxGeo &)fg, fg.energy, b0, row0, slot_row,
+                       blk_beg, n_slots, base, ang, su, se, t.us_sorted, ev, blk);
+    return hipGetLastError();
+}
+
+namespace {
+
+// the workspace of one group of realisations
+struct Carve {
+    float *fbox, *I, *T, *pb, *S, *SP;
+    int slots;   // slots whose spectra fit
+    Carve(const Geo &g, const FluxGeo &fg, float *ws, size_t floats, int n_real) {
+        float *p = ws;
+        auto take = [&](size_t per) { float *q = p; p += n_real * up64(per); return q; };
+        fbox = take(fg.N ? fg.nb : 0);
+        I = take((size_t)2 * fg.N * fg.np64);
+        T = take(fg.N ? (size_t)(fg.N + kTap - 1) * fg.nb : 0);
+        pb = take((size_t)flux_rows(fg) * g.n_qpad);
+        const size_t used = (size_t)(p - ws), room = floats > used ? floats - used : 0;
+        slots = (int)std::min<size_t>(room / per_slot(g, fg), 1 << 30);
+        S = p;
+        SP = p + (size_t)slots * g.n_p * fg.K;
+    }
+};
+
+// means of blocks [b0, b1), whose records begin at row row0
+void launch_means(const FluxRun &p, int slot_base, int s0, int b0, int b1, int row0, const Carve &w, const float *f) {
+    const Geo &g = *p.g;
+    const FluxGeo &fg = *p.fg;
+    if (fg.N) {
+        hipLaunchKernelGGL(k_flux_means<3>, dim3(b1 - b0), dim3(256), 0, p.st, g, fg, p.ev, p.blk + b0, p.t->us_sorted, p.alist,
+                           p.n_list, slot_base, s0, row0, p.row_base, w.S, w.SP, p.mean, p.inv, p.skipped);
+        return;
+    }
+    // lanes per event: about as many as the ends it reaches
+    const double ends = g.n_p * 6.0 * g.sig_u / std::max(std::max(fg.W, fg.Hh) * g.dx, 6.0 * g.sig_u);
+    const int lanes = ends < 48.0 ? 16 : ends < 160.0 ? 32 : 64;
+    const int j0 = p.blk_rows(b0), j1 = p.blk_rows(b1);
+    auto *kern = lanes == 16 ? k_flux_means_primary<16> : lanes == 32 ? k_flux_means_primary<32> : k_flux_means_primary<64>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(((size_t)(j1 - j0) * lanes + 255) / 256)), dim3(256), 0, p.st, g, fg, *p.ft, p.ev,
+                       p.t->us_sorted, p.t->s_sorted, p.alist, p.n_list, slot_base, j0, j1, row0, p.row_base, f, p.mean,
+                       p.inv, p.skipped);
+}
+
+}  // namespace
+
+// row of a block's first event (the host's copy of the slots' first rows and blocks)
+int FluxRun::blk_rows(int b) const {
+    const int *k = std::upper_bound(blk_host, blk_host + n_real * n_list, b) - 1;   // the last slot at or before b
+    const int s = (int)(k - blk_host);
+    return std::min(slot_rows[s] + 64 * (b - blk_host[s]), slot_rows[s + 1]);
+}
+
+hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
+    const Geo &g = *p.g;
+    const FluxGeo &fg = *p.fg;   // (without the fits: kernel arguments)
+    const FluxTables &ft = *p.ft;
+    const bool sc = fg.N > 0;
+    const int grp = flux_group(g, fg, p.ws_floats, p.n_real, p.n_list), n_rows = flux_rows(fg);
+    const int ca = flux_angles(g, fg, p.n_list);
+    if (grp < 1) return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    for (int ra = 0; ra < p.n_real; ra += grp) {
+        const int nr = std::min(grp, p.n_real - ra);
+        const Carve w(g, fg, p.ws, p.ws_floats, nr);
+        const int n_slots = nr * p.n_list, sb = ra * p.n_list;
+        float *f = p.f + (size_t)ra * g.n_qpad;
+        if (p.means && sc) {
+            e = stage(0, [&] {
+                // the box copy of the estimate: the previous sub-iteration's
+                // update left it, unless the workspace served others since
+                if (p.box || grp < p.n_real)
+                    hipLaunchKernelGGL(k_flux_box, dim3((g.n_p + 255) / 256, nr), dim3(256), 0, p.st, g, fg, ft, f, w.fbox);
+                hipLaunchKernelGGL(k_flux_spread, dim3(fg.n_blk, fg.N / kSec, nr), dim3(256), 0, p.st, g, fg, ft, ft.beg,
+                                   ft.rec_off, ft.rec_w, ft.sym, w.fbox, w.I);
+                return hipGetLastError();
+            });
+            if (e != hipSuccess) return e;
+        }
+        // chunks of slots: whole realisations, or ca angles of one
+        for (int s0 = 0, s1; s0 < n_slots; s0 = s1) {
+            if (ca == p.n_list) s1 = std::min(n_slots, s0 + std::max(1, w.slots / p.n_list) * p.n_list);
+            else s1 = std::min(s0 + ca, (s0 / p.n_list + 1) * p.n_list);
+            const int ns = s1 - s0;
+            if (ns > w.slots) return hipErrorInvalidValue;
+            if (p.means) {
+                const int b0 = p.blk_host[sb + s0], b1 = p.blk_host[sb + s1];
+                e = stage(0, [&] {
+                    if (sc)
+                        hipLaunchKernelGGL(k_flux_spectra, dim3((g.n_p + 31) / 32, ns, (fg.K + 16 * kSpecTiles - 1) / (16 * kSpecTiles)),
+                                           dim3(256), 0,
+                                           p.st, g, fg, ft, p.alist, p.n_list, s0, w.I, f, w.S, w.SP);
+                    for (int a = b0, b; a < b1; a = b) {
+                        b = p.fill ? std::min(b1, a + p.ev_cap / 64) : b1;
+                        hipError_t fe = hipSuccess;
+                        if (p.fill && (fe = p.fill(a, b)) != hipSuccess) return fe;
+                        launch_means(p, sb, s0, a, b, p.fill ? p.blk_rows(a) : 0, w, f);
+                    }
+                    return hipGetLastError();
+                });
+                if (e != hipSuccess) return e;
+            }
+            if (!adjoint) continue;
+            e = stage(1, [&] {
+                const dim3 ag((g.n_p + 15) / 16, ns);
+                const int zr = (s1 - 1) / p.n_list - s0 / p.n_list + 1;
+                // 16-node tiles of the energy nodes held in registers
+                auto *adj = !sc ? k_flux_adjoint<0> : fg.K <= 96 ? k_flux_adjoint<6> : k_flux_adjoint<kMaxTiles>;
+                hipLaunchKernelGGL(adj, ag, dim3(64), 0, p.st, g, fg, ft, p.ev, p.blk, p.t->us_sorted, p.alist, p.blk_beg + sb,
+                                   p.n_list, s0, p.row_base, p.inv, w.S, w.SP);
+                if (sc) {
+                    hipLaunchKernelGGL(k_flux_fields, dim3((g.n_p + 31) / 32, (fg.N + 31) / 32, zr), dim3(256), 0, p.st, g,
+                                       fg, ft, p.alist, p.n_list, s0, ns, w.S, w.SP, w.T, w.pb);
+                } else {
+                    hipLaunchKernelGGL(k_flux_primary_back, dim3(fg.n_blk, zr), dim3(256), 0, p.st, g, ft, p.alist, p.n_list,
+                                       s0, ns, w.SP, w.pb);
+                }
+                return hipGetLastError();
+            });
+            if (e != hipSuccess) return e;
+        }
+        if (!adjoint) continue;
+        if (sc) {
+            e = stage(1, [&] {
+                hipLaunchKernelGGL(k_flux_gather, dim3(fg.n_blk * (fg.N / kSec), nr), dim3(256), 0, p.st, g, fg, ft, ft.beg,
+                                   ft.rec_off, ft.rec_w, ft.sym, w.T, w.pb);
+                return hipGetLastError();
+            });
+            if (e != hipSuccess) return e;
+        }
+        // the log-likelihood reads the means and the estimate before its update
+        if (p.want_ll && (e = launch_loglik(g, p.rrange + ra, nr, p.mean, f, p.sens, p.ll + ra, p.st)) != hipSuccess)
+            return e;
+        e = stage(2, [&] {
+            const dim3 ug((g.n_p + 63) / 64, nr);
+            auto *kern = p.sens ? k_flux_update<false> : k_flux_update<true>;
+            hipLaunchKernelGGL(kern, ug, dim3(64), 0, p.st, g, fg, ft, n_rows, w.pb, p.sens, f, w.fbox);
+            return hipGetLastError();
+        });
+        if (e != hipSuccess) return e;
+    }
+    return e;
+}
+
+}  // namespace lmo

@@ -119,10 +119,118 @@ hipError_t scratch_address(void **ptr);
 // bytes of the scratch array that forward_noalloc needs for n events
 hipError_t forward_noalloc_bytes(const Geo &g, int64_t n, int ev_tile, size_t &need);
 // per-event means of the (validated) events at the image, in the caller's
-// event order, every buffer in the scratch array; synchronises st
+// event order, every buffer in the scratch array (with flux: its stages on
+// the context's workspace, the rest filled in here); synchronises st
 hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &ev, int ev_tile, const float *image,
                            float *mean_out, unsigned long long *skipped, hipStream_t st, int64_t &terms,
-                           int64_t &useful);
+                           int64_t &useful, struct FluxRun *flux);
+
+// ---- sub-iterations through directional flux (flux.hip) ----
+constexpr int kFluxMaxN = 960;             // direction nodes
+constexpr int kFluxMaxK = 192;             // energy nodes (48 KB of LDS in the adjoint)
+constexpr int64_t kFluxMaxG = 1 << 27;     // entries of the energy-response table (512 MB)
+
+// eight-point interpolation exact for e^(b_m x): w_i = sum_m v[i][m] e^(b_m t)
+struct FluxFit {
+    double b[8], v[8][8];
+};
+
+struct FluxGeo {
+    int N, K;              // direction and energy nodes (0: primary paths only)
+    double e_lo, h;        // energy node k at e_lo + (k - 3) h
+    double e_mid;          // middle of the end energies
+    int x0, y0, W, Hh, nb; // the support's bounding box
+    int n_blk, np64;       // blocks of 64 support pixels
+    float inv_zk;
+};
+
+// with what only the table and event builds need
+struct FluxModel : FluxGeo {
+    FluxFit direction, energy;
+};
+
+// per attenuation map; x is the flux order's index of a support pixel
+struct FluxTables {
+    int *sup = nullptr;        // [n_p] support index of x
+    int *box = nullptr;        // [n_p] index in the bounding box
+    float *mu_s = nullptr;     // [n_p]
+    int *rank_of = nullptr;    // [n_angles][n_p] rank of x
+    int *x_of = nullptr;       // [n_angles][n_p] x by rank
+    float *pw = nullptr, *pwr = nullptr;   // [n_angles][n_p] primary path weight by x, by rank
+    float *Lx = nullptr;       // [n_angles][n_p] attenuation to the detector
+    int *beg = nullptr;        // [n_blk * N + 1] first pair record of each (block, direction interval)
+    int *rec_off = nullptr;    // [records] box offset
+    float *rec_w = nullptr;    // [records][8] direction weights
+    float *sym = nullptr;      // [records][64] symmetric pair factors
+    float *G = nullptr;        // [n_angles][N][K]
+    float *psi = nullptr, *rho = nullptr;   // [n_angles][N]
+};
+
+struct FluxEvent {
+    double u;        // position, cm
+    int slot;        // its (realisation, angle) slot in its subset
+    int row;         // its row of the set
+    int r0, r1;      // path-end ranks its response reaches
+    int et;          // first of its eight energy nodes
+    float g0;        // energy response of the primary path
+    float w[8];      // their interpolation weights
+};
+
+// 64 events (fewer at a slot's end) that are neighbours in position, their
+// records ordered by energy
+struct FluxBlock {
+    double u0, u1;   // first and last position
+    int slot, row, n, pad;
+};
+
+// One sub-iteration's inputs and outputs.  Slots are (realisation, angle of
+// the list) pairs, realisation-major; their events are consecutive rows.
+struct FluxRun {
+    const Geo *g;
+    const FluxModel *fg;
+    const FluxTables *ft;
+    const Tables *t;
+    float *ws;                 // workspace
+    size_t ws_floats;
+    const int *alist;          // device: angles of the list
+    int n_list, n_real;
+    const int *slot_rows;      // host [n_real * n_list + 1]: first row of each slot, counted over the set
+    const int *blk_host;       // host [n_real * n_list + 1]: first block of each slot, counted over the set
+    const int *blk_beg;        // the same on the device
+    const FluxEvent *ev;       // event records by row of the set
+    const FluxBlock *blk;      // event blocks of the set
+    int row_base;              // the sub-iteration's first row
+    // or, for callers without room for every record: fills the records of
+    // blocks [a, b), at most ev_cap events, at ev[0] (forward only)
+    std::function<hipError_t(int, int)> fill;
+    int ev_cap = 0;
+    int blk_rows(int b) const;
+    bool means;                // form the event means (else inv holds the backprojection's weights)
+    bool box;                  // the estimate is new to the workspace
+    float *f;                  // [n_real][n_qpad]
+    float *mean, *inv;
+    unsigned long long *skipped;
+    const float *sens;         // update f; null: f receives the backprojection
+    bool want_ll;
+    const int *rrange;         // device [n_real + 1]
+    double *ll;
+    hipStream_t st;
+};
+// wraps the launches of one stage (0 means, 1 backprojection, 2 update)
+using FluxStage = std::function<hipError_t(int, const std::function<hipError_t()> &)>;
+
+// false: outside the nodes' limits; order: the flux order
+bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order);
+hipError_t build_flux(const Geo &g, const FluxModel &fg, const std::vector<int> &order, const Tables &t, FluxTables &ft,
+                      hipStream_t st, int64_t &bytes);
+void free_flux(FluxTables &ft);
+int flux_angles(const Geo &g, const FluxGeo &fg, int n_list);
+size_t flux_ws_floats(const Geo &g, const FluxGeo &fg, int n_real, int n_slots);
+int flux_group(const Geo &g, const FluxGeo &fg, size_t floats, int n_real, int n_list);
+hipError_t flux_events(const Geo &g, const FluxModel &fg, int b0, int b1, int row0, const int *slot_row,
+                       const int *blk_beg, int n_slots, const int *base, const int *ang, const float *su,
+                       const float *se, const Tables &t, FluxEvent *ev, FluxBlock *blk, hipStream_t st);
+hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage);
 
 // ---- binned data (binned.hip) ----
 hipError_t launch_binned_rows(const Geo &g, const Tables &t, int n_pos, const double *edges_dev, int n_e,
@@ -229,6 +337,8 @@ struct EvSet {
     float *e = nullptr;      // energy minus the encoding centre, keV
     float *efac = nullptr;   // 2^(-c2 e^2) / Z_K per event
     int *orig = nullptr;     // original event index
+    struct FluxEvent *fev = nullptr;   // event records and blocks of the flux stages (null: term by term)
+    struct FluxBlock *fblk = nullptr;
     // per subset
     std::vector<int> row_off;               // [n_subsets+1] rows of each subset
     std::vector<int> tile_off;              // [n_subsets+1]

@@ -110,7 +110,7 @@ hipError_t forward_noalloc_bytes(const Geo &g, int64_t n, int ev_tile, size_t &n
 
 hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &ev, int ev_tile, const float *image,
                            float *mean_out, unsigned long long *skipped, hipStream_t st, int64_t &terms,
-                           int64_t &useful) {
+                           int64_t &useful, FluxRun *flux) {
     terms = useful = 0;
     void *base = nullptr;
     hipError_t e = scratch_address(&base);
@@ -154,13 +154,57 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
     if (nt > L.max_tiles) return hipErrorInvalidValue;
     if ((e = hipMemcpyAsync(tiles, th.data(), sizeof(Tile) * nt, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
     if ((e = launch_tile_ranks(g, tiles, nt, t.us_sorted, u, terms_d, useful_d, st)) != hipSuccess) return e;
-    // the forward projection chunk by chunk of whole tiles, in the transient
-    // region (the sort's buffers are dead by now in stream order)
+    // in the transient region (the sort's buffers are dead by now in stream
+    // order): the flux stages' angle lists and a run of event records at a time, or
+    std::vector<int> lists;
+    if (flux) {
+        // the angles with events, their first rows and first blocks
+        std::vector<int> beg(1, 0), blk(1, 0);
+        for (int a = 0; a < g.n_angles; ++a)
+            if (cnt[a] > 0) {
+                lists.push_back(a);
+                beg.push_back(beg.back() + cnt[a]);
+                blk.push_back(blk.back() + (cnt[a] + 63) / 64);
+            }
+        const int nl = (int)lists.size(), n_blk = blk.back();
+        lists.insert(lists.end(), beg.begin(), beg.end());
+        lists.insert(lists.end(), blk.begin(), blk.end());
+        int *d = reinterpret_cast<int *>(b + L.trans);
+        if ((e = hipMemcpyAsync(d, lists.data(), sizeof(int) * lists.size(), hipMemcpyHostToDevice, st)) != hipSuccess) return e;
+        const size_t at_blk = up(L.trans + sizeof(int) * lists.size()), at = up(at_blk + sizeof(FluxBlock) * n_blk);
+        FluxBlock *fblk = reinterpret_cast<FluxBlock *>(b + at_blk);
+        FluxEvent *fev = reinterpret_cast<FluxEvent *>(b + at);
+        flux->alist = d;
+        flux->n_list = nl;
+        flux->n_real = 1;
+        flux->slot_rows = lists.data() + nl;
+        flux->blk_host = lists.data() + 2 * nl + 1;
+        flux->blk_beg = d + 2 * nl + 1;
+        flux->ev = fev;
+        flux->blk = fblk;
+        if (at + 64 * sizeof(FluxEvent) > kScratchSize) return hipErrorInvalidValue;
+        flux->ev_cap = (int)std::min<size_t>((kScratchSize - at) / sizeof(FluxEvent), (size_t)64 * n_blk);
+        flux->fill = [&, fblk, fev, d, nl](int a, int z) {
+            return flux_events(g, *flux->fg, a, z, flux->blk_rows(a), d + nl, flux->blk_beg, nl, nullptr, ang, u, en, t, fev,
+                               fblk, st);
+        };
+        flux->box = true;
+        flux->means = true;
+        flux->f = f;
+        flux->mean = mean;
+        flux->inv = inv;
+        flux->skipped = skipped;
+        flux->st = st;
+        e = flux_run(*flux, false, [](int, const std::function<hipError_t()> &launch) { return launch(); });
+        flux->fill = nullptr;
+        if (e != hipSuccess) return e;
+    }
+    // the forward projection chunk by chunk of whole tiles
     float *H = reinterpret_cast<float *>(b + L.trans);
     const int64_t rows_max = L.chunk_rows;
     float *pmean = reinterpret_cast<float *>(b + L.trans + up(sizeof(float) * (size_t)rows_max * g.n_qpad));
     const int groups = forward_groups(g);
-    for (int t0 = 0; t0 < nt;) {
+    for (int t0 = flux ? nt : 0; t0 < nt;) {
         const int row_base = th[t0].e0;
         int rows = 0, t1 = t0;
         while (t1 < nt && rows + th[t1].n <= rows_max) rows += th[t1++].n;

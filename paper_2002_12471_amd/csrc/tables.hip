@@ -134,7 +134,12 @@ __global__ void k_rank(Geo g, const int *__restrict__ p_pix, const double *__res
 __device__ inline float2 path_code(const Geo &g, PathW p, double log2_gnorm) {
     if (!(p.w > 0.0)) return make_float2(kNegHuge, 0.0f);
     const double ec = p.ep - g.e_c;
-    return make_float2((float)(log2(p.w) + log2_gnorm - g.c2 * ec * ec), (float)(2.0 * g.c2 * ec));
+    // beta's rounding is taken up by alpha at the path's own end energy, where
+    // its events are (the primary paths share one beta, whose rounding would
+    // otherwise shift every photopeak mean by 1.9e-7 the same way)
+    const double b = 2.0 * g.c2 * ec;
+    const float beta = (float)b;
+    return make_float2((float)(log2(p.w) + log2_gnorm - g.c2 * ec * ec + (b - (double)beta) * ec), beta);
 }
 
 // Path table and per-angle sensitivities.  One thread per (angle, emission
