@@ -41,6 +41,8 @@ struct lmosem_ctx {
     std::vector<int> flux_order;   // the flux order's support indices
     float *fws = nullptr;          // workspace of one realisation
     size_t fws_floats = 0;
+    int64_t flux_bytes = 0;
+    bool lazy_table = false;       // the path table is filled for the first row cache only
     // HIP graphs: one captured iteration per prepared set, replayed on an
     // internal stream ordered after the caller's stream by events
     bool graphs = true;
@@ -259,15 +261,19 @@ std::string cap_msg(const lmosem_ctx *c, const char *what, int64_t more) {
            " device bytes, above its cap of " + std::to_string(c->mem_cap) + " (lmosem_set_memory_cap)";
 }
 
-// Whether a sub-iteration of so many terms runs faster through the flux
-// stages than term by term (8.6e12 terms/s and about 20 us of launches): the
-// stages' own time hardly depends on the events; measured 110 us on a support
-// of 156 pixels, 235 us on 1436, 880 us on 5736.  Without scatter they always
-// do (the term-by-term kernels visit every path end all the same).
-bool flux_pays(const Geo &g, int64_t terms) {
-    const double kpix = 1e-3 * g.n_p;
-    return !g.scatter || 20.0 + terms / 8.6e6 > 90.0 + 60.0 * kpix * sqrt(kpix);
-}
+// Supports whose every list-mode call runs through the flux stages: from 512
+// pixels the path table that the term-by-term kernels read takes more time to
+// fill (6.4 ms and 2 GB on 1436 pixels) than they save on small event sets.
+constexpr int kFluxAlways = 512;
+
+bool flux_always(const lmosem_ctx *c) { return c->flux_fits && c->g.n_p >= kFluxAlways; }
+
+// The terms from which a sub-iteration runs faster through the flux stages
+// than term by term (8.6e12 terms/s and about 20 us of launches): the
+// stages' own time hardly depends on the events, 110 us on a support of 156
+// pixels.  Without scatter they always do (the term-by-term kernels visit
+// every path end all the same).
+int64_t flux_from(const lmosem_ctx *c) { return flux_always(c) || !c->g.scatter ? -1 : 800'000'000; }
 
 // The angle lists, slots and event records of a flux set: all angles of each
 // subset, or (one given subset) the angles that have events; and the set's own
@@ -359,7 +365,7 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
         free_set(s);
         return e == hipErrorOutOfMemory ? set_err(c, LMOSEM_ENOMEM, why) : set_err(c, LMOSEM_EDEVICE, why);
     }
-    s->flux = c->flux && flux_pays(c->g, *std::max_element(s->s.terms_sub.begin(), s->s.terms_sub.end()));
+    s->flux = c->flux && *std::max_element(s->s.terms_sub.begin(), s->s.terms_sub.end()) > flux_from(c);
     lmosem_status ws = s->flux ? plan_flux(c, s, force_subset, kept) : LMOSEM_OK;
     if (ws == LMOSEM_OK) ws = alloc_workspace(c, s);
     if (ws != LMOSEM_OK) { free_set(s); return ws; }
@@ -616,6 +622,50 @@ lmosem_status iterate_set(lmosem_ctx *c, lmosem_evset *s, int n_iters, double *l
         if ((c)->poisoned) return LMOSEM_ESTATE;                              \
     } while (0)
 
+void free_paths(lmosem_ctx *c) {
+    hipFree(c->t.T); hipFree(c->t.prim); hipFree(c->t.sens); hipFree(c->t.sens_all);
+    hipFree(c->t.band); hipFree(c->t.band_lo);
+    c->t.T = nullptr; c->t.prim = nullptr; c->t.sens = nullptr; c->t.sens_all = nullptr;
+    c->t.band = nullptr; c->t.band_lo = nullptr;
+}
+
+void drop_flux(lmosem_ctx *c) {
+    if (!c->flux) return;
+    c->flux = false;
+    c->table_bytes -= c->flux_bytes;
+    free_flux(c->ft);
+    hipFree(c->fws);
+    c->fws = nullptr;
+    c->fws_floats = 0;
+    c->flux_bytes = 0;
+}
+
+// the flux stages' tables and workspace, beside tables of `others` bytes still
+// to come; without room for them (in memory or under the cap) the context runs
+// term by term
+lmosem_status ensure_flux(lmosem_ctx *c, int64_t others) {
+    int64_t fb = 0;
+    hipError_t e = build_flux(c->g, c->fg, c->flux_order, c->t, c->ft, c->lazy_table, c->st, fb);
+    if (e == hipSuccess) {
+        // one realisation and a chunk of angles
+        c->fws_floats = flux_ws_floats(c->g, c->fg, 1, flux_angles(c->g, c->fg, c->g.n_angles));
+        fb += (int64_t)(sizeof(float) * c->fws_floats);
+        e = over_cap(c, fb + others) ? hipErrorOutOfMemory : hipMalloc(&c->fws, sizeof(float) * c->fws_floats);
+    }
+    if (e != hipSuccess && e != hipErrorOutOfMemory) return dev_err(c, "flux tables", e);
+    if (e == hipSuccess) {
+        c->flux = true;
+        c->flux_bytes = fb;
+        c->table_bytes += fb;
+    } else {
+        (void)hipGetLastError();
+        free_flux(c->ft);
+        c->fws = nullptr;
+        c->fws_floats = 0;
+    }
+    return LMOSEM_OK;
+}
+
 // build the list-mode tables on first use; a failed build frees what it
 // allocated and leaves the context usable (ENOMEM for a table too large)
 lmosem_status ensure_paths(lmosem_ctx *c) {
@@ -628,47 +678,44 @@ lmosem_status ensure_paths(lmosem_ctx *c) {
     const auto t0 = std::chrono::steady_clock::now();
     std::string err;
     int64_t bytes = 0;
-    const hipError_t e = build_paths(c->g, c->t, !c->surrogate, c->surrogate, c->st, err, bytes);
-    if (e != hipSuccess) {
-        hipStreamSynchronize(c->st);
-        hipFree(c->t.T); hipFree(c->t.prim); hipFree(c->t.sens); hipFree(c->t.sens_all);
-        hipFree(c->t.band); hipFree(c->t.band_lo);
-        c->t.T = nullptr; c->t.prim = nullptr; c->t.sens = nullptr; c->t.sens_all = nullptr;
-        c->t.band = nullptr; c->t.band_lo = nullptr;
-        return alloc_err(c, ("path tables: " + err).c_str(), e);
+    // where every list-mode call runs through the flux stages, the path table's
+    // bytes are held (a table that the device has no room for is refused) but
+    // filled only for the first row cache
+    c->lazy_table = flux_always(c);
+    if (c->lazy_table) {
+        size_t room = 0, total = 0;
+        hipError_t e = hipMemGetInfo(&room, &total);
+        if (e != hipSuccess) return dev_err(c, "path tables", e);
+        if ((int64_t)room < predicted) return set_err(c, LMOSEM_ENOMEM, "path tables: out of device memory");
+        e = hipMalloc(&c->t.sens, sizeof(float) * g.n_subsets * g.n_qpad);
+        if (e == hipSuccess) e = hipMalloc(&c->t.sens_all, sizeof(float) * g.n_qpad);
+        if (e != hipSuccess) { free_paths(c); return alloc_err(c, "path tables", e); }
     }
-    if (over_cap(c, bytes)) {   // the near-field band's width is known only once built
-        const std::string msg = cap_msg(c, "the path tables", bytes);
-        hipStreamSynchronize(c->st);
-        hipFree(c->t.T); hipFree(c->t.prim); hipFree(c->t.sens); hipFree(c->t.sens_all);
-        hipFree(c->t.band); hipFree(c->t.band_lo);
-        c->t.T = nullptr; c->t.prim = nullptr; c->t.sens = nullptr; c->t.sens_all = nullptr;
-        c->t.band = nullptr; c->t.band_lo = nullptr;
-        return set_err(c, LMOSEM_ENOMEM, msg);
+    if (c->flux_fits) {
+        const lmosem_status fs = ensure_flux(c, predicted);
+        if (fs != LMOSEM_OK) return fs;
+    }
+    if (c->lazy_table && c->flux) {
+        bytes = predicted;
+    } else {
+        c->lazy_table = false;
+        free_paths(c);
+        const hipError_t e = build_paths(c->g, c->t, !c->surrogate, c->surrogate, c->st, err, bytes);
+        if (e != hipSuccess) {
+            hipStreamSynchronize(c->st);
+            free_paths(c);
+            drop_flux(c);
+            return alloc_err(c, ("path tables: " + err).c_str(), e);
+        }
+        if (over_cap(c, bytes)) {   // the near-field band's width is known only once built
+            const std::string msg = cap_msg(c, "the path tables", bytes);
+            hipStreamSynchronize(c->st);
+            free_paths(c);
+            drop_flux(c);
+            return set_err(c, LMOSEM_ENOMEM, msg);
+        }
     }
     c->table_bytes += bytes;
-    // the flux stages' tables and workspace; without room for them (in memory
-    // or under the cap) the context runs term by term
-    if (c->flux_fits) {
-        int64_t fb = 0;
-        hipError_t fe = build_flux(c->g, c->fg, c->flux_order, c->t, c->ft, c->st, fb);
-        if (fe == hipSuccess) {
-            // one realisation and a chunk of angles
-            c->fws_floats = flux_ws_floats(g, c->fg, 1, flux_angles(g, c->fg, g.n_angles));
-            fb += (int64_t)(sizeof(float) * c->fws_floats);
-            fe = over_cap(c, fb) ? hipErrorOutOfMemory : hipMalloc(&c->fws, sizeof(float) * c->fws_floats);
-        }
-        if (fe != hipSuccess && fe != hipErrorOutOfMemory) return dev_err(c, "flux tables", fe);
-        if (fe == hipSuccess) {
-            c->flux = true;
-            c->table_bytes += fb;
-        } else {
-            (void)hipGetLastError();
-            free_flux(c->ft);
-            c->fws = nullptr;
-            c->fws_floats = 0;
-        }
-    }
     c->table_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     c->paths_ready = true;
     return LMOSEM_OK;
@@ -949,7 +996,7 @@ lmosem_status lmosem_forward_noalloc(lmosem_ctx *c, const lmosem_events *ev, con
     fr.ws = c->fws;
     fr.ws_floats = c->fws_floats;
     e = forward_noalloc(c->g, c->t, *ev, c->ev_tile, image_dev, event_mean_dev, c->skipped_dev, c->st, terms, useful,
-                        c->flux ? &fr : nullptr);
+                        c->flux ? &fr : nullptr, flux_from(c));
     if (e != hipSuccess) return dev_err(c, "forward (no allocation)", e);
     c->terms += terms;
     c->useful += useful;
@@ -1310,7 +1357,12 @@ lmosem_status lmosem_cache_rows(lmosem_ctx *c, lmosem_evset *s, int32_t enable) 
     const size_t n = (size_t)std::max<int64_t>(s->s.n, 1) * c->g.n_qpad;
     if (over_cap(c, (int64_t)(sizeof(float) * n)))
         return set_err(c, LMOSEM_ENOMEM, cap_msg(c, "the row cache", (int64_t)(sizeof(float) * n)));
-    hipError_t e = hipMalloc(&s->Hc, sizeof(float) * n);
+    hipError_t e = hipSuccess;
+    if (!c->t.T && !c->surrogate) {   // the rows' path table, held since the first list-mode call
+        e = build_path_table(c->g, c->t, c->st);
+        if (e != hipSuccess) return alloc_err(c, "path table", e);
+    }
+    e = hipMalloc(&s->Hc, sizeof(float) * n);
     if (e != hipSuccess) {
         s->Hc = nullptr;
         (void)hipGetLastError();

@@ -119,7 +119,8 @@ __global__ __launch_bounds__(64) void k_flux_pairs(Geo g, FluxGeo fg, FluxFit fi
                                                    const float *__restrict__ mu, const double *__restrict__ Bt,
                                                    const int *__restrict__ cnt, const int2 *__restrict__ off, int cap,
                                                    int *__restrict__ beg, int *__restrict__ rec_off,
-                                                   float *__restrict__ rec_w, float *__restrict__ sym) {
+                                                   float *__restrict__ rec_w, double *__restrict__ rec_w64,
+                                                   float *__restrict__ sym) {
     const int n = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
     const int x = b * 64 + lane < g.n_p ? sup[b * 64 + lane] : -1;
     const int px = x >= 0 ? p_pix[x] : -1;
@@ -144,7 +145,10 @@ __global__ __launch_bounds__(64) void k_flux_pairs(Geo g, FluxGeo fg, FluxFit fi
                 double w[kTap];
                 fit_weights(fit, node_pos(d.x, d.y, fg.N) - n, w);
 #pragma unroll
-                for (int i = 0; i < kTap; ++i) rec_w[(size_t)at * kTap + i] = (float)w[i];
+                for (int i = 0; i < kTap; ++i) {
+                    rec_w[(size_t)at * kTap + i] = (float)w[i];
+                    rec_w64[(size_t)at * kTap + i] = w[i];
+                }
             }
         }
         ++at;
@@ -182,13 +186,14 @@ __global__ __launch_bounds__(256) void k_flux_angles(Geo g, FluxGeo fg, const do
 // angle rank, primary weight and attenuation, and the order's index by rank
 __global__ void k_flux_support(Geo g, FluxGeo fg, const int *__restrict__ sup, const int *__restrict__ p_pix,
                                const float *__restrict__ mu, int *__restrict__ pos, int *__restrict__ box,
-                               float *__restrict__ mu_s) {
+                               float *__restrict__ mu_s, float *__restrict__ mu_box) {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= g.n_p) return;
     const int pix = p_pix[sup[x]];
     pos[sup[x]] = x;
     box[x] = (pix / g.nx - fg.y0) * fg.W + (pix % g.nx - fg.x0);
     mu_s[x] = mu[pix];
+    mu_box[box[x]] = mu[pix];
 }
 
 __global__ void k_flux_ranks(Geo g, const int *__restrict__ pos, const int *__restrict__ s_sorted,
@@ -877,6 +882,173 @@ __global__ __launch_bounds__(64) void k_flux_events(Geo g, FluxGeo fg, FluxFit f
     if (lane == 0) blk[b] = FluxBlock{u0, u1, e.slot, first, n, 0};
 }
 
+// ---------------------------------------------------------------- sensitivity (once per attenuation map, FP64)
+// sens_i(q) = T sum_{a in i} (e^(-L_a(q)) D_a(q) W(e0) + sum_s B(q, s) h_a(s, phi_qs)),
+// h_a(s, phi) = Psi/Psi_bar e^(-rho L_a(s)) D_a(s) W(E'): the adjoint stages once
+// more, with the window's acceptance in place of the events, in FP64 with the
+// FP64 pair factors.  One path walk per (angle, pixel, path end) took 6.4 ms
+// on brain64 (75 ms on brain128), most of it exp, log1p and erf; here these
+// are evaluated per (angle, direction node, scatter point).
+
+// per (angle, node): Psi/Psi_bar times the window's acceptance, and rho
+__global__ void k_flux_sens_angles(Geo g, FluxGeo fg, const double *__restrict__ cs, double2 *__restrict__ tab) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= g.n_angles * fg.N) return;
+    const int a = i / fg.N, n = i - a * fg.N;
+    const double ph = 2.0 * M_PI * n / fg.N;
+    const double c = cos(ph) * cs[2 * a] + sin(ph) * cs[2 * a + 1];
+    const double t = 1.0 + g.kappa * (1.0 - c), P = 1.0 / t, ep = g.e0 * P, s2 = M_SQRT2 * g.sig_e;
+    const double win = 0.5 * (erf((g.win_hi - ep) / s2) - erf((g.win_lo - ep) / s2));
+    tab[i] = make_double2(P * P * (P + t - 1.0 + c * c) / g.psi_bar * win, kn_total(ep) / g.sigma_kn_e0);
+}
+
+// U[n + 3][box][C] = mu(s) sum_{a in subset i0 + c} h_a(s, phi_n), direction
+// rows -3 .. N + 3 as in the fields
+template <int C>
+__global__ __launch_bounds__(64) void k_flux_sens_fields(Geo g, FluxGeo fg, FluxTables ft, int i0,
+                                                         const double2 *__restrict__ tab,
+                                                         const double *__restrict__ Ld,
+                                                         const double *__restrict__ D_sorted, double *__restrict__ U) {
+    const int x = blockIdx.x * 64 + threadIdx.x, n = blockIdx.y;
+    if (x >= g.n_p) return;
+    const int s = ft.sup[x];
+    double u[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) u[c] = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if (i0 + c < g.n_subsets)
+            for (int a = i0 + c; a < g.n_angles; a += g.n_subsets) {
+                const size_t o = (size_t)a * g.n_p;
+                const double2 h = tab[a * fg.N + n];
+                u[c] += h.x * exp(-h.y * Ld[o + s]) * D_sorted[o + ft.rank_of[o + x]];
+            }
+    const double m = ft.mu_s[x];
+    double *o = U + ((size_t)(n + 3) * fg.nb + ft.box[x]) * C;
+    const ptrdiff_t turn = (ptrdiff_t)fg.N * fg.nb * C;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        o[c] = m * u[c];
+        if (n < 4) o[c + turn] = m * u[c];
+        if (n >= fg.N - 3) o[c - turn] = m * u[c];
+    }
+}
+
+// part[sector][c][x] of C subsets: one wave per (pixel block, kWaveSec node
+// intervals)
+template <int C>
+__global__ __launch_bounds__(64) void k_flux_sens_pairs(Geo g, FluxGeo fg, FluxTables ft,
+                                                        const int *__restrict__ rec_off,
+                                                        const double *__restrict__ rec_w,
+                                                        const int *__restrict__ p_pix,
+                                                        const int *__restrict__ q_of_pix,
+                                                        const double *__restrict__ Bt, const double *__restrict__ U,
+                                                        double *__restrict__ part) {
+    const int b = blockIdx.x, sec = blockIdx.y, lane = threadIdx.x, x = b * 64 + lane;
+    const int q = x < g.n_p ? ft.sup[x] : -1;
+    const int lin = q >= 0 ? ft.box[x] : 0;
+    const unsigned top = (unsigned)fg.nb - 1;
+    double acc[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = 0.0;
+    for (int k = 0; k < kWaveSec; ++k) {
+        const int n = sec * kWaveSec + k;
+        for (int e = ft.beg[b * fg.N + n]; e < ft.beg[b * fg.N + n + 1]; ++e) {
+            const unsigned at = min((unsigned)(lin + rec_off[e]), top);
+            const bool on = q >= 0 && q < g.n_q && ft.sym[(size_t)e * 64 + lane] != 0.0f;
+            if (__ballot(on) == 0) continue;
+            double B = 0.0;
+            if (on) {
+                const int j = (int)at / fg.W, i = (int)at - j * fg.W;
+                const int s = q_of_pix[(j + fg.y0) * g.nx + i + fg.x0];
+                B = Bt[(size_t)s * g.n_p + q] / (double)ft.mu_box[at];
+            }
+            double v[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[c] = 0.0;
+#pragma unroll
+            for (int i = 0; i < kTap; ++i) {
+                const double w = rec_w[(size_t)e * kTap + i];
+                const double *u = U + ((size_t)(n + i) * fg.nb + at) * C;
+#pragma unroll
+                for (int c = 0; c < C; ++c) v[c] = fma(w, u[c], v[c]);
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] = on ? fma(B, v[c], acc[c]) : acc[c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) part[((size_t)sec * C + c) * fg.np64 + x] = acc[c];
+}
+
+// sens[i][q] of C subsets: the partial sums and the primary paths; total[q]
+// collects the subsets in order
+template <int C>
+__global__ void k_flux_sens_sum(Geo g, FluxGeo fg, FluxTables ft, int i0, int n_part, const double *__restrict__ part,
+                                const double *__restrict__ Ld, const double *__restrict__ D_sorted,
+                                float *__restrict__ sens, double *__restrict__ total, float *__restrict__ sens_all) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= g.n_p) return;
+    const int q = ft.sup[x];
+    if (q >= g.n_q) return;
+    const double s2 = M_SQRT2 * g.sig_e;
+    const double w0 = 0.5 * (erf((g.win_hi - g.e0) / s2) - erf((g.win_lo - g.e0) / s2));
+    double tot = i0 ? total[q] : 0.0;
+    for (int c = 0; c < C && i0 + c < g.n_subsets; ++c) {
+        double s = 0.0;
+        for (int k = 0; k < n_part; ++k) s += part[((size_t)k * C + c) * fg.np64 + x];
+        for (int a = i0 + c; a < g.n_angles; a += g.n_subsets) {
+            const size_t o = (size_t)a * g.n_p;
+            s += exp(-Ld[o + q]) * D_sorted[o + ft.rank_of[o + x]] * w0;
+        }
+        sens[(size_t)(i0 + c) * g.n_qpad + q] = (float)(g.acq_time * s);
+        tot += s;
+    }
+    total[q] = tot;
+    if (i0 + C >= g.n_subsets) sens_all[q] = (float)(g.acq_time * tot);
+}
+
+template <int C>
+static hipError_t sens_subsets(const Geo &g, const FluxGeo &fg, const Tables &t, const FluxTables &ft, const double *w64,
+                               const double2 *tab, double *U, double *part, double *total, hipStream_t st) {
+    const int n_part = fg.N / kWaveSec;
+    for (int i0 = 0; i0 < g.n_subsets; i0 += C) {
+        if (fg.N) {
+            hipLaunchKernelGGL(k_flux_sens_fields<C>, dim3(fg.n_blk, fg.N), dim3(64), 0, st, g, fg, ft, i0, tab, t.Ld,
+                               t.D_sorted, U);
+            hipLaunchKernelGGL(k_flux_sens_pairs<C>, dim3(fg.n_blk, n_part), dim3(64), 0, st, g, fg, ft, ft.rec_off, w64,
+                               t.p_pix, t.p_pix + g.n_p, t.Bt, U, part);
+        }
+        hipLaunchKernelGGL(k_flux_sens_sum<C>, dim3((g.n_p + 63) / 64), dim3(64), 0, st, g, fg, ft, i0, n_part, part, t.Ld,
+                           t.D_sorted, t.sens, total, t.sens_all);
+    }
+    return hipGetLastError();
+}
+
+// t.sens and t.sens_all (allocated, zero beyond the emission set)
+static hipError_t flux_sensitivity(const Geo &g, const FluxGeo &fg, const Tables &t, const FluxTables &ft,
+                                   const double *w64, hipStream_t st) {
+    const int C = g.n_subsets >= 8 ? 8 : g.n_subsets >= 4 ? 4 : g.n_subsets >= 2 ? 2 : 1;
+    double2 *tab = nullptr;
+    double *ws = nullptr;
+    const size_t nU = fg.N ? (size_t)(fg.N + kTap - 1) * fg.nb * C : 0, nP = (size_t)(fg.N / kWaveSec) * C * fg.np64;
+    hipError_t e = launch_fill(t.sens, (size_t)g.n_subsets * g.n_qpad, 0.0f, st);
+    if (e == hipSuccess) e = launch_fill(t.sens_all, g.n_qpad, 0.0f, st);
+    if (e == hipSuccess && fg.N) e = hipMalloc(&tab, sizeof(double2) * (size_t)g.n_angles * fg.N);
+    if (e == hipSuccess) e = hipMalloc(&ws, sizeof(double) * (nU + nP + g.n_q));
+    if (e == hipSuccess) {
+        if (fg.N)
+            hipLaunchKernelGGL(k_flux_sens_angles, dim3((unsigned)(((size_t)g.n_angles * fg.N + 255) / 256)), dim3(256), 0, st,
+                               g, fg, t.cs, tab);
+        auto run = C == 8 ? sens_subsets<8> : C == 4 ? sens_subsets<4> : C == 2 ? sens_subsets<2> : sens_subsets<1>;
+        e = run(g, fg, t, ft, w64, tab, ws, ws + nU, ws + nU + nP, st);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    hipFree(tab);
+    hipFree(ws);
+    return e;
+}
+
 // ---------------------------------------------------------------- host side
 // weights exact for exponents at the Chebyshev points of [-b, b] (per node
 // spacing): the inverse of their values at the nodes -3 .. 4, in extended
@@ -961,7 +1133,7 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
 }
 
 void free_flux(FluxTables &ft) {
-    for (void *p : {(void *)ft.sup, (void *)ft.box, (void *)ft.mu_s, (void *)ft.rank_of, (void *)ft.x_of, (void *)ft.pw,
+    for (void *p : {(void *)ft.sup, (void *)ft.box, (void *)ft.mu_s, (void *)ft.mu_box, (void *)ft.rank_of, (void *)ft.x_of, (void *)ft.pw,
                     (void *)ft.pwr, (void *)ft.Lx, (void *)ft.beg, (void *)ft.rec_off, (void *)ft.rec_w, (void *)ft.sym,
                     (void *)ft.G, (void *)ft.psi, (void *)ft.rho})
         hipFree(p);
@@ -969,15 +1141,16 @@ void free_flux(FluxTables &ft) {
 }
 
 hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> &order, const Tables &t, FluxTables &ft,
-                      hipStream_t st, int64_t &bytes) {
+                      bool sens, hipStream_t st, int64_t &bytes) {
     const FluxGeo &fg = fm;
     hipError_t e = hipSuccess;
     int *cnt = nullptr, *pos = nullptr;
     int2 *off = nullptr;
+    double *w64 = nullptr;
     void *tmp = nullptr;
     int64_t held = 0;
     auto done = [&](hipError_t err) {
-        hipFree(cnt); hipFree(off); hipFree(tmp); hipFree(pos);
+        hipFree(cnt); hipFree(off); hipFree(tmp); hipFree(pos); hipFree(w64);
         if (err != hipSuccess) { hipStreamSynchronize(st); free_flux(ft); }
         else bytes += held;
         return err;
@@ -987,17 +1160,20 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
         return e = hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(*p));
     };
     const size_t na_np = (size_t)g.n_angles * g.n_p;
-    if (al(ft.sup, g.n_p) || al(ft.box, g.n_p) || al(ft.mu_s, g.n_p) || al(ft.rank_of, na_np) || al(ft.x_of, na_np) ||
+    if (al(ft.sup, g.n_p) || al(ft.box, g.n_p) || al(ft.mu_s, g.n_p) || al(ft.mu_box, fg.nb) || al(ft.rank_of, na_np) || al(ft.x_of, na_np) ||
         al(ft.pw, na_np) || al(ft.pwr, na_np) || al(ft.Lx, na_np))
         return done(e);
     if ((e = hipMalloc(&pos, sizeof(int) * g.n_p)) != hipSuccess) return done(e);
     if ((e = hipMemcpyAsync(ft.sup, order.data(), sizeof(int) * g.n_p, hipMemcpyHostToDevice, st)) != hipSuccess) return done(e);
     hipLaunchKernelGGL(k_flux_support, dim3((g.n_p + 255) / 256), dim3(256), 0, st, g, fg, ft.sup, t.p_pix, t.mu, pos,
-                       ft.box, ft.mu_s);
+                       ft.box, ft.mu_s, ft.mu_box);
     hipLaunchKernelGGL(k_flux_ranks, dim3((unsigned)((na_np + 255) / 256)), dim3(256), 0, st, g, pos, t.s_sorted, t.Ld,
                        ft.rank_of, ft.x_of, ft.pw, ft.pwr, ft.Lx);
     if ((e = hipGetLastError()) != hipSuccess) return done(e);
-    if (!g.scatter) return done(hipStreamSynchronize(st));
+    if (!g.scatter) {
+        if (sens) e = flux_sensitivity(g, fg, t, ft, nullptr, st);
+        return done(e == hipSuccess ? hipStreamSynchronize(st) : e);
+    }
     const size_t an = (size_t)g.n_angles * fg.N;
     if (al(ft.psi, an) || al(ft.rho, an) || al(ft.G, an * fg.K)) return done(e);
     hipLaunchKernelGGL(k_flux_angles, dim3(fg.N / 16, g.n_angles), dim3(256), 0, st, g, fg, t.cs, ft.psi, ft.rho, ft.G);
@@ -1018,7 +1194,7 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     const dim3 grid(fg.N, fg.n_blk);
     const int *q_of_pix = t.p_pix + g.n_p;
     hipLaunchKernelGGL(k_flux_pairs<0>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
-                       cap, ft.beg, (int *)nullptr, (float *)nullptr, (float *)nullptr);
+                       cap, ft.beg, (int *)nullptr, (float *)nullptr, (double *)nullptr, (float *)nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return done(e);
     if ((e = launch_fill(reinterpret_cast<float *>(ft.beg + nbin), 1, 0.0f, st)) != hipSuccess) return done(e);
     if ((e = hipcub::DeviceScan::ExclusiveSum(tmp, tmp_bytes, ft.beg, ft.beg, nbin + 1, st)) != hipSuccess) return done(e);
@@ -1026,10 +1202,12 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     if ((e = hipMemcpyAsync(&total, ft.beg + nbin, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return done(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return done(e);
     if (al(ft.rec_off, total) || al(ft.rec_w, (size_t)total * kTap) || al(ft.sym, (size_t)total * 64)) return done(e);
+    if ((e = hipMalloc(&w64, std::max<size_t>(total, 1) * kTap * sizeof(double))) != hipSuccess) return done(e);
     hipLaunchKernelGGL(k_flux_pairs<1>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
-                       cap, ft.beg, ft.rec_off, ft.rec_w, ft.sym);
-    if ((e = hipGetLastError()) != hipSuccess) return done(e);
-    return done(hipStreamSynchronize(st));
+                       cap, ft.beg, ft.rec_off, ft.rec_w, w64, ft.sym);
+    if ((e = hipGetLastError()) == hipSuccess && sens) e = flux_sensitivity(g, fg, t, ft, w64, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    return done(e);
 }
 
 static size_t up64(size_t n) { return (n + 63) & ~size_t(63); }

@@ -82,7 +82,10 @@ struct Tables {
 };
 
 // ---- table build (tables.hip) ----
-// build_base at create; build_paths before the first list-mode use
+// build_base at create; build_paths before the first list-mode use (or, where
+// the flux stages serve every list-mode call, build_path_table before the
+// first one that wants rows)
+hipError_t build_path_table(const Geo &g, Tables &t, hipStream_t st);
 hipError_t build_base(const Geo &g, Tables &t, hipStream_t st, std::string &err, int64_t &bytes);
 hipError_t build_paths(const Geo &g, Tables &t, bool store_paths, bool store_band, hipStream_t st,
                        std::string &err, int64_t &bytes);
@@ -119,11 +122,11 @@ hipError_t scratch_address(void **ptr);
 // bytes of the scratch array that forward_noalloc needs for n events
 hipError_t forward_noalloc_bytes(const Geo &g, int64_t n, int ev_tile, size_t &need);
 // per-event means of the (validated) events at the image, in the caller's
-// event order, every buffer in the scratch array (with flux: its stages on
-// the context's workspace, the rest filled in here); synchronises st
+// event order, every buffer in the scratch array (with flux and more than
+// flux_from terms: its stages on the context's workspace, the rest filled in here); synchronises st
 hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &ev, int ev_tile, const float *image,
                            float *mean_out, unsigned long long *skipped, hipStream_t st, int64_t &terms,
-                           int64_t &useful, struct FluxRun *flux);
+                           int64_t &useful, struct FluxRun *flux, int64_t flux_from);
 
 // ---- sub-iterations through directional flux (flux.hip) ----
 constexpr int kFluxMaxN = 960;             // direction nodes
@@ -154,6 +157,7 @@ struct FluxTables {
     int *sup = nullptr;        // [n_p] support index of x
     int *box = nullptr;        // [n_p] index in the bounding box
     float *mu_s = nullptr;     // [n_p]
+    float *mu_box = nullptr;   // [nb] mu on the support, by box index
     int *rank_of = nullptr;    // [n_angles][n_p] rank of x
     int *x_of = nullptr;       // [n_angles][n_p] x by rank
     float *pw = nullptr, *pwr = nullptr;   // [n_angles][n_p] primary path weight by x, by rank
@@ -221,8 +225,9 @@ using FluxStage = std::function<hipError_t(int, const std::function<hipError_t()
 
 // false: outside the nodes' limits; order: the flux order
 bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order);
+// sens: also the sensitivities, into t.sens and t.sens_all
 hipError_t build_flux(const Geo &g, const FluxModel &fg, const std::vector<int> &order, const Tables &t, FluxTables &ft,
-                      hipStream_t st, int64_t &bytes);
+                      bool sens, hipStream_t st, int64_t &bytes);
 void free_flux(FluxTables &ft);
 int flux_angles(const Geo &g, const FluxGeo &fg, int n_list);
 size_t flux_ws_floats(const Geo &g, const FluxGeo &fg, int n_real, int n_slots);

@@ -110,7 +110,7 @@ hipError_t forward_noalloc_bytes(const Geo &g, int64_t n, int ev_tile, size_t &n
 
 hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &ev, int ev_tile, const float *image,
                            float *mean_out, unsigned long long *skipped, hipStream_t st, int64_t &terms,
-                           int64_t &useful, FluxRun *flux) {
+                           int64_t &useful, FluxRun *flux, int64_t flux_from) {
     terms = useful = 0;
     void *base = nullptr;
     hipError_t e = scratch_address(&base);
@@ -154,6 +154,13 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
     if (nt > L.max_tiles) return hipErrorInvalidValue;
     if ((e = hipMemcpyAsync(tiles, th.data(), sizeof(Tile) * nt, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
     if ((e = launch_tile_ranks(g, tiles, nt, t.us_sorted, u, terms_d, useful_d, st)) != hipSuccess) return e;
+    std::vector<long long> tv(nt), uv(nt);
+    if ((e = hipMemcpyAsync(tv.data(), terms_d, sizeof(long long) * nt, hipMemcpyDeviceToHost, st)) != hipSuccess ||
+        (e = hipMemcpyAsync(uv.data(), useful_d, sizeof(long long) * nt, hipMemcpyDeviceToHost, st)) != hipSuccess ||
+        (e = hipStreamSynchronize(st)) != hipSuccess)
+        return e;
+    for (int k = 0; k < nt; ++k) { terms += tv[k]; useful += uv[k]; }
+    if (terms <= flux_from) flux = nullptr;   // as lmosem_forward chooses
     // in the transient region (the sort's buffers are dead by now in stream
     // order): the flux stages' angle lists and a run of event records at a time, or
     std::vector<int> lists;
@@ -215,13 +222,7 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
         t0 = t1;
     }
     if ((e = launch_scatter_rows(mean, orig, n, mean_out, st)) != hipSuccess) return e;
-    std::vector<long long> tv(nt), uv(nt);
-    if ((e = hipMemcpyAsync(tv.data(), terms_d, sizeof(long long) * nt, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipMemcpyAsync(uv.data(), useful_d, sizeof(long long) * nt, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipStreamSynchronize(st)) != hipSuccess)
-        return e;
-    for (int k = 0; k < nt; ++k) { terms += tv[k]; useful += uv[k]; }
-    return hipSuccess;
+    return hipStreamSynchronize(st);
 }
 
 }  // namespace lmo

@@ -282,6 +282,25 @@ hipError_t build_base(const Geo &g, Tables &t, hipStream_t st, std::string &err,
     return hipSuccess;
 }
 
+// The path table alone, for contexts whose sensitivities came without it.
+hipError_t build_path_table(const Geo &g, Tables &t, hipStream_t st) {
+    double *sens_a = nullptr;
+    float *prim = nullptr;
+    hipError_t e = hipMalloc(&t.T, sizeof(float2) * (size_t)g.n_angles * g.n_rpad * g.n_qpad);
+    if (e == hipSuccess) e = hipMalloc(&sens_a, sizeof(double) * g.n_angles * g.n_qpad);
+    if (e == hipSuccess) e = hipMalloc(&prim, sizeof(float) * g.n_angles * g.n_p);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_path_table, dim3((g.n_qpad + 63) / 64, g.n_angles), dim3(64), 0, st, g, t.p_pix, t.cs, t.Ld,
+                           t.Bt, t.s_sorted, t.D_sorted, t.T, sens_a, prim);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    hipFree(sens_a);
+    hipFree(prim);
+    if (e != hipSuccess) { hipFree(t.T); t.T = nullptr; }
+    return e;
+}
+
 // What list-mode work needs on top of build_base: the per-subset
 // sensitivities, the primary weights, and the path table (store_paths) or the
 // near-field band (store_band).  Adds its device bytes to `bytes`.
