@@ -981,31 +981,41 @@ __global__ __launch_bounds__(64) void k_flux_sens_pairs(Geo g, FluxGeo fg, FluxT
     for (int c = 0; c < C; ++c) part[((size_t)sec * C + c) * fg.np64 + x] = acc[c];
 }
 
-// sens[i][q] of C subsets: the partial sums and the primary paths; total[q]
-// collects the subsets in order
+// sens of one of C subsets (blockIdx.y): the partial sums and the primary
+// paths, kept in FP64 for the sum over subsets; four lanes per pixel
 template <int C>
-__global__ void k_flux_sens_sum(Geo g, FluxGeo fg, FluxTables ft, int i0, int n_part, const double *__restrict__ part,
-                                const double *__restrict__ Ld, const double *__restrict__ D_sorted,
-                                float *__restrict__ sens, double *__restrict__ total, float *__restrict__ sens_all) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= g.n_p) return;
-    const int q = ft.sup[x];
-    if (q >= g.n_q) return;
-    const double s2 = M_SQRT2 * g.sig_e;
-    const double w0 = 0.5 * (erf((g.win_hi - g.e0) / s2) - erf((g.win_lo - g.e0) / s2));
-    double tot = i0 ? total[q] : 0.0;
-    for (int c = 0; c < C && i0 + c < g.n_subsets; ++c) {
-        double s = 0.0;
-        for (int k = 0; k < n_part; ++k) s += part[((size_t)k * C + c) * fg.np64 + x];
-        for (int a = i0 + c; a < g.n_angles; a += g.n_subsets) {
+__global__ __launch_bounds__(256) void k_flux_sens_sum(Geo g, FluxGeo fg, FluxTables ft, int i0, int n_part,
+                                                       const double *__restrict__ part, const double *__restrict__ Ld,
+                                                       const double *__restrict__ D_sorted, float *__restrict__ sens,
+                                                       double *__restrict__ sens64) {
+    __shared__ double red[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, x = blockIdx.x * 64 + lane, c = blockIdx.y, i = i0 + c;
+    if (i >= g.n_subsets) return;
+    const int q = x < g.n_p ? ft.sup[x] : g.n_q;
+    double s = 0.0;
+    if (q < g.n_q) {
+        const double s2 = M_SQRT2 * g.sig_e;
+        const double w0 = 0.5 * (erf((g.win_hi - g.e0) / s2) - erf((g.win_lo - g.e0) / s2));
+        for (int k = w; k < n_part; k += 4) s += part[((size_t)k * C + c) * fg.np64 + x];
+        for (int a = i + w * g.n_subsets; a < g.n_angles; a += 4 * g.n_subsets) {
             const size_t o = (size_t)a * g.n_p;
             s += exp(-Ld[o + q]) * D_sorted[o + ft.rank_of[o + x]] * w0;
         }
-        sens[(size_t)(i0 + c) * g.n_qpad + q] = (float)(g.acq_time * s);
-        tot += s;
     }
-    total[q] = tot;
-    if (i0 + C >= g.n_subsets) sens_all[q] = (float)(g.acq_time * tot);
+    red[w][lane] = s;
+    __syncthreads();
+    if (w || q >= g.n_q) return;
+    s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    sens64[(size_t)i * g.n_q + q] = s;
+    sens[(size_t)i * g.n_qpad + q] = (float)(g.acq_time * s);
+}
+
+__global__ void k_flux_sens_total(Geo g, const double *__restrict__ sens64, float *__restrict__ sens_all) {
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= g.n_q) return;
+    double s = 0.0;
+    for (int i = 0; i < g.n_subsets; ++i) s += sens64[(size_t)i * g.n_q + q];
+    sens_all[q] = (float)(g.acq_time * s);
 }
 
 template <int C>
@@ -1019,9 +1029,10 @@ static hipError_t sens_subsets(const Geo &g, const FluxGeo &fg, const Tables &t,
             hipLaunchKernelGGL(k_flux_sens_pairs<C>, dim3(fg.n_blk, n_part), dim3(64), 0, st, g, fg, ft, ft.rec_off, w64,
                                t.p_pix, t.p_pix + g.n_p, t.Bt, U, part);
         }
-        hipLaunchKernelGGL(k_flux_sens_sum<C>, dim3((g.n_p + 63) / 64), dim3(64), 0, st, g, fg, ft, i0, n_part, part, t.Ld,
-                           t.D_sorted, t.sens, total, t.sens_all);
+        hipLaunchKernelGGL(k_flux_sens_sum<C>, dim3(fg.n_blk, C), dim3(256), 0, st, g, fg, ft, i0, n_part, part, t.Ld,
+                           t.D_sorted, t.sens, total);
     }
+    hipLaunchKernelGGL(k_flux_sens_total, dim3((g.n_q + 63) / 64), dim3(64), 0, st, g, total, t.sens_all);
     return hipGetLastError();
 }
 
@@ -1035,7 +1046,7 @@ static hipError_t flux_sensitivity(const Geo &g, const FluxGeo &fg, const Tables
     hipError_t e = launch_fill(t.sens, (size_t)g.n_subsets * g.n_qpad, 0.0f, st);
     if (e == hipSuccess) e = launch_fill(t.sens_all, g.n_qpad, 0.0f, st);
     if (e == hipSuccess && fg.N) e = hipMalloc(&tab, sizeof(double2) * (size_t)g.n_angles * fg.N);
-    if (e == hipSuccess) e = hipMalloc(&ws, sizeof(double) * (nU + nP + g.n_q));
+    if (e == hipSuccess) e = hipMalloc(&ws, sizeof(double) * (nU + nP + (size_t)g.n_subsets * g.n_q));
     if (e == hipSuccess) {
         if (fg.N)
             hipLaunchKernelGGL(k_flux_sens_angles, dim3((unsigned)(((size_t)g.n_angles * fg.N + 255) / 256)), dim3(256), 0, st,
