@@ -231,14 +231,34 @@ __global__ void k_flux_box(Geo g, FluxGeo fg, FluxTables ft, const float *__rest
 // kSec + 7 nodes, so even and odd sectors write two separate copies (24 nodes
 // each, the rest zero) that the next stage adds.
 constexpr int kWaveSec = kSec / 4;             // intervals of one wave
+static_assert(kWaveSec == 3, "the spread's interval bounds");
 constexpr int kWaveNodes = kWaveSec + kTap - 1;
-constexpr int kBatch = 8;                      // pairs loaded ahead
+constexpr int kBatch = 8;                      // pairs loaded together
+
+// up to 64 pair records of a wave: each lane fetches one (its box offset stays
+// in the lane, to be read back as a scalar; its weights go to LDS, to be read
+// back as a broadcast), so that the pair loop itself waits for no scalar load
+struct WaveRecords {
+    int off;
+    __device__ __forceinline__ void load(const int *__restrict__ rec_off, const float *__restrict__ rec_w, int e, int e1,
+                                         float (*w)[kTap], int lane) {
+        const int i = min(e + lane, e1 - 1);
+        off = rec_off[i];
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(rec_w + (size_t)i * kTap);
+        const f32x4 lo = src[0], hi = src[1];
+        *reinterpret_cast<f32x4 *>(&w[lane][0]) = lo;
+        *reinterpret_cast<f32x4 *>(&w[lane][4]) = hi;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+        __builtin_amdgcn_wave_barrier();
+    }
+};
 
 __global__ __launch_bounds__(256) void k_flux_spread(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ beg_all,
                                                      const int *__restrict__ rec_off, const float *__restrict__ rec_w,
                                                      const float *__restrict__ sym, const float *__restrict__ fbox,
                                                      float *__restrict__ I) {
     __shared__ float part[4][kWaveNodes][64];
+    __shared__ __align__(16) float w_s[4][64][kTap];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int sec = blockIdx.y, b = blockIdx.x, r = blockIdx.z;
     const int s = b * 64 + lane;
@@ -249,31 +269,40 @@ __global__ __launch_bounds__(256) void k_flux_spread(Geo g, FluxGeo fg, FluxTabl
 #pragma unroll
     for (int i = 0; i < kTap; ++i) acc[i] = 0.0f;
     const int *beg = beg_all + b * fg.N + sec * kSec + wave * kWaveSec;
-    const int e1 = beg[kWaveSec];
-    int k = 0, next = beg[1];
-    for (int e = beg[0]; e < e1; e += kBatch) {
-        float v[kBatch];
+    const int e0 = beg[0], e1 = beg[kWaveSec];
+    int bound[kWaveSec];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int eu = min(e + u, e1 - 1);
-            const float y = sym[(size_t)eu * 64 + lane];
-            const unsigned at = min((unsigned)(lin + rec_off[eu]), top);
-            const float fy = fr[at];
-            v[u] = y != 0.0f ? y * fy : 0.0f;
-        }
+    for (int i = 0; i < kWaveSec; ++i) bound[i] = beg[i + 1];
+    int k = 0, next = bound[0];
+    for (int c0 = e0; c0 < e1; c0 += 64) {
+        WaveRecords rec;
+        rec.load(rec_off, rec_w, c0, e1, w_s[wave], lane);
+        const int n = min(64, e1 - c0);
+        const float *__restrict__ sy = sym + (size_t)c0 * 64 + lane;
+#pragma unroll 2
+        for (int u0 = 0; u0 < n; u0 += kBatch) {
+            float y[kBatch], v[kBatch];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            if (e + u < e1) {
-                while (e + u >= next) {   // the lowest node is complete: on to the next interval
-                    part[wave][k][lane] = acc[0];
+            for (int u = 0; u < kBatch; ++u) {
+                const int i = min(u0 + u, n - 1);
+                y[u] = sy[(size_t)i * 64];
+                v[u] = fr[min((unsigned)(lin + __builtin_amdgcn_readlane(rec.off, i)), top)];
+            }
 #pragma unroll
-                    for (int i = 0; i + 1 < kTap; ++i) acc[i] = acc[i + 1];
-                    acc[kTap - 1] = 0.0f;
-                    ++k;
-                    next = beg[k + 1];
+            for (int u = 0; u < kBatch; ++u) {
+                if (u0 + u < n) {
+                    while (c0 + u0 + u >= next) {   // the lowest node is complete: on to the next interval
+                        part[wave][k][lane] = acc[0];
+#pragma unroll
+                        for (int i = 0; i + 1 < kTap; ++i) acc[i] = acc[i + 1];
+                        acc[kTap - 1] = 0.0f;
+                        ++k;
+                        next = k == 1 ? bound[1] : bound[2];
+                    }
+                    const float p = y[u] != 0.0f ? y[u] * v[u] : 0.0f;
+#pragma unroll
+                    for (int i = 0; i < kTap; ++i) acc[i] = fmaf(w_s[wave][u0 + u][i], p, acc[i]);
                 }
-#pragma unroll
-                for (int i = 0; i < kTap; ++i) acc[i] = fmaf(rec_w[(size_t)(e + u) * kTap + i], v[u], acc[i]);
             }
         }
     }
@@ -397,6 +426,8 @@ __global__ __launch_bounds__(256) void k_flux_means(Geo g, FluxGeo fg, const Flu
                                                     float *__restrict__ inv, unsigned long long *__restrict__ skipped) {
     __shared__ float w_s[4][16][kTap];
     __shared__ int et_s[4][16];
+    __shared__ double us_s[4][64];
+    __shared__ float pr_s[4][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int c = lane & 15, q = lane >> 4;
     const FluxBlock bk = blk[blockIdx.x];
@@ -438,16 +469,42 @@ __global__ __launch_bounds__(256) void k_flux_means(Geo g, FluxGeo fg, const Flu
         f32x4 acc[TILES];
 #pragma unroll
         for (int t = 0; t < TILES; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-        for (int k = r0; k < r1; k += 4) {
-            const int kr = min(k + q, r1 - 1);
-            float kv = response(e.u - us[kr], inv2s2, edge);
-            kv = k + q < r1 ? kv : 0.0f;
-            if (tb == t0) prim = fmaf(kv, Pr[kr], prim);
-            const float *row = Sr + (size_t)kr * fg.K + 16 * tb + c;
+        // path ends go to LDS 64 at a time: read from memory where they are
+        // used, they would cost the vector cache as much as the spectra do.
+        // 16 ranks' spectra are read before the first is used.
+        const float *Sc = Sr + 16 * tb + c;
+#pragma unroll 1
+        for (int kc = r0; kc < r1; kc += 64) {
+            const int kl = min(kc + lane, r1 - 1);
+            const double ul = us[kl];
+            const float pl = Pr[kl];
+            __builtin_amdgcn_wave_barrier();
+            us_s[wave][lane] = ul;
+            pr_s[wave][lane] = pl;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+            __builtin_amdgcn_wave_barrier();
+            const int n = min(64, r1 - kc);
+#pragma unroll 1
+            for (int k0 = 0; k0 < n; k0 += 16) {
+                float sv[4][TILES];
 #pragma unroll
-            for (int t = 0; t < TILES; ++t)
-                if (t < nt) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, row[16 * t], acc[t], 0, 0, 0);
+                for (int j = 0; j < 4; ++j) {
+                    const float *row = Sc + (size_t)min(kc + k0 + 4 * j + q, r1 - 1) * fg.K;
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t)
+                        if (t < nt) sv[j][t] = row[16 * t];
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = k0 + 4 * j + q;
+                    float kv = response(e.u - us_s[wave][k], inv2s2, edge);
+                    kv = k < n ? kv : 0.0f;
+                    if (tb == t0) prim = fmaf(kv, pr_s[wave][k], prim);
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t)
+                        if (t < nt) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, sv[j][t], acc[t], 0, 0, 0);
+                }
+            }
         }
 #pragma unroll
         for (int t = 0; t < TILES; ++t)
@@ -547,25 +604,34 @@ __device__ __forceinline__ int wave_search(const FluxBlock *blk, int lo, int hi,
 }
 
 // R_as(k) = sum_j w_j K_js l_k(E_j) (and the primary's R0 = sum_j w_j K_js g0_j)
-// of 16 path ends of one slot on the matrix cores: one wave walks the event
-// blocks that reach any of its ends, four events per product (A: responses of
-// 16 ends to four events; B: the events' interpolation weights spread over a
-// 16-node tile).  The events' energy order within a block keeps four events'
-// nodes to one or two tiles; the others are skipped.  Every sum has one owner
-// and a fixed order.  Rows are written in flux order.
+// of 16 path ends of one slot on the matrix cores: the workgroup's four waves
+// walk the event blocks that reach any of its ends, every fourth block each,
+// four events per product (A: responses of 16 ends to four events; B: the
+// events' interpolation weights spread over a 16-node tile).  The events'
+// energy order within a block keeps four events' nodes to one or two tiles;
+// the others are skipped.  Every sum has one owner and a fixed order.  Rows
+// are written in flux order.
 template <int TILES>
-__global__ __launch_bounds__(64) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTables ft, const FluxEvent *__restrict__ ev,
-                                                     const FluxBlock *__restrict__ blk,
-                                                     const double *__restrict__ us_sorted,
-                                                     const int *__restrict__ alist, const int *__restrict__ blk_beg,
-                                                     int n_list, int slot0, int row_base,
-                                                     const float *__restrict__ wgt, float *__restrict__ R,
-                                                     float *__restrict__ R0) {
-    __shared__ __align__(16) float w_s[64][kTap];   // weight times interpolation weights
-    __shared__ float p_s[64];                       // weight times the primary's energy response
-    __shared__ int et_s[64];
-    __shared__ double u_s[64];
-    const int lane = threadIdx.x, c = lane & 15, q = lane >> 4;
+__global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTables ft, const FluxEvent *__restrict__ ev,
+                                                      const FluxBlock *__restrict__ blk,
+                                                      const double *__restrict__ us_sorted,
+                                                      const int *__restrict__ alist, const int *__restrict__ blk_beg,
+                                                      int n_list, int slot0, int row_base,
+                                                      const float *__restrict__ wgt, float *__restrict__ R,
+                                                      float *__restrict__ R0) {
+    constexpr int NT = TILES > 0 ? TILES : 1;
+    union Shared {
+        struct {
+            float w[4][64][kTap];   // weight times interpolation weights
+            double u[4][64];
+            float p[4][64];         // weight times the primary's energy response
+            int et[4][64];
+        } in;
+        f32x4 red[3][NT][64];
+    };
+    __shared__ __align__(16) Shared sh;
+    __shared__ float red0[4][16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
     const int ls = blockIdx.y, slot = slot0 + ls;
     const int r = slot / n_list, a = alist[slot - r * n_list];
     const double *us = us_sorted + (size_t)a * g.n_p;
@@ -576,54 +642,76 @@ __global__ __launch_bounds__(64) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTabl
     const int b1 = wave_search<true>(blk, b0, blk_beg[slot + 1], us[min(k0 + 15, g.n_p - 1)] + reach, lane);
     const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
     const float edge = expf(-4.5f);
-    f32x4 acc[TILES > 0 ? TILES : 1];
+    f32x4 acc[NT];
 #pragma unroll
-    for (int t = 0; t < TILES; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float r0 = 0.0f;
-    for (int b = b0; b < b1; ++b) {
+    for (int b = b0 + wave; b < b1; b += 4) {
         const FluxBlock bk = blk[b];
-        __syncthreads();
         {
             const FluxEvent e = ev[bk.row + min(lane, bk.n - 1)];
             const float y = lane < bk.n ? wgt[e.row - row_base] * fg.inv_zk : 0.0f;
-            u_s[lane] = e.u;
-            p_s[lane] = y * e.g0;
+            __builtin_amdgcn_wave_barrier();
+            sh.in.u[wave][lane] = e.u;
+            sh.in.p[wave][lane] = y * e.g0;
             if (TILES > 0) {
 #pragma unroll
-                for (int i = 0; i < kTap; ++i) w_s[lane][i] = y * e.w[i];
-                et_s[lane] = e.et;
+                for (int i = 0; i < kTap; ++i) sh.in.w[wave][lane][i] = y * e.w[i];
+                sh.in.et[wave][lane] = e.et;
             }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+            __builtin_amdgcn_wave_barrier();
         }
-        __syncthreads();
-#pragma unroll 2
-        for (int i = 0; i < bk.n; i += 4) {
-            const float kv = response(u_s[i + q] - my_u, inv2s2, edge);
-            r0 = fmaf(kv, p_s[i + q], r0);
-            if (TILES > 0) {
-                const int et = et_s[i + q];
-                // energies ascend: the four events' first and last tiles
-                const int t0 = __builtin_amdgcn_readfirstlane(et_s[i]) >> 4;
-                const int t1 = (__builtin_amdgcn_readfirstlane(et_s[i + 3]) + kTap - 1) >> 4;
+#pragma unroll 1
+        for (int i0 = 0; i0 < bk.n; i0 += 16) {
+            float kv[4];
+            int et[4];
 #pragma unroll
-                for (int t = 0; t < TILES; ++t)
-                    if (t >= t0 && t <= t1) {
-                        const int d = 16 * t + c - et;
-                        const float w = (unsigned)d < kTap ? w_s[i + q][d & 7] : 0.0f;
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, w, acc[t], 0, 0, 0);
-                    }
+            for (int j = 0; j < 4; ++j) {
+                const int i = i0 + 4 * j + q;
+                kv[j] = response(sh.in.u[wave][i] - my_u, inv2s2, edge);
+                r0 = fmaf(kv[j], sh.in.p[wave][i], r0);
+                if (TILES > 0) et[j] = sh.in.et[wave][i];
+            }
+            if (TILES > 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    // energies ascend: the four events' first and last tiles
+                    const int t0 = __builtin_amdgcn_readlane(et[j], 0) >> 4;
+                    const int t1 = (__builtin_amdgcn_readlane(et[j], 63) + kTap - 1) >> 4;
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t)
+                        if (t >= t0 && t <= t1) {
+                            const int d = 16 * t + c - et[j];
+                            const float w = (unsigned)d < kTap ? sh.in.w[wave][i0 + 4 * j + q][d & 7] : 0.0f;
+                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j], w, acc[t], 0, 0, 0);
+                        }
+                }
             }
         }
     }
     r0 += __shfl_xor(r0, 16, 64);
     r0 += __shfl_xor(r0, 32, 64);
-    if (lane < 16 && k0 + c < g.n_p) R0[(size_t)ls * g.n_p + x_of[k0 + c]] = r0;
+    if (lane < 16) red0[wave][c] = r0;
+    __syncthreads();
+    if (TILES > 0 && wave > 0) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) sh.red[wave - 1][t][lane] = acc[t];
+    }
+    __syncthreads();
+    if (wave) return;
+    if (lane < 16 && k0 + c < g.n_p)
+        R0[(size_t)ls * g.n_p + x_of[k0 + c]] = (red0[0][c] + red0[1][c]) + (red0[2][c] + red0[3][c]);
+    if (TILES == 0) return;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = (acc[t] + sh.red[0][t][lane]) + (sh.red[1][t][lane] + sh.red[2][t][lane]);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int k = k0 + 4 * q + v;
-        if (TILES == 0 || k >= g.n_p) continue;
+        if (k >= g.n_p) continue;
         float *row = R + ((size_t)ls * g.n_p + x_of[k]) * fg.K + c;
 #pragma unroll
-        for (int t = 0; t < TILES; ++t)
+        for (int t = 0; t < NT; ++t)
             if (16 * t < fg.K) row[16 * t] = acc[t][v];
     }
 }
@@ -634,8 +722,11 @@ __global__ __launch_bounds__(64) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTabl
 // One workgroup: 32 directions x 32 scatter points, its four waves every
 // fourth angle each, added in LDS; the energy sum on the matrix cores with
 // both operands read as float4 along k (lane group q takes k = 16 i + 4 q + v
-// in step v).  Rows of T run from direction -3 to N + 4, so that the next
-// stage reads eight neighbours without wrapping.
+// in step v).  T holds groups of four directions, [group][box pixel][4], group
+// 0 directions -4 .. -1 and the last N .. N + 3, so that the next stage reads
+// eight neighbours in two or three wide loads and without wrapping.
+__host__ __device__ inline int field_groups(const FluxGeo &fg) { return fg.N / 4 + 2; }
+
 __global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ alist,
                                                      int n_list, int slot0, int n_slots, const float *__restrict__ R,
                                                      const float *__restrict__ R0, float *__restrict__ T,
@@ -717,27 +808,34 @@ __global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTabl
     if ((t == 1 && !two) || x >= g.n_p) return;
     const f32x4 v = (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
     const float m = ft.mu_s[x];
-    float *Tr = T + (size_t)r * (fg.N + kTap - 1) * fg.nb + ft.box[x];
+    f32x4 *Tr = reinterpret_cast<f32x4 *>(T) + (size_t)r * field_groups(fg) * fg.nb + ft.box[x];
+    const int d = n0 / 4 + 4 * t + q;   // directions 4 d .. 4 d + 3: group d + 1
+    f32x4 *o = Tr + (size_t)(d + 1) * fg.nb;
+    f32x4 y = first ? f32x4{0.f, 0.f, 0.f, 0.f} : *o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int n = n0 + 16 * t + 4 * q + i;
-        float *o = Tr + (size_t)(n + 3) * fg.nb;
-        const float y = first ? m * v[i] : fmaf(m, v[i], *o);
-        *o = y;
-        if (n < 4) o[(size_t)fg.N * fg.nb] = y;
-        if (n >= fg.N - 3) o[-(ptrdiff_t)fg.N * fg.nb] = y;
-    }
+    for (int i = 0; i < 4; ++i) y[i] = fmaf(m, v[i], y[i]);
+    *o = y;
+    if (d == 0) o[(size_t)(fg.N / 4) * fg.nb] = y;
+    if (d == fg.N / 4 - 1) *Tr = y;
 }
 
 // b_q: one workgroup per (block of 64 emission pixels, sector), as
 // k_flux_spread with the sums the other way round: the field's eight nodes
-// around each offset's direction, read along the pixels.  Each XCD takes a
-// run of sectors, so that its L2 holds the few rows of the field they read.
+// around each offset's direction, read along the pixels.  Interval n takes
+// directions n - 3 .. n + 4, values (n + 1) % 4 .. + 7 of the groups from
+// (n + 1) / 4 on: three float4 loads and twelve weights (zeros around the
+// eight).  Eight separate rows asked the vector cache for as many cycles but
+// for three times the lines, which then had to come from the L2 again for the
+// next offset.  Each XCD takes a run of sectors, so that its L2 holds the few
+// groups of the field they read.
+constexpr int kGroupTap = 12;
+
 __global__ __launch_bounds__(256) void k_flux_gather(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ beg_all,
                                                      const int *__restrict__ rec_off, const float *__restrict__ rec_w,
                                                      const float *__restrict__ sym, const float *__restrict__ T,
                                                      float *__restrict__ pb) {
     __shared__ float part[4][64];
+    __shared__ __align__(16) float w_s[4][64][kGroupTap];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n_sec = fg.N / kSec;
     const int item = xcd_logical(blockIdx.x, gridDim.x);
@@ -747,19 +845,50 @@ __global__ __launch_bounds__(256) void k_flux_gather(Geo g, FluxGeo fg, FluxTabl
     const unsigned top = (unsigned)fg.nb - 1;
     const size_t nb = fg.nb;
     float acc = 0.0f;
-    const int *beg = beg_all + b * fg.N + sec * kSec + wave * kWaveSec;
-    const float *__restrict__ Tk = T + ((size_t)r * (fg.N + kTap - 1) + sec * kSec + wave * kWaveSec) * nb;
-#pragma unroll 1
-    for (int k = 0; k < kWaveSec; ++k, Tk += nb) {
-        const int e0 = beg[k], e1 = beg[k + 1];
-#pragma unroll 4
-        for (int e = e0; e < e1; ++e) {
-            const float y = sym[(size_t)e * 64 + lane];
-            const unsigned at = min((unsigned)(lin + rec_off[e]), top);
-            float v = 0.0f;
+    const int n0 = sec * kSec + wave * kWaveSec;   // the wave's first interval
+    const int *beg = beg_all + b * fg.N + n0;
+    const int e0 = beg[0], e1 = beg[kWaveSec], b1 = beg[1], b2 = beg[2];
+    const f32x4 *__restrict__ Tr = reinterpret_cast<const f32x4 *>(T) + (size_t)r * field_groups(fg) * nb;
+    for (int c0 = e0; c0 < e1; c0 += 64) {
+        const int mine = min(c0 + lane, e1 - 1);
+        const int off = rec_off[mine], shift = (n0 + (mine >= b1) + (mine >= b2) + 1) & 3;
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(rec_w + (size_t)mine * kTap);
+        const f32x4 lo = src[0], hi = src[1];
+        float *w = w_s[wave][lane];
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int i = 0; i < kTap; ++i) v = fmaf(rec_w[(size_t)e * kTap + i], Tk[i * nb + at], v);
-            acc = y != 0.0f ? fmaf(y, v, acc) : acc;
+        for (int i = 0; i < kGroupTap; ++i) w[i] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w[shift + i] = lo[i];
+            w[shift + 4 + i] = hi[i];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+        __builtin_amdgcn_wave_barrier();
+        const int n = min(64, e1 - c0);
+        const float *__restrict__ sy = sym + (size_t)c0 * 64 + lane;
+#pragma unroll 1
+        for (int u0 = 0; u0 < n; u0 += 4) {
+            float y[4];
+            f32x4 t[4][3];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = min(u0 + u, n - 1), m = n0 + (c0 + i >= b1) + (c0 + i >= b2) + 1;
+                y[u] = u0 + u < n ? sy[(size_t)i * 64] : 0.0f;
+                const unsigned at = min((unsigned)(lin + __builtin_amdgcn_readlane(off, i)), top);
+                const f32x4 *__restrict__ T0 = Tr + (size_t)(m >> 2) * nb;
+                t[u][0] = T0[at];
+                t[u][1] = (T0 + nb)[at];
+                t[u][2] = (T0 + (m & 3 ? 2 * nb : nb))[at];   // (all eight in two groups: no third)
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float *wu = w_s[wave][min(u0 + u, n - 1)];
+                float v = 0.0f;
+#pragma unroll
+                for (int j = 0; j < kGroupTap; ++j) v = fmaf(wu[j], t[u][j >> 2][j & 3], v);
+                acc = y[u] != 0.0f ? fmaf(y[u], v, acc) : acc;
+            }
         }
     }
     part[wave][lane] = acc;
@@ -1224,7 +1353,7 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
 static size_t up64(size_t n) { return (n + 63) & ~size_t(63); }
 int flux_rows(const FluxGeo &fg) { return fg.N / kSec + 1; }
 static size_t per_real(const Geo &g, const FluxGeo &fg) {
-    return up64(fg.N ? fg.nb : 0) + up64((size_t)2 * fg.N * fg.np64) + up64(fg.N ? (size_t)(fg.N + kTap - 1) * fg.nb : 0) +
+    return up64(fg.N ? fg.nb : 0) + up64((size_t)2 * fg.N * fg.np64) + up64(fg.N ? (size_t)4 * field_groups(fg) * fg.nb : 0) +
            up64((size_t)flux_rows(fg) * g.n_qpad);
 }
 static size_t per_slot(const Geo &g, const FluxGeo &fg) { return (size_t)g.n_p * (fg.K + 1); }
@@ -1267,7 +1396,7 @@ struct Carve {
         auto take = [&](size_t per) { float *q = p; p += n_real * up64(per); return q; };
         fbox = take(fg.N ? fg.nb : 0);
         I = take((size_t)2 * fg.N * fg.np64);
-        T = take(fg.N ? (size_t)(fg.N + kTap - 1) * fg.nb : 0);
+        T = take(fg.N ? (size_t)4 * field_groups(fg) * fg.nb : 0);
         pb = take((size_t)flux_rows(fg) * g.n_qpad);
         const size_t used = (size_t)(p - ws), room = floats > used ? floats - used : 0;
         slots = (int)std::min<size_t>(room / per_slot(g, fg), 1 << 30);
@@ -1359,7 +1488,7 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
                 const int zr = (s1 - 1) / p.n_list - s0 / p.n_list + 1;
                 // 16-node tiles of the energy nodes held in registers
                 auto *adj = !sc ? k_flux_adjoint<0> : fg.K <= 96 ? k_flux_adjoint<6> : k_flux_adjoint<kMaxTiles>;
-                hipLaunchKernelGGL(adj, ag, dim3(64), 0, p.st, g, fg, ft, p.ev, p.blk, p.t->us_sorted, p.alist, p.blk_beg + sb,
+                hipLaunchKernelGGL(adj, ag, dim3(256), 0, p.st, g, fg, ft, p.ev, p.blk, p.t->us_sorted, p.alist, p.blk_beg + sb,
                                    p.n_list, s0, p.row_base, p.inv, w.S, w.SP);
                 if (sc) {
                     hipLaunchKernelGGL(k_flux_fields, dim3((g.n_p + 31) / 32, (fg.N + 31) / 32, zr), dim3(256), 0, p.st, g,
