@@ -47,7 +47,7 @@ namespace lmo {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kSec = 12;    // direction nodes per sector (one wave's share of a pixel block's pairs)
+constexpr int kSec = 12;    // direction intervals per sector (a workgroup's share of a pixel block's pairs)
 constexpr int kTap = 8;     // interpolation points
 constexpr int kStrip = 16;  // columns of a strip of the flux order
 
@@ -66,7 +66,9 @@ __device__ __forceinline__ void fit_weights(const FluxFit &fit, double t, double
 }
 
 // workgroups are dealt to the 8 XCDs round-robin: the item that gives each
-// XCD one contiguous run
+// XCD one contiguous run.  Each XCD's L2 starts a kernel empty, so what all
+// eight read crosses the fabric eight times: the stages order their items so
+// that a run shares its larger operand.
 __device__ __forceinline__ int xcd_logical(int p, int n) {
     const int x = p % 8, m = n / 8, rem = n % 8;
     return x * m + min(x, rem) + p / 8;
@@ -119,7 +121,7 @@ __global__ __launch_bounds__(64) void k_flux_pairs(Geo g, FluxGeo fg, FluxFit fi
                                                    const float *__restrict__ mu, const double *__restrict__ Bt,
                                                    const int *__restrict__ cnt, const int2 *__restrict__ off, int cap,
                                                    int *__restrict__ beg, int *__restrict__ rec_off,
-                                                   float *__restrict__ rec_w, double *__restrict__ rec_w64,
+                                                   int *__restrict__ rec_n, float *__restrict__ rec_w, double *__restrict__ rec_w64,
                                                    float *__restrict__ sym) {
     const int n = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
     const int x = b * 64 + lane < g.n_p ? sup[b * 64 + lane] : -1;
@@ -142,6 +144,7 @@ __global__ __launch_bounds__(64) void k_flux_pairs(Geo g, FluxGeo fg, FluxFit fi
             sym[(size_t)at * 64 + lane] = (float)v;
             if (lane == 0) {
                 rec_off[at] = d.y * fg.W + d.x;
+                rec_n[at] = n;
                 double w[kTap];
                 fit_weights(fit, node_pos(d.x, d.y, fg.N) - n, w);
 #pragma unroll
@@ -223,109 +226,101 @@ __global__ void k_flux_box(Geo g, FluxGeo fg, FluxTables ft, const float *__rest
 }
 
 // I_s(n): one workgroup per (block of 64 scatter points, sector of kSec node
-// intervals), each of its four waves a quarter of the sector.  Every lane
-// visits the same offset, so its direction's weights and nodes are scalars
-// and the eight sums of the current interval's nodes sit in registers, moving
-// on by one node per interval; the pair factors stream in as written, one per
-// lane.  The waves' nodes overlap and are added in LDS; a sector touches
-// kSec + 7 nodes, so even and odd sectors write two separate copies (24 nodes
-// each, the rest zero) that the next stage adds.
-constexpr int kWaveSec = kSec / 4;             // intervals of one wave
-static_assert(kWaveSec == 3, "the spread's interval bounds");
-constexpr int kWaveNodes = kWaveSec + kTap - 1;
-constexpr int kBatch = 8;                      // pairs loaded together
+// intervals); its eight waves share the sector's pairs evenly (a sector that
+// looks across the object has four times the average, and would be the last to
+// end by far).  Every lane visits the same offset, so its direction's weights
+// are broadcasts and the eight sums of the current interval's nodes sit in
+// registers, moving on by one node per interval; the pair factors stream in as
+// written, one per lane.  The waves' nodes overlap and are added in LDS; a
+// sector touches kSec + 7 nodes, so even and odd sectors write two separate
+// copies (24 nodes each, the rest zero) that the next stage adds.
+constexpr int kPairWaves = 8;   // waves of a workgroup of the pair stages
+constexpr int kBatch = 8;       // pairs loaded together
+constexpr int kChunk = 32;      // pairs whose records a wave holds
+constexpr int kSecNodes = kSec + kTap - 1;
 
-// up to 64 pair records of a wave: each lane fetches one (its box offset stays
-// in the lane, to be read back as a scalar; its weights go to LDS, to be read
-// back as a broadcast), so that the pair loop itself waits for no scalar load
-struct WaveRecords {
-    int off;
-    __device__ __forceinline__ void load(const int *__restrict__ rec_off, const float *__restrict__ rec_w, int e, int e1,
-                                         float (*w)[kTap], int lane) {
-        const int i = min(e + lane, e1 - 1);
-        off = rec_off[i];
-        const f32x4 *src = reinterpret_cast<const f32x4 *>(rec_w + (size_t)i * kTap);
-        const f32x4 lo = src[0], hi = src[1];
-        *reinterpret_cast<f32x4 *>(&w[lane][0]) = lo;
-        *reinterpret_cast<f32x4 *>(&w[lane][4]) = hi;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
-        __builtin_amdgcn_wave_barrier();
-    }
-};
-
-__global__ __launch_bounds__(256) void k_flux_spread(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ beg_all,
-                                                     const int *__restrict__ rec_off, const float *__restrict__ rec_w,
-                                                     const float *__restrict__ sym, const float *__restrict__ fbox,
-                                                     float *__restrict__ I) {
-    __shared__ float part[4][kWaveNodes][64];
-    __shared__ __align__(16) float w_s[4][64][kTap];
+__global__ __launch_bounds__(64 * kPairWaves) void k_flux_spread(Geo g, FluxGeo fg, FluxTables ft,
+                                                                 const int *__restrict__ beg_all,
+                                                                 const int *__restrict__ rec_off,
+                                                                 const float *__restrict__ rec_w,
+                                                                 const float *__restrict__ sym,
+                                                                 const float *__restrict__ fbox, float *__restrict__ I) {
+    __shared__ float part[kPairWaves][kSecNodes][64];
+    __shared__ __align__(16) float w_s[kPairWaves][kChunk][kTap];
+    __shared__ int span[kPairWaves][2];   // nodes that a wave has written
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int sec = blockIdx.y, b = blockIdx.x, r = blockIdx.z;
     const int s = b * 64 + lane;
     const int lin = s < g.n_p ? ft.box[s] : 0;
     const float *__restrict__ fr = fbox + (size_t)r * fg.nb;
     const unsigned top = (unsigned)fg.nb - 1;
-    float acc[kTap];
+    const int bound = beg_all[b * fg.N + sec * kSec + min(lane, kSec)];   // lane i: first record of interval i
+    const int first = __builtin_amdgcn_readlane(bound, 0), end = __builtin_amdgcn_readlane(bound, kSec);
+    const int share = (end - first + kPairWaves - 1) / kPairWaves;
+    const int e0 = min(first + wave * share, end), e1 = min(e0 + share, end);
+    // the interval of the wave's first pair
+    int k = __popcll(__ballot(lane > 0 && lane < kSec && bound <= e0));
+    if (lane == 0) span[wave][0] = k;
+    if (e0 < e1) {
+        float acc[kTap];
 #pragma unroll
-    for (int i = 0; i < kTap; ++i) acc[i] = 0.0f;
-    const int *beg = beg_all + b * fg.N + sec * kSec + wave * kWaveSec;
-    const int e0 = beg[0], e1 = beg[kWaveSec];
-    int bound[kWaveSec];
-#pragma unroll
-    for (int i = 0; i < kWaveSec; ++i) bound[i] = beg[i + 1];
-    int k = 0, next = bound[0];
-    for (int c0 = e0; c0 < e1; c0 += 64) {
-        WaveRecords rec;
-        rec.load(rec_off, rec_w, c0, e1, w_s[wave], lane);
-        const int n = min(64, e1 - c0);
-        const float *__restrict__ sy = sym + (size_t)c0 * 64 + lane;
+        for (int i = 0; i < kTap; ++i) acc[i] = 0.0f;
+        int next = __builtin_amdgcn_readlane(bound, k + 1);
+        for (int c0 = e0; c0 < e1; c0 += kChunk) {
+            // a lane fetches a pair's record: the box offset stays there, to be
+            // read back as a scalar, and the weights go to LDS, to be read back
+            // as a broadcast, so that the pair loop waits for no scalar load
+            const int mine = min(c0 + (lane & (kChunk - 1)), e1 - 1);
+            const int off = rec_off[mine];
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(rec_w + (size_t)mine * kTap);
+            const f32x4 half = src[lane / kChunk];
+            __builtin_amdgcn_wave_barrier();
+            *reinterpret_cast<f32x4 *>(&w_s[wave][lane & (kChunk - 1)][4 * (lane / kChunk)]) = half;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+            __builtin_amdgcn_wave_barrier();
+            const int n = min(kChunk, e1 - c0);
+            const float *__restrict__ sy = sym + (size_t)c0 * 64 + lane;
 #pragma unroll 2
-        for (int u0 = 0; u0 < n; u0 += kBatch) {
-            float y[kBatch], v[kBatch];
+            for (int u0 = 0; u0 < n; u0 += kBatch) {
+                float y[kBatch], v[kBatch];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int i = min(u0 + u, n - 1);
-                y[u] = sy[(size_t)i * 64];
-                v[u] = fr[min((unsigned)(lin + __builtin_amdgcn_readlane(rec.off, i)), top)];
-            }
+                for (int u = 0; u < kBatch; ++u) {
+                    const int i = min(u0 + u, n - 1);
+                    y[u] = sy[(size_t)i * 64];
+                    v[u] = fr[min((unsigned)(lin + __builtin_amdgcn_readlane(off, i)), top)];
+                }
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                if (u0 + u < n) {
-                    while (c0 + u0 + u >= next) {   // the lowest node is complete: on to the next interval
-                        part[wave][k][lane] = acc[0];
+                for (int u = 0; u < kBatch; ++u) {
+                    if (u0 + u < n) {
+                        while (c0 + u0 + u >= next) {   // the lowest node is complete: on to the next interval
+                            part[wave][k][lane] = acc[0];
 #pragma unroll
-                        for (int i = 0; i + 1 < kTap; ++i) acc[i] = acc[i + 1];
-                        acc[kTap - 1] = 0.0f;
-                        ++k;
-                        next = k == 1 ? bound[1] : bound[2];
+                            for (int i = 0; i + 1 < kTap; ++i) acc[i] = acc[i + 1];
+                            acc[kTap - 1] = 0.0f;
+                            ++k;
+                            next = __builtin_amdgcn_readlane(bound, k + 1);
+                        }
+                        const float p = y[u] != 0.0f ? y[u] * v[u] : 0.0f;
+#pragma unroll
+                        for (int i = 0; i < kTap; ++i) acc[i] = fmaf(w_s[wave][u0 + u][i], p, acc[i]);
                     }
-                    const float p = y[u] != 0.0f ? y[u] * v[u] : 0.0f;
-#pragma unroll
-                    for (int i = 0; i < kTap; ++i) acc[i] = fmaf(w_s[wave][u0 + u][i], p, acc[i]);
                 }
             }
         }
-    }
-    for (; k < kWaveSec; ++k) {
-        part[wave][k][lane] = acc[0];
 #pragma unroll
-        for (int i = 0; i + 1 < kTap; ++i) acc[i] = acc[i + 1];
-        acc[kTap - 1] = 0.0f;
+        for (int i = 0; i < kTap; ++i) part[wave][k + i][lane] = acc[i];
     }
-#pragma unroll
-    for (int i = 0; i + 1 < kTap; ++i) part[wave][kWaveSec + i][lane] = acc[i];
+    if (lane == 0) span[wave][1] = e0 < e1 ? k + kTap : 0;
     __syncthreads();
     // directions of flight q -> s are opposite to the offsets s -> q
     const int n0 = sec * kSec - 3 + fg.N / 2;
     const float m = s < g.n_p ? ft.mu_s[s] : 0.0f;
     float *out = I + ((size_t)(r * 2 + (sec & 1)) * fg.N) * fg.np64 + s;
-    for (int j = wave; j < 2 * kSec; j += 4) {
+    for (int j = wave; j < 2 * kSec; j += kPairWaves) {
         float t = 0.0f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int l = j - w * kWaveSec;
-            if (l >= 0 && l < kWaveNodes) t += part[w][l][lane];
-        }
+        for (int w = 0; w < kPairWaves; ++w)
+            if (j >= span[w][0] && j < span[w][1]) t += part[w][j][lane];
         out[(size_t)wrap(n0 + j, fg.N) * fg.np64] = m * t;
     }
 }
@@ -333,23 +328,28 @@ __global__ __launch_bounds__(256) void k_flux_spread(Geo g, FluxGeo fg, FluxTabl
 // S_as(k) and P_as of a chunk of (realisation, angle) slots, in rank order:
 // C[s][k] = sum_n A[s][n] G_a[n][k] on v_mfma_f32_16x16x4_f32 with
 // A = I psi e^(-rho L) formed in the operand registers.  One workgroup: 32
-// scatter points x up to 96 energy nodes, its four waves a quarter of the
-// directions each, added in LDS (small problems would otherwise be one long
-// chain of loads per wave).
-constexpr int kSpecTiles = 6;   // 16-node tiles of one workgroup
+// scatter points x NT tiles of 16 energy nodes, its eight waves an eighth of
+// the directions each, added in LDS: one wave's share is a chain of loads from
+// the L2, and a small problem has few workgroups.
+constexpr int kSpecTiles = 6;   // most 16-node tiles of one workgroup
+constexpr int kSpecWaves = 8;
 
-__global__ __launch_bounds__(256) void k_flux_spectra(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ alist,
-                                                      int n_list, int slot0, const float *__restrict__ I,
-                                                      const float *__restrict__ f, float *__restrict__ S,
-                                                      float *__restrict__ SP) {
-    __shared__ f32x4 red[4][2 * kSpecTiles][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+template <int NT>
+__global__ __launch_bounds__(64 * kSpecWaves) void k_flux_spectra(Geo g, FluxGeo fg, FluxTables ft,
+                                                                  const int *__restrict__ alist, int n_list, int per,
+                                                                  int slot0, const float *__restrict__ I, const float *__restrict__ f,
+                                                                  float *__restrict__ S, float *__restrict__ SP) {
+    __shared__ f32x4 red[kSpecWaves / 2][2 * NT][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c = lane & 15, q = lane >> 4;
-    const int s0 = blockIdx.x * 32, ls = blockIdx.y, slot = slot0 + ls;
+    // items: point tiles, all of a realisation's angles in turn (per: its slots here)
+    const int n_s = (g.n_p + 31) / 32, item = xcd_logical(blockIdx.x, gridDim.x);
+    const int grp = item / (n_s * per), tile_s = (item - grp * n_s * per) / per;
+    const int s0 = tile_s * 32, ls = grp * per + (item - (grp * n_s + tile_s) * per), slot = slot0 + ls;
     const int r = slot / n_list, a = alist[slot - r * n_list];
-    const int kb = blockIdx.z * 16 * kSpecTiles, n_kt = min(kSpecTiles, (fg.K - kb) / 16);
+    const int kb = blockIdx.y * 16 * NT, n_kt = min(NT, (fg.K - kb) / 16);
     const int *rank = ft.rank_of + (size_t)a * g.n_p;
-    if (blockIdx.z == 0 && threadIdx.x < 32) {
+    if (blockIdx.y == 0 && threadIdx.x < 32) {
         const int s = s0 + threadIdx.x;
         if (s < g.n_p) {
             const int p = ft.sup[s];
@@ -360,36 +360,59 @@ __global__ __launch_bounds__(256) void k_flux_spectra(Geo g, FluxGeo fg, FluxTab
     const float *psi = ft.psi + (size_t)a * fg.N, *rho = ft.rho + (size_t)a * fg.N;
     const float *G = ft.G + (size_t)a * fg.N * fg.K + kb + c;
     float L[2];
-    f32x4 acc[2][kSpecTiles];
+    f32x4 acc[2][NT];
+    int tile[NT];   // (a last part may have fewer tiles: the rest repeat its last and are dropped)
+#pragma unroll
+    for (int kt = 0; kt < NT; ++kt) tile[kt] = 16 * min(kt, n_kt - 1);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         L[t] = ft.Lx[(size_t)a * g.n_p + min(s0 + 16 * t + c, g.n_p - 1)];
 #pragma unroll
-        for (int kt = 0; kt < kSpecTiles; ++kt) acc[t][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kt = 0; kt < NT; ++kt) acc[t][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const int nq = fg.N / 4;
-#pragma unroll 3
-    for (int n = wave * nq + q; n < (wave + 1) * nq; n += 4) {
-        const float ps = psi[n], rh = rho[n];
-        float gv[kSpecTiles];
+    // N is a multiple of 48: groups of four directions go round the waves
+    // three at a time, so that a wave has all operands of 12 in flight
+    for (int n1 = wave * 12; n1 < fg.N; n1 += 12 * kSpecWaves) {
+        float ps[3], rh[3], gv[3][NT], iv[3][2];
 #pragma unroll
-        for (int kt = 0; kt < kSpecTiles; ++kt) gv[kt] = kt < n_kt ? G[(size_t)n * fg.K + 16 * kt] : 0.0f;
+        for (int j = 0; j < 3; ++j) {
+            const int n = n1 + 4 * j + q;
+            ps[j] = psi[n];
+            rh[j] = rho[n];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const size_t at = (size_t)n * fg.np64 + 16 * t;   // np64 covers whole groups of 32
-            const float av = (I0[at] + I1[at]) * ps * __builtin_amdgcn_exp2f(rh * L[t]);
+            for (int kt = 0; kt < NT; ++kt) gv[j][kt] = G[(unsigned)(n * fg.K + tile[kt])];
 #pragma unroll
-            for (int kt = 0; kt < kSpecTiles; ++kt)
-                if (kt < n_kt) acc[t][kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, gv[kt], acc[t][kt], 0, 0, 0);
+            for (int t = 0; t < 2; ++t) {
+                const unsigned at = (unsigned)n * fg.np64 + 16 * t;   // np64 covers whole groups of 32
+                iv[j][t] = I0[at] + I1[at];
+            }
         }
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float av = iv[j][t] * ps[j] * __builtin_amdgcn_exp2f(rh[j] * L[t]);
+#pragma unroll
+                for (int kt = 0; kt < NT; ++kt)
+                    acc[t][kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, gv[j][kt], acc[t][kt], 0, 0, 0);
+            }
     }
+    if (wave >= kSpecWaves / 2) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int kt = 0; kt < kSpecTiles; ++kt) red[wave][t * kSpecTiles + kt][lane] = acc[t][kt];
+            for (int kt = 0; kt < NT; ++kt) red[wave - kSpecWaves / 2][t * NT + kt][lane] = acc[t][kt];
+    }
     __syncthreads();
-    for (int i = wave; i < 2 * kSpecTiles; i += 4) {
-        const int t = i / kSpecTiles, kt = i - t * kSpecTiles;
+    if (wave < kSpecWaves / 2) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int kt = 0; kt < NT; ++kt) red[wave][t * NT + kt][lane] += acc[t][kt];
+    }
+    __syncthreads();
+    for (int i = wave; i < 2 * NT; i += kSpecWaves) {
+        const int t = i / NT, kt = i - t * NT;
         if (kt >= n_kt) continue;
         const f32x4 v = (red[0][i][lane] + red[1][i][lane]) + (red[2][i][lane] + red[3][i][lane]);
 #pragma unroll
@@ -409,74 +432,100 @@ __device__ __forceinline__ float response(double d, float inv2s2, float edge) {
 
 // Event means on the matrix cores.  Events come in blocks of 64 neighbours in
 // position, ordered by energy within a block; a wave takes 16 of them:
-// V[j][k] = sum_s K_js S_as(k) over the ends that any of them reaches and the
-// 16-node tiles that their eight nodes touch, then mean_j = sum_k l_k(E_j) V[j][k].
-// The responses are the A operand, formed in registers (one per event and
-// end); 16 events share each read of the spectra.  The energy order keeps a
-// wave's nodes to two or three tiles.
+// V[k][j] = sum_s S_as(k) K_js over the ends that any of them reaches and the
+// 16-node tiles that their eight nodes touch, then mean_j = sum_k l_k(E_j) V[k][j].
+// The spectra are the A operand, the responses, formed in registers (one per
+// end and event), the B operand: a lane's sums then all belong to one event,
+// its weights are read four nodes at a time from a row with zeros around the
+// eight, and three additions end the sum.  16 events share each read of the
+// spectra, and the energy order keeps a wave's nodes to two or three tiles.
+//
+// SPLIT waves share the ends of 16 events: one where events reach few ends (a
+// wave's work is then mostly its start and end), two where they reach more (a
+// single small set would otherwise be a long chain on few waves).  The waves of
+// a workgroup that work on the same ends read the same spectra.
 constexpr int kMaxTiles = kFluxMaxK / 16;
+constexpr int kEvRow = 28;   // floats of an event's row in LDS: head 8, zeros 4, weights 8, zeros 4
 
-template <int TILES>
-__global__ __launch_bounds__(256) void k_flux_means(Geo g, FluxGeo fg, const FluxEvent *__restrict__ ev,
+// minimum and maximum over 16 lanes
+__device__ __forceinline__ int dpp(int x, const int ctrl) {
+    switch (ctrl) {
+        case 0: return __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xf, 0xf, false);    // lane ^ 1
+        case 1: return __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xf, 0xf, false);    // lane ^ 2
+        case 2: return __builtin_amdgcn_update_dpp(x, x, 0x141, 0xf, 0xf, false);   // 7 - lane of 8
+        default: return __builtin_amdgcn_update_dpp(x, x, 0x140, 0xf, 0xf, false);  // 15 - lane of 16
+    }
+}
+
+template <int TILES, int SPLIT>
+__global__ __launch_bounds__(256 * SPLIT) void k_flux_means(Geo g, FluxGeo fg, const FluxEvent *__restrict__ ev,
                                                     const FluxBlock *__restrict__ blk,
                                                     const double *__restrict__ us_sorted,
                                                     const int *__restrict__ alist, int n_list, int slot_base, int slot0,
                                                     int row0, int row_base, const float *__restrict__ S,
                                                     const float *__restrict__ SP, float *__restrict__ mean,
                                                     float *__restrict__ inv, unsigned long long *__restrict__ skipped) {
-    __shared__ float w_s[4][16][kTap];
-    __shared__ int et_s[4][16];
-    __shared__ double us_s[4][64];
-    __shared__ float pr_s[4][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    static_assert(sizeof(FluxEvent) == 64 && kTap == 8, "four 16-byte pieces: head, ranks, weights");
+    constexpr int WAVES = 4 * SPLIT;
+    __shared__ __align__(16) float ev_s[WAVES][16][kEvRow];
+    __shared__ double us_s[WAVES][64];
+    __shared__ float pr_s[WAVES][64], sum_s[WAVES][16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c = lane & 15, q = lane >> 4;
-    const FluxBlock bk = blk[blockIdx.x];
-    const int i = wave * 16 + c;   // this lane's event in the block
-    const bool on = i < bk.n;
-    if (wave * 16 >= bk.n) return;
+    const int item = xcd_logical(blockIdx.x, gridDim.x);   // (runs of slots: their spectra)
+    const FluxBlock bk = blk[item];
+    const int part = wave / 4, i0 = 16 * (wave % 4);   // the wave's share of the ends, its first event in the block
+    const bool idle = i0 >= bk.n;
+    if (SPLIT == 1 && idle) return;
     const int slot = bk.slot - slot_base, ls = slot - slot0, r = slot / n_list;
     const size_t ao = (size_t)alist[slot - r * n_list] * g.n_p;
     const double *us = us_sorted + ao;
-    FluxEvent e = ev[bk.row + min(i, bk.n - 1) - row0];
-    if (q == 0) {
-#pragma unroll
-        for (int t = 0; t < kTap; ++t) w_s[wave][c][t] = on ? e.w[t] : 0.0f;
-        et_s[wave][c] = e.et;
+    {
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(ev + (bk.row + min(i0 + (lane >> 2), bk.n - 1) - row0));
+        const int piece = lane & 3;
+        const f32x4 v = src[piece];
+        float *row = ev_s[wave][lane >> 2];
+        *reinterpret_cast<f32x4 *>(row + 4 * piece + (piece >= 2 ? 4 : 0)) = v;
+        if (piece < 2) *reinterpret_cast<f32x4 *>(row + (piece ? 20 : 8)) = f32x4{0.f, 0.f, 0.f, 0.f};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+        __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
-    __builtin_amdgcn_wave_barrier();
-    // the wave's ranks and tiles
-    int r0 = e.r0, r1 = e.r1, t0 = e.et >> 4, t1 = (e.et + kTap - 1) >> 4;
+    const FluxEvent &e = *reinterpret_cast<const FluxEvent *>(ev_s[wave][c]);   // (its weights lie four floats on)
+    const double u = e.u;
+    const int et = e.et;
+    // the wave's ranks and tiles (energies ascend)
+    int r0 = e.r0, r1 = e.r1;
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-        r0 = min(r0, __shfl_xor(r0, o, 64));
-        r1 = max(r1, __shfl_xor(r1, o, 64));
-        t0 = min(t0, __shfl_xor(t0, o, 64));
-        t1 = max(t1, __shfl_xor(t1, o, 64));
+    for (int o = 0; o < 4; ++o) {
+        r0 = min(r0, dpp(r0, o));
+        r1 = max(r1, dpp(r1, o));
     }
     r0 = __builtin_amdgcn_readfirstlane(r0);
     r1 = __builtin_amdgcn_readfirstlane(r1);
-    t0 = __builtin_amdgcn_readfirstlane(t0);
-    t1 = __builtin_amdgcn_readfirstlane(t1);
+    const int t0 = __builtin_amdgcn_readlane(et, 0) >> 4, t1 = (__builtin_amdgcn_readlane(et, 15) + kTap - 1) >> 4;
+    if (SPLIT > 1) {   // this wave's share
+        const int per = ((r1 - r0 + SPLIT - 1) / SPLIT + 3) & ~3;
+        r0 = min(r0 + part * per, r1);
+        r1 = idle ? r0 : min(r0 + per, r1);
+    }
     const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
     const float edge = expf(-4.5f);
     const float *Sr = S + (size_t)ls * g.n_p * fg.K, *Pr = SP + (size_t)ls * g.n_p;
-    float total[4] = {0.f, 0.f, 0.f, 0.f};   // of events 4 q + v, this lane's nodes
-    float prim = 0.0f;
+    const unsigned K = fg.K, last = (unsigned)(r1 - 1) * K + c;
+    float total = 0.0f, prim = 0.0f;   // of this lane's event and nodes
     // up to TILES tiles at a time
     for (int tb = t0; tb <= t1; tb += TILES) {
         const int nt = min(TILES, t1 + 1 - tb);
         f32x4 acc[TILES];
 #pragma unroll
         for (int t = 0; t < TILES; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // path ends go to LDS 64 at a time: read from memory where they are
-        // used, they would cost the vector cache as much as the spectra do.
-        // 16 ranks' spectra are read before the first is used.
-        const float *Sc = Sr + 16 * tb + c;
+        const float *Sc = Sr + 16 * tb;
+        // path ends go to LDS 64 at a time, those past the wave's out of
+        // reach; 16 ranks' spectra are read before the first is used
 #pragma unroll 1
         for (int kc = r0; kc < r1; kc += 64) {
             const int kl = min(kc + lane, r1 - 1);
-            const double ul = us[kl];
+            const double ul = kc + lane < r1 ? us[kl] : 1e30;
             const float pl = Pr[kl];
             __builtin_amdgcn_wave_barrier();
             us_s[wave][lane] = ul;
@@ -484,54 +533,51 @@ __global__ __launch_bounds__(256) void k_flux_means(Geo g, FluxGeo fg, const Flu
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
             __builtin_amdgcn_wave_barrier();
             const int n = min(64, r1 - kc);
+            unsigned at = (unsigned)(kc + q) * K + c;
 #pragma unroll 1
             for (int k0 = 0; k0 < n; k0 += 16) {
                 float sv[4][TILES];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float *row = Sc + (size_t)min(kc + k0 + 4 * j + q, r1 - 1) * fg.K;
+                    const unsigned o = min(at, last);
+                    at += 4 * K;
 #pragma unroll
                     for (int t = 0; t < TILES; ++t)
-                        if (t < nt) sv[j][t] = row[16 * t];
+                        if (t < nt) sv[j][t] = Sc[o + 16 * t];
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int k = k0 + 4 * j + q;
-                    float kv = response(e.u - us_s[wave][k], inv2s2, edge);
-                    kv = k < n ? kv : 0.0f;
+                    const float kv = response(u - us_s[wave][k], inv2s2, edge);
                     if (tb == t0) prim = fmaf(kv, pr_s[wave][k], prim);
 #pragma unroll
                     for (int t = 0; t < TILES; ++t)
-                        if (t < nt) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, sv[j][t], acc[t], 0, 0, 0);
+                        if (t < nt) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sv[j][t], kv, acc[t], 0, 0, 0);
                 }
             }
         }
 #pragma unroll
         for (int t = 0; t < TILES; ++t)
-            if (t < nt)
+            if (t < nt) {
+                const int d = 16 * (tb + t) + 4 * q - et;   // of the lane's first node in the event's eight
+                const float *w = &ev_s[wave][c][12 + min(max(d, -4), kTap)];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int d = 16 * (tb + t) + c - et_s[wave][4 * q + v];
-                    const float w = (unsigned)d < kTap ? w_s[wave][4 * q + v][d & 7] : 0.0f;
-                    total[v] = fmaf(w, acc[t][v], total[v]);
-                }
+                for (int v = 0; v < 4; ++v) total = fmaf(w[v], acc[t][v], total);
+            }
     }
-    prim += __shfl_xor(prim, 16, 64);
-    prim += __shfl_xor(prim, 32, 64);
+    float s = fmaf(prim, e.g0, total);
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if (SPLIT > 1) {
+        if (lane < 16) sum_s[wave][c] = s;
+        __syncthreads();
+        if (part || idle) return;
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) total[v] += __shfl_xor(total[v], o, 64);
-    // event c sits in lane group c / 4, element c % 4
-    float s = 0.0f;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const float x = __shfl(total[v], (c >> 2) * 16, 64);
-        s = (c & 3) == v ? x : s;
+        for (int p = 1; p < SPLIT; ++p) s += sum_s[wave + 4 * p][c];
     }
     int dead = 0;
-    if (q == 0 && on) {
-        s = (s + prim * e.g0) * fg.inv_zk;
+    if (q == 0 && i0 + c < bk.n) {
+        s *= fg.inv_zk;
         const int j = e.row - row_base;
         mean[j] = s;
         dead = !(s > 1e-30f);
@@ -632,11 +678,12 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
     __shared__ __align__(16) Shared sh;
     __shared__ float red0[4][16];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
-    const int ls = blockIdx.y, slot = slot0 + ls;
+    const int item = xcd_logical(blockIdx.x, gridDim.x), n_k = (g.n_p + 15) / 16;   // (runs of slots: their events)
+    const int ls = item / n_k, slot = slot0 + ls;
     const int r = slot / n_list, a = alist[slot - r * n_list];
     const double *us = us_sorted + (size_t)a * g.n_p;
     const int *x_of = ft.x_of + (size_t)a * g.n_p;
-    const int k0 = blockIdx.x * 16, rank = min(k0 + c, g.n_p - 1);
+    const int k0 = (item - ls * n_k) * 16, rank = min(k0 + c, g.n_p - 1);
     const double my_u = us[rank], reach = 3.0 * g.sig_u;
     const int b0 = wave_search<false>(blk, blk_beg[slot], blk_beg[slot + 1], us[k0] - reach, lane);
     const int b1 = wave_search<true>(blk, b0, blk_beg[slot + 1], us[min(k0 + 15, g.n_p - 1)] + reach, lane);
@@ -719,25 +766,30 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
 // T_s(n) = mu(s) sum_a psi_a(n) e^(-rho_a(n) L_a(s)) sum_k G_a[n][k] R_as(k),
 // over the chunk's angles of one realisation (added to the stored field from
 // the second chunk on), and the primary paths' share of the backprojection.
-// One workgroup: 32 directions x 32 scatter points, its four waves every
-// fourth angle each, added in LDS; the energy sum on the matrix cores with
+// One workgroup: 32 directions x 32 scatter points, its eight waves every
+// eighth angle each, added in LDS; the energy sum on the matrix cores with
 // both operands read as float4 along k (lane group q takes k = 16 i + 4 q + v
 // in step v).  T holds groups of four directions, [group][box pixel][4], group
 // 0 directions -4 .. -1 and the last N .. N + 3, so that the next stage reads
 // eight neighbours in two or three wide loads and without wrapping.
 __host__ __device__ inline int field_groups(const FluxGeo &fg) { return fg.N / 4 + 2; }
 
-__global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ alist,
+constexpr int kFieldWaves = 8;
+
+__global__ __launch_bounds__(64 * kFieldWaves) void k_flux_fields(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ alist,
                                                      int n_list, int slot0, int n_slots, const float *__restrict__ R,
                                                      const float *__restrict__ R0, float *__restrict__ T,
                                                      float *__restrict__ pb) {
-    __shared__ f32x4 red[4][4][64];   // [wave][direction tile * 2 + point tile]
-    __shared__ float red0[4][32];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ f32x4 red[kFieldWaves][4][64];   // [wave][direction tile * 2 + point tile]
+    __shared__ float red0[kFieldWaves][32];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c = lane & 15, q = lane >> 4;
-    const int n0 = blockIdx.y * 32, s0 = blockIdx.x * 32;
+    // items: point tiles, all directions in turn (they share the tile's rows of R)
+    const int n_n = (fg.N + 31) / 32, n_s = (g.n_p + 31) / 32, item = xcd_logical(blockIdx.x, gridDim.x);
+    const int z = item / (n_s * n_n), tile_s = (item - z * n_s * n_n) / n_n, tile_n = item - (z * n_s + tile_s) * n_n;
+    const int n0 = tile_n * 32, s0 = tile_s * 32;
     const int s[2] = {min(s0 + c, g.n_p - 1), min(s0 + 16 + c, g.n_p - 1)};
-    const int r = slot0 / n_list + blockIdx.z;
+    const int r = slot0 / n_list + z;
     const int a_lo = max(0, slot0 - r * n_list), a_hi = min(n_list, slot0 + n_slots - r * n_list);
     const bool two = n0 + 16 < fg.N;   // N is a multiple of 16
     f32x4 tot[2][2];
@@ -746,7 +798,7 @@ __global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTabl
 #pragma unroll
         for (int u = 0; u < 2; ++u) tot[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
     float prim[2] = {0.0f, 0.0f};
-    for (int ai = a_lo + wave; ai < a_hi; ai += 4) {
+    for (int ai = a_lo + wave; ai < a_hi; ai += kFieldWaves) {
         const int a = alist[ai], ls = r * n_list + ai - slot0;
         const float *R1 = R + ((size_t)ls * g.n_p + s[0]) * fg.K + 4 * q, *R2 = R + ((size_t)ls * g.n_p + s[1]) * fg.K + 4 * q;
         const float *G1 = ft.G + ((size_t)a * fg.N + n0 + c) * fg.K + 4 * q, *G2 = two ? G1 + (size_t)16 * fg.K : G1;
@@ -754,7 +806,7 @@ __global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTabl
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             L[u] = ft.Lx[(size_t)a * g.n_p + s[u]];
-            if (blockIdx.y == 0) prim[u] = fmaf(ft.pw[(size_t)a * g.n_p + s[u]], R0[(size_t)ls * g.n_p + s[u]], prim[u]);
+            if (tile_n == 0) prim[u] = fmaf(ft.pw[(size_t)a * g.n_p + s[u]], R0[(size_t)ls * g.n_p + s[u]], prim[u]);
         }
         f32x4 acc[2][2];
 #pragma unroll
@@ -795,18 +847,21 @@ __global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTabl
     }
     __syncthreads();
     const bool first = a_lo == 0;
-    if (blockIdx.y == 0 && threadIdx.x < 32 && s0 + threadIdx.x < g.n_p) {
+    if (tile_n == 0 && threadIdx.x < 32 && s0 + threadIdx.x < g.n_p) {
         const int i = threadIdx.x, p = ft.sup[s0 + i];
         if (p < g.n_q) {
             float *o = pb + (size_t)r * (fg.N / kSec + 1) * g.n_qpad + p;
-            const float v = (red0[0][i] + red0[1][i]) + (red0[2][i] + red0[3][i]);
+            const float v = ((red0[0][i] + red0[1][i]) + (red0[2][i] + red0[3][i])) +
+                            ((red0[4][i] + red0[5][i]) + (red0[6][i] + red0[7][i]));
             *o = first ? v : *o + v;
         }
     }
+    if (wave >= 4) return;
     // wave w finishes direction tile w / 2, point tile w % 2
     const int t = wave >> 1, x = s0 + 16 * (wave & 1) + c;
     if ((t == 1 && !two) || x >= g.n_p) return;
-    const f32x4 v = (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
+    const f32x4 v = ((red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane])) +
+                    ((red[4][wave][lane] + red[5][wave][lane]) + (red[6][wave][lane] + red[7][wave][lane]));
     const float m = ft.mu_s[x];
     f32x4 *Tr = reinterpret_cast<f32x4 *>(T) + (size_t)r * field_groups(fg) * fg.nb + ft.box[x];
     const int d = n0 / 4 + 4 * t + q;   // directions 4 d .. 4 d + 3: group d + 1
@@ -826,18 +881,22 @@ __global__ __launch_bounds__(256) void k_flux_fields(Geo g, FluxGeo fg, FluxTabl
 // (n + 1) / 4 on: three float4 loads and twelve weights (zeros around the
 // eight).  Eight separate rows asked the vector cache for as many cycles but
 // for three times the lines, which then had to come from the L2 again for the
-// next offset.  Each XCD takes a run of sectors, so that its L2 holds the few
-// groups of the field they read.
+// next offset.  The same lines serve neighbours in the pair order, so the
+// waves walk it together, four pairs each in turn (a run of its own for each
+// wave would be more than the vector cache holds), and each XCD takes a run of
+// sectors, so that its L2 holds the few directions they read.
 constexpr int kGroupTap = 12;
 
-__global__ __launch_bounds__(256) void k_flux_gather(Geo g, FluxGeo fg, FluxTables ft, const int *__restrict__ beg_all,
-                                                     const int *__restrict__ rec_off, const float *__restrict__ rec_w,
-                                                     const float *__restrict__ sym, const float *__restrict__ T,
-                                                     float *__restrict__ pb) {
-    __shared__ float part[4][64];
-    __shared__ __align__(16) float w_s[4][64][kGroupTap];
+__global__ __launch_bounds__(64 * kPairWaves) void k_flux_gather(Geo g, FluxGeo fg, FluxTables ft,
+                                                                 const int *__restrict__ beg_all,
+                                                                 const int *__restrict__ rec_off,
+                                                                 const int *__restrict__ rec_n,
+                                                                 const float *__restrict__ rec_w,
+                                                                 const float *__restrict__ sym,
+                                                                 const float *__restrict__ T, float *__restrict__ pb) {
+    __shared__ float sum[kPairWaves][64];
+    __shared__ __align__(16) float w_s[kPairWaves][kChunk][kGroupTap];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int n_sec = fg.N / kSec;
     const int item = xcd_logical(blockIdx.x, gridDim.x);
     const int sec = item / fg.n_blk, b = item - sec * fg.n_blk, r = blockIdx.y;
     const int x = b * 64 + lane;
@@ -845,37 +904,40 @@ __global__ __launch_bounds__(256) void k_flux_gather(Geo g, FluxGeo fg, FluxTabl
     const unsigned top = (unsigned)fg.nb - 1;
     const size_t nb = fg.nb;
     float acc = 0.0f;
-    const int n0 = sec * kSec + wave * kWaveSec;   // the wave's first interval
-    const int *beg = beg_all + b * fg.N + n0;
-    const int e0 = beg[0], e1 = beg[kWaveSec], b1 = beg[1], b2 = beg[2];
+    const int start = beg_all[b * fg.N + sec * kSec], end = beg_all[b * fg.N + (sec + 1) * kSec];
     const f32x4 *__restrict__ Tr = reinterpret_cast<const f32x4 *>(T) + (size_t)r * field_groups(fg) * nb;
-    for (int c0 = e0; c0 < e1; c0 += 64) {
-        const int mine = min(c0 + lane, e1 - 1);
-        const int off = rec_off[mine], shift = (n0 + (mine >= b1) + (mine >= b2) + 1) & 3;
+    // four neighbours at a time go round the waves
+    for (int c0 = start + 4 * wave; c0 < end; c0 += kPairWaves * kChunk) {
+        const int mine = min(c0 + 4 * kPairWaves * ((lane & (kChunk - 1)) >> 2) + (lane & 3), end - 1);
+        const int off = rec_off[mine], m1 = rec_n[mine] + 1;
         const f32x4 *src = reinterpret_cast<const f32x4 *>(rec_w + (size_t)mine * kTap);
         const f32x4 lo = src[0], hi = src[1];
-        float *w = w_s[wave][lane];
         __builtin_amdgcn_wave_barrier();
+        if (lane < kChunk) {
+            float *w = w_s[wave][lane] + (m1 & 3);
 #pragma unroll
-        for (int i = 0; i < kGroupTap; ++i) w[i] = 0.0f;
+            for (int i = 0; i < 4; ++i) {
+                w[i] = lo[i];
+                w[4 + i] = hi[i];
+            }
+            // the four places around the eight
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            w[shift + i] = lo[i];
-            w[shift + 4 + i] = hi[i];
+            for (int i = 0; i < 4; ++i) w_s[wave][lane][i < (m1 & 3) ? i : 8 + i] = 0.0f;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
         __builtin_amdgcn_wave_barrier();
-        const int n = min(64, e1 - c0);
         const float *__restrict__ sy = sym + (size_t)c0 * 64 + lane;
 #pragma unroll 1
-        for (int u0 = 0; u0 < n; u0 += 4) {
+        for (int u0 = 0; u0 < kChunk; u0 += 4) {
+            const int at0 = kPairWaves * u0, left = end - c0 - at0;   // (records of this four and after)
+            if (left <= 0) break;
             float y[4];
             f32x4 t[4][3];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int i = min(u0 + u, n - 1), m = n0 + (c0 + i >= b1) + (c0 + i >= b2) + 1;
-                y[u] = u0 + u < n ? sy[(size_t)i * 64] : 0.0f;
-                const unsigned at = min((unsigned)(lin + __builtin_amdgcn_readlane(off, i)), top);
+                const int m = __builtin_amdgcn_readlane(m1, u0 + u);
+                y[u] = u < left ? sy[(size_t)(at0 + u) * 64] : 0.0f;
+                const unsigned at = min((unsigned)(lin + __builtin_amdgcn_readlane(off, u0 + u)), top);
                 const f32x4 *__restrict__ T0 = Tr + (size_t)(m >> 2) * nb;
                 t[u][0] = T0[at];
                 t[u][1] = (T0 + nb)[at];
@@ -883,7 +945,7 @@ __global__ __launch_bounds__(256) void k_flux_gather(Geo g, FluxGeo fg, FluxTabl
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float *wu = w_s[wave][min(u0 + u, n - 1)];
+                const float *wu = w_s[wave][u0 + u];
                 float v = 0.0f;
 #pragma unroll
                 for (int j = 0; j < kGroupTap; ++j) v = fmaf(wu[j], t[u][j >> 2][j & 3], v);
@@ -891,13 +953,14 @@ __global__ __launch_bounds__(256) void k_flux_gather(Geo g, FluxGeo fg, FluxTabl
             }
         }
     }
-    part[wave][lane] = acc;
+    sum[wave][lane] = acc;
     __syncthreads();
     if (wave == 0 && x < g.n_p) {
         const int p = ft.sup[x];
-        if (p < g.n_q)
-            pb[((size_t)r * (n_sec + 1) + 1 + sec) * g.n_qpad + p] =
-                (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kPairWaves; ++w) v += sum[w][lane];
+        if (p < g.n_q) pb[((size_t)r * (fg.N / kSec + 1) + 1 + sec) * g.n_qpad + p] = v;
     }
 }
 
@@ -1062,6 +1125,8 @@ __global__ __launch_bounds__(64) void k_flux_sens_fields(Geo g, FluxGeo fg, Flux
         if (n >= fg.N - 3) o[c - turn] = m * u[c];
     }
 }
+
+constexpr int kWaveSec = 3;   // intervals of one wave of the FP64 sensitivities
 
 // part[sector][c][x] of C subsets: one wave per (pixel block, kWaveSec node
 // intervals)
@@ -1274,7 +1339,7 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
 
 void free_flux(FluxTables &ft) {
     for (void *p : {(void *)ft.sup, (void *)ft.box, (void *)ft.mu_s, (void *)ft.mu_box, (void *)ft.rank_of, (void *)ft.x_of, (void *)ft.pw,
-                    (void *)ft.pwr, (void *)ft.Lx, (void *)ft.beg, (void *)ft.rec_off, (void *)ft.rec_w, (void *)ft.sym,
+                    (void *)ft.pwr, (void *)ft.Lx, (void *)ft.beg, (void *)ft.rec_off, (void *)ft.rec_n, (void *)ft.rec_w, (void *)ft.sym,
                     (void *)ft.G, (void *)ft.psi, (void *)ft.rho})
         hipFree(p);
     ft = FluxTables{};
@@ -1334,17 +1399,17 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     const dim3 grid(fg.N, fg.n_blk);
     const int *q_of_pix = t.p_pix + g.n_p;
     hipLaunchKernelGGL(k_flux_pairs<0>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
-                       cap, ft.beg, (int *)nullptr, (float *)nullptr, (double *)nullptr, (float *)nullptr);
+                       cap, ft.beg, (int *)nullptr, (int *)nullptr, (float *)nullptr, (double *)nullptr, (float *)nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return done(e);
     if ((e = launch_fill(reinterpret_cast<float *>(ft.beg + nbin), 1, 0.0f, st)) != hipSuccess) return done(e);
     if ((e = hipcub::DeviceScan::ExclusiveSum(tmp, tmp_bytes, ft.beg, ft.beg, nbin + 1, st)) != hipSuccess) return done(e);
     int total = 0;
     if ((e = hipMemcpyAsync(&total, ft.beg + nbin, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return done(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return done(e);
-    if (al(ft.rec_off, total) || al(ft.rec_w, (size_t)total * kTap) || al(ft.sym, (size_t)total * 64)) return done(e);
+    if (al(ft.rec_off, total) || al(ft.rec_n, total) || al(ft.rec_w, (size_t)total * kTap) || al(ft.sym, (size_t)total * 64)) return done(e);
     if ((e = hipMalloc(&w64, std::max<size_t>(total, 1) * kTap * sizeof(double))) != hipSuccess) return done(e);
     hipLaunchKernelGGL(k_flux_pairs<1>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
-                       cap, ft.beg, ft.rec_off, ft.rec_w, w64, ft.sym);
+                       cap, ft.beg, ft.rec_off, ft.rec_n, ft.rec_w, w64, ft.sym);
     if ((e = hipGetLastError()) == hipSuccess && sens) e = flux_sensitivity(g, fg, t, ft, w64, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     return done(e);
@@ -1405,17 +1470,28 @@ struct Carve {
     }
 };
 
+// Ends of an event for which two waves share them (a function of the geometry
+// alone: a realisation's sums are the same in any batch).  Below, a wave's work
+// is mostly its start and end; above, a wave has long enough a run of its own,
+// and halves cost more (94 -> 113 us at 128x128 with 125k events, some 280 ends
+// each; 31 -> 23 us at 64x64 with 25k events, some 70).
+constexpr double kSplitEnds = 32.0, kWholeEnds = 160.0;
+constexpr int kSplit = 2;
+
 // means of blocks [b0, b1), whose records begin at row row0
 void launch_means(const FluxRun &p, int slot_base, int s0, int b0, int b1, int row0, const Carve &w, const float *f) {
     const Geo &g = *p.g;
     const FluxGeo &fg = *p.fg;
+    // ends that an event reaches, about
+    const double ends = g.n_p * 6.0 * g.sig_u / std::max(std::max(fg.W, fg.Hh) * g.dx, 6.0 * g.sig_u);
     if (fg.N) {
-        hipLaunchKernelGGL(k_flux_means<3>, dim3(b1 - b0), dim3(256), 0, p.st, g, fg, p.ev, p.blk + b0, p.t->us_sorted, p.alist,
-                           p.n_list, slot_base, s0, row0, p.row_base, w.S, w.SP, p.mean, p.inv, p.skipped);
+        const int split = ends >= kSplitEnds && ends < kWholeEnds ? kSplit : 1;
+        hipLaunchKernelGGL((split > 1 ? k_flux_means<3, kSplit> : k_flux_means<3, 1>), dim3(b1 - b0), dim3(256 * split), 0, p.st, g,
+                           fg, p.ev, p.blk + b0, p.t->us_sorted, p.alist, p.n_list, slot_base, s0, row0, p.row_base, w.S,
+                           w.SP, p.mean, p.inv, p.skipped);
         return;
     }
-    // lanes per event: about as many as the ends it reaches
-    const double ends = g.n_p * 6.0 * g.sig_u / std::max(std::max(fg.W, fg.Hh) * g.dx, 6.0 * g.sig_u);
+    // lanes per event: about as many as it has ends
     const int lanes = ends < 48.0 ? 16 : ends < 160.0 ? 32 : 64;
     const int j0 = p.blk_rows(b0), j1 = p.blk_rows(b1);
     auto *kern = lanes == 16 ? k_flux_means_primary<16> : lanes == 32 ? k_flux_means_primary<32> : k_flux_means_primary<64>;
@@ -1453,7 +1529,7 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
                 // update left it, unless the workspace served others since
                 if (p.box || grp < p.n_real)
                     hipLaunchKernelGGL(k_flux_box, dim3((g.n_p + 255) / 256, nr), dim3(256), 0, p.st, g, fg, ft, f, w.fbox);
-                hipLaunchKernelGGL(k_flux_spread, dim3(fg.n_blk, fg.N / kSec, nr), dim3(256), 0, p.st, g, fg, ft, ft.beg,
+                hipLaunchKernelGGL(k_flux_spread, dim3(fg.n_blk, fg.N / kSec, nr), dim3(64 * kPairWaves), 0, p.st, g, fg, ft, ft.beg,
                                    ft.rec_off, ft.rec_w, ft.sym, w.fbox, w.I);
                 return hipGetLastError();
             });
@@ -1468,10 +1544,13 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
             if (p.means) {
                 const int b0 = p.blk_host[sb + s0], b1 = p.blk_host[sb + s1];
                 e = stage(0, [&] {
-                    if (sc)
-                        hipLaunchKernelGGL(k_flux_spectra, dim3((g.n_p + 31) / 32, ns, (fg.K + 16 * kSpecTiles - 1) / (16 * kSpecTiles)),
-                                           dim3(256), 0,
-                                           p.st, g, fg, ft, p.alist, p.n_list, s0, w.I, f, w.S, w.SP);
+                    if (sc) {
+                        // even parts of at most kSpecTiles tiles
+                        const int kt = fg.K / 16, nz = (kt + kSpecTiles - 1) / kSpecTiles, nt = (kt + nz - 1) / nz;
+                        hipLaunchKernelGGL(nt <= 4 ? k_flux_spectra<4> : nt == 5 ? k_flux_spectra<5> : k_flux_spectra<6>,
+                                           dim3((g.n_p + 31) / 32 * ns, nz), dim3(64 * kSpecWaves), 0, p.st, g, fg, ft,
+                                           p.alist, p.n_list, std::min(ns, p.n_list), s0, w.I, f, w.S, w.SP);
+                    }
                     for (int a = b0, b; a < b1; a = b) {
                         b = p.fill ? std::min(b1, a + p.ev_cap / 64) : b1;
                         hipError_t fe = hipSuccess;
@@ -1484,14 +1563,14 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
             }
             if (!adjoint) continue;
             e = stage(1, [&] {
-                const dim3 ag((g.n_p + 15) / 16, ns);
+                const dim3 ag((g.n_p + 15) / 16 * ns);
                 const int zr = (s1 - 1) / p.n_list - s0 / p.n_list + 1;
                 // 16-node tiles of the energy nodes held in registers
                 auto *adj = !sc ? k_flux_adjoint<0> : fg.K <= 96 ? k_flux_adjoint<6> : k_flux_adjoint<kMaxTiles>;
                 hipLaunchKernelGGL(adj, ag, dim3(256), 0, p.st, g, fg, ft, p.ev, p.blk, p.t->us_sorted, p.alist, p.blk_beg + sb,
                                    p.n_list, s0, p.row_base, p.inv, w.S, w.SP);
                 if (sc) {
-                    hipLaunchKernelGGL(k_flux_fields, dim3((g.n_p + 31) / 32, (fg.N + 31) / 32, zr), dim3(256), 0, p.st, g,
+                    hipLaunchKernelGGL(k_flux_fields, dim3((g.n_p + 31) / 32 * ((fg.N + 31) / 32) * zr), dim3(64 * kFieldWaves), 0, p.st, g,
                                        fg, ft, p.alist, p.n_list, s0, ns, w.S, w.SP, w.T, w.pb);
                 } else {
                     hipLaunchKernelGGL(k_flux_primary_back, dim3(fg.n_blk, zr), dim3(256), 0, p.st, g, ft, p.alist, p.n_list,
@@ -1504,8 +1583,8 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
         if (!adjoint) continue;
         if (sc) {
             e = stage(1, [&] {
-                hipLaunchKernelGGL(k_flux_gather, dim3(fg.n_blk * (fg.N / kSec), nr), dim3(256), 0, p.st, g, fg, ft, ft.beg,
-                                   ft.rec_off, ft.rec_w, ft.sym, w.T, w.pb);
+                hipLaunchKernelGGL(k_flux_gather, dim3(fg.n_blk * (fg.N / kSec), nr), dim3(64 * kPairWaves), 0, p.st, g, fg, ft, ft.beg,
+                                   ft.rec_off, ft.rec_n, ft.rec_w, ft.sym, w.T, w.pb);
                 return hipGetLastError();
             });
             if (e != hipSuccess) return e;

@@ -164,6 +164,7 @@ struct FluxTables {
     float *Lx = nullptr;       // [n_angles][n_p] attenuation to the detector
     int *beg = nullptr;        // [n_blk * N + 1] first pair record of each (block, direction interval)
     int *rec_off = nullptr;    // [records] box offset
+    int *rec_n = nullptr;      // [records] direction interval
     float *rec_w = nullptr;    // [records][8] direction weights
     float *sym = nullptr;      // [records][64] symmetric pair factors
     float *G = nullptr;        // [n_angles][N][K]
