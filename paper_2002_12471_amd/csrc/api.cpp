@@ -1252,7 +1252,11 @@ lmosem_status lmosem_binned_reconstruct(lmosem_ctx *c, int32_t n_pos, const doub
     std::vector<int> row_bin, sub_off(g.n_subsets + 1, 0), chunk_off(g.n_subsets + 1, 0);
     std::vector<Chunk> chunks;
     std::vector<int> cr;   // per subset {0, n_chunks}
-    const int kRows = 256;
+    // rows per backprojection chunk: as few (8 to 256) as make a workgroup per
+    // compute unit (15 -> 4 us for 960 rows of 1472)
+    const int64_t sub_rows = (int64_t)((g.n_angles + g.n_subsets - 1) / g.n_subsets) * per_angle;
+    const int64_t blocks = sub_rows * ((g.n_qpad + 1023) / 1024);   // (one row each)
+    const int kRows = (int)std::min<int64_t>(256, std::max<int64_t>(8, (blocks / 256 + 7) / 8 * 8));
     for (int i = 0; i < g.n_subsets; ++i) {
         sub_off[i] = (int)row_bin.size();
         for (int a = i; a < g.n_angles; a += g.n_subsets)

@@ -70,11 +70,20 @@ __global__ __launch_bounds__(256) void k_binned_rows(Geo g, const int *__restric
 // most W consecutive position bins, and path ends are ranked by position, so
 // one thread per (angle, emission pixel) walks the ranks once, evaluating each
 // path weight once (rather than once per bin that the path reaches), with W
-// bins of accumulators that slide along the detector.  The position-bin
-// masses depend on the rank only and come precomputed (k_rank_bin_masses).
+// bins of accumulators that slide along the detector.
+//
+// What a path takes from its direction of flight at an angle (Klein-Nishina
+// factor, attenuation ratio, mass of the energy response over each energy bin)
+// depends on the pixel offset q -> s alone: it is evaluated once per (angle,
+// offset), some (2 nx - 1)(2 ny - 1) of them, instead of once per path, n_p n_q
+// of them.  A path then costs one exponential and 24 bytes from the L2, which
+// bound it: 6.06 ms -> 1.04 ms for 120 angles x 1436 x 1436 paths.  What depends
+// on the rank only comes precomputed as well (k_rank_terms), read as scalars.
 template <int W>
-__global__ void k_rank_bin_masses(Geo g, const double *__restrict__ us_sorted, int n_pos, int *__restrict__ rb0,
-                                  double *__restrict__ rpm) {
+__global__ void k_rank_terms(Geo g, const int *__restrict__ p_pix, const double *__restrict__ Ld,
+                             const int *__restrict__ s_sorted, const double *__restrict__ us_sorted, int n_pos,
+                             int *__restrict__ rb0, int *__restrict__ roff, double *__restrict__ rL,
+                             double *__restrict__ rpm) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x, a = blockIdx.y;
     if (r >= g.n_p) return;
     const size_t o = (size_t)a * g.n_p + r;
@@ -82,6 +91,9 @@ __global__ void k_rank_bin_masses(Geo g, const double *__restrict__ us_sorted, i
     const double width = 2.0 * g.half_len / n_pos;
     const int b0 = min(max((int)floor((us - 3.0 * g.sig_u + g.half_len) / width), 0), n_pos - 1);
     rb0[o] = b0;
+    const int s = s_sorted[o];
+    roff[o] = p_pix[s] / g.nx * (2 * g.nx - 1) + p_pix[s] % g.nx;
+    rL[o] = Ld[(size_t)a * g.n_p + s];
     for (int i = 0; i < W; ++i) {
         const int b = b0 + i;
         const double u0 = -g.half_len + b * width, u1 = u0 + width;
@@ -89,19 +101,54 @@ __global__ void k_rank_bin_masses(Geo g, const double *__restrict__ us_sorted, i
     }
 }
 
+// tab[angle - a0][1 + n_e][offset]: attenuation ratio, and Klein-Nishina factor
+// times the energy-bin masses of a flight along (di, dj), offset
+// (dj + ny - 1) (2 nx - 1) + di + nx - 1 (0 for no offset: the primary path,
+// which the rows weigh by themselves)
+__global__ __launch_bounds__(256) void k_direction_terms(Geo g, const double *__restrict__ cs, int a0,
+                                                         const double *__restrict__ edges, int n_e,
+                                                         double *__restrict__ tab) {
+    const int w = 2 * g.nx - 1, n = w * (2 * g.ny - 1);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, a = a0 + blockIdx.y;
+    if (i >= n) return;
+    const int di = i % w - (g.nx - 1), dj = i / w - (g.ny - 1);
+    double *out = tab + (size_t)blockIdx.y * (1 + n_e) * n + i;
+    if (di == 0 && dj == 0) {
+        for (int k = 0; k < 1 + n_e; ++k) out[(size_t)k * n] = 0.0;
+        return;
+    }
+    const Flight fl = flight(g, di, dj, cs[2 * a], cs[2 * a + 1]);
+    out[0] = fl.rho;
+    for (int k = 0; k < n_e; ++k)
+        out[(size_t)(1 + k) * n] = fl.psi / g.psi_bar * energy_mass(g, fl.ep, edges[k], edges[k + 1]);
+}
+
+// One wave per (angle, 64 emission pixels); an XCD takes a run of angles, whose
+// direction terms then stay in its L2.  The loads of
+// the next kAhead ranks are on their way while the current ones are used.
 template <int W, int KMAX>
 __global__ __launch_bounds__(64) void k_binned_rows_all(Geo g, const int *__restrict__ p_pix,
-                                                        const double *__restrict__ cs, const double *__restrict__ Ld,
-                                                        const double *__restrict__ Bt,
+                                                        const double *__restrict__ Ld, const double *__restrict__ Bt,
                                                         const int *__restrict__ s_sorted, const int *__restrict__ rb0,
+                                                        const int *__restrict__ roff, const double *__restrict__ rL,
                                                         const double *__restrict__ rpm, int n_pos,
                                                         const double *__restrict__ edges, int n_e,
+                                                        const double *__restrict__ tab, int a0, int n_a,
                                                         const int *__restrict__ angle_row0, float *__restrict__ H) {
-    const int a = blockIdx.y;
-    const int q = blockIdx.x * 64 + threadIdx.x;   // n_qpad is a multiple of 64
+    constexpr int kAhead = 4;
+    const int item = xcd_logical(blockIdx.x, gridDim.x);
+    const int n_qb = g.n_qpad / 64, al = item / n_qb, qb = item - al * n_qb, a = a0 + al;
+    const int q = qb * 64 + threadIdx.x;   // n_qpad is a multiple of 64
     const bool active = q < g.n_q;
-    const double nx = cs[2 * a], ny = cs[2 * a + 1];
-    const double s2 = M_SQRT2 * g.sig_e;
+    const int qc = min(q, g.n_q - 1), pq = p_pix[qc];
+    const int n_off = (2 * g.nx - 1) * (2 * g.ny - 1);
+    const int from = (g.ny - 1 - pq / g.nx) * (2 * g.nx - 1) + (g.nx - 1 - pq % g.nx);
+    const double *ta = g.scatter ? tab + (size_t)al * (1 + n_e) * n_off : nullptr;
+    // the primary path
+    const double w0 = active ? exp(-Ld[(size_t)a * g.n_p + qc]) : 0.0;
+    double em0[KMAX];
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) em0[k] = k < n_e ? energy_mass(g, g.e0, edges[k], edges[k + 1]) : 0.0;
     float *Hq = H + (size_t)angle_row0[a] * g.n_qpad + q;
     double acc[W][KMAX];
 #pragma unroll
@@ -122,23 +169,56 @@ __global__ __launch_bounds__(64) void k_binned_rows_all(Geo g, const int *__rest
         for (int k = 0; k < KMAX; ++k) acc[W - 1][k] = 0.0;
         ++base;
     };
-    for (int r = 0; r < g.n_p; ++r) {
-        const size_t o = (size_t)a * g.n_p + r;
-        const int b0 = rb0[o];
-        while (base < b0) shift();
-        if (!active) continue;
-        const PathW pw = path_weight(g, p_pix, Ld, Bt, nx, ny, a, q, s_sorted[o]);
-        if (!(pw.w > 0.0)) continue;
-        double ef[KMAX + 1];
+    const size_t o = (size_t)a * g.n_p;
+    struct Ranks {
+        int s[kAhead];
+        double B[kAhead], rho[kAhead], em[kAhead][KMAX];
+    };
+    auto load = [&](Ranks &x, int r0) {
 #pragma unroll
-        for (int k = 0; k <= KMAX; ++k) ef[k] = k <= n_e ? erf((edges[k] - pw.ep) / s2) : 0.0;
+        for (int u = 0; u < kAhead; ++u) {
+            const int r = min(r0 + u, g.n_p - 1);
+            x.s[u] = s_sorted[o + r];
+            if (!g.scatter) {
 #pragma unroll
-        for (int i = 0; i < W; ++i) {
-            const double wp = pw.w * rpm[o * W + i];
+                for (int k = 0; k < KMAX; ++k) x.em[u][k] = 0.0;
+                continue;
+            }
+            const double *td = ta + from + roff[o + r];
+            x.B[u] = Bt[(size_t)x.s[u] * g.n_p + qc];
+            x.rho[u] = td[0];
 #pragma unroll
-            for (int k = 0; k < KMAX; ++k)
-                if (k < n_e) acc[i][k] += wp * (0.5 * (ef[k + 1] - ef[k]));
+            for (int k = 0; k < KMAX; ++k) x.em[u][k] = td[(size_t)(1 + min(k, n_e - 1)) * n_off];
         }
+    };
+    auto use = [&](const Ranks &x, int r0) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int r = r0 + u;
+            if (r >= g.n_p) break;
+            const int b0 = rb0[o + r];
+            while (base < b0) shift();
+            const bool self = x.s[u] == qc;
+            if (!g.scatter && __ballot(self) == 0) continue;
+            double w = 0.0;
+            if (g.scatter) w = active ? x.B[u] * exp(-x.rho[u] * rL[o + r]) : 0.0;
+            w = self ? w0 : w;
+            const double *pm = rpm + (o + r) * W;
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) {
+                const double we = w * (self ? em0[k] : x.em[u][k]);
+#pragma unroll
+                for (int i = 0; i < W; ++i) acc[i][k] = fma(we, pm[i], acc[i][k]);
+            }
+        }
+    };
+    Ranks x, y;
+    load(x, 0);
+    for (int r0 = 0; r0 < g.n_p; r0 += 2 * kAhead) {
+        load(y, r0 + kAhead);
+        use(x, r0);
+        load(x, r0 + 2 * kAhead);
+        use(y, r0 + kAhead);
     }
     while (base < n_pos) shift();
 }
@@ -184,20 +264,36 @@ hipError_t launch_binned_rows(const Geo &g, const Tables &t, int n_pos, const do
     return hipGetLastError();
 }
 
+// scratch of the rows of every bin
+struct RowScratch {
+    int *rb0 = nullptr, *roff = nullptr;
+    double *rL = nullptr, *rpm = nullptr, *tab = nullptr;
+    int n_a = 0;   // angles whose direction terms fit
+};
+
 template <int W, int KMAX>
-void launch_rows_all(const Geo &g, const Tables &t, int n_pos, const double *edges_dev, int n_e,
-                     const int *angle_row0_dev, int *rb0, double *rpm, float *H, hipStream_t st) {
-    hipLaunchKernelGGL(k_rank_bin_masses<W>, dim3((unsigned)((g.n_p + 255) / 256), (unsigned)g.n_angles), dim3(256),
-                       0, st, g, t.us_sorted, n_pos, rb0, rpm);
-    hipLaunchKernelGGL((k_binned_rows_all<W, KMAX>), dim3((unsigned)(g.n_qpad / 64), (unsigned)g.n_angles), dim3(64),
-                       0, st, g, t.p_pix, t.cs, t.Ld, t.Bt, t.s_sorted, rb0, rpm, n_pos, edges_dev, n_e,
-                       angle_row0_dev, H);
+hipError_t launch_rows_all(const Geo &g, const Tables &t, int n_pos, const double *edges_dev, int n_e,
+                           const int *angle_row0_dev, const RowScratch &w, float *H, hipStream_t st) {
+    hipLaunchKernelGGL(k_rank_terms<W>, dim3((unsigned)((g.n_p + 255) / 256), (unsigned)g.n_angles), dim3(256), 0, st,
+                       g, t.p_pix, t.Ld, t.s_sorted, t.us_sorted, n_pos, w.rb0, w.roff, w.rL, w.rpm);
+    const int n_off = (2 * g.nx - 1) * (2 * g.ny - 1);
+    for (int a0 = 0; a0 < g.n_angles; a0 += w.n_a) {
+        const int n_a = std::min(w.n_a, g.n_angles - a0);
+        if (g.scatter)
+            hipLaunchKernelGGL(k_direction_terms, dim3((unsigned)((n_off + 255) / 256), (unsigned)n_a), dim3(256), 0, st, g,
+                               t.cs, a0, edges_dev, n_e, w.tab);
+        hipLaunchKernelGGL((k_binned_rows_all<W, KMAX>), dim3((unsigned)(g.n_qpad / 64 * n_a)), dim3(64), 0, st, g, t.p_pix,
+                           t.Ld, t.Bt, t.s_sorted, w.rb0, w.roff, w.rL, w.rpm, n_pos, edges_dev, n_e, w.tab, a0, n_a,
+                           angle_row0_dev, H);
+    }
+    return hipGetLastError();
 }
 
 // Rows of every bin, angle a's rows starting at angle_row0[a] in (position
 // bin, energy bin) order.  hipErrorNotSupported when a position response
 // spans more bins, or there are more energy bins, than the instantiated
-// windows hold (the caller then lists the bins for k_binned_rows).
+// windows hold, or the scratch does not fit (the caller then lists the bins for
+// k_binned_rows, which needs none).
 hipError_t launch_binned_rows_all(const Geo &g, const Tables &t, int n_pos, const double *edges_dev, int n_e,
                                   const int *angle_row0_dev, float *H, hipStream_t st) {
     if (!t.Ld) return hipErrorInvalidValue;
@@ -205,24 +301,30 @@ hipError_t launch_binned_rows_all(const Geo &g, const Tables &t, int n_pos, cons
     const int span = (int)ceil(6.0 * g.sig_u / width) + 2;   // bins a response can touch
     const int W = span <= 8 ? 8 : span <= 16 ? 16 : 0;
     if (W == 0 || n_e > (W == 8 ? 4 : 2)) return hipErrorNotSupported;
-    int *rb0 = nullptr;
-    double *rpm = nullptr;
+    RowScratch w;
     const size_t na_np = (size_t)g.n_angles * g.n_p;
-    hipError_t e = hipMalloc(&rb0, sizeof(int) * na_np);
-    if (e == hipSuccess) e = hipMalloc(&rpm, sizeof(double) * na_np * W);
+    // direction terms of as many angles as 64 MB hold (all of them for maps up
+    // to 128 x 128: the chip is full with a few tens of angles)
+    const size_t per = (size_t)(2 * g.nx - 1) * (2 * g.ny - 1) * (1 + n_e) * sizeof(double);
+    w.n_a = g.scatter ? (int)std::min<size_t>(g.n_angles, std::max<size_t>(1, (size_t(64) << 20) / per)) : g.n_angles;
+    hipError_t e = hipMalloc(&w.rb0, sizeof(int) * na_np);
+    if (e == hipSuccess) e = hipMalloc(&w.roff, sizeof(int) * na_np);
+    if (e == hipSuccess) e = hipMalloc(&w.rL, sizeof(double) * na_np);
+    if (e == hipSuccess) e = hipMalloc(&w.rpm, sizeof(double) * na_np * W);
+    if (e == hipSuccess && g.scatter) e = hipMalloc(&w.tab, per * w.n_a);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        e = hipErrorNotSupported;
+    }
     if (e == hipSuccess) {
         // the fewest accumulators that hold the energy bins
-        if (W == 8 && n_e == 1) launch_rows_all<8, 1>(g, t, n_pos, edges_dev, n_e, angle_row0_dev, rb0, rpm, H, st);
-        else if (W == 8 && n_e == 2) launch_rows_all<8, 2>(g, t, n_pos, edges_dev, n_e, angle_row0_dev, rb0, rpm, H, st);
-        else if (W == 8) launch_rows_all<8, 4>(g, t, n_pos, edges_dev, n_e, angle_row0_dev, rb0, rpm, H, st);
-        else if (n_e == 1) launch_rows_all<16, 1>(g, t, n_pos, edges_dev, n_e, angle_row0_dev, rb0, rpm, H, st);
-        else launch_rows_all<16, 2>(g, t, n_pos, edges_dev, n_e, angle_row0_dev, rb0, rpm, H, st);
-        e = hipGetLastError();
+        auto rows = W == 8 ? (n_e == 1 ? launch_rows_all<8, 1> : n_e == 2 ? launch_rows_all<8, 2> : launch_rows_all<8, 4>)
+                           : (n_e == 1 ? launch_rows_all<16, 1> : launch_rows_all<16, 2>);
+        e = rows(g, t, n_pos, edges_dev, n_e, angle_row0_dev, w, H, st);
     }
     // the scratch is released once the kernels are done
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    hipFree(rb0);
-    hipFree(rpm);
+    for (void *p : {(void *)w.rb0, (void *)w.roff, (void *)w.rL, (void *)w.rpm, (void *)w.tab}) hipFree(p);
     return e;
 }
 

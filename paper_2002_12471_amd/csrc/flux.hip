@@ -65,15 +65,6 @@ __device__ __forceinline__ void fit_weights(const FluxFit &fit, double t, double
     }
 }
 
-// workgroups are dealt to the 8 XCDs round-robin: the item that gives each
-// XCD one contiguous run.  Each XCD's L2 starts a kernel empty, so what all
-// eight read crosses the fabric eight times: the stages order their items so
-// that a run shares its larger operand.
-__device__ __forceinline__ int xcd_logical(int p, int n) {
-    const int x = p % 8, m = n / 8, rem = n % 8;
-    return x * m + min(x, rem) + p / 8;
-}
-
 __device__ __forceinline__ int wrap(int n, int N) { return n < 0 ? n + N : (n >= N ? n - N : n); }
 
 // ---------------------------------------------------------------- tables (once per attenuation map)

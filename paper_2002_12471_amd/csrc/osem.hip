@@ -616,6 +616,7 @@ __global__ void k_sum_real(Geo g, const int *__restrict__ crange, const float *_
     const int r = blockIdx.y;
     if (q >= g.n_qpad) return;
     float b = 0.0f;
+#pragma unroll 16
     for (int c = crange[r]; c < crange[r + 1]; ++c) b += pb[(size_t)c * g.n_qpad + q];
     out[(size_t)r * g.n_qpad + q] = q < g.n_q ? b : 0.0f;
 }

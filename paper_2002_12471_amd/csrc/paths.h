@@ -1,5 +1,6 @@
-// Per-path weights of the model, shared by the table build and the exact
-// training targets of the learned scatter term (device code, FP64).
+// Device code that the kernels share: the order of work over the XCDs, and the
+// per-path weights of the model (FP64: table build, binned rows, the exact
+// training targets of the learned scatter term).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -9,12 +10,35 @@
 
 namespace lmo {
 
+// workgroups are dealt to the 8 XCDs round-robin: the item that gives each
+// XCD one contiguous run.  Each XCD's L2 starts a kernel empty, so what all
+// eight read crosses the fabric eight times: kernels order their items so
+// that a run shares its larger operand.
+__device__ __forceinline__ int xcd_logical(int p, int n) {
+    const int x = p % 8, m = n / 8, rem = n % 8;
+    return x * m + min(x, rem) + p / 8;
+}
+
 // Klein-Nishina total cross-section in units of r_e^2.
 __device__ __host__ inline double kn_total(double e) {
     double k = e / kMeC2;
     double l = log1p(2.0 * k);
     double k1 = 1.0 + k, k2 = 1.0 + 2.0 * k;
     return 2.0 * M_PI * (k1 / (k * k) * (2.0 * k1 / k2 - l / k) + l / (2.0 * k) - (1.0 + 3.0 * k) / (k2 * k2));
+}
+
+// What a path takes from its flight along (di, dj) pixels to a scatter towards
+// (nx, ny): end energy E', Klein-Nishina shape, attenuation ratio at E'.
+struct Flight {
+    double ep, psi, rho;
+};
+
+__device__ inline Flight flight(const Geo &g, int di, int dj, double nx, double ny) {
+    const double c = (di * nx + dj * ny) / sqrt((double)(di * di + dj * dj));
+    const double t = 1.0 + g.kappa * (1.0 - c);
+    const double P = 1.0 / t;
+    const double ep = g.e0 * P;
+    return {ep, P * P * (P + t - 1.0 + c * c), kn_total(ep) / g.sigma_kn_e0};
 }
 
 // Weight w and end energy E' of the path from emission pixel q through path
@@ -29,13 +53,8 @@ __device__ inline PathW path_weight(const Geo &g, const int *__restrict__ p_pix,
     if (!g.scatter) return {0.0, g.e0};
     const int pq = p_pix[q], ps = p_pix[s];
     const int di = ps % g.nx - pq % g.nx, dj = ps / g.nx - pq / g.nx;
-    const double c = (di * nx + dj * ny) / sqrt((double)(di * di + dj * dj));
-    const double t = 1.0 + g.kappa * (1.0 - c);
-    const double P = 1.0 / t;
-    const double ep = g.e0 * P;
-    const double psi = P * P * (P + t - 1.0 + c * c);
-    const double rho = kn_total(ep) / g.sigma_kn_e0;
-    return {Bt[(size_t)s * g.n_p + q] * psi / g.psi_bar * exp(-rho * L[(size_t)a * g.n_p + s]), ep};
+    const Flight f = flight(g, di, dj, nx, ny);
+    return {Bt[(size_t)s * g.n_p + q] * f.psi / g.psi_bar * exp(-f.rho * L[(size_t)a * g.n_p + s]), f.ep};
 }
 
 }  // namespace lmo
