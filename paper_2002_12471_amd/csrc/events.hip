@@ -70,13 +70,29 @@ __global__ void k_keys(Geo g, int64_t n, int n_real, const int64_t *__restrict__
     idx[j] = (int)j;
 }
 
-__global__ void k_gather_events(Geo g, int64_t n, const uint64_t *__restrict__ keys,
+// The events in sorted order, and (the workgroups past them) each group's
+// count, by two searches in the sorted keys: counting by atomics took most of
+// the ingest where many events share few groups (5000 events of 16 groups: 59 us
+// with them, 8 us so; 25 ms of atomics for 12.8M events).
+__global__ void k_gather_events(Geo g, int64_t n, int n_groups, const uint64_t *__restrict__ keys,
                                 const int *__restrict__ idx, const float *__restrict__ u_bin,
                                 const float *__restrict__ energy, const int32_t *__restrict__ angle,
                                 int *__restrict__ sa, float *__restrict__ su,
                                 float *__restrict__ se, float *__restrict__ efac, int *__restrict__ orig,
                                 int *__restrict__ counts) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t padded = (n + blockDim.x - 1) / blockDim.x * blockDim.x;
+    if (k >= padded) {
+        const int64_t grp = k - padded;
+        if (grp >= n_groups) return;
+        auto first_of = [&](uint64_t key) {   // first event whose key is at least this
+            int64_t lo = 0, hi = n;
+            while (lo < hi) { const int64_t m = (lo + hi) >> 1; if (keys[m] >= key) hi = m; else lo = m + 1; }
+            return lo;
+        };
+        counts[grp] = (int)(first_of((uint64_t)(grp + 1) << 32) - first_of((uint64_t)grp << 32));
+        return;
+    }
     if (k >= n) return;
     int j = idx[k];
     sa[k] = angle[j];
@@ -85,39 +101,45 @@ __global__ void k_gather_events(Geo g, int64_t n, const uint64_t *__restrict__ k
     se[k] = (float)x;
     efac[k] = (float)(exp2(-g.c2 * x * x) / g.zk);
     orig[k] = j;
-    atomicAdd(&counts[keys[k] >> 32], 1);
 }
 
 // Rank ranges of the tiles, and per tile the number of terms the forward
-// kernel evaluates and the number with a non-zero position response.
-__global__ void k_tile_ranks(Geo g, Tile *__restrict__ tiles, int n_tiles,
-                             const double *__restrict__ us_sorted, const float *__restrict__ su,
-                             long long *__restrict__ terms, long long *__restrict__ useful) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_tiles) return;
+// kernel evaluates and the number with a non-zero position response: 16 lanes
+// per tile, an event each in turn (its two searches are chains of dependent
+// loads: 18 -> 5 us for 5000 events, 42 -> 10 us for 7000 on 61 x 53 pixels).
+__global__ __launch_bounds__(256) void k_tile_ranks(Geo g, Tile *__restrict__ tiles, int n_tiles,
+                                                    const double *__restrict__ us_sorted,
+                                                    const float *__restrict__ su, long long *__restrict__ terms,
+                                                    long long *__restrict__ useful) {
+    const int t = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4), sub = threadIdx.x & 15;
+    if (t >= n_tiles) return;   // (whole groups of lanes)
     Tile tl = tiles[t];
     const double *us = us_sorted + (size_t)tl.angle * g.n_p;
     const double reach = 3.0 * g.sig_u;
-    auto first_above = [&](double v) {      // first rank with us > v
-        int lo = 0, hi = g.n_p;
-        while (lo < hi) { int m = (lo + hi) >> 1; if (us[m] > v) hi = m; else lo = m + 1; }
-        return lo;
-    };
-    auto first_at_least = [&](double v) {   // first rank with us >= v
-        int lo = 0, hi = g.n_p;
-        while (lo < hi) { int m = (lo + hi) >> 1; if (us[m] >= v) hi = m; else lo = m + 1; }
-        return lo;
-    };
-    double u_first = ((double)su[tl.e0] - 0.5 * g.n_bins) * g.bin_cm;
-    double u_last = ((double)su[tl.e0 + tl.n - 1] - 0.5 * g.n_bins) * g.bin_cm;
-    tl.r0 = first_above(u_first - reach);
-    tl.r1 = max(tl.r0, first_at_least(u_last + reach));
-    tiles[t] = tl;
+    int r0 = g.n_p, r1 = 0;
     long long use = 0;
-    for (int e = 0; e < tl.n; ++e) {
-        double u = ((double)su[tl.e0 + e] - 0.5 * g.n_bins) * g.bin_cm;
-        use += first_at_least(u + reach) - first_above(u - reach);
+    for (int e = sub; e < tl.n; e += 16) {
+        const double u = ((double)su[tl.e0 + e] - 0.5 * g.n_bins) * g.bin_cm;
+        int lo = 0, hi = g.n_p;   // first rank with us > u - reach
+        while (lo < hi) { int m = (lo + hi) >> 1; if (us[m] > u - reach) hi = m; else lo = m + 1; }
+        const int above = lo;
+        lo = 0;
+        hi = g.n_p;               // first rank with us >= u + reach
+        while (lo < hi) { int m = (lo + hi) >> 1; if (us[m] >= u + reach) hi = m; else lo = m + 1; }
+        use += lo - above;
+        r0 = min(r0, above);
+        r1 = max(r1, lo);
     }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        r0 = min(r0, __shfl_xor(r0, o, 16));
+        r1 = max(r1, __shfl_xor(r1, o, 16));
+        use += __shfl_xor(use, o, 16);
+    }
+    if (sub) return;
+    tl.r0 = r0;
+    tl.r1 = max(r0, r1);
+    tiles[t] = tl;
     terms[t] = (long long)(tl.r1 - tl.r0) * tl.n * g.n_q;
     useful[t] = use * g.n_q;
 }
@@ -130,18 +152,18 @@ hipError_t launch_event_keys(const Geo &g, int64_t n, int n_real, const int64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_gather_events(const Geo &g, int64_t n, const uint64_t *keys, const int *idx, const lmosem_events &ev,
+hipError_t launch_gather_events(const Geo &g, int64_t n, int n_groups, const uint64_t *keys, const int *idx, const lmosem_events &ev,
                                 int *sa, float *su, float *se, float *efac, int *orig, int *counts, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_events, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, n, keys, idx,
-                       ev.u_bin, ev.energy_kev, ev.angle, sa, su, se, efac, orig, counts);
+    hipLaunchKernelGGL(k_gather_events, dim3((unsigned)((n + 255) / 256 + (n_groups + 255) / 256)), dim3(256), 0, st, g,
+                       n, n_groups, keys, idx, ev.u_bin, ev.energy_kev, ev.angle, sa, su, se, efac, orig, counts);
     return hipGetLastError();
 }
 
 hipError_t launch_tile_ranks(const Geo &g, Tile *tiles, int n_tiles, const double *us_sorted, const float *su,
                              long long *terms, long long *useful, hipStream_t st) {
     if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tile_ranks, dim3((unsigned)((n_tiles + 127) / 128)), dim3(128), 0, st, g, tiles, n_tiles,
+    hipLaunchKernelGGL(k_tile_ranks, dim3((unsigned)((n_tiles + 15) / 16)), dim3(256), 0, st, g, tiles, n_tiles,
                        us_sorted, su, terms, useful);
     return hipGetLastError();
 }
@@ -202,7 +224,6 @@ hipError_t sort_events(const Geo &g, const Tables &tb, const lmosem_events &ev,
     CK(hipMalloc(&set.orig, sizeof(int) * nn), "alloc events");
     CK(hipMalloc(&set.efac, sizeof(float) * nn), "alloc events");
     CK(hipMalloc(&counts, sizeof(int) * std::max(n_groups, 1)), "alloc counts");
-    CK(hipMemsetAsync(counts, 0, sizeof(int) * std::max(n_groups, 1), st), "clear counts");
     if (n > 0) {
         CK(hipMalloc(&keys, sizeof(uint64_t) * n), "alloc keys");
         CK(hipMalloc(&keys2, sizeof(uint64_t) * n), "alloc keys");
@@ -211,25 +232,18 @@ hipError_t sort_events(const Geo &g, const Tables &tb, const lmosem_events &ev,
         CK(hipMalloc(&offs_d, sizeof(int64_t) * offs.size()), "alloc offsets");
         CK(hipMemcpyAsync(offs_d, offs.data(), sizeof(int64_t) * offs.size(), hipMemcpyHostToDevice, st),
            "upload offsets");
-        unsigned blocks = (unsigned)((n + 255) / 256);
-        hipLaunchKernelGGL(k_keys, dim3(blocks), dim3(256), 0, st, g, n, n_real, offs_d, ev.angle,
-                           ev.u_bin, force_subset, keys, idx);
-        CK(hipGetLastError(), "keys");
-        int hi_bits = 1;
-        while ((1ll << hi_bits) < (long long)n_groups) ++hi_bits;
+        CK(launch_event_keys(g, n, n_real, offs_d, ev.angle, ev.u_bin, force_subset, keys, idx, st), "keys");
         size_t tmp_bytes = 0;
-        CK(hipcub::DeviceRadixSort::SortPairs(nullptr, tmp_bytes, keys, keys2, idx, idx2, (int)n, 0,
-                                              32 + hi_bits, st), "sort size");
+        CK(sort_pairs_bytes(n, n_groups, tmp_bytes), "sort size");
         CK(hipMalloc(&tmp, tmp_bytes), "alloc sort");
-        CK(hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, keys, keys2, idx, idx2, (int)n, 0,
-                                              32 + hi_bits, st), "sort");
-        hipLaunchKernelGGL(k_gather_events, dim3(blocks), dim3(256), 0, st, g, n, keys2, idx2, ev.u_bin,
-                           ev.energy_kev, ev.angle, set.ang, set.u, set.e, set.efac, set.orig, counts);
-        CK(hipGetLastError(), "gather events");
+        CK(sort_pairs(tmp, tmp_bytes, keys, keys2, idx, idx2, n, n_groups, st), "sort");
+        CK(launch_gather_events(g, n, n_groups, keys2, idx2, ev, set.ang, set.u, set.e, set.efac, set.orig, counts, st),
+           "gather events");
     }
     set.counts.assign(std::max(n_groups, 1), 0);
-    CK(hipMemcpyAsync(set.counts.data(), counts, sizeof(int) * std::max(n_groups, 1), hipMemcpyDeviceToHost, st),
-       "download counts");
+    if (n > 0)
+        CK(hipMemcpyAsync(set.counts.data(), counts, sizeof(int) * n_groups, hipMemcpyDeviceToHost, st),
+           "download counts");
     CK(hipStreamSynchronize(st), "ingest");
     cleanup();
 #undef CK
@@ -306,9 +320,7 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
        "upload ranges");
     std::vector<long long> terms(nt, 0), useful(nt, 0);
     if (!tiles.empty()) {
-        hipLaunchKernelGGL(k_tile_ranks, dim3((unsigned)((tiles.size() + 127) / 128)), dim3(128), 0, st, g,
-                           set.tiles, (int)tiles.size(), tb.us_sorted, set.u, terms_d, useful_d);
-        CK(hipGetLastError(), "tile ranks");
+        CK(launch_tile_ranks(g, set.tiles, (int)tiles.size(), tb.us_sorted, set.u, terms_d, useful_d, st), "tile ranks");
         CK(hipMemcpyAsync(terms.data(), terms_d, sizeof(long long) * tiles.size(), hipMemcpyDeviceToHost, st),
            "download counters");
         CK(hipMemcpyAsync(useful.data(), useful_d, sizeof(long long) * tiles.size(), hipMemcpyDeviceToHost,

@@ -102,7 +102,7 @@ hipError_t plan_tiles(const Geo &g, const Tables &t, EvSet &set, int ev_tile, in
 // the steps of the ingest on buffers the caller provides (no allocation)
 hipError_t launch_event_keys(const Geo &g, int64_t n, int n_real, const int64_t *offs_dev, const int32_t *angle,
                              const float *u_bin, int force_subset, uint64_t *keys, int *idx, hipStream_t st);
-hipError_t launch_gather_events(const Geo &g, int64_t n, const uint64_t *keys, const int *idx, const lmosem_events &ev,
+hipError_t launch_gather_events(const Geo &g, int64_t n, int n_groups, const uint64_t *keys, const int *idx, const lmosem_events &ev,
                                 int *sa, float *su, float *se, float *efac, int *orig, int *counts, hipStream_t st);
 hipError_t launch_tile_ranks(const Geo &g, Tile *tiles, int n_tiles, const double *us_sorted, const float *su,
                              long long *terms, long long *useful, hipStream_t st);

@@ -138,12 +138,10 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
     // order the events by (angle, position), as lmosem_forward's ingest does
     // with every event in subset 0 and one realisation
     const int64_t offs_h[2] = {0, (int64_t)n};
-    // the per-angle counters start at zero (a fill kernel: all-zero bits)
-    if ((e = launch_fill(reinterpret_cast<float *>(counts), (size_t)g.n_angles, 0.0f, st)) != hipSuccess) return e;
     if ((e = hipMemcpyAsync(offs, offs_h, sizeof offs_h, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
     if ((e = launch_event_keys(g, n, 1, offs, ev.angle, ev.u_bin, 0, keys, idx, st)) != hipSuccess) return e;
     if ((e = sort_pairs(tmp, L.tmp_bytes, keys, keys2, idx, idx2, n, g.n_angles, st)) != hipSuccess) return e;
-    if ((e = launch_gather_events(g, n, keys2, idx2, ev, ang, u, en, efac, orig, counts, st)) != hipSuccess) return e;
+    if ((e = launch_gather_events(g, n, g.n_angles, keys2, idx2, ev, ang, u, en, efac, orig, counts, st)) != hipSuccess) return e;
     std::vector<int> cnt(g.n_angles);
     if ((e = hipMemcpyAsync(cnt.data(), counts, sizeof(int) * g.n_angles, hipMemcpyDeviceToHost, st)) != hipSuccess)
         return e;

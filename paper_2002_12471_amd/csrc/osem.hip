@@ -615,10 +615,10 @@ __global__ void k_sum_real(Geo g, const int *__restrict__ crange, const float *_
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     const int r = blockIdx.y;
     if (q >= g.n_qpad) return;
-    float b = 0.0f;
+    double b = 0.0;
 #pragma unroll 16
     for (int c = crange[r]; c < crange[r + 1]; ++c) b += pb[(size_t)c * g.n_qpad + q];
-    out[(size_t)r * g.n_qpad + q] = q < g.n_q ? b : 0.0f;
+    out[(size_t)r * g.n_qpad + q] = q < g.n_q ? (float)b : 0.0f;
 }
 
 hipError_t launch_sum_real(const Geo &g, const int *crange, int n_real, const float *pb, float *out,
