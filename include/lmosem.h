@@ -285,7 +285,9 @@ lmosem_status lmosem_autotune(lmosem_ctx *ctx, lmosem_evset *set, int32_t *event
  * before they are allocated (for scatter_model 2, whose near-field band's
  * width is known only once built, they are freed again), an event set after
  * its sort is planned, a row cache before it is allocated.  Memory a call
- * uses only while it runs is not counted.  Errors: EINVAL (bytes < 0). */
+ * uses only while it runs is not counted; without a cap a context keeps up to
+ * 128 MB of it for its next call, until it is destroyed or given a cap.
+ * Errors: EINVAL (bytes < 0). */
 lmosem_status lmosem_set_memory_cap(lmosem_ctx *ctx, int64_t bytes);
 /* The device bytes the context holds as the cap counts them. */
 lmosem_status lmosem_memory_held(const lmosem_ctx *ctx, int64_t *bytes);

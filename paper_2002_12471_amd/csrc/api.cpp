@@ -59,6 +59,7 @@ struct lmosem_ctx {
     // bytes held by its live event sets
     int64_t mem_cap = 0;
     int64_t set_bytes = 0;
+    Arena arena;               // event sets and buffers of one call
     bool inject_failure = false;   // the next launch reports a HIP failure (testing hook)
 };
 
@@ -87,6 +88,7 @@ struct lmosem_evset {
     // slot: [angles][first rows][first blocks][first slot of each subset] on the
     // device, rows and blocks on the host too
     int *lists = nullptr;
+    std::vector<int> lists_host;   // what lists was copied from
     std::vector<int> list_off, slot_off, n_list, slot_rows, slot_blk;
     int lists_rows = 0, lists_blk = 0;   // where rows and blocks begin in lists
     size_t pb_chunks = 0;     // chunk rows allocated in pb
@@ -165,17 +167,23 @@ bool check_cfg(const lmosem_config *c, std::string &why) {
     return true;
 }
 
+bool check_arrays(lmosem_ctx *c, const lmosem_events *ev, lmosem_status &st) {
+    if (ev && ev->n >= 0 && ev->n <= 0x7fffffffLL && (ev->n == 0 || (ev->angle && ev->u_bin && ev->energy_kev))) return true;
+    st = set_err(c, LMOSEM_EINVAL, "bad event arrays");
+    return false;
+}
+
+lmosem_status bad_events(lmosem_ctx *c, int64_t bad) {
+    return set_err(c, LMOSEM_ERANGE, std::to_string(bad) + " events outside angle/position/energy range");
+}
+
 bool check_events(lmosem_ctx *c, const lmosem_events *ev, lmosem_status &st) {
-    if (!ev || ev->n < 0 || ev->n > 0x7fffffffLL ||
-        (ev->n > 0 && (!ev->angle || !ev->u_bin || !ev->energy_kev))) {
-        st = set_err(c, LMOSEM_EINVAL, "bad event arrays");
-        return false;
-    }
+    if (!check_arrays(c, ev, st)) return false;
     int64_t bad = 0;
     hipError_t e = validate_events(c->g, *ev, &bad, c->bad_dev, c->st);
     if (e != hipSuccess) { st = dev_err(c, "validate events", e); return false; }
     if (bad) {
-        st = set_err(c, LMOSEM_ERANGE, std::to_string(bad) + " events outside angle/position/energy range");
+        st = bad_events(c, bad);
         return false;
     }
     return true;
@@ -190,11 +198,12 @@ void free_set(lmosem_evset *s) {
     if (!s) return;
     if (s->s.ctx) s->s.ctx->set_bytes -= s->bytes;
     drop_graphs(s);
-    hipFree(s->s.u); hipFree(s->s.e); hipFree(s->s.efac); hipFree(s->s.orig); hipFree(s->s.tiles); hipFree(s->s.chunks);
-    hipFree(s->s.crange); hipFree(s->s.rrange);
-    hipFree(s->H); hipFree(s->Hc); hipFree(s->pmean); hipFree(s->mean); hipFree(s->inv); hipFree(s->pb); hipFree(s->f);
-    hipFree(s->ll); hipFree(s->col); hipFree(s->X); hipFree(s->s.ang);
-    hipFree(s->s.fev); hipFree(s->s.fblk); hipFree(s->lists); hipFree(s->fws);
+    for (void *p : {(void *)s->s.u, (void *)s->s.e, (void *)s->s.efac, (void *)s->s.orig, (void *)s->s.ang, s->s.plan,
+                    (void *)s->H, (void *)s->Hc, (void *)s->pmean, (void *)s->mean, (void *)s->inv, (void *)s->pb,
+                    (void *)s->f, (void *)s->ll, (void *)s->col, (void *)s->X, (void *)s->s.fev, (void *)s->s.fblk,
+                    (void *)s->lists, (void *)s->fws})
+        dev_give(s->s.arena, p);
+    if (s->s.arena) s->s.arena->end();
     delete s;
 }
 
@@ -229,14 +238,14 @@ lmosem_status alloc_workspace(lmosem_ctx *c, lmosem_evset *s, bool for_rows = fa
     hipError_t e;
     // a flux set works without rows until they are cached (then in the cache)
     const bool direct = !s->flux || for_rows;
-#define AL(p, bytes) do { if (!(p)) { e = hipMalloc(&(p), (bytes)); if (e != hipSuccess) return alloc_err(c, "workspace", e); } } while (0)
+#define AL(p, bytes) do { if (!(p)) { e = dev_take(s->s.arena, &(p), (bytes)); if (e != hipSuccess) return alloc_err(c, "workspace", e); } } while (0)
     if (direct) AL(s->H, sizeof(float) * rows * g.n_qpad);
-    if (s->pmean && s->pmean_groups < groups) { hipFree(s->pmean); s->pmean = nullptr; }
+    if (s->pmean && s->pmean_groups < groups) { dev_give(s->s.arena, s->pmean); s->pmean = nullptr; }
     if (!s->pmean) s->pmean_groups = groups;
     if (direct) AL(s->pmean, sizeof(float) * rows * groups);
     AL(s->mean, sizeof(float) * rows);
     AL(s->inv, sizeof(float) * rows);
-    if (s->pb && s->pb_chunks < chunks) { hipFree(s->pb); s->pb = nullptr; }
+    if (s->pb && s->pb_chunks < chunks) { dev_give(s->s.arena, s->pb); s->pb = nullptr; }
     if (!s->pb) s->pb_chunks = chunks;
     if (direct) AL(s->pb, sizeof(float) * chunks * g.n_qpad);
     AL(s->f, sizeof(float) * (size_t)s->s.n_real * g.n_qpad);
@@ -314,19 +323,19 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
     s->slot_blk.push_back(blk);
     s->lists_rows = na;
     s->lists_blk = na + n_slots + 1;
-    std::vector<int> up(angles);
+    std::vector<int> &up = s->lists_host;
+    up = angles;
     up.insert(up.end(), s->slot_rows.begin(), s->slot_rows.end());
     up.insert(up.end(), s->slot_blk.begin(), s->slot_blk.end());
     up.insert(up.end(), s->slot_off.begin(), s->slot_off.end());
-    hipError_t e = hipMalloc(&s->lists, sizeof(int) * up.size());
-    if (e == hipSuccess) e = hipMalloc(&v.fev, sizeof(FluxEvent) * (size_t)std::max<int64_t>(v.n, 1));
-    if (e == hipSuccess) e = hipMalloc(&v.fblk, sizeof(FluxBlock) * (size_t)std::max(blk, 1));
+    hipError_t e = dev_take(v.arena, &s->lists, sizeof(int) * up.size());
+    if (e == hipSuccess) e = dev_take(v.arena, &v.fev, sizeof(FluxEvent) * (size_t)std::max<int64_t>(v.n, 1));
+    if (e == hipSuccess) e = dev_take(v.arena, &v.fblk, sizeof(FluxBlock) * (size_t)std::max(blk, 1));
     if (e == hipSuccess) e = hipMemcpyAsync(s->lists, up.data(), sizeof(int) * up.size(), hipMemcpyHostToDevice, c->st);
     if (e == hipSuccess)
         e = flux_events(g, c->fg, 0, blk, 0, s->lists + s->lists_rows, s->lists + s->lists_blk, n_slots,
                         force_subset >= 0 ? nullptr : s->lists + s->lists_blk + n_slots + 1, v.ang, v.u, v.e, c->t, v.fev,
                         v.fblk, c->st);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->st);
     if (e != hipSuccess) return alloc_err(c, "event records", e);
     if (!kept && v.n_real == 1) return LMOSEM_OK;
     const size_t budget = (size_t)std::max(v.max_rows, 1) * g.n_qpad;
@@ -334,7 +343,7 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
     if (need > budget && budget <= c->fws_floats) return LMOSEM_OK;
     const size_t floats = std::min(need, budget);
     if (flux_group(g, c->fg, floats, v.n_real, max_list) < 1) return LMOSEM_OK;
-    e = hipMalloc(&s->fws, sizeof(float) * floats);
+    e = dev_take(v.arena, &s->fws, sizeof(float) * floats);
     if (e != hipSuccess) return alloc_err(c, "workspace", e);
     s->fws_floats = floats;
     return LMOSEM_OK;
@@ -344,14 +353,16 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
                        lmosem_evset **out, bool kept = false) {
     lmosem_status st = LMOSEM_OK;
     if (c->surrogate && !c->net) return set_err(c, LMOSEM_ESTATE, "scatter_model 2 needs a network (lmosem_set_surrogate)");
-    if (!check_events(c, ev, st)) return st;
+    if (!check_arrays(c, ev, st)) return st;
     std::vector<int64_t> offs;
     if (batch) {
-        if (batch->n_real < 1 || !batch->offsets) return set_err(c, LMOSEM_EINVAL, "bad batch");
+        // (events out of range are reported before a bad batch)
+        auto bad_batch = [&](const char *msg) { return check_events(c, ev, st) ? set_err(c, LMOSEM_EINVAL, msg) : st; };
+        if (batch->n_real < 1 || !batch->offsets) return bad_batch("bad batch");
         offs.assign(batch->offsets, batch->offsets + batch->n_real + 1);
-        if (offs[0] != 0 || offs.back() != ev->n) return set_err(c, LMOSEM_EINVAL, "batch offsets must span the events");
+        if (offs[0] != 0 || offs.back() != ev->n) return bad_batch("batch offsets must span the events");
         for (int r = 0; r < batch->n_real; ++r)
-            if (offs[r + 1] < offs[r]) return set_err(c, LMOSEM_EINVAL, "batch offsets must not decrease");
+            if (offs[r + 1] < offs[r]) return bad_batch("batch offsets must not decrease");
     } else {
         offs = {0, ev->n};
     }
@@ -359,8 +370,18 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
     s->s.ctx = c;
     s->s.ev_tile = c->ev_tile;
     s->s.fwd_waves = c->pixel_waves;
+    // (under a memory cap a call's blocks go when it ends, as it counts them)
+    if (!kept && c->mem_cap == 0 && !c->arena.open) {
+        c->arena.begin();
+        s->s.arena = &c->arena;
+    }
     std::string why;
-    hipError_t e = sort_events(c->g, c->t, *ev, offs, force_subset, s->s, c->st, why);
+    int64_t bad = 0;
+    hipError_t e = sort_events(c->g, c->t, *ev, offs, force_subset, s->s, c->st, bad, why);
+    if (e == hipSuccess && bad) {
+        free_set(s);
+        return bad_events(c, bad);
+    }
     if (e != hipSuccess) {
         free_set(s);
         return e == hipErrorOutOfMemory ? set_err(c, LMOSEM_ENOMEM, why) : set_err(c, LMOSEM_EDEVICE, why);
@@ -847,6 +868,7 @@ void lmosem_destroy(lmosem_ctx *c) {
     hipFree(c->t.prim); hipFree(c->t.band); hipFree(c->t.band_lo); hipFree(c->t.Ld); hipFree(c->t.Bt);
     hipFree(c->t.D_sorted); hipFree(c->bad_dev); hipFree(c->skipped_dev);
     free_flux(c->ft); hipFree(c->fws);
+    c->arena.release();
     delete c;
 }
 
@@ -1137,6 +1159,7 @@ lmosem_status lmosem_set_surrogate(lmosem_ctx *c, lmosem_net *net) {
 lmosem_status lmosem_set_memory_cap(lmosem_ctx *c, int64_t bytes) {
     GUARD(c);
     if (bytes < 0) return set_err(c, LMOSEM_EINVAL, "the memory cap must be >= 0");
+    if (bytes > 0 && !c->arena.open) c->arena.release();
     c->mem_cap = bytes;
     return LMOSEM_OK;
 }
@@ -1286,7 +1309,9 @@ lmosem_status lmosem_binned_reconstruct(lmosem_ctx *c, int32_t n_pos, const doub
     Chunk *d_chunks = nullptr;
     unsigned long long *dead = nullptr;
     hipError_t e = hipSuccess;
-    auto al = [&](void **p, size_t bytes) { if (e == hipSuccess) e = hipMalloc(p, bytes); };
+    Arena *arena = c->mem_cap == 0 && !c->arena.open ? &c->arena : nullptr;
+    if (arena) arena->begin();
+    auto al = [&](void **p, size_t bytes) { if (e == hipSuccess) e = dev_take(arena, p, bytes); };
     al((void **)&H, sizeof(float) * (size_t)n_rows * g.n_qpad);
     al((void **)&y, sizeof(float) * n_rows);
     al((void **)&mean, sizeof(float) * max_rows);
@@ -1312,7 +1337,7 @@ lmosem_status lmosem_binned_reconstruct(lmosem_ctx *c, int32_t n_pos, const doub
     up(d_chunks, chunks.data(), sizeof(Chunk) * chunks.size());
     if (e == hipSuccess) e = launch_fill(ones, max_rows, 1.0f, c->st);
     if (e == hipSuccess) {
-        e = launch_binned_rows_all(g, c->t, n_pos, edges, n_ebins, d_row0, H, c->st);
+        e = launch_binned_rows_all(g, c->t, n_pos, edges, n_ebins, d_row0, H, arena, c->st);
         if (e == hipErrorNotSupported) e = launch_binned_rows(g, c->t, n_pos, edges, n_ebins, d_rows, n_rows, H, c->st);
     }
     if (e == hipSuccess) e = launch_gather_counts(counts_dev, d_rows, n_rows, y, c->st);
@@ -1338,7 +1363,8 @@ lmosem_status lmosem_binned_reconstruct(lmosem_ctx *c, int32_t n_pos, const doub
     for (void *p : {(void *)H, (void *)y, (void *)mean, (void *)inv, (void *)w, (void *)ones, (void *)pb, (void *)sens,
                     (void *)f, (void *)d_rows, (void *)d_cr, (void *)d_rr, (void *)d_row0, (void *)d_chunks, (void *)dead,
                     (void *)edges})
-        hipFree(p);
+        dev_give(arena, p);
+    if (arena) arena->end();
     if (e == hipErrorOutOfMemory) { (void)hipGetLastError(); return set_err(c, LMOSEM_ENOMEM, "binned reconstruction: out of memory"); }
     return e == hipSuccess ? LMOSEM_OK : dev_err(c, "binned reconstruction", e);
 }

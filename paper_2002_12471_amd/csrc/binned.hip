@@ -295,7 +295,7 @@ hipError_t launch_rows_all(const Geo &g, const Tables &t, int n_pos, const doubl
 // windows hold, or the scratch does not fit (the caller then lists the bins for
 // k_binned_rows, which needs none).
 hipError_t launch_binned_rows_all(const Geo &g, const Tables &t, int n_pos, const double *edges_dev, int n_e,
-                                  const int *angle_row0_dev, float *H, hipStream_t st) {
+                                  const int *angle_row0_dev, float *H, Arena *arena, hipStream_t st) {
     if (!t.Ld) return hipErrorInvalidValue;
     const double width = 2.0 * g.half_len / n_pos;
     const int span = (int)ceil(6.0 * g.sig_u / width) + 2;   // bins a response can touch
@@ -307,11 +307,11 @@ hipError_t launch_binned_rows_all(const Geo &g, const Tables &t, int n_pos, cons
     // to 128 x 128: the chip is full with a few tens of angles)
     const size_t per = (size_t)(2 * g.nx - 1) * (2 * g.ny - 1) * (1 + n_e) * sizeof(double);
     w.n_a = g.scatter ? (int)std::min<size_t>(g.n_angles, std::max<size_t>(1, (size_t(64) << 20) / per)) : g.n_angles;
-    hipError_t e = hipMalloc(&w.rb0, sizeof(int) * na_np);
-    if (e == hipSuccess) e = hipMalloc(&w.roff, sizeof(int) * na_np);
-    if (e == hipSuccess) e = hipMalloc(&w.rL, sizeof(double) * na_np);
-    if (e == hipSuccess) e = hipMalloc(&w.rpm, sizeof(double) * na_np * W);
-    if (e == hipSuccess && g.scatter) e = hipMalloc(&w.tab, per * w.n_a);
+    hipError_t e = dev_take(arena, &w.rb0, sizeof(int) * na_np);
+    if (e == hipSuccess) e = dev_take(arena, &w.roff, sizeof(int) * na_np);
+    if (e == hipSuccess) e = dev_take(arena, &w.rL, sizeof(double) * na_np);
+    if (e == hipSuccess) e = dev_take(arena, &w.rpm, sizeof(double) * na_np * W);
+    if (e == hipSuccess && g.scatter) e = dev_take(arena, &w.tab, per * w.n_a);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         e = hipErrorNotSupported;
@@ -324,7 +324,7 @@ hipError_t launch_binned_rows_all(const Geo &g, const Tables &t, int n_pos, cons
     }
     // the scratch is released once the kernels are done
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    for (void *p : {(void *)w.rb0, (void *)w.roff, (void *)w.rL, (void *)w.rpm, (void *)w.tab}) hipFree(p);
+    for (void *p : {(void *)w.rb0, (void *)w.roff, (void *)w.rL, (void *)w.rpm, (void *)w.tab}) dev_give(arena, p);
     return e;
 }
 

@@ -12,10 +12,50 @@
 
 #include <algorithm>
 #include <cstdio>
+#include <cstring>
 
 #include "lmosem_int.h"
 
 namespace lmo {
+
+void Arena::begin() {
+    used = 0;
+    open = true;
+    if (asked > size && size < kArenaBytes) {
+        release();
+        const size_t want = std::min(kArenaBytes, (asked + asked / 4 + (size_t(1) << 20) - 1) >> 20 << 20);
+        if (hipMalloc(&base, want) == hipSuccess) size = want;
+        else { (void)hipGetLastError(); base = nullptr; }
+    }
+    asked = 0;
+}
+
+void Arena::release() {
+    hipFree(base);
+    base = nullptr;
+    size = 0;
+}
+
+hipError_t dev_take(Arena *a, void **p, size_t bytes) {
+    const size_t b = (bytes + 255) & ~size_t(255);
+    if (a && a->open && b <= kArenaBytes / 2) {
+        a->asked += b;
+        if (a->used + b <= a->size) {
+            *p = a->base + a->used;
+            a->used += b;
+            return hipSuccess;
+        }
+    }
+    return hipMalloc(p, bytes);
+}
+
+void dev_give(Arena *a, void *p) {
+    if (!a || !a->owns(p)) hipFree(p);
+}
+
+__device__ inline bool valid_event(const Geo &g, int a, float u, float e) {
+    return a >= 0 && a < g.n_angles && u >= 0.0f && u < (float)g.n_bins && (double)e >= g.win_lo && (double)e <= g.win_hi;
+}
 
 __global__ void k_validate(Geo g, int64_t n, const int32_t *__restrict__ angle,
                            const float *__restrict__ u_bin, const float *__restrict__ energy,
@@ -23,11 +63,7 @@ __global__ void k_validate(Geo g, int64_t n, const int32_t *__restrict__ angle,
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int local = 0;
     if (j < n) {
-        int a = angle[j];
-        float u = u_bin[j], e = energy[j];
-        bool ok = a >= 0 && a < g.n_angles && u >= 0.0f && u < (float)g.n_bins &&
-                  (double)e >= g.win_lo && (double)e <= g.win_hi;
-        local = ok ? 0 : 1;
+        local = valid_event(g, angle[j], u_bin[j], energy[j]) ? 0 : 1;
     }
     // one atomic per wave
     unsigned long long m = __ballot(local);
@@ -50,24 +86,30 @@ hipError_t validate_events(const Geo &g, const lmosem_events &ev, int64_t *bad_h
     return hipSuccess;
 }
 
-// key = (group << 32) | position bits; group = (subset * R + realisation) * N_A + angle
-__global__ void k_keys(Geo g, int64_t n, int n_real, const int64_t *__restrict__ offs,
+// key = (group << 32) | position bits; group = (subset * R + realisation) * N_A + angle,
+// n_groups for an event outside the ranges
+__global__ void k_keys(Geo g, int64_t n, int n_groups, int n_real, const int64_t *__restrict__ offs,
                        const int32_t *__restrict__ angle, const float *__restrict__ u_bin,
-                       int force_subset, uint64_t *__restrict__ keys, int *__restrict__ idx) {
+                       const float *__restrict__ energy, int force_subset, uint64_t *__restrict__ keys,
+                       int *__restrict__ idx) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
+    idx[j] = (int)j;
+    int a = angle[j];
+    float u = u_bin[j];
+    if (!valid_event(g, a, u, energy[j])) {
+        keys[j] = (uint64_t)n_groups << 32;
+        return;
+    }
     int lo = 0, hi = n_real;           // realisation r with offs[r] <= j < offs[r+1]
     while (hi - lo > 1) {
         int mid = (lo + hi) >> 1;
         if (offs[mid] <= j) lo = mid; else hi = mid;
     }
-    int a = angle[j];
     int sub = force_subset >= 0 ? force_subset : a % g.n_subsets;
     uint64_t grp = ((uint64_t)sub * n_real + lo) * g.n_angles + a;
-    float u = u_bin[j];
     uint32_t bits = u > 0.0f ? __float_as_uint(u) : 0u;   // positions are >= 0: bits sort like values
     keys[j] = (grp << 32) | bits;
-    idx[j] = (int)j;
 }
 
 // The events in sorted order, and (the workgroups past them) each group's
@@ -144,11 +186,11 @@ __global__ __launch_bounds__(256) void k_tile_ranks(Geo g, Tile *__restrict__ ti
     useful[t] = use * g.n_q;
 }
 
-hipError_t launch_event_keys(const Geo &g, int64_t n, int n_real, const int64_t *offs_dev, const int32_t *angle,
-                             const float *u_bin, int force_subset, uint64_t *keys, int *idx, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, n, n_real, offs_dev, angle,
-                       u_bin, force_subset, keys, idx);
+hipError_t launch_event_keys(const Geo &g, int n_groups, int n_real, const int64_t *offs_dev, const lmosem_events &ev,
+                             int force_subset, uint64_t *keys, int *idx, hipStream_t st) {
+    if (ev.n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_keys, dim3((unsigned)((ev.n + 255) / 256)), dim3(256), 0, st, g, ev.n, n_groups, n_real, offs_dev,
+                       ev.angle, ev.u_bin, ev.energy_kev, force_subset, keys, idx);
     return hipGetLastError();
 }
 
@@ -201,7 +243,7 @@ void host_tiles(const Geo &g, const std::vector<int> &counts, int n_angles_used,
 
 hipError_t sort_events(const Geo &g, const Tables &tb, const lmosem_events &ev,
                        const std::vector<int64_t> &offs, int force_subset, EvSet &set,
-                       hipStream_t st, std::string &err) {
+                       hipStream_t st, int64_t &bad, std::string &err) {
     hipError_t e = hipSuccess;
     const int64_t n = ev.n;
     const int n_real = (int)offs.size() - 1;
@@ -210,44 +252,51 @@ hipError_t sort_events(const Geo &g, const Tables &tb, const lmosem_events &ev,
     int *idx = nullptr, *idx2 = nullptr, *counts = nullptr;
     int64_t *offs_d = nullptr;
     void *tmp = nullptr;
+    bad = 0;
+    auto take = [&](auto **p, size_t bytes) { return dev_take(set.arena, p, bytes); };
     auto cleanup = [&]() {
-        hipFree(keys); hipFree(keys2); hipFree(idx); hipFree(idx2); hipFree(counts);
-        hipFree(offs_d); hipFree(tmp);
+        for (void *p : {(void *)keys, (void *)keys2, (void *)idx, (void *)idx2, (void *)counts, (void *)offs_d, tmp})
+            dev_give(set.arena, p);
     };
 #define CK(call, what) do { e = (call); if (e != hipSuccess) { err = std::string(what) + ": " + hipGetErrorString(e); cleanup(); return e; } } while (0)
     set.n = n;
     set.n_real = n_real;
     size_t nn = (size_t)std::max<int64_t>(n, 1);
-    CK(hipMalloc(&set.ang, sizeof(int) * nn), "alloc events");
-    CK(hipMalloc(&set.u, sizeof(float) * nn), "alloc events");
-    CK(hipMalloc(&set.e, sizeof(float) * nn), "alloc events");
-    CK(hipMalloc(&set.orig, sizeof(int) * nn), "alloc events");
-    CK(hipMalloc(&set.efac, sizeof(float) * nn), "alloc events");
-    CK(hipMalloc(&counts, sizeof(int) * std::max(n_groups, 1)), "alloc counts");
+    CK(take(&set.ang, sizeof(int) * nn), "alloc events");
+    CK(take(&set.u, sizeof(float) * nn), "alloc events");
+    CK(take(&set.e, sizeof(float) * nn), "alloc events");
+    CK(take(&set.orig, sizeof(int) * nn), "alloc events");
+    CK(take(&set.efac, sizeof(float) * nn), "alloc events");
+    set.counts.assign(n_groups + 1, 0);
     if (n > 0) {
-        CK(hipMalloc(&keys, sizeof(uint64_t) * n), "alloc keys");
-        CK(hipMalloc(&keys2, sizeof(uint64_t) * n), "alloc keys");
-        CK(hipMalloc(&idx, sizeof(int) * n), "alloc idx");
-        CK(hipMalloc(&idx2, sizeof(int) * n), "alloc idx");
-        CK(hipMalloc(&offs_d, sizeof(int64_t) * offs.size()), "alloc offsets");
-        CK(hipMemcpyAsync(offs_d, offs.data(), sizeof(int64_t) * offs.size(), hipMemcpyHostToDevice, st),
-           "upload offsets");
-        CK(launch_event_keys(g, n, n_real, offs_d, ev.angle, ev.u_bin, force_subset, keys, idx, st), "keys");
+        CK(take(&counts, sizeof(int) * (n_groups + 1)), "alloc counts");
+        CK(take(&keys, sizeof(uint64_t) * n), "alloc keys");
+        CK(take(&keys2, sizeof(uint64_t) * n), "alloc keys");
+        CK(take(&idx, sizeof(int) * n), "alloc idx");
+        CK(take(&idx2, sizeof(int) * n), "alloc idx");
+        if (n_real > 1) {
+            CK(take(&offs_d, sizeof(int64_t) * offs.size()), "alloc offsets");
+            CK(hipMemcpyAsync(offs_d, offs.data(), sizeof(int64_t) * offs.size(), hipMemcpyHostToDevice, st),
+               "upload offsets");
+        }
+        // events are checked as they are keyed: the invalid ones count as one
+        // more group, behind the others
+        CK(launch_event_keys(g, n_groups, n_real, offs_d, ev, force_subset, keys, idx, st), "keys");
         size_t tmp_bytes = 0;
-        CK(sort_pairs_bytes(n, n_groups, tmp_bytes), "sort size");
-        CK(hipMalloc(&tmp, tmp_bytes), "alloc sort");
-        CK(sort_pairs(tmp, tmp_bytes, keys, keys2, idx, idx2, n, n_groups, st), "sort");
-        CK(launch_gather_events(g, n, n_groups, keys2, idx2, ev, set.ang, set.u, set.e, set.efac, set.orig, counts, st),
+        CK(sort_pairs_bytes(n, n_groups + 1, tmp_bytes), "sort size");
+        CK(take(&tmp, tmp_bytes), "alloc sort");
+        CK(sort_pairs(tmp, tmp_bytes, keys, keys2, idx, idx2, n, n_groups + 1, st), "sort");
+        CK(launch_gather_events(g, n, n_groups + 1, keys2, idx2, ev, set.ang, set.u, set.e, set.efac, set.orig, counts, st),
            "gather events");
-    }
-    set.counts.assign(std::max(n_groups, 1), 0);
-    if (n > 0)
-        CK(hipMemcpyAsync(set.counts.data(), counts, sizeof(int) * n_groups, hipMemcpyDeviceToHost, st),
+        CK(hipMemcpyAsync(set.counts.data(), counts, sizeof(int) * (n_groups + 1), hipMemcpyDeviceToHost, st),
            "download counts");
-    CK(hipStreamSynchronize(st), "ingest");
+        CK(hipStreamSynchronize(st), "ingest");
+    }
+    bad = set.counts[n_groups];
+    set.counts.resize(std::max(n_groups, 1));
     cleanup();
 #undef CK
-    return plan_tiles(g, tb, set, set.ev_tile, set.chunk_rows, st, err);
+    return bad ? hipSuccess : plan_tiles(g, tb, set, set.ev_tile, set.chunk_rows, st, err);
 }
 
 // Tiles of ev_tile consecutive events per (subset, realisation, angle) group
@@ -256,10 +305,11 @@ hipError_t sort_events(const Geo &g, const Tables &tb, const lmosem_events &ev,
 hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, int chunk_rows,
                       hipStream_t st, std::string &err) {
     hipError_t e = hipSuccess;
-    long long *terms_d = nullptr, *useful_d = nullptr;
-    auto cleanup = [&]() { hipFree(terms_d); hipFree(useful_d); };
+    long long *terms_d = nullptr;   // [tiles] terms, then [tiles] useful
+    auto cleanup = [&]() { dev_give(set.arena, terms_d); };
 #define CK(call, what) do { e = (call); if (e != hipSuccess) { err = std::string(what) + ": " + hipGetErrorString(e); cleanup(); return e; } } while (0)
-    hipFree(set.tiles); hipFree(set.chunks); hipFree(set.crange); hipFree(set.rrange);
+    dev_give(set.arena, set.plan);
+    set.plan = nullptr;
     set.tiles = nullptr; set.chunks = nullptr; set.crange = nullptr; set.rrange = nullptr;
     set.ev_tile = ev_tile;
     set.chunk_rows = chunk_rows;
@@ -301,30 +351,30 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
     set.row_off[g.n_subsets] = (int)pos;
     set.tile_off[g.n_subsets] = (int)tiles.size();
     set.chunk_off[g.n_subsets] = (int)chunks.size();
-    size_t nt = std::max<size_t>(tiles.size(), 1), nc = std::max<size_t>(chunks.size(), 1);
-    CK(hipMalloc(&set.tiles, sizeof(Tile) * nt), "alloc tiles");
-    CK(hipMalloc(&set.chunks, sizeof(Chunk) * nc), "alloc chunks");
-    CK(hipMalloc(&set.crange, sizeof(int) * crange.size()), "alloc ranges");
-    CK(hipMalloc(&set.rrange, sizeof(int) * rrange.size()), "alloc ranges");
-    CK(hipMalloc(&terms_d, sizeof(long long) * nt), "alloc counters");
-    CK(hipMalloc(&useful_d, sizeof(long long) * nt), "alloc counters");
-    if (!tiles.empty())
-        CK(hipMemcpyAsync(set.tiles, tiles.data(), sizeof(Tile) * tiles.size(), hipMemcpyHostToDevice, st),
-           "upload tiles");
-    if (!chunks.empty())
-        CK(hipMemcpyAsync(set.chunks, chunks.data(), sizeof(Chunk) * chunks.size(), hipMemcpyHostToDevice,
-                          st), "upload chunks");
-    CK(hipMemcpyAsync(set.crange, crange.data(), sizeof(int) * crange.size(), hipMemcpyHostToDevice, st),
-       "upload ranges");
-    CK(hipMemcpyAsync(set.rrange, rrange.data(), sizeof(int) * rrange.size(), hipMemcpyHostToDevice, st),
-       "upload ranges");
-    std::vector<long long> terms(nt, 0), useful(nt, 0);
+    // [tiles][chunks][crange][rrange] in one block and one copy
+    size_t nt = std::max<size_t>(tiles.size(), 1);
+    std::vector<char> up;
+    auto add = [&](const auto &v) {
+        const size_t at = up.size(), bytes = sizeof(v[0]) * v.size();
+        up.resize((at + std::max<size_t>(bytes, 1) + 15) & ~size_t(15));
+        if (bytes) memcpy(up.data() + at, v.data(), bytes);
+        return at;
+    };
+    const size_t o_tiles = add(tiles), o_chunks = add(chunks), o_crange = add(crange), o_rrange = add(rrange);
+    CK(dev_take(set.arena, &set.plan, up.size()), "alloc tiles");
+    char *plan = static_cast<char *>(set.plan);
+    set.tiles = reinterpret_cast<Tile *>(plan + o_tiles);
+    set.chunks = reinterpret_cast<Chunk *>(plan + o_chunks);
+    set.crange = reinterpret_cast<int *>(plan + o_crange);
+    set.rrange = reinterpret_cast<int *>(plan + o_rrange);
+    CK(dev_take(set.arena, &terms_d, 2 * sizeof(long long) * nt), "alloc counters");
+    CK(hipMemcpyAsync(plan, up.data(), up.size(), hipMemcpyHostToDevice, st), "upload tiles");
+    std::vector<long long> terms(2 * nt, 0);
+    const long long *useful = terms.data() + nt;
     if (!tiles.empty()) {
-        CK(launch_tile_ranks(g, set.tiles, (int)tiles.size(), tb.us_sorted, set.u, terms_d, useful_d, st), "tile ranks");
-        CK(hipMemcpyAsync(terms.data(), terms_d, sizeof(long long) * tiles.size(), hipMemcpyDeviceToHost, st),
+        CK(launch_tile_ranks(g, set.tiles, (int)tiles.size(), tb.us_sorted, set.u, terms_d, terms_d + nt, st), "tile ranks");
+        CK(hipMemcpyAsync(terms.data(), terms_d, 2 * sizeof(long long) * nt, hipMemcpyDeviceToHost, st),
            "download counters");
-        CK(hipMemcpyAsync(useful.data(), useful_d, sizeof(long long) * tiles.size(), hipMemcpyDeviceToHost,
-                          st), "download counters");
     }
     CK(hipStreamSynchronize(st), "tile plan");
     set.terms_sub.assign(g.n_subsets, 0);

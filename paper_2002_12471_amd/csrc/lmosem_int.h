@@ -90,18 +90,46 @@ hipError_t build_base(const Geo &g, Tables &t, hipStream_t st, std::string &err,
 hipError_t build_paths(const Geo &g, Tables &t, bool store_paths, bool store_band, hipStream_t st,
                        std::string &err, int64_t &bytes);
 
+// ---- device memory of one call (events.hip) ----
+// Blocks that live no longer than one call on a context, carved from a buffer
+// that the context keeps: an allocation and its release cost 5 to 10 us each,
+// and a call on unprepared events makes some 25.  The buffer grows to what the
+// calls before asked for, up to kArenaBytes, and goes with its context; larger
+// blocks, and what does not fit, are allocated and released as they come.  One
+// call at a time uses it (a context's calls do not run at once), all on the
+// context's stream, which orders reuse.
+constexpr size_t kArenaBytes = size_t(128) << 20;
+
+struct Arena {
+    char *base = nullptr;
+    size_t size = 0, used = 0, asked = 0;
+    bool open = false;
+    void begin();                  // no block is live: grow if the last call wanted more
+    void end() { open = false; }
+    void release();
+    bool owns(const void *p) const { return p >= base && p < base + size; }
+};
+
+// a block from the arena (null: always its own allocation), and its return
+hipError_t dev_take(Arena *a, void **p, size_t bytes);
+void dev_give(Arena *a, void *p);
+template <class T>
+hipError_t dev_take(Arena *a, T **p, size_t bytes) { return dev_take(a, reinterpret_cast<void **>(p), bytes); }
+
 // ---- event ingest (events.hip) ----
 struct EvSet;
 hipError_t validate_events(const Geo &g, const lmosem_events &ev, int64_t *bad_host, int *bad_dev,
                            hipStream_t st);
+// (bad: events outside the angle, position or energy range; nothing is planned then)
 hipError_t sort_events(const Geo &g, const Tables &t, const lmosem_events &ev,
                        const std::vector<int64_t> &offs, int force_subset, EvSet &set,
-                       hipStream_t st, std::string &err);
+                       hipStream_t st, int64_t &bad, std::string &err);
 hipError_t plan_tiles(const Geo &g, const Tables &t, EvSet &set, int ev_tile, int chunk_rows,
                       hipStream_t st, std::string &err);
 // the steps of the ingest on buffers the caller provides (no allocation)
-hipError_t launch_event_keys(const Geo &g, int64_t n, int n_real, const int64_t *offs_dev, const int32_t *angle,
-                             const float *u_bin, int force_subset, uint64_t *keys, int *idx, hipStream_t st);
+// (offs_dev may be null for one realisation; invalid events sort behind all groups)
+hipError_t launch_event_keys(const Geo &g, int n_groups, int n_real, const int64_t *offs_dev, const lmosem_events &ev,
+                             int force_subset, uint64_t *keys, int *idx, hipStream_t st);
 hipError_t launch_gather_events(const Geo &g, int64_t n, int n_groups, const uint64_t *keys, const int *idx, const lmosem_events &ev,
                                 int *sa, float *su, float *se, float *efac, int *orig, int *counts, hipStream_t st);
 hipError_t launch_tile_ranks(const Geo &g, Tile *tiles, int n_tiles, const double *us_sorted, const float *su,
@@ -245,7 +273,7 @@ hipError_t launch_image_max(const float *img, int n, float *out, hipStream_t st)
 hipError_t launch_emission_mask(const Geo &g, const float *mu, const float *img, double thr, int margin, float *mask,
                                 hipStream_t st);
 hipError_t launch_binned_rows_all(const Geo &g, const Tables &t, int n_pos, const double *edges_dev, int n_e,
-                                  const int *angle_row0_dev, float *H, hipStream_t st);
+                                  const int *angle_row0_dev, float *H, Arena *arena, hipStream_t st);
 hipError_t launch_bin_events(const Geo &g, const lmosem_events &ev, int n_pos, const double *edges_dev, int n_e,
                              float *counts, hipStream_t st);
 hipError_t launch_gather_counts(const float *counts, const int *row_bin, int n_rows, float *y, hipStream_t st);
@@ -349,6 +377,8 @@ struct EvSet {
     std::vector<int> row_off;               // [n_subsets+1] rows of each subset
     std::vector<int> tile_off;              // [n_subsets+1]
     std::vector<int> chunk_off;             // [n_subsets+1]
+    Arena *arena = nullptr;                 // where the set's device memory comes from (null: its own allocations)
+    void *plan = nullptr;                   // holds the four below
     Tile *tiles = nullptr;                  // all tiles, subset-major
     Chunk *chunks = nullptr;                // all chunks, subset-major
     int *crange = nullptr;                  // [n_subsets][n_real+1] chunk ranges per realisation

@@ -54,7 +54,7 @@ namespace {
 // region holds the sort's keys, indices and temporary storage, and after the
 // sort the system rows and partial means of one chunk of tiles.
 struct Layout {
-    size_t f, counts, offs, ang, u, e, efac, orig, mean, inv, tiles, terms, useful;
+    size_t f, counts, ang, u, e, efac, orig, mean, inv, tiles, terms, useful;
     size_t trans, keys, keys2, idx, idx2, tmp, tmp_bytes, sort_end;
     int max_tiles;
     int64_t chunk_rows;   // rows of one chunk that fit after the transient offset
@@ -69,7 +69,6 @@ hipError_t layout(const Geo &g, int64_t n, int ev_tile, Layout &L) {
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     L.f = take(sizeof(float) * g.n_qpad);
     L.counts = take(sizeof(int) * g.n_angles);
-    L.offs = take(sizeof(int64_t) * 2);
     L.ang = take(sizeof(int) * nn);
     L.u = take(sizeof(float) * nn);
     L.e = take(sizeof(float) * nn);
@@ -121,7 +120,6 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
     char *b = static_cast<char *>(base);
     float *f = reinterpret_cast<float *>(b + L.f);
     int *counts = reinterpret_cast<int *>(b + L.counts);
-    int64_t *offs = reinterpret_cast<int64_t *>(b + L.offs);
     int *ang = reinterpret_cast<int *>(b + L.ang), *orig = reinterpret_cast<int *>(b + L.orig);
     float *u = reinterpret_cast<float *>(b + L.u), *en = reinterpret_cast<float *>(b + L.e);
     float *efac = reinterpret_cast<float *>(b + L.efac);
@@ -137,9 +135,7 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
     if (n == 0) return hipStreamSynchronize(st);
     // order the events by (angle, position), as lmosem_forward's ingest does
     // with every event in subset 0 and one realisation
-    const int64_t offs_h[2] = {0, (int64_t)n};
-    if ((e = hipMemcpyAsync(offs, offs_h, sizeof offs_h, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
-    if ((e = launch_event_keys(g, n, 1, offs, ev.angle, ev.u_bin, 0, keys, idx, st)) != hipSuccess) return e;
+    if ((e = launch_event_keys(g, g.n_angles, 1, nullptr, ev, 0, keys, idx, st)) != hipSuccess) return e;
     if ((e = sort_pairs(tmp, L.tmp_bytes, keys, keys2, idx, idx2, n, g.n_angles, st)) != hipSuccess) return e;
     if ((e = launch_gather_events(g, n, g.n_angles, keys2, idx2, ev, ang, u, en, efac, orig, counts, st)) != hipSuccess) return e;
     std::vector<int> cnt(g.n_angles);
