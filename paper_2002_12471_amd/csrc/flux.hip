@@ -1329,12 +1329,37 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
 }
 
 void free_flux(FluxTables &ft) {
-    for (void *p : {(void *)ft.sup, (void *)ft.box, (void *)ft.mu_s, (void *)ft.mu_box, (void *)ft.rank_of, (void *)ft.x_of, (void *)ft.pw,
-                    (void *)ft.pwr, (void *)ft.Lx, (void *)ft.beg, (void *)ft.rec_off, (void *)ft.rec_n, (void *)ft.rec_w, (void *)ft.sym,
-                    (void *)ft.G, (void *)ft.psi, (void *)ft.rho})
-        hipFree(p);
+    hipFree(ft.mem[0]);
+    hipFree(ft.mem[1]);
     ft = FluxTables{};
 }
+
+namespace {
+
+// arrays that share one allocation: sized with a null base, then placed
+struct Slab {
+    char *base = nullptr;
+    size_t used = 0;
+    template <class T>
+    void add(T *&p, size_t n) {
+        if (base) p = reinterpret_cast<T *>(base + used);
+        used += (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~size_t(255);
+    }
+};
+
+template <class F>
+hipError_t place(void *&mem, int64_t &held, F &&arrays) {
+    Slab s;
+    arrays(s);
+    const hipError_t e = hipMalloc(&mem, s.used);
+    if (e != hipSuccess) { mem = nullptr; return e; }
+    held += (int64_t)s.used;
+    s = Slab{static_cast<char *>(mem), 0};
+    arrays(s);
+    return hipSuccess;
+}
+
+}  // namespace
 
 hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> &order, const Tables &t, FluxTables &ft,
                       bool sens, hipStream_t st, int64_t &bytes) {
@@ -1343,23 +1368,50 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     int *cnt = nullptr, *pos = nullptr;
     int2 *off = nullptr;
     double *w64 = nullptr;
-    void *tmp = nullptr;
-    int64_t held = 0;
+    char *tmp = nullptr;
+    void *scratch[2] = {nullptr, nullptr};   // for the build only
+    int64_t held = 0, own = 0;
     auto done = [&](hipError_t err) {
-        hipFree(cnt); hipFree(off); hipFree(tmp); hipFree(pos); hipFree(w64);
+        hipFree(scratch[0]);
+        hipFree(scratch[1]);
         if (err != hipSuccess) { hipStreamSynchronize(st); free_flux(ft); }
         else bytes += held;
         return err;
     };
-    auto al = [&](auto &p, size_t n) {
-        held += (int64_t)(n * sizeof(*p));
-        return e = hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(*p));
-    };
-    const size_t na_np = (size_t)g.n_angles * g.n_p;
-    if (al(ft.sup, g.n_p) || al(ft.box, g.n_p) || al(ft.mu_s, g.n_p) || al(ft.mu_box, fg.nb) || al(ft.rank_of, na_np) || al(ft.x_of, na_np) ||
-        al(ft.pw, na_np) || al(ft.pwr, na_np) || al(ft.Lx, na_np))
+    const size_t na_np = (size_t)g.n_angles * g.n_p, an = g.scatter ? (size_t)g.n_angles * fg.N : 0;
+    // offsets of one direction interval: the lattice points of a sector of
+    // the box's diagonal, with room for the lattice lines along it
+    const double diag = sqrt((double)fg.W * fg.W + (double)fg.Hh * fg.Hh);
+    const int cap = (int)std::min(0.5 * diag * diag * 2.0 * M_PI / std::max(fg.N, 1) + 4.0 * diag + 64.0,
+                                  4.0 * (double)fg.W * fg.Hh);
+    const int nbin = fg.n_blk * fg.N;
+    size_t tmp_bytes = 0;
+    if (g.scatter && (e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, ft.beg, ft.beg, nbin + 1, st)) != hipSuccess)
         return done(e);
-    if ((e = hipMalloc(&pos, sizeof(int) * g.n_p)) != hipSuccess) return done(e);
+    e = place(ft.mem[0], held, [&](Slab &s) {
+        s.add(ft.sup, g.n_p);
+        s.add(ft.box, g.n_p);
+        s.add(ft.mu_s, g.n_p);
+        s.add(ft.mu_box, fg.nb);
+        s.add(ft.rank_of, na_np);
+        s.add(ft.x_of, na_np);
+        s.add(ft.pw, na_np);
+        s.add(ft.pwr, na_np);
+        s.add(ft.Lx, na_np);
+        s.add(ft.psi, an);
+        s.add(ft.rho, an);
+        s.add(ft.G, an * fg.K);
+        s.add(ft.beg, (size_t)nbin + 1);
+    });
+    if (e == hipSuccess)
+        e = place(scratch[0], own, [&](Slab &s) {
+            s.add(pos, g.n_p);
+            if (!g.scatter) return;
+            s.add(cnt, fg.N);
+            s.add(off, (size_t)fg.N * cap);
+            s.add(tmp, tmp_bytes);
+        });
+    if (e != hipSuccess) return done(e);
     if ((e = hipMemcpyAsync(ft.sup, order.data(), sizeof(int) * g.n_p, hipMemcpyHostToDevice, st)) != hipSuccess) return done(e);
     hipLaunchKernelGGL(k_flux_support, dim3((g.n_p + 255) / 256), dim3(256), 0, st, g, fg, ft.sup, t.p_pix, t.mu, pos,
                        ft.box, ft.mu_s, ft.mu_box);
@@ -1370,22 +1422,7 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
         if (sens) e = flux_sensitivity(g, fg, t, ft, nullptr, st);
         return done(e == hipSuccess ? hipStreamSynchronize(st) : e);
     }
-    const size_t an = (size_t)g.n_angles * fg.N;
-    if (al(ft.psi, an) || al(ft.rho, an) || al(ft.G, an * fg.K)) return done(e);
     hipLaunchKernelGGL(k_flux_angles, dim3(fg.N / 16, g.n_angles), dim3(256), 0, st, g, fg, t.cs, ft.psi, ft.rho, ft.G);
-    if ((e = hipGetLastError()) != hipSuccess) return done(e);
-    // offsets of one direction interval: the lattice points of a sector of
-    // the box's diagonal, with room for the lattice lines along it
-    const double diag = sqrt((double)fg.W * fg.W + (double)fg.Hh * fg.Hh);
-    const int cap = (int)std::min(0.5 * diag * diag * 2.0 * M_PI / fg.N + 4.0 * diag + 64.0,
-                                  4.0 * (double)fg.W * fg.Hh);
-    const int nbin = fg.n_blk * fg.N;
-    size_t tmp_bytes = 0;
-    if ((e = hipMalloc(&cnt, sizeof(int) * fg.N)) != hipSuccess) return done(e);
-    if ((e = hipMalloc(&off, sizeof(int2) * (size_t)fg.N * cap)) != hipSuccess) return done(e);
-    if (al(ft.beg, (size_t)nbin + 1)) return done(e);
-    if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, ft.beg, ft.beg, nbin + 1, st)) != hipSuccess) return done(e);
-    if ((e = hipMalloc(&tmp, tmp_bytes)) != hipSuccess) return done(e);
     hipLaunchKernelGGL(k_flux_offsets, dim3(fg.N), dim3(256), 0, st, fg.W, fg.Hh, fg.N, cap, cnt, off);
     const dim3 grid(fg.N, fg.n_blk);
     const int *q_of_pix = t.p_pix + g.n_p;
@@ -1397,8 +1434,14 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     int total = 0;
     if ((e = hipMemcpyAsync(&total, ft.beg + nbin, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return done(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return done(e);
-    if (al(ft.rec_off, total) || al(ft.rec_n, total) || al(ft.rec_w, (size_t)total * kTap) || al(ft.sym, (size_t)total * 64)) return done(e);
-    if ((e = hipMalloc(&w64, std::max<size_t>(total, 1) * kTap * sizeof(double))) != hipSuccess) return done(e);
+    e = place(ft.mem[1], held, [&](Slab &s) {
+        s.add(ft.rec_off, total);
+        s.add(ft.rec_n, total);
+        s.add(ft.rec_w, (size_t)total * kTap);
+        s.add(ft.sym, (size_t)total * 64);
+    });
+    if (e == hipSuccess) e = place(scratch[1], own, [&](Slab &s) { s.add(w64, (size_t)total * kTap); });
+    if (e != hipSuccess) return done(e);
     hipLaunchKernelGGL(k_flux_pairs<1>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
                        cap, ft.beg, ft.rec_off, ft.rec_n, ft.rec_w, w64, ft.sym);
     if ((e = hipGetLastError()) == hipSuccess && sens) e = flux_sensitivity(g, fg, t, ft, w64, st);

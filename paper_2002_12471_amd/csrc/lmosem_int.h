@@ -197,6 +197,7 @@ struct FluxTables {
     float *sym = nullptr;      // [records][64] symmetric pair factors
     float *G = nullptr;        // [n_angles][N][K]
     float *psi = nullptr, *rho = nullptr;   // [n_angles][N]
+    void *mem[2] = {nullptr, nullptr};      // the allocations that hold them
 };
 
 struct FluxEvent {
