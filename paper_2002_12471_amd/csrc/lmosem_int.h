@@ -342,8 +342,6 @@ hipError_t net_gradient(Net *n, const float *X, const float *dy, int count, floa
 hipError_t net_forward_train(Net *n, const float *X, int count, float *y);
 hipError_t net_train(Net *n, const float *X, const float *t, int64_t count, int batch, int epochs, float lr,
                      float lr_decay, double *loss_host);
-hipError_t gemm_nt(const uint16_t *A, int lda, const uint16_t *Bt, int ldb, float *C, int ldc, int M, int N,
-                   int K, bool accumulate, hipStream_t st, float *split_ws = nullptr);
 hipError_t surrogate_samples(const Geo &g, const Tables &t, const int32_t *pixel, const int32_t *angle,
                              const float *u_bin, const float *energy, int64_t n, float *X, float *target,
                              float *scatter, hipStream_t st);

@@ -2,13 +2,16 @@
 // (tanh form), bf16 weights and activations, FP32 accumulation (MFMA), FP32
 // master weights and Adam.
 //
-// Every matrix product is one kernel, C[m][n] = sum_k A[m][k] Bt[n][k], with
-// both operands row-major bf16 and contiguous in k, which is the operand
-// layout of v_mfma_f32_16x16x16_bf16 (lane l holds A[l%16][4(l/16)..+3] and
+// Every matrix product is C[m][n] = sum_k A[m][k] Bt[n][k], with both operands
+// row-major bf16 and contiguous in k, which is the operand layout of
+// v_mfma_f32_16x16x16_bf16 (lane l holds A[l%16][4(l/16)..+3] and
 // B[4(l/16)..+3][l%16]; D[4(l/16)+v][l%16] comes back in register v):
 //   forward       Z[b][out]  = H[b][in]   . Wt[out][in]
 //   data grad     dH[b][in]  = D[b][out]  . W[in][out]
 //   weight grad   dW[in][out] = Ht[in][b] . Dt[out][b]
+// A training step is three kernels: forward and data gradients of 16 samples
+// per workgroup (k_train), the weight and bias gradients in slices of the
+// batch (k_weight_grads), and the sum of the slices (k_sum_grads).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -43,92 +46,6 @@ __device__ inline float gelu_grad(float x) {
     return 0.5f * (1.0f + t) + 0.5f * x * (1.0f - t * t) * kGeluC * (1.0f + 3.0f * kGeluA * x * x);
 }
 
-// C[M][N] (+)= A[M][K] . Bt[N][K]^T; M, N, K multiples of 16, lda/ldb multiples of 4.
-// 64x64 block per workgroup, 32x32 per wave (2x2 MFMA tiles).  With split K,
-// blockIdx.z takes k in [z k_slice, (z+1) k_slice) and writes its partial
-// product to C + z c_stride.
-__global__ __launch_bounds__(256) void k_gemm_nt(const uint16_t *__restrict__ A, int lda,
-                                                 const uint16_t *__restrict__ Bt, int ldb,
-                                                 float *__restrict__ C, int ldc, int M, int N, int K,
-                                                 int accumulate, int k_slice, size_t c_stride) {
-    const int kz0 = blockIdx.z * k_slice, kz1 = min(K, kz0 + k_slice);
-    C += blockIdx.z * c_stride;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int m_base = blockIdx.y * 64 + (wave >> 1) * 32;
-    const int n_base = blockIdx.x * 64 + (wave & 1) * 32;
-    const int r = lane & 15, kq = (lane >> 4) * 4;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16x4 zero = {0, 0, 0, 0};
-    for (int k0 = kz0; k0 < kz1; k0 += 16) {
-        bf16x4 a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int m = m_base + 16 * i + r;
-            a[i] = m < M ? *reinterpret_cast<const bf16x4 *>(A + (size_t)m * lda + k0 + kq) : zero;
-            const int n = n_base + 16 * i + r;
-            b[i] = n < N ? *reinterpret_cast<const bf16x4 *>(Bt + (size_t)n * ldb + k0 + kq) : zero;
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int m = m_base + 16 * i + (lane >> 4) * 4 + v;
-                const int n = n_base + 16 * j + r;
-                if (m < M && n < N) {
-                    float *c = C + (size_t)m * ldc + n;
-                    *c = accumulate ? *c + acc[i][j][v] : acc[i][j][v];
-                }
-            }
-}
-
-// C[m][n] = sum over the S partial products (fixed order)
-__global__ void k_sum_slices(const float *__restrict__ part, int S, int M, int N, float *__restrict__ C, int ldc) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= M * N) return;
-    float s = 0.0f;
-    for (int z = 0; z < S; ++z) s += part[(size_t)z * M * N + idx];
-    C[(size_t)(idx / N) * ldc + idx % N] = s;
-}
-
-constexpr int kSplitMax = 32;   // partial products per split-K product (workspace slices)
-
-// Products with few output blocks and a long K (the weight gradients, K = the
-// batch) are split over K into up to kSplitMax slices of at least 256 in
-// split_ws ([kSplitMax][M][N]) and summed in a fixed order.
-hipError_t gemm_nt(const uint16_t *A, int lda, const uint16_t *Bt, int ldb, float *C, int ldc, int M, int N,
-                   int K, bool accumulate, hipStream_t st, float *split_ws) {
-    if (M % 16 || N % 16 || K % 16 || lda % 4 || ldb % 4) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-    const int blocks_mn = (int)(grid.x * grid.y);
-    int S = 1;
-    if (split_ws && !accumulate && M * N <= 128 * 128 && K >= 512)
-        S = std::min(kSplitMax, std::max(1, std::min(K / 256, 256 / blocks_mn)));
-    if (S <= 1) {
-        hipLaunchKernelGGL(k_gemm_nt, grid, dim3(256), 0, st, A, lda, Bt, ldb, C, ldc, M, N, K, accumulate ? 1 : 0,
-                           K, (size_t)0);
-        return hipGetLastError();
-    }
-    const int k_slice = ((K + S - 1) / S + 15) / 16 * 16;
-    S = (K + k_slice - 1) / k_slice;
-    grid.z = (unsigned)S;
-    hipLaunchKernelGGL(k_gemm_nt, grid, dim3(256), 0, st, A, lda, Bt, ldb, split_ws, N, M, N, K, 0, k_slice,
-                       (size_t)M * N);
-    hipLaunchKernelGGL(k_sum_slices, dim3((M * N + 255) / 256), dim3(256), 0, st, split_ws, S, M, N, C, ldc);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------- network state
 // Parameter order (flat FP32 master copy): W1[8][128] b1[128] W2[128][128] b2
 // W3[128][128] b3 W4[128][1] b4[1]; W[in][out].
@@ -160,119 +77,206 @@ __global__ void k_pack(const float *__restrict__ p, NetBf16 nb) {
     if (idx < kHid) nb.w4[idx] = f2bf(p[kOffW4 + idx]);
 }
 
-// X [n][8] f32 -> bf16 [n][16] (zero padded) and its transpose [16][n]
-__global__ void k_input(const float *__restrict__ X, int n, uint16_t *__restrict__ xb, uint16_t *__restrict__ xt) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
+// what the weight gradients read, transposed bf16 [unit][n], and the batch's
+// output gradients
+struct Transposed {
+    uint16_t *xt;                 // [16][n], inputs zero-padded
+    uint16_t *h1t, *h2t, *h3t;    // [128][n]
+    uint16_t *d1t, *d2t, *d3t;    // [128][n]
+    float *dy;                    // [n]
+};
+
+enum class Step { outputs, gradient, train };   // y alone; from given dy; from targets
+
+// One step of 16 samples, one workgroup: wave w holds hidden units 16 w .. 16 w
+// + 15 of every layer, a lane one unit and four samples (4 q + v).  Activations
+// and deltas pass through LDS to be the next product's A operand, the weights
+// come from the L2 as they are (32 KB a matrix; the next matrix is on its way
+// while the current layer's GELU is evaluated), pre-activations never leave the
+// registers (their GELU slopes do the rest), and what the weight gradients need
+// is written transposed, 8 bytes a lane.  A chain of six layers on one workgroup
+// per compute unit bounds it: 18 us for 4096 samples (20 with four waves of 32
+// units), where 12 kernels that passed 30 MB through memory took 83 us.
+constexpr int kRows = 16;
+constexpr int kTrainThreads = 64 * kHid / 16;
+
+template <Step STEP>
+__global__ __launch_bounds__(kTrainThreads) void k_train(const float *__restrict__ X, const float *__restrict__ p,
+                                                         NetBf16 nb, int n, const float *__restrict__ dy_in,
+                                                         const float *__restrict__ target, float inv_total,
+                                                         float *__restrict__ y, Transposed tr,
+                                                         double *__restrict__ loss_part) {
+    typedef uint16_t Rows[kHid + 8];
+    __shared__ __align__(16) Rows act[2][kRows];
+    __shared__ float dy_s[kRows];
+    __shared__ double loss_s[kRows];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4, b0 = blockIdx.x * kRows;
+    const int unit = 16 * wave + r;
+    constexpr int kSteps = kHid / 16;
+    bf16x4 w[kSteps];
+    auto weights = [&](const uint16_t *Bt) {
 #pragma unroll
-    for (int i = 0; i < kInPad; ++i) {
-        const uint16_t v = i < kIn ? f2bf(X[(size_t)b * kIn + i]) : 0;
-        xb[(size_t)b * kInPad + i] = v;
-        if (xt) xt[(size_t)i * n + b] = v;
+        for (int k = 0; k < kSteps; ++k) w[k] = *reinterpret_cast<const bf16x4 *>(Bt + unit * kHid + 16 * k + 4 * q);
+    };
+    f32x4 acc;
+    auto product = [&](const Rows *A) {
+        acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kSteps; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4 *>(&A[r][16 * k + 4 * q]), w[k], acc,
+                                                            0, 0, 0);
+    };
+    // the lane's unit, samples 4 q + v: to LDS, and transposed to memory
+    auto put = [&](Rows *A, uint16_t *out, const uint16_t (&v)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) A[4 * q + i][unit] = v[i];
+        if (STEP != Step::outputs) {
+            const bf16x4 x = {(short)v[0], (short)v[1], (short)v[2], (short)v[3]};
+            *reinterpret_cast<bf16x4 *>(out + (size_t)unit * n + b0 + 4 * q) = x;
+        }
+        __syncthreads();
+    };
+    // inputs, zero-padded to 16
+    if (threadIdx.x < kRows * kInPad) {
+        const int b = threadIdx.x >> 4, i = threadIdx.x & 15;
+        act[0][b][i] = i < kIn ? f2bf(X[(size_t)(b0 + b) * kIn + i]) : 0;
+        // (transposed: a row per 16 threads)
+        if (STEP != Step::outputs) tr.xt[(size_t)b * n + b0 + i] = b < kIn ? f2bf(X[(size_t)(b0 + i) * kIn + b]) : 0;
     }
-}
-
-// The elementwise training kernels work on tiles of 16 samples x 128 hidden
-// units (256 threads): the row-major [b][k] values are read and written
-// along k, and the transposed bf16 copy [k][b] goes through LDS so that it
-// is written along b (32 contiguous bytes per hidden unit).
-constexpr int kTileB = 16;
-
-template <typename F>
-__device__ __forceinline__ void tile_rows_and_transpose(int n, uint16_t *__restrict__ d, uint16_t *__restrict__ dt,
-                                                        F value) {
-    __shared__ uint16_t tile[kTileB][kHid + 2];
-    const int b0 = blockIdx.x * kTileB;
-    for (int i = threadIdx.x; i < kTileB * kHid; i += 256) {
-        const int bl = i / kHid, k = i % kHid, b = b0 + bl;
-        if (b < n) {
-            const uint16_t v = value((size_t)b * kHid + k, b, k);
-            d[(size_t)b * kHid + k] = v;
-            tile[bl][k] = v;
+    const bf16x4 w1 = *reinterpret_cast<const bf16x4 *>(nb.w1t + unit * kInPad + 4 * q);
+    weights(nb.w2t);
+    __syncthreads();
+    float slope[3][4];
+    auto layer = [&](int l, const float *bias, Rows *A, uint16_t *out) {
+        const float bj = bias[unit];
+        uint16_t h[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float z = acc[v] + bj;
+            h[v] = f2bf(gelu(z));
+            slope[l][v] = gelu_grad(z);
+        }
+        put(A, out, h);
+    };
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const bf16x4 *>(&act[0][r][4 * q]), w1,
+                                                    f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    layer(0, p + kOffB1, act[1], tr.h1t);
+    product(act[1]);
+    weights(nb.w3t);
+    layer(1, p + kOffB2, act[0], tr.h2t);
+    product(act[0]);
+    weights(nb.w3);
+    layer(2, p + kOffB3, act[1], tr.h3t);
+    if (STEP == Step::gradient) {
+        if (threadIdx.x < kRows) dy_s[threadIdx.x] = dy_in[b0 + threadIdx.x];
+    } else if (threadIdx.x < kRows) {
+        const int b = threadIdx.x;
+        float s = 0.0f;
+        for (int k = 0; k < kHid; ++k) s = fmaf(bf2f(act[1][b][k]), bf2f(nb.w4[k]), s);
+        s += p[kOffB4];
+        if (STEP == Step::outputs) {
+            y[b0 + b] = s;
+        } else {   // mean squared error
+            const float e = s - target[b0 + b];
+            dy_s[b] = 2.0f * e * inv_total;
+            loss_s[b] = (double)e * e;
         }
     }
-    if (!dt) return;
+    if (STEP == Step::outputs) return;
     __syncthreads();
-    for (int i = threadIdx.x; i < kTileB * kHid; i += 256) {
-        const int k = i / kTileB, bl = i % kTileB, b = b0 + bl;
-        if (b < n) dt[(size_t)k * n + b] = tile[bl][k];
+    if (threadIdx.x < kRows) tr.dy[b0 + threadIdx.x] = dy_s[threadIdx.x];
+    if (STEP == Step::train && threadIdx.x == 0) {
+        double l = 0.0;
+        for (int b = 0; b < kRows; ++b) l += loss_s[b];
+        loss_part[blockIdx.x] = l;
     }
+    // deltas d[b][k] = dh[b][k] gelu'(z[b][k]), the last layer's dh from the output row
+    uint16_t d[4];
+    const float w4 = bf2f(nb.w4[unit]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) d[v] = f2bf(dy_s[4 * q + v] * w4 * slope[2][v]);
+    put(act[0], tr.d3t, d);
+    auto delta = [&](int l, Rows *A, uint16_t *out) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) d[v] = f2bf(acc[v] * slope[l][v]);
+        put(A, out, d);
+    };
+    product(act[0]);
+    weights(nb.w2);
+    delta(1, act[1], tr.d2t);
+    product(act[1]);
+    delta(0, act[0], tr.d1t);
 }
 
-// h = gelu(z + bias): z kept (with bias) for the backward pass; h in bf16,
-// optionally also transposed
-__global__ __launch_bounds__(256) void k_bias_gelu(float *__restrict__ z, const float *__restrict__ bias, int n,
-                                                   uint16_t *__restrict__ h, uint16_t *__restrict__ ht) {
-    tile_rows_and_transpose(n, h, ht, [&](size_t idx, int, int k) {
-        const float v = z[idx] + bias[k];
-        z[idx] = v;
-        return f2bf(gelu(v));
-    });
+// Weight gradients dW[in][out] = sum_b Ht[in][b] Dt[out][b] and the bias
+// gradients, in one launch: the products have few output blocks and a long K
+// (the batch), so they are split over K into slices whose partial products
+// k_sum_grads adds in a fixed order; the bias sums fill the rest of the chip
+// meanwhile.  A 64x64 block per workgroup, 32x32 per wave (2x2 MFMA tiles).
+constexpr int kSplitMax = 32;   // slices of one product
+constexpr int kPartial = 2 * kHid * kHid + kInPad * kHid;   // one slice of all three products: W3, W2, W1 (padded)
+
+// slices of a batch of n: at least 256 samples each
+static int grad_slices(int n, int &slice) {
+    const int s = std::max(1, std::min(kSplitMax, n / 256));
+    slice = ((n + s - 1) / s + 15) / 16 * 16;
+    return (n + slice - 1) / slice;
 }
 
-// y[b] = sum_k h[b][k] w4[k] + b4  (one wave per sample group of 64)
-__global__ void k_output(const uint16_t *__restrict__ h, const uint16_t *__restrict__ w4,
-                         const float *__restrict__ p, int n, float *__restrict__ y) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    float s = 0.0f;
-    const uint16_t *hb = h + (size_t)b * kHid;
-    for (int k = 0; k < kHid; ++k) s = fmaf(bf2f(hb[k]), bf2f(w4[k]), s);
-    y[b] = s + p[kOffB4];
-}
-
-// loss partial sums and dy = 2 (y - t) / n_total
-__global__ void k_mse(const float *__restrict__ y, const float *__restrict__ t, int n, float inv_total,
-                      float *__restrict__ dy, double *__restrict__ loss_part) {
-    __shared__ double red[256];
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    double l = 0.0;
-    if (b < n) {
-        const float r = y[b] - t[b];
-        dy[b] = 2.0f * r * inv_total;
-        l = (double)r * r;
-    }
-    red[threadIdx.x] = l;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0];
-}
-
-// output layer backward: d3[b][k] = dy[b] w4[k] gelu'(z3[b][k]) (bf16, both layouts)
-__global__ __launch_bounds__(256) void k_out_back(const float *__restrict__ dy, const uint16_t *__restrict__ w4,
-                                                  const float *__restrict__ z3, int n, uint16_t *__restrict__ d,
-                                                  uint16_t *__restrict__ dt) {
-    tile_rows_and_transpose(n, d, dt, [&](size_t idx, int b, int k) {
-        return f2bf(dy[b] * bf2f(w4[k]) * gelu_grad(z3[idx]));
-    });
-}
-
-// hidden layer backward: d[b][k] = dh[b][k] gelu'(z[b][k]) (bf16, both layouts)
-__global__ __launch_bounds__(256) void k_gelu_back(const float *__restrict__ dh, const float *__restrict__ z, int n,
-                                                   uint16_t *__restrict__ d, uint16_t *__restrict__ dt) {
-    tile_rows_and_transpose(n, d, dt, [&](size_t idx, int, int) { return f2bf(dh[idx] * gelu_grad(z[idx])); });
-}
-
-// bias gradients: column sums of the transposed bf16 deltas dt[k][b]; the
-// output layer's from dy and h3t
-__global__ void k_bias_grads(const uint16_t *__restrict__ d1t, const uint16_t *__restrict__ d2t,
-                             const uint16_t *__restrict__ d3t, const uint16_t *__restrict__ h3t,
-                             const float *__restrict__ dy, int n, float *__restrict__ g) {
+__global__ __launch_bounds__(256) void k_weight_grads(Transposed tr, int n, int slices, int slice,
+                                                      float *__restrict__ part, float *__restrict__ g) {
     __shared__ float red[256];
-    const int row = blockIdx.x;   // 0..127 b1, 128..255 b2, 256..383 b3, 384..511 w4, 512 b4
+    const int blocks = 10 * slices;   // W3: 4 blocks of 64 x 64, W2: 4, W1 (16 rows): 2
+    if ((int)blockIdx.x < blocks) {
+        const int z = blockIdx.x / 10, job = blockIdx.x - 10 * z;
+        const uint16_t *A = job < 4 ? tr.h2t : job < 8 ? tr.h1t : tr.xt;
+        const uint16_t *Bt = job < 4 ? tr.d3t : job < 8 ? tr.d2t : tr.d1t;
+        float *C = part + (size_t)z * kPartial + (job < 4 ? 0 : job < 8 ? kHid * kHid : 2 * kHid * kHid);
+        const int M = job < 8 ? kHid : kInPad;
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, kq = (lane >> 4) * 4;
+        const int m_base = (job < 8 ? (job & 3) >> 1 : 0) * 64 + (wave >> 1) * 32, n_base = (job & 1) * 64 + (wave & 1) * 32;
+        if (m_base >= M) return;
+        f32x4 acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const uint16_t *a0 = A + (size_t)(m_base + r) * n + kq, *a1 = m_base + 16 < M ? a0 + (size_t)16 * n : a0;
+        const uint16_t *c0 = Bt + (size_t)(n_base + r) * n + kq, *c1 = c0 + (size_t)16 * n;
+        const int k1 = min(n, (z + 1) * slice);
+#pragma unroll 8
+        for (int k = z * slice; k < k1; k += 16) {
+            const bf16x4 a[2] = {*reinterpret_cast<const bf16x4 *>(a0 + k), *reinterpret_cast<const bf16x4 *>(a1 + k)};
+            const bf16x4 b[2] = {*reinterpret_cast<const bf16x4 *>(c0 + k), *reinterpret_cast<const bf16x4 *>(c1 + k)};
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int m = m_base + 16 * i + kq + v;
+                    if (m < M) C[(size_t)m * kHid + n_base + 16 * j + r] = acc[i][j][v];
+                }
+        return;
+    }
+    // row sums: the transposed deltas (b1, b2, b3), h3t dy (w4), dy (b4)
+    const int row = blockIdx.x - blocks, k = row % kHid, layer = row / kHid;
+    const uint16_t *d = (layer == 0 ? tr.d1t : layer == 1 ? tr.d2t : layer == 2 ? tr.d3t : tr.h3t) + (size_t)k * n;
     float s = 0.0f;
-    if (row < 3 * kHid) {
-        const uint16_t *dt = row < kHid ? d1t : (row < 2 * kHid ? d2t : d3t);
-        const int k = row % kHid;
-        for (int b = threadIdx.x; b < n; b += 256) s += bf2f(dt[(size_t)k * n + b]);
-    } else if (row < 4 * kHid) {
-        const int k = row - 3 * kHid;
-        for (int b = threadIdx.x; b < n; b += 256) s += bf2f(h3t[(size_t)k * n + b]) * dy[b];
+    if (layer < 3) {
+#pragma unroll 8
+        for (int b = threadIdx.x; b < n; b += 256) s += bf2f(d[b]);
+    } else if (layer == 3) {
+#pragma unroll 8
+        for (int b = threadIdx.x; b < n; b += 256) s += bf2f(d[b]) * tr.dy[b];
     } else {
-        for (int b = threadIdx.x; b < n; b += 256) s += dy[b];
+        for (int b = threadIdx.x; b < n; b += 256) s += tr.dy[b];
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -280,21 +284,19 @@ __global__ void k_bias_grads(const uint16_t *__restrict__ d1t, const uint16_t *_
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        int off;
-        if (row < kHid) off = kOffB1 + row;
-        else if (row < 2 * kHid) off = kOffB2 + row - kHid;
-        else if (row < 3 * kHid) off = kOffB3 + row - 2 * kHid;
-        else if (row < 4 * kHid) off = kOffW4 + row - 3 * kHid;
-        else off = kOffB4;
-        g[off] = red[0];
-    }
+    if (threadIdx.x == 0)
+        g[layer == 0 ? kOffB1 + k : layer == 1 ? kOffB2 + k : layer == 2 ? kOffB3 + k : layer == 3 ? kOffW4 + k : kOffB4] = red[0];
 }
 
-// dW1[i][o] from the padded 16-row product: keep the 8 real input rows
-__global__ void k_copy_w1_grad(const float *__restrict__ gw1pad, float *__restrict__ g) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < kIn * kHid) g[kOffW1 + idx] = gw1pad[idx];
+// the weight gradients: the slices added in order (of W1, the 8 real input rows)
+__global__ __launch_bounds__(256) void k_sum_grads(const float *__restrict__ part, int slices, float *__restrict__ g) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int kW = kHid * kHid;
+    if (i >= 2 * kW + kIn * kHid) return;
+    float s = 0.0f;
+#pragma unroll 8
+    for (int z = 0; z < slices; ++z) s += part[(size_t)z * kPartial + i];
+    g[i < kW ? kOffW3 + i : i < 2 * kW ? kOffW2 + i - kW : kOffW1 + i - 2 * kW] = s;
 }
 
 __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
@@ -353,10 +355,11 @@ struct XSource {
 
 // per-epoch loss: fixed-order sum of the minibatch's partial sums
 __global__ void k_loss_add(const double *__restrict__ parts, int nparts, double *__restrict__ loss) {
-    if (threadIdx.x != 0) return;
     double s = 0.0;
-    for (int i = 0; i < nparts; ++i) s += parts[i];
-    *loss += s;
+    for (int i = threadIdx.x; i < nparts; i += 64) s += parts[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) *loss += s;
 }
 
 // ---------------------------------------------------------------- host side
@@ -369,23 +372,17 @@ struct Net {
     int step = 0;
     // batch workspace
     int cap = 0;
-    uint16_t *xb = nullptr, *xt = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr;
-    uint16_t *h1t = nullptr, *h2t = nullptr, *h3t = nullptr;
-    uint16_t *d1 = nullptr, *d2 = nullptr, *d3 = nullptr, *d1t = nullptr, *d2t = nullptr, *d3t = nullptr;
-    float *z1 = nullptr, *z2 = nullptr, *z3 = nullptr, *dh = nullptr, *dy = nullptr, *gw1 = nullptr;
-    float *split = nullptr;   // split-K partial products [kSplitMax][128][128]
+    Transposed tr{};
+    float *part = nullptr;    // partial weight gradients [kSplitMax][kPartial]
     double *loss_part = nullptr;
 };
 
 static void free_ws(Net &n) {
-    for (void *q : {(void *)n.xb, (void *)n.xt, (void *)n.h1, (void *)n.h2, (void *)n.h3, (void *)n.h1t,
-                    (void *)n.h2t, (void *)n.h3t, (void *)n.d1, (void *)n.d2, (void *)n.d3, (void *)n.d1t,
-                    (void *)n.d2t, (void *)n.d3t, (void *)n.z1, (void *)n.z2, (void *)n.z3, (void *)n.dh,
-                    (void *)n.dy, (void *)n.gw1, (void *)n.split, (void *)n.loss_part})
+    for (void *q : {(void *)n.tr.xt, (void *)n.tr.h1t, (void *)n.tr.h2t, (void *)n.tr.h3t, (void *)n.tr.d1t,
+                    (void *)n.tr.d2t, (void *)n.tr.d3t, (void *)n.tr.dy, (void *)n.part, (void *)n.loss_part})
         hipFree(q);
-    n.xb = n.xt = n.h1 = n.h2 = n.h3 = n.h1t = n.h2t = n.h3t = nullptr;
-    n.d1 = n.d2 = n.d3 = n.d1t = n.d2t = n.d3t = nullptr;
-    n.z1 = n.z2 = n.z3 = n.dh = n.dy = n.gw1 = n.split = nullptr;
+    n.tr = Transposed{};
+    n.part = nullptr;
     n.loss_part = nullptr;
     n.cap = 0;
 }
@@ -396,14 +393,11 @@ static hipError_t ensure_ws(Net &n, int cap) {
     hipError_t e;
     const size_t c = (size_t)cap;
 #define A(ptr, bytes) if ((e = hipMalloc(&(ptr), (bytes))) != hipSuccess) { free_ws(n); return e; }
-    A(n.xb, c * kInPad * 2) A(n.xt, c * kInPad * 2)
-    A(n.h1, c * kHid * 2) A(n.h2, c * kHid * 2) A(n.h3, c * kHid * 2)
-    A(n.h1t, c * kHid * 2) A(n.h2t, c * kHid * 2) A(n.h3t, c * kHid * 2)
-    A(n.d1, c * kHid * 2) A(n.d2, c * kHid * 2) A(n.d3, c * kHid * 2)
-    A(n.d1t, c * kHid * 2) A(n.d2t, c * kHid * 2) A(n.d3t, c * kHid * 2)
-    A(n.z1, c * kHid * 4) A(n.z2, c * kHid * 4) A(n.z3, c * kHid * 4) A(n.dh, c * kHid * 4)
-    A(n.dy, c * 4) A(n.gw1, kInPad * kHid * 4) A(n.loss_part, (c / 256 + 2) * 8)
-    A(n.split, (size_t)kSplitMax * kHid * kHid * 4)
+    A(n.tr.xt, c * kInPad * 2)
+    A(n.tr.h1t, c * kHid * 2) A(n.tr.h2t, c * kHid * 2) A(n.tr.h3t, c * kHid * 2)
+    A(n.tr.d1t, c * kHid * 2) A(n.tr.d2t, c * kHid * 2) A(n.tr.d3t, c * kHid * 2)
+    A(n.tr.dy, c * 4) A(n.loss_part, (c / kRows) * 8)
+    A(n.part, (size_t)kSplitMax * kPartial * 4)
 #undef A
     n.cap = cap;
     return hipSuccess;
@@ -455,44 +449,13 @@ hipError_t net_get_params(Net *n, float *host) {
 }
 
 static inline unsigned blocks(size_t n) { return (unsigned)((n + 255) / 256); }
-static inline unsigned tiles(int nb) { return (unsigned)((nb + kTileB - 1) / kTileB); }
-
-// forward pass of one batch of nb samples (nb a multiple of 16); keeps the
-// activations for the backward pass when train is set
-static hipError_t forward_batch(Net &n, const float *X, int nb, float *y, bool train) {
-    hipError_t e;
-    hipStream_t st = n.st;
-    hipLaunchKernelGGL(k_input, dim3(blocks(nb)), dim3(256), 0, st, X, nb, n.xb, train ? n.xt : nullptr);
-    if ((e = gemm_nt(n.xb, kInPad, n.nb.w1t, kInPad, n.z1, kHid, nb, kHid, kInPad, false, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bias_gelu, dim3(tiles(nb)), dim3(256), 0, st, n.z1, n.p + kOffB1, nb, n.h1,
-                       train ? n.h1t : nullptr);
-    if ((e = gemm_nt(n.h1, kHid, n.nb.w2t, kHid, n.z2, kHid, nb, kHid, kHid, false, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bias_gelu, dim3(tiles(nb)), dim3(256), 0, st, n.z2, n.p + kOffB2, nb, n.h2,
-                       train ? n.h2t : nullptr);
-    if ((e = gemm_nt(n.h2, kHid, n.nb.w3t, kHid, n.z3, kHid, nb, kHid, kHid, false, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bias_gelu, dim3(tiles(nb)), dim3(256), 0, st, n.z3, n.p + kOffB3, nb, n.h3,
-                       train ? n.h3t : nullptr);
-    hipLaunchKernelGGL(k_output, dim3(blocks(nb)), dim3(256), 0, st, n.h3, n.nb.w4, n.p, nb, y);
-    return hipGetLastError();
-}
-
-// gradients of sum_b dy[b] y[b] into n.g (after forward_batch with train)
-static hipError_t backward_batch(Net &n, const float *dy, int nb) {
-    hipError_t e;
-    hipStream_t st = n.st;
-    hipLaunchKernelGGL(k_out_back, dim3(tiles(nb)), dim3(256), 0, st, dy, n.nb.w4, n.z3, nb, n.d3, n.d3t);
-    // dW3[in][out] = h2t . d3t ; dh2 = d3 . W3
-    if ((e = gemm_nt(n.h2t, nb, n.d3t, nb, n.g + kOffW3, kHid, kHid, kHid, nb, false, st, n.split)) != hipSuccess)
-        return e;
-    if ((e = gemm_nt(n.d3, kHid, n.nb.w3, kHid, n.dh, kHid, nb, kHid, kHid, false, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gelu_back, dim3(tiles(nb)), dim3(256), 0, st, n.dh, n.z2, nb, n.d2, n.d2t);
-    if ((e = gemm_nt(n.h1t, nb, n.d2t, nb, n.g + kOffW2, kHid, kHid, kHid, nb, false, st, n.split)) != hipSuccess)
-        return e;
-    if ((e = gemm_nt(n.d2, kHid, n.nb.w2, kHid, n.dh, kHid, nb, kHid, kHid, false, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gelu_back, dim3(tiles(nb)), dim3(256), 0, st, n.dh, n.z1, nb, n.d1, n.d1t);
-    if ((e = gemm_nt(n.xt, nb, n.d1t, nb, n.gw1, kHid, kInPad, kHid, nb, false, st, n.split)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_copy_w1_grad, dim3(blocks(kIn * kHid)), dim3(256), 0, st, n.gw1, n.g);
-    hipLaunchKernelGGL(k_bias_grads, dim3(4 * kHid + 1), dim3(256), 0, st, n.d1t, n.d2t, n.d3t, n.h3t, dy, nb, n.g);
+// gradients into n.g, after k_train
+static hipError_t weight_grads(Net &n, int nb) {
+    int slice = 0;
+    const int slices = grad_slices(nb, slice);
+    hipLaunchKernelGGL(k_weight_grads, dim3(10 * slices + 4 * kHid + 1), dim3(256), 0, n.st, n.tr, nb, slices, slice, n.part,
+                       n.g);
+    hipLaunchKernelGGL(k_sum_grads, dim3(blocks(2 * kHid * kHid + kIn * kHid)), dim3(256), 0, n.st, n.part, slices, n.g);
     return hipGetLastError();
 }
 
@@ -512,15 +475,20 @@ hipError_t net_forward(Net *n, const float *X, int64_t count, float *y, hipStrea
 
 hipError_t net_forward_train(Net *n, const float *X, int count, float *y) {
     if (count <= 0 || count % 16) return hipErrorInvalidValue;
-    hipError_t e = ensure_ws(*n, count);
-    return e == hipSuccess ? forward_batch(*n, X, count, y, false) : e;
+    hipLaunchKernelGGL(k_train<Step::outputs>, dim3(count / kRows), dim3(kTrainThreads), 0, n->st, X, n->p, n->nb, count, nullptr,
+                       nullptr, 0.0f, y, Transposed{}, nullptr);
+    return hipGetLastError();
 }
 
 hipError_t net_gradient(Net *n, const float *X, const float *dy, int count, float *grad_host) {
     if (count <= 0 || count % 16) return hipErrorInvalidValue;
     hipError_t e = ensure_ws(*n, count);
-    if (e == hipSuccess) e = forward_batch(*n, X, count, n->dy, true);
-    if (e == hipSuccess) e = backward_batch(*n, dy, count);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_train<Step::gradient>, dim3(count / kRows), dim3(kTrainThreads), 0, n->st, X, n->p, n->nb, count, dy,
+                           nullptr, 0.0f, nullptr, n->tr, nullptr);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = weight_grads(*n, count);
     if (e == hipSuccess) e = hipMemcpyAsync(grad_host, n->g, kNParams * 4, hipMemcpyDeviceToHost, n->st);
     if (e == hipSuccess) e = hipStreamSynchronize(n->st);
     return e;
@@ -533,23 +501,19 @@ hipError_t net_train(Net *n, const float *X, const float *t, int64_t count, int 
                      float lr_decay, double *loss_host) {
     if (batch <= 0 || batch % 16 || count < batch || epochs < 0) return hipErrorInvalidValue;
     hipError_t e = ensure_ws(*n, batch);
-    float *y = nullptr;
     double *loss = nullptr;
-    if (e == hipSuccess) e = hipMalloc(&y, (size_t)batch * 4);
     if (e == hipSuccess) e = hipMalloc(&loss, sizeof(double) * std::max(epochs, 1));
     if (e == hipSuccess) e = hipMemsetAsync(loss, 0, sizeof(double) * std::max(epochs, 1), n->st);
     const int64_t n_batches = count / batch;
-    const int nparts = (batch + 255) / 256;
+    const int nparts = batch / kRows;
     for (int ep = 0; ep < epochs && e == hipSuccess; ++ep) {
         for (int64_t bi = 0; bi < n_batches && e == hipSuccess; ++bi) {
             const float *xb = X + bi * batch * kIn;
             const float *tb = t + bi * batch;
-            e = forward_batch(*n, xb, batch, y, true);
-            if (e != hipSuccess) break;
-            hipLaunchKernelGGL(k_mse, dim3(nparts), dim3(256), 0, n->st, y, tb, batch, 1.0f / batch, n->dy,
-                               n->loss_part);
+            hipLaunchKernelGGL(k_train<Step::train>, dim3(batch / kRows), dim3(kTrainThreads), 0, n->st, xb, n->p, n->nb, batch,
+                               nullptr, tb, 1.0f / batch, nullptr, n->tr, n->loss_part);
             hipLaunchKernelGGL(k_loss_add, dim3(1), dim3(64), 0, n->st, n->loss_part, nparts, loss + ep);
-            if ((e = backward_batch(*n, n->dy, batch)) != hipSuccess) break;
+            if ((e = weight_grads(*n, batch)) != hipSuccess) break;
             ++n->step;
             const float c1 = 1.0f - powf(0.9f, (float)n->step), c2 = 1.0f - powf(0.999f, (float)n->step);
             hipLaunchKernelGGL(k_adam, dim3(blocks(kNParams)), dim3(256), 0, n->st, n->p, n->g, n->m, n->v, kNParams,
@@ -569,7 +533,6 @@ hipError_t net_train(Net *n, const float *X, const float *t, int64_t count, int 
     if (e == hipSuccess) e = hipStreamSynchronize(n->st);
     if (e == hipSuccess && loss_host)
         for (int ep = 0; ep < epochs; ++ep) loss_host[ep] = tot[ep] / ((double)n_batches * batch);
-    hipFree(y);
     hipFree(loss);
     return e;
 }
