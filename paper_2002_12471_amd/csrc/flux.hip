@@ -38,6 +38,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "lmosem_int.h"
@@ -431,10 +432,10 @@ __device__ __forceinline__ float response(double d, float inv2s2, float edge) {
 // eight, and three additions end the sum.  16 events share each read of the
 // spectra, and the energy order keeps a wave's nodes to two or three tiles.
 //
-// SPLIT waves share the ends of 16 events: one where events reach few ends (a
-// wave's work is then mostly its start and end), two where they reach more (a
-// single small set would otherwise be a long chain on few waves).  The waves of
-// a workgroup that work on the same ends read the same spectra.
+// SPLIT waves share the ends of 16 events (kSplitEnds); the waves of a workgroup
+// that work on the same ends read the same spectra.  It is bound by its vector
+// instructions: 200k events of 12 to 20 ends in 15 us, where a branch per tile
+// in the inner loop cost as much again.
 constexpr int kMaxTiles = kFluxMaxK / 16;
 constexpr int kEvRow = 28;   // floats of an event's row in LDS: head 8, zeros 4, weights 8, zeros 4
 
@@ -448,7 +449,7 @@ __device__ __forceinline__ int dpp(int x, const int ctrl) {
     }
 }
 
-template <int TILES, int SPLIT>
+template <int SPLIT>
 __global__ __launch_bounds__(256 * SPLIT) void k_flux_means(Geo g, FluxGeo fg, const FluxEvent *__restrict__ ev,
                                                     const FluxBlock *__restrict__ blk,
                                                     const double *__restrict__ us_sorted,
@@ -504,12 +505,13 @@ __global__ __launch_bounds__(256 * SPLIT) void k_flux_means(Geo g, FluxGeo fg, c
     const float *Sr = S + (size_t)ls * g.n_p * fg.K, *Pr = SP + (size_t)ls * g.n_p;
     const unsigned K = fg.K, last = (unsigned)(r1 - 1) * K + c;
     float total = 0.0f, prim = 0.0f;   // of this lane's event and nodes
-    // up to TILES tiles at a time
-    for (int tb = t0; tb <= t1; tb += TILES) {
-        const int nt = min(TILES, t1 + 1 - tb);
-        f32x4 acc[TILES];
+    // NT tiles from tb on (a compile-time count: no branch between a rank's loads
+    // and products)
+    auto tiles = [&](auto count, int tb) {
+        constexpr int NT = decltype(count)::value;
+        f32x4 acc[NT];
 #pragma unroll
-        for (int t = 0; t < TILES; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         const float *Sc = Sr + 16 * tb;
         // path ends go to LDS 64 at a time, those past the wave's out of
         // reach; 16 ranks' spectra are read before the first is used
@@ -517,7 +519,7 @@ __global__ __launch_bounds__(256 * SPLIT) void k_flux_means(Geo g, FluxGeo fg, c
         for (int kc = r0; kc < r1; kc += 64) {
             const int kl = min(kc + lane, r1 - 1);
             const double ul = kc + lane < r1 ? us[kl] : 1e30;
-            const float pl = Pr[kl];
+            const float pl = tb == t0 ? Pr[kl] : 0.0f;   // (the primary paths once)
             __builtin_amdgcn_wave_barrier();
             us_s[wave][lane] = ul;
             pr_s[wave][lane] = pl;
@@ -527,34 +529,37 @@ __global__ __launch_bounds__(256 * SPLIT) void k_flux_means(Geo g, FluxGeo fg, c
             unsigned at = (unsigned)(kc + q) * K + c;
 #pragma unroll 1
             for (int k0 = 0; k0 < n; k0 += 16) {
-                float sv[4][TILES];
+                float sv[4][NT];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const unsigned o = min(at, last);
                     at += 4 * K;
 #pragma unroll
-                    for (int t = 0; t < TILES; ++t)
-                        if (t < nt) sv[j][t] = Sc[o + 16 * t];
+                    for (int t = 0; t < NT; ++t) sv[j][t] = Sc[o + 16 * t];
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int k = k0 + 4 * j + q;
                     const float kv = response(u - us_s[wave][k], inv2s2, edge);
-                    if (tb == t0) prim = fmaf(kv, pr_s[wave][k], prim);
+                    prim = fmaf(kv, pr_s[wave][k], prim);
 #pragma unroll
-                    for (int t = 0; t < TILES; ++t)
-                        if (t < nt) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sv[j][t], kv, acc[t], 0, 0, 0);
+                    for (int t = 0; t < NT; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sv[j][t], kv, acc[t], 0, 0, 0);
                 }
             }
         }
 #pragma unroll
-        for (int t = 0; t < TILES; ++t)
-            if (t < nt) {
-                const int d = 16 * (tb + t) + 4 * q - et;   // of the lane's first node in the event's eight
-                const float *w = &ev_s[wave][c][12 + min(max(d, -4), kTap)];
+        for (int t = 0; t < NT; ++t) {
+            const int d = 16 * (tb + t) + 4 * q - et;   // of the lane's first node in the event's eight
+            const float *w = &ev_s[wave][c][12 + min(max(d, -4), kTap)];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) total = fmaf(w[v], acc[t][v], total);
-            }
+            for (int v = 0; v < 4; ++v) total = fmaf(w[v], acc[t][v], total);
+        }
+    };
+    for (int tb = t0; tb <= t1; tb += 3) {
+        if (t1 - tb >= 2) tiles(std::integral_constant<int, 3>(), tb);
+        else if (t1 - tb == 1) tiles(std::integral_constant<int, 2>(), tb);
+        else tiles(std::integral_constant<int, 1>(), tb);
     }
     float s = fmaf(prim, e.g0, total);
     s += __shfl_xor(s, 16, 64);
@@ -1504,12 +1509,11 @@ struct Carve {
     }
 };
 
-// Ends of an event for which two waves share them (a function of the geometry
-// alone: a realisation's sums are the same in any batch).  Below, a wave's work
-// is mostly its start and end; above, a wave has long enough a run of its own,
-// and halves cost more (94 -> 113 us at 128x128 with 125k events, some 280 ends
-// each; 31 -> 23 us at 64x64 with 25k events, some 70).
-constexpr double kSplitEnds = 32.0, kWholeEnds = 160.0;
+// Ends of an event from which two waves share them (a function of the geometry
+// alone: a realisation's sums are the same in any batch).  With fewer, a wave's
+// work is mostly its start and end; with more, halves take 15 -> 13 us at 64x64
+// (25k events, few waves) and nothing at 128x128 (125k events, 49 and 50 us).
+constexpr double kSplitEnds = 32.0;
 constexpr int kSplit = 2;
 
 // means of blocks [b0, b1), whose records begin at row row0
@@ -1519,8 +1523,8 @@ void launch_means(const FluxRun &p, int slot_base, int s0, int b0, int b1, int r
     // ends that an event reaches, about
     const double ends = g.n_p * 6.0 * g.sig_u / std::max(std::max(fg.W, fg.Hh) * g.dx, 6.0 * g.sig_u);
     if (fg.N) {
-        const int split = ends >= kSplitEnds && ends < kWholeEnds ? kSplit : 1;
-        hipLaunchKernelGGL((split > 1 ? k_flux_means<3, kSplit> : k_flux_means<3, 1>), dim3(b1 - b0), dim3(256 * split), 0, p.st, g,
+        const int split = ends >= kSplitEnds ? kSplit : 1;
+        hipLaunchKernelGGL((split > 1 ? k_flux_means<kSplit> : k_flux_means<1>), dim3(b1 - b0), dim3(256 * split), 0, p.st, g,
                            fg, p.ev, p.blk + b0, p.t->us_sorted, p.alist, p.n_list, slot_base, s0, row0, p.row_base, w.S,
                            w.SP, p.mean, p.inv, p.skipped);
         return;
