@@ -650,9 +650,10 @@ __device__ __forceinline__ int wave_search(const FluxBlock *blk, int lo, int hi,
 // walk the event blocks that reach any of its ends, every fourth block each,
 // four events per product (A: responses of 16 ends to four events; B: the
 // events' interpolation weights spread over a 16-node tile).  The events'
-// energy order within a block keeps four events' nodes to one or two tiles;
-// the others are skipped.  Every sum has one owner and a fixed order.  Rows
-// are written in flux order.
+// energy order within a block makes those that touch a tile neighbours: per
+// tile, one loop without branches over their groups of four.  (A tile test per
+// group instead cost five scalar instructions and an LDS wait a product.)
+// Every sum has one owner and a fixed order.  Rows are written in flux order.
 template <int TILES>
 __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTables ft, const FluxEvent *__restrict__ ev,
                                                       const FluxBlock *__restrict__ blk,
@@ -662,9 +663,11 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
                                                       const float *__restrict__ wgt, float *__restrict__ R,
                                                       float *__restrict__ R0) {
     constexpr int NT = TILES > 0 ? TILES : 1;
+    constexpr int kRow = kTap + 3;   // a zero, the weights, a zero (odd: rows start at different banks)
     union Shared {
         struct {
-            float w[4][64][kTap];   // weight times interpolation weights
+            float w[4][TILES > 0 ? 64 : 1][kRow];   // weight times interpolation weights
+            float kv[4][TILES > 0 ? 16 : 1][64];    // responses, [group of four events][lane]
             double u[4][64];
             float p[4][64];         // weight times the primary's energy response
             int et[4][64];
@@ -673,7 +676,7 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
     };
     __shared__ __align__(16) Shared sh;
     __shared__ float red0[4][16];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
     const int item = xcd_logical(blockIdx.x, gridDim.x), n_k = (g.n_p + 15) / 16;   // (runs of slots: their events)
     const int ls = item / n_k, slot = slot0 + ls;
     const int r = slot / n_list, a = alist[slot - r * n_list];
@@ -689,46 +692,44 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float r0 = 0.0f;
+    if (TILES > 0) sh.in.w[wave][lane][0] = sh.in.w[wave][lane][kTap + 1] = 0.0f;
     for (int b = b0 + wave; b < b1; b += 4) {
         const FluxBlock bk = blk[b];
-        {
-            const FluxEvent e = ev[bk.row + min(lane, bk.n - 1)];
-            const float y = lane < bk.n ? wgt[e.row - row_base] * fg.inv_zk : 0.0f;
-            __builtin_amdgcn_wave_barrier();
-            sh.in.u[wave][lane] = e.u;
-            sh.in.p[wave][lane] = y * e.g0;
-            if (TILES > 0) {
+        const FluxEvent e = ev[bk.row + min(lane, bk.n - 1)];
+        const float y = lane < bk.n ? wgt[e.row - row_base] * fg.inv_zk : 0.0f;
+        __builtin_amdgcn_wave_barrier();
+        sh.in.u[wave][lane] = e.u;
+        sh.in.p[wave][lane] = y * e.g0;
+        if (TILES > 0) {
 #pragma unroll
-                for (int i = 0; i < kTap; ++i) sh.in.w[wave][lane][i] = y * e.w[i];
-                sh.in.et[wave][lane] = e.et;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
-            __builtin_amdgcn_wave_barrier();
+            for (int i = 0; i < kTap; ++i) sh.in.w[wave][lane][1 + i] = y * e.w[i];
+            sh.in.et[wave][lane] = e.et;
         }
-#pragma unroll 1
-        for (int i0 = 0; i0 < bk.n; i0 += 16) {
-            float kv[4];
-            int et[4];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+        __builtin_amdgcn_wave_barrier();
+        const int groups = (bk.n + 3) / 4;
+#pragma unroll 4
+        for (int k = 0; k < groups; ++k) {
+            const int i = 4 * k + q;
+            const float kv = response(sh.in.u[wave][i] - my_u, inv2s2, edge);
+            r0 = fmaf(kv, sh.in.p[wave][i], r0);
+            if (TILES > 0) sh.in.kv[wave][k][lane] = kv;
+        }
+        if (TILES > 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = i0 + 4 * j + q;
-                kv[j] = response(sh.in.u[wave][i] - my_u, inv2s2, edge);
-                r0 = fmaf(kv[j], sh.in.p[wave][i], r0);
-                if (TILES > 0) et[j] = sh.in.et[wave][i];
-            }
-            if (TILES > 0) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    // energies ascend: the four events' first and last tiles
-                    const int t0 = __builtin_amdgcn_readlane(et[j], 0) >> 4;
-                    const int t1 = (__builtin_amdgcn_readlane(et[j], 63) + kTap - 1) >> 4;
-#pragma unroll
-                    for (int t = 0; t < TILES; ++t)
-                        if (t >= t0 && t <= t1) {
-                            const int d = 16 * t + c - et[j];
-                            const float w = (unsigned)d < kTap ? sh.in.w[wave][i0 + 4 * j + q][d & 7] : 0.0f;
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j], w, acc[t], 0, 0, 0);
-                        }
+            for (int t = 0; t < TILES; ++t) {
+                // the events that touch the tile: neighbours (energies ascend)
+                const unsigned long long m = __ballot(lane < bk.n && e.et < 16 * (t + 1) && e.et + kTap > 16 * t);
+                if (m == 0) continue;
+                const int g1 = (63 - __clzll(m)) / 4;
+#pragma unroll 4
+                for (int k = (__ffsll(m) - 1) / 4; k <= g1; ++k) {
+                    const int i = 4 * k + q;
+                    const int d = 16 * t + c - sh.in.et[wave][i];
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sh.in.kv[wave][k][lane],
+                                                                  sh.in.w[wave][i][min(max(d, -1), kTap) + 1], acc[t], 0, 0, 0);
                 }
             }
         }
