@@ -1037,7 +1037,9 @@ lmosem_status lmosem_backproject(lmosem_ctx *c, const lmosem_events *ev, const f
     const EvSet &v = s->s;
     const int rows = v.row_off[1];
     hipError_t e = launch_fill(s->f, (size_t)g.n_qpad, 0.0f, c->st);
-    if (e == hipSuccess) e = launch_gather_rows(weights_dev, v.orig, rows, s->inv, c->st);
+    if (e == hipSuccess)
+        e = s->flux ? flux_weights(v.fev, v.orig, rows, weights_dev, s->inv, c->st)
+                    : launch_gather_rows(weights_dev, v.orig, rows, s->inv, c->st);
     if (s->flux) {
         if (e == hipSuccess) e = flux_subset(c, s, 0, true, false, true, nullptr, false, c->st);
     } else {

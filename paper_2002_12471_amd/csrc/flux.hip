@@ -577,7 +577,7 @@ __global__ __launch_bounds__(256 * SPLIT) void k_flux_means(Geo g, FluxGeo fg, c
         const int j = e.row - row_base;
         mean[j] = s;
         dead = !(s > 1e-30f);
-        inv[j] = dead ? 0.0f : 1.0f / s;
+        inv[bk.row + i0 + c - row_base] = dead ? 0.0f : 1.0f / s;   // (in record order, as the adjoint reads it)
     }
     const unsigned long long m = __ballot(dead);
     if (lane == 0 && m) atomicAdd(skipped, (unsigned long long)__popcll(m));
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(256) void k_flux_means_primary(Geo g, FluxGeo fg, F
             const int j = e.row - row_base;
             mean[j] = s;
             dead = !(s > 1e-30f);
-            inv[j] = dead ? 0.0f : 1.0f / s;
+            inv[i - row_base] = dead ? 0.0f : 1.0f / s;   // (in record order)
         }
     }
     const unsigned long long m = __ballot(dead);
@@ -693,10 +693,23 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float r0 = 0.0f;
     if (TILES > 0) sh.in.w[wave][lane][0] = sh.in.w[wave][lane][kTap + 1] = 0.0f;
+    // the next block's records and weights are on their way while the current
+    // one is used, and the one's after it known
+    FluxBlock bk = blk[min(b0 + wave, max(b1 - 1, 0))], next = bk;
+    FluxEvent e;
+    float y = 0.0f;
+    auto load = [&](const FluxBlock &k) {
+        const int at = k.row + min(lane, k.n - 1);
+        e = ev[at];
+        y = wgt[at - row_base];
+    };
+    if (b0 + wave < b1) {
+        load(bk);
+        next = blk[min(b0 + wave + 4, b1 - 1)];
+    }
     for (int b = b0 + wave; b < b1; b += 4) {
-        const FluxBlock bk = blk[b];
-        const FluxEvent e = ev[bk.row + min(lane, bk.n - 1)];
-        const float y = lane < bk.n ? wgt[e.row - row_base] * fg.inv_zk : 0.0f;
+        y = lane < bk.n ? y * fg.inv_zk : 0.0f;
+        const int et = e.et, n = bk.n;
         __builtin_amdgcn_wave_barrier();
         sh.in.u[wave][lane] = e.u;
         sh.in.p[wave][lane] = y * e.g0;
@@ -707,7 +720,12 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
         __builtin_amdgcn_wave_barrier();
-        const int groups = (bk.n + 3) / 4;
+        bk = next;
+        if (b + 4 < b1) {
+            load(bk);
+            next = blk[min(b + 8, b1 - 1)];
+        }
+        const int groups = (n + 3) / 4;
 #pragma unroll 4
         for (int k = 0; k < groups; ++k) {
             const int i = 4 * k + q;
@@ -721,7 +739,7 @@ __global__ __launch_bounds__(256) void k_flux_adjoint(Geo g, FluxGeo fg, FluxTab
 #pragma unroll
             for (int t = 0; t < TILES; ++t) {
                 // the events that touch the tile: neighbours (energies ascend)
-                const unsigned long long m = __ballot(lane < bk.n && e.et < 16 * (t + 1) && e.et + kTap > 16 * t);
+                const unsigned long long m = __ballot(lane < n && et < 16 * (t + 1) && et + kTap > 16 * t);
                 if (m == 0) continue;
                 const int g1 = (63 - __clzll(m)) / 4;
 #pragma unroll 4
@@ -1453,6 +1471,19 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     if ((e = hipGetLastError()) == hipSuccess && sens) e = flux_sensitivity(g, fg, t, ft, w64, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     return done(e);
+}
+
+// weights in the caller's event order -> record order (rows [0, n) of one list)
+__global__ void k_flux_weights(const FluxEvent *__restrict__ ev, const int *__restrict__ orig, int n,
+                               const float *__restrict__ src, float *__restrict__ dst) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = src[orig[ev[i].row]];
+}
+
+hipError_t flux_weights(const FluxEvent *ev, const int *orig, int n, const float *src, float *dst, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_flux_weights, dim3((n + 255) / 256), dim3(256), 0, st, ev, orig, n, src, dst);
+    return hipGetLastError();
 }
 
 static size_t up64(size_t n) { return (n + 63) & ~size_t(63); }

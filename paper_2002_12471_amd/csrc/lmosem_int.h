@@ -239,7 +239,7 @@ struct FluxRun {
     std::function<hipError_t(int, int)> fill;
     int ev_cap = 0;
     int blk_rows(int b) const;
-    bool means;                // form the event means (else inv holds the backprojection's weights)
+    bool means;                // form the event means (else inv holds the backprojection's weights); inv is in record order
     bool box;                  // the estimate is new to the workspace
     float *f;                  // [n_real][n_qpad]
     float *mean, *inv;
@@ -262,6 +262,7 @@ void free_flux(FluxTables &ft);
 int flux_angles(const Geo &g, const FluxGeo &fg, int n_list);
 size_t flux_ws_floats(const Geo &g, const FluxGeo &fg, int n_real, int n_slots);
 int flux_group(const Geo &g, const FluxGeo &fg, size_t floats, int n_real, int n_list);
+hipError_t flux_weights(const FluxEvent *ev, const int *orig, int n, const float *src, float *dst, hipStream_t st);
 hipError_t flux_events(const Geo &g, const FluxModel &fg, int b0, int b1, int row0, const int *slot_row,
                        const int *blk_beg, int n_slots, const int *base, const int *ang, const float *su,
                        const float *se, const Tables &t, FluxEvent *ev, FluxBlock *blk, hipStream_t st);
