@@ -896,21 +896,26 @@ __global__ __launch_bounds__(64 * kFieldWaves) void k_flux_fields(Geo g, FluxGeo
 // (n + 1) / 4 on: three float4 loads and twelve weights (zeros around the
 // eight).  Eight separate rows asked the vector cache for as many cycles but
 // for three times the lines, which then had to come from the L2 again for the
-// next offset.  The same lines serve neighbours in the pair order, so the
-// waves walk it together, four pairs each in turn (a run of its own for each
-// wave would be more than the vector cache holds), and each XCD takes a run of
-// sectors, so that its L2 holds the few directions they read.
+// next offset.  The same lines serve neighbours in the pair order, so sixteen
+// waves walk it together, two pairs each in turn: what they read at a time
+// should fit the vector cache, and the misses still bound it.  135 us for 688k
+// pair rows of 64 at 128x128, 19 us for 55k at 64x64 (eight waves of four: 162
+// and 24, of two: 158 and 25; sixteen of four: 146 and 22, of one: 147 and 23; a
+// run of its own for each wave: 176 and 27).  Each XCD takes a run of sectors,
+// so that its L2 holds the few directions they read.
 constexpr int kGroupTap = 12;
+constexpr int kGatherWaves = 16;
+constexpr int kGatherBatch = 2;   // pairs that a wave loads together
 
-__global__ __launch_bounds__(64 * kPairWaves) void k_flux_gather(Geo g, FluxGeo fg, FluxTables ft,
+__global__ __launch_bounds__(64 * kGatherWaves) void k_flux_gather(Geo g, FluxGeo fg, FluxTables ft,
                                                                  const int *__restrict__ beg_all,
                                                                  const int *__restrict__ rec_off,
                                                                  const int *__restrict__ rec_n,
                                                                  const float *__restrict__ rec_w,
                                                                  const float *__restrict__ sym,
                                                                  const float *__restrict__ T, float *__restrict__ pb) {
-    __shared__ float sum[kPairWaves][64];
-    __shared__ __align__(16) float w_s[kPairWaves][kChunk][kGroupTap];
+    __shared__ float sum[kGatherWaves][64];
+    __shared__ __align__(16) float w_s[kGatherWaves][kChunk][kGroupTap];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int item = xcd_logical(blockIdx.x, gridDim.x);
     const int sec = item / fg.n_blk, b = item - sec * fg.n_blk, r = blockIdx.y;
@@ -921,9 +926,10 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_flux_gather(Geo g, FluxGeo 
     float acc = 0.0f;
     const int start = beg_all[b * fg.N + sec * kSec], end = beg_all[b * fg.N + (sec + 1) * kSec];
     const f32x4 *__restrict__ Tr = reinterpret_cast<const f32x4 *>(T) + (size_t)r * field_groups(fg) * nb;
-    // four neighbours at a time go round the waves
-    for (int c0 = start + 4 * wave; c0 < end; c0 += kPairWaves * kChunk) {
-        const int mine = min(c0 + 4 * kPairWaves * ((lane & (kChunk - 1)) >> 2) + (lane & 3), end - 1);
+    // kGatherBatch neighbours at a time go round the waves
+    constexpr int kB = kGatherBatch;
+    for (int c0 = start + kB * wave; c0 < end; c0 += kGatherWaves * kChunk) {
+        const int l = lane & (kChunk - 1), mine = min(c0 + kB * kGatherWaves * (l / kB) + l % kB, end - 1);
         const int off = rec_off[mine], m1 = rec_n[mine] + 1;
         const f32x4 *src = reinterpret_cast<const f32x4 *>(rec_w + (size_t)mine * kTap);
         const f32x4 lo = src[0], hi = src[1];
@@ -943,13 +949,13 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_flux_gather(Geo g, FluxGeo 
         __builtin_amdgcn_wave_barrier();
         const float *__restrict__ sy = sym + (size_t)c0 * 64 + lane;
 #pragma unroll 1
-        for (int u0 = 0; u0 < kChunk; u0 += 4) {
-            const int at0 = kPairWaves * u0, left = end - c0 - at0;   // (records of this four and after)
+        for (int u0 = 0; u0 < kChunk; u0 += kB) {
+            const int at0 = kGatherWaves * u0, left = end - c0 - at0;   // (records of this batch and after)
             if (left <= 0) break;
-            float y[4];
-            f32x4 t[4][3];
+            float y[kB];
+            f32x4 t[kB][3];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kB; ++u) {
                 const int m = __builtin_amdgcn_readlane(m1, u0 + u);
                 y[u] = u < left ? sy[(size_t)(at0 + u) * 64] : 0.0f;
                 const unsigned at = min((unsigned)(lin + __builtin_amdgcn_readlane(off, u0 + u)), top);
@@ -959,7 +965,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_flux_gather(Geo g, FluxGeo 
                 t[u][2] = (T0 + (m & 3 ? 2 * nb : nb))[at];   // (all eight in two groups: no third)
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kB; ++u) {
                 const float *wu = w_s[wave][u0 + u];
                 float v = 0.0f;
 #pragma unroll
@@ -974,7 +980,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_flux_gather(Geo g, FluxGeo 
         const int p = ft.sup[x];
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kPairWaves; ++w) v += sum[w][lane];
+        for (int w = 0; w < kGatherWaves; ++w) v += sum[w][lane];
         if (p < g.n_q) pb[((size_t)r * (fg.N / kSec + 1) + 1 + sec) * g.n_qpad + p] = v;
     }
 }
@@ -1653,7 +1659,7 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
         if (!adjoint) continue;
         if (sc) {
             e = stage(1, [&] {
-                hipLaunchKernelGGL(k_flux_gather, dim3(fg.n_blk * (fg.N / kSec), nr), dim3(64 * kPairWaves), 0, p.st, g, fg, ft, ft.beg,
+                hipLaunchKernelGGL(k_flux_gather, dim3(fg.n_blk * (fg.N / kSec), nr), dim3(64 * kGatherWaves), 0, p.st, g, fg, ft, ft.beg,
                                    ft.rec_off, ft.rec_n, ft.rec_w, ft.sym, w.T, w.pb);
                 return hipGetLastError();
             });
