@@ -59,11 +59,10 @@ struct SurrTables {
     float inv_nx, inv_nq;        // 1 / nx and 1 / n_q, rounded to FP32 on the host
 };
 
-// Column features of the detector line {r : r . t_a = u}: its extent inside
-// the body along n_a, by boundary-to-boundary traversal from its entry into
-// the grid, and its response-weighted attenuation over the reachable ranks.
-// out = (d_in, d_out, ck, hit).
-__device__ float4 column(const Geo &g, const SurrTables &st, int a, double u, int2 *reach_ranks = nullptr) {
+// Column features (d_in, d_out, ck, hit) of the detector line {r : r . t_a = u}.
+// d_in, d_out, hit: its extent inside the body along n_a, by
+// boundary-to-boundary traversal from its entry into the grid.
+__device__ float3 line_extent(const Geo &g, const SurrTables &st, int a, double u) {
     const double nx = st.cs[2 * a], ny = st.cs[2 * a + 1];
     const double tx = -ny, ty = nx;
     double d_in = 0.0, d_out = 0.0;
@@ -96,19 +95,39 @@ __device__ float4 column(const Geo &g, const SurrTables &st, int a, double u, in
         double tmx = sx ? ((i + (sx > 0 ? 1 : 0) - 0.5 * g.nx) * g.dx - px) / nx : inf;
         double tmy = sy ? ((j + (sy > 0 ? 1 : 0) - 0.5 * g.ny) * g.dx - py) / ny : inf;
         const double tdx = sx ? g.dx / fabs(nx) : inf, tdy = sy ? g.dx / fabs(ny) : inf;
-        for (int guard = 0; guard < 4 * (g.nx + g.ny) + 8; ++guard) {
-            const double tn = fmin(fmin(tmx, tmy), t1);
-            if (tn > t && st.mu[j * g.nx + i] > 0.0f) {
-                if (!hit) d_in = t;
-                d_out = tn;
-                hit = true;
+        // eight crossings at a time: where they lie does not depend on the
+        // map, so its values come eight at once instead of one after another
+        constexpr int kStep = 8;
+        bool on = true;
+        for (int guard = 4 * (g.nx + g.ny) + 8; on && guard > 0; guard -= kStep) {
+            double from[kStep], to[kStep];
+            float m[kStep];
+#pragma unroll
+            for (int k = 0; k < kStep; ++k) {
+                const double tn = fmin(fmin(tmx, tmy), t1);
+                from[k] = t;
+                to[k] = tn;
+                m[k] = on && k < guard && tn > t ? st.mu[j * g.nx + i] : 0.0f;
+                if (!on) continue;
+                t = tn;
+                if (t >= t1) { on = false; continue; }
+                if (tmx <= tmy) { i += sx; tmx += tdx; } else { j += sy; tmy += tdy; }
+                on = i >= 0 && i < g.nx && j >= 0 && j < g.ny;
             }
-            t = tn;
-            if (t >= t1) break;
-            if (tmx <= tmy) { i += sx; tmx += tdx; } else { j += sy; tmy += tdy; }
-            if (i < 0 || i >= g.nx || j < 0 || j >= g.ny) break;
+#pragma unroll
+            for (int k = 0; k < kStep; ++k)
+                if (m[k] > 0.0f) {
+                    if (!hit) d_in = from[k];
+                    d_out = to[k];
+                    hit = true;
+                }
         }
     }
+    return make_float3((float)d_in, (float)d_out, hit ? 1.0f : 0.0f);
+}
+
+// ck: the response-weighted attenuation over the reachable ranks [x, y)
+__device__ float reached(const Geo &g, const SurrTables &st, int a, double u, int2 &ranks) {
     const double *us = st.us_sorted + (size_t)a * g.n_p;
     const float *mus = st.mu_sorted + (size_t)a * g.n_p;
     const double reach = 3.0 * g.sig_u;
@@ -118,9 +137,17 @@ __device__ float4 column(const Geo &g, const SurrTables &st, int a, double u, in
     while (lo2 < hi2) { const int m = (lo2 + hi2) >> 1; if (us[m] >= u + reach) hi2 = m; else lo2 = m + 1; }
     const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
     float ck = 0.0f;
+#pragma unroll 8
     for (int r = lo; r < lo2; ++r) ck = fmaf(mus[r], k_resp_f((float)(u - us[r]), inv2s2), ck);
-    if (reach_ranks) *reach_ranks = make_int2(lo, lo2);
-    return make_float4((float)d_in, (float)d_out, ck * (float)g.dx, hit ? 1.0f : 0.0f);
+    ranks = make_int2(lo, lo2);
+    return ck * (float)g.dx;
+}
+
+__device__ float4 column(const Geo &g, const SurrTables &st, int a, double u) {
+    int2 ranks;
+    const float ck = reached(g, st, a, u, ranks);
+    const float3 x = line_extent(g, st, a, u);
+    return make_float4(x.x, x.y, ck, x.z);
 }
 
 // k / d for 0 <= k <= 2^24 (exact in float; pixel indices of grids up to
@@ -199,15 +226,23 @@ __global__ void k_surr_samples(Geo g, SurrTables st, const int *__restrict__ q_o
 }
 
 // per event: column features of its detector line and the rank range
-// [r0, r1) of path ends its position response reaches
-__global__ void k_event_column(Geo g, SurrTables st, const int *__restrict__ ev_angle, const float *__restrict__ su,
+// [r0, r1) of path ends its position response reaches; 64 events per workgroup,
+// the two chains of dependent loads on a wave each (49 -> 31 us for 6250 events)
+__global__ __launch_bounds__(128) void k_event_column(Geo g, SurrTables st, const int *__restrict__ ev_angle, const float *__restrict__ su,
                                int n, float4 *__restrict__ col, int2 *__restrict__ rr) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    const double u = ((double)su[j] - 0.5 * g.n_bins) * g.bin_cm;
-    int2 r;
-    col[j] = column(g, st, ev_angle[j], u, &r);
-    rr[j] = r;
+    __shared__ float ck[64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, j = blockIdx.x * 64 + lane, jc = min(j, n - 1);
+    const double u = ((double)su[jc] - 0.5 * g.n_bins) * g.bin_cm;
+    float3 x = make_float3(0.0f, 0.0f, 0.0f);
+    if (wave) {
+        int2 r;
+        ck[lane] = reached(g, st, ev_angle[jc], u, r);
+        if (j < n) rr[j] = r;
+    } else {
+        x = line_extent(g, st, ev_angle[jc], u);
+    }
+    __syncthreads();
+    if (wave == 0 && j < n) col[j] = make_float4(x.x, x.y, ck[lane], x.z);
 }
 
 // Inference, step 1: for rows [j0, j0 + rows) of the sub-iteration and every
@@ -269,71 +304,121 @@ struct PairSource {
 
 // Inference, step 3: the near field, exact.  The emission pixels within the
 // event's own position response (|u - u_q| < 3 sig_u) are exactly the
-// emission pixels among the path ends it reaches (its rank range), so one
-// block per event row walks that range: the event's position response at
-// every reached path end is staged in LDS first (one exp and an FP64 offset
-// per path end instead of per term), then each group of 16 lanes takes one
-// such pixel q, its lanes share the scatter terms of the reached ends (all
-// inside q's band, stored contiguously per q, so the group's loads are
-// contiguous), and the group's first lane adds the primary term and writes
-// H over the network's value.  Ranges longer than the staging buffer fall
-// back to evaluating the response per term.
-constexpr int kNearStage = 2048;
+// emission pixels among the path ends it reaches (its rank range).  One block
+// takes up to kNearEv consecutive rows of one angle (neighbours in position:
+// their ranges nearly coincide) and walks the union of their ranges: the
+// events' position responses at every path end of it are staged in LDS first
+// (one exp and an FP64 offset per path end instead of per term, 0 outside an
+// event's own range), then each group of 16 lanes takes one such pixel q, its
+// lanes share the scatter terms of the ends (all inside q's band, stored
+// contiguously per q, so the group's loads are contiguous, and read once for
+// all the events), and the group's first lane adds the primary terms and
+// writes H over the network's values.  Unions longer than the staging buffer
+// fall back to single rows, and a single row's longer range to evaluating the
+// response per term.  82 -> 59 us for 6250 rows of 64x64 pixels, by the band
+// entries that are no longer read per event; the exponentials bound the rest.
+constexpr int kNearEv = 4;
+constexpr int kNearStage = 2048;   // path ends staged: all of one event, a fourth of it of each of four
+
+template <int EV>
+__device__ __forceinline__ void near_rows(const Geo &g, const SurrTables &st, const float2 *__restrict__ band, int band_w,
+                                          const int *__restrict__ band_lo, int a, const float *__restrict__ su,
+                                          const float *__restrict__ se, const float *__restrict__ efac,
+                                          const int2 *__restrict__ rr, int row_base, int jr, float *Kr,
+                                          float *__restrict__ H) {
+    constexpr int kStage = kNearStage / EV;
+    double u[EV];
+    float et[EV];
+    int2 r[EV], all;
+#pragma unroll
+    for (int e = 0; e < EV; ++e) {
+        u[e] = ((double)su[row_base + jr + e] - 0.5 * g.n_bins) * g.bin_cm;
+        et[e] = se[row_base + jr + e];
+        r[e] = rr[jr + e];
+        all = e == 0 ? r[0] : make_int2(min(all.x, r[e].x), max(all.y, r[e].y));
+    }
+    const double *us = st.us_sorted + (size_t)a * g.n_p;
+    const int *ss = st.s_sorted + (size_t)a * g.n_p;
+    const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
+    const bool staged = EV > 1 || all.y - all.x <= kStage;
+    __syncthreads();   // (the buffer's last readers, where a block takes row after row)
+    if (staged)
+        for (int i = threadIdx.x; i < all.y - all.x; i += blockDim.x) {
+            const double ui = us[all.x + i];
+#pragma unroll
+            for (int e = 0; e < EV; ++e)
+                Kr[e * kStage + i] = all.x + i >= r[e].x && all.x + i < r[e].y ? k_resp_f((float)(u[e] - ui), inv2s2) : 0.0f;
+        }
+    __syncthreads();
+    const int grp = threadIdx.x >> 4, l = threadIdx.x & 15;
+    // every group runs the same number of passes, so the 16-lane sums below
+    // always see all of their lanes
+    for (int rank0 = all.x; rank0 < all.y; rank0 += 16) {
+        const int rank = rank0 + grp;
+        const int q = rank < all.y ? ss[rank] : g.n_q;
+        float h[EV];
+#pragma unroll
+        for (int e = 0; e < EV; ++e) h[e] = 0.0f;
+        if (q < g.n_q) {
+            const int lo = band_lo[(size_t)a * g.n_p + q];
+            const float2 *bq = band + ((size_t)a * g.n_qpad + q) * band_w;
+            const int b0 = max(all.x - lo, 0), b1 = min(all.y - lo, band_w);
+            if (staged) {
+                const float *kq = Kr + (lo - all.x);
+#pragma unroll 4
+                for (int b = b0 + l; b < b1; b += 16) {
+                    const float2 ab = bq[b];
+#pragma unroll
+                    for (int e = 0; e < EV; ++e)
+                        h[e] = fmaf(kq[e * kStage + b], __builtin_amdgcn_exp2f(fmaf(ab.y, et[e], ab.x)), h[e]);
+                }
+            } else {
+                for (int b = b0 + l; b < b1; b += 16) {
+                    const float2 ab = bq[b];
+                    h[0] = fmaf(k_resp_f((float)(u[0] - us[lo + b]), inv2s2), __builtin_amdgcn_exp2f(fmaf(ab.y, et[0], ab.x)),
+                                h[0]);
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < EV; ++e)
+#pragma unroll
+            for (int off = 8; off >= 1; off >>= 1) h[e] += __shfl_xor(h[e], off, 64);
+        if (l == 0 && q < g.n_q) {
+            const float beta0 = (float)(2.0 * g.c2 * (g.e0 - g.e_c));
+            const float prim = st.prim[(size_t)a * g.n_p + q];
+#pragma unroll
+            for (int e = 0; e < EV; ++e) {
+                if (rank < r[e].x || rank >= r[e].y) continue;
+                const float kp = staged ? Kr[e * kStage + rank - all.x] : k_resp_f((float)(u[e] - us[rank]), inv2s2);
+                H[(size_t)(jr + e) * g.n_qpad + q] =
+                    (h[e] + kp * __builtin_amdgcn_exp2f(fmaf(beta0, et[e], prim))) * efac[row_base + jr + e];
+            }
+        }
+    }
+}
 
 __global__ __launch_bounds__(256) void k_surr_near(Geo g, SurrTables st, const float2 *__restrict__ band, int band_w,
                                                    const int *__restrict__ band_lo, const int *__restrict__ ev_angle,
                                                    const float *__restrict__ su, const float *__restrict__ se,
                                                    const float *__restrict__ efac, const int2 *__restrict__ rr,
-                                                   int row_base, int j0, int rows, float *__restrict__ H) {
+                                                   int row_base, int rows, float *__restrict__ H) {
     __shared__ float Kr[kNearStage];
-    const int lr = blockIdx.x;   // row within the batch
-    if (lr >= rows) return;
-    const int jr = j0 + lr, j = row_base + jr;
-    const int a = ev_angle[j];
-    const double u = ((double)su[j] - 0.5 * g.n_bins) * g.bin_cm;
-    const float et = se[j];
-    const int2 r = rr[jr];
-    const double *us = st.us_sorted + (size_t)a * g.n_p;
-    const int *ss = st.s_sorted + (size_t)a * g.n_p;
-    const float inv2s2 = (float)(1.0 / (2.0 * g.sig_u * g.sig_u));
-    const bool staged = r.y - r.x <= kNearStage;
-    if (staged)
-        for (int i = threadIdx.x; i < r.y - r.x; i += blockDim.x) Kr[i] = k_resp_f((float)(u - us[r.x + i]), inv2s2);
-    __syncthreads();
-    const int grp = threadIdx.x >> 4, l = threadIdx.x & 15;
-    // every group runs the same number of passes, so the 16-lane sums below
-    // always see all of their lanes
-    for (int rank0 = r.x; rank0 < r.y; rank0 += 16) {
-        const int rank = rank0 + grp;
-        const int q = rank < r.y ? ss[rank] : g.n_q;
-        float h = 0.0f;
-        if (q < g.n_q) {
-            const int lo = band_lo[(size_t)a * g.n_p + q];
-            const float2 *bq = band + ((size_t)a * g.n_qpad + q) * band_w;
-            const int b0 = max(r.x - lo, 0), b1 = min(r.y - lo, band_w);
-            if (staged) {
-                const float *kq = Kr + (lo - r.x);
-#pragma unroll 4
-                for (int b = b0 + l; b < b1; b += 16) {
-                    const float2 ab = bq[b];
-                    h = fmaf(kq[b], __builtin_amdgcn_exp2f(fmaf(ab.y, et, ab.x)), h);
-                }
-            } else {
-                for (int b = b0 + l; b < b1; b += 16) {
-                    const float2 ab = bq[b];
-                    h = fmaf(k_resp_f((float)(u - us[lo + b]), inv2s2), __builtin_amdgcn_exp2f(fmaf(ab.y, et, ab.x)),
-                             h);
-                }
-            }
-        }
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) h += __shfl_xor(h, off, 64);
-        if (l == 0 && q < g.n_q) {
-            const float beta0 = (float)(2.0 * g.c2 * (g.e0 - g.e_c));
-            const float kp = staged ? Kr[rank - r.x] : k_resp_f((float)(u - us[rank]), inv2s2);
-            h += kp * __builtin_amdgcn_exp2f(fmaf(beta0, et, st.prim[(size_t)a * g.n_p + q]));
-            H[(size_t)jr * g.n_qpad + q] = h * efac[j];
-        }
+    const int jr = blockIdx.x * kNearEv, n = min(kNearEv, rows - jr);
+    if (n <= 0) return;
+    const int a = ev_angle[row_base + jr];
+    bool same = n == kNearEv;
+    int2 all = rr[jr];
+    for (int e = 1; e < n; ++e) {
+        same = same && ev_angle[row_base + jr + e] == a;
+        all = make_int2(min(all.x, rr[jr + e].x), max(all.y, rr[jr + e].y));
+    }
+    // (each uniform over the block)
+    if (same && all.y - all.x <= kNearStage / kNearEv) {
+        near_rows<kNearEv>(g, st, band, band_w, band_lo, a, su, se, efac, rr, row_base, jr, Kr, H);
+    } else {
+        for (int e = 0; e < n; ++e)
+            near_rows<1>(g, st, band, band_w, band_lo, ev_angle[row_base + jr + e], su, se, efac, rr, row_base, jr + e, Kr, H);
     }
 }
 
@@ -390,7 +475,7 @@ hipError_t surrogate_rows(const Geo &g, const Tables &t, Net *net, const int *ev
     float4 *col4 = reinterpret_cast<float4 *>(col);
     int2 *rr = reinterpret_cast<int2 *>(col4 + rows);   // the workspace holds 6 words per event
     hipError_t e;
-    hipLaunchKernelGGL(k_event_column, dim3((rows + 63) / 64), dim3(64), 0, st, g, s, ev_angle + row_base,
+    hipLaunchKernelGGL(k_event_column, dim3((rows + 63) / 64), dim3(128), 0, st, g, s, ev_angle + row_base,
                        su + row_base, rows, col4, rr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int rows_per = (int)std::max<int64_t>(1, pair_cap / g.n_q);
@@ -404,11 +489,10 @@ hipError_t surrogate_rows(const Geo &g, const Tables &t, Net *net, const int *ev
         auto run_net = [&]() { return launch_mlp_pairs(net, src, pairs, st); };
         if ((e = wrap_net ? (*wrap_net)(run_net) : run_net()) != hipSuccess) return e;
     }
-    // the near field of every row in one launch, over the network's values
-    // (one block per row: a launch per batch of rows left most of the
-    // GPU's block slots empty)
-    hipLaunchKernelGGL(k_surr_near, dim3((unsigned)rows), dim3(256), 0, st, g, s, t.band, t.band_w, t.band_lo,
-                       ev_angle, su, se, efac, rr, row_base, 0, rows, H);
+    // the near field of every row in one launch, over the network's values (a
+    // launch per batch of rows left most of the GPU's block slots empty)
+    hipLaunchKernelGGL(k_surr_near, dim3((unsigned)((rows + kNearEv - 1) / kNearEv)), dim3(256), 0, st, g, s, t.band,
+                       t.band_w, t.band_lo, ev_angle, su, se, efac, rr, row_base, rows, H);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_row_mean, dim3(rows), dim3(64), 0, st, g, rrange, n_real, rows, H, f, pmean);
     return hipGetLastError();
