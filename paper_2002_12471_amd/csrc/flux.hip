@@ -1009,6 +1009,35 @@ __global__ __launch_bounds__(256) void k_flux_primary_back(Geo g, FluxTables ft,
     *o = a_lo == 0 ? v : *o + v;
 }
 
+// the primary paths' backprojection b and f <- f b / sens at once (BACK: b
+// itself), where one chunk holds every slot: without scatter a sub-iteration is
+// a few short kernels, and this saves one of four (7.5 -> 3.7 us)
+template <bool BACK>
+__global__ __launch_bounds__(256) void k_flux_primary_update(Geo g, FluxTables ft, const int *__restrict__ alist,
+                                                             int n_list, const float *__restrict__ R0,
+                                                             const float *__restrict__ sens, float *__restrict__ f) {
+    __shared__ float part[4][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, x = blockIdx.x * 64 + lane, r = blockIdx.y;
+    float s = 0.0f;
+    if (x < g.n_p)
+#pragma unroll 4
+        for (int ai = wave; ai < n_list; ai += 4)
+            s = fmaf(ft.pw[(size_t)alist[ai] * g.n_p + x], R0[(size_t)(r * n_list + ai) * g.n_p + x], s);
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave || x >= g.n_p) return;
+    const int p = ft.sup[x];
+    if (p >= g.n_q) return;
+    const float b = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    float *fp = f + (size_t)r * g.n_qpad + p;
+    if (BACK) {
+        *fp = b;
+        return;
+    }
+    const float se = sens[p], v = *fp;
+    *fp = se > 0.0f ? (v * b) / se : v;
+}
+
 // f <- f b / sens with b the sum of the realisation's partial rows (the
 // primary's first), and the box copy of the new estimate; BACK: b itself
 template <bool BACK>
@@ -1612,11 +1641,13 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
             if (e != hipSuccess) return e;
         }
         // chunks of slots: whole realisations, or ca angles of one
+        bool whole = false;   // a single chunk
         for (int s0 = 0, s1; s0 < n_slots; s0 = s1) {
             if (ca == p.n_list) s1 = std::min(n_slots, s0 + std::max(1, w.slots / p.n_list) * p.n_list);
             else s1 = std::min(s0 + ca, (s0 / p.n_list + 1) * p.n_list);
             const int ns = s1 - s0;
             if (ns > w.slots) return hipErrorInvalidValue;
+            whole = ns == n_slots;
             if (p.means) {
                 const int b0 = p.blk_host[sb + s0], b1 = p.blk_host[sb + s1];
                 e = stage(0, [&] {
@@ -1648,7 +1679,7 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
                 if (sc) {
                     hipLaunchKernelGGL(k_flux_fields, dim3((g.n_p + 31) / 32 * ((fg.N + 31) / 32) * zr), dim3(64 * kFieldWaves), 0, p.st, g,
                                        fg, ft, p.alist, p.n_list, s0, ns, w.S, w.SP, w.T, w.pb);
-                } else {
+                } else if (ns < n_slots) {
                     hipLaunchKernelGGL(k_flux_primary_back, dim3(fg.n_blk, zr), dim3(256), 0, p.st, g, ft, p.alist, p.n_list,
                                        s0, ns, w.SP, w.pb);
                 }
@@ -1670,6 +1701,11 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
             return e;
         e = stage(2, [&] {
             const dim3 ug((g.n_p + 63) / 64, nr);
+            if (!sc && whole) {
+                hipLaunchKernelGGL(p.sens ? k_flux_primary_update<false> : k_flux_primary_update<true>, ug, dim3(256), 0, p.st, g,
+                                   ft, p.alist, p.n_list, w.SP, p.sens, f);
+                return hipGetLastError();
+            }
             auto *kern = p.sens ? k_flux_update<false> : k_flux_update<true>;
             hipLaunchKernelGGL(kern, ug, dim3(64), 0, p.st, g, fg, ft, n_rows, w.pb, p.sens, f, w.fbox);
             return hipGetLastError();

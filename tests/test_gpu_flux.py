@@ -136,3 +136,23 @@ def test_flux_batch_equals_single_runs_and_cached_rows(dev, name):
     on = mu > 0
     assert np.max(np.abs(flux - rows)[on] / np.maximum(rows[on], 1e-3 * rows.max())) <= 1e-4
     np.testing.assert_allclose(ll2, ll, rtol=1e-6)
+
+
+def test_primary_batch_with_fewer_events_than_slots(dev):
+    """Four realisations of 10 events on 16 angles, without scatter: the
+    workspace (no larger than the rows of the events) takes the slots in more
+    than one chunk, so that backprojection and update run apart; bit for bit
+    each realisation's own run, where they are one kernel."""
+    L, g, act, mu, ev = _make("primary16", dev)
+    g = dict(g, n_subsets=1)
+    pick = {k: ev[k][:40] for k in ev}
+    cat = L.events_to_device(pick, dev)
+    ctx = L.Context(g, torch.as_tensor(mu, device=dev))
+    try:
+        batch = ctx.reconstruct(cat, 2, batch_offsets=[0, 10, 20, 30, 40]).cpu().numpy()
+        for r in range(4):
+            one = L.events_to_device({k: pick[k][10 * r:10 * r + 10].copy() for k in pick}, dev)
+            assert np.array_equal(batch[r], ctx.reconstruct(one, 2).cpu().numpy()), r
+    finally:
+        ctx.close()
+    assert batch.any()
