@@ -737,6 +737,34 @@ def main():
             "backproject_gbps": row_bytes / bp_s / 1e9 if bp_s > 0 else None,
             "update_avg_ms": ks["update_ms"] / max(1, ks["update_launches"]),
         }
+    elif launches > n_it * g["n_subsets"]:
+        # the flux stages (two timed intervals before the backprojection in
+        # each sub-iteration, where the term-by-term path has one): they do not
+        # evaluate terms, so what a sub-iteration cannot do without is its
+        # events and images; the kernels' own bounds are in profiles/
+        sub_s = ms_step * 1e-3 / g["n_subsets"]
+        need = (12.0 * J + 8.0 * n_real * n_qpad * g["n_subsets"]) / g["n_subsets"]
+        roof = {
+            "bound": "hbm",
+            "kernel": "one sub-iteration through directional flux (spread, spectra, means, adjoint, fields, gather, update)",
+            "achieved": need / sub_s / 1e9,
+            "peak": HBM_PEAK_GBS,
+            "unit": "GB/s",
+            "frac": need / sub_s / 1e9 / HBM_PEAK_GBS,
+            "traffic": None,
+            "per_unit": "12 bytes per event (angle, position, energy) and 8 per emission pixel (estimate read and "
+                        "written): the inputs and outputs alone; the stages are bound by FP32 matrix products, "
+                        "vector-cache misses and the length of a sub-iteration's chain of seven short kernels",
+            "avg_sub_iteration_ms": sub_s * 1e3,
+            "means_ms_per_iteration": ks["forward_ms"] / n_it,
+            "backproject_ms_per_iteration": ks["backproject_ms"] / n_it,
+            "update_ms_per_iteration": ks["update_ms"] / n_it,
+            "terms_covered_per_s": useful_per_iter / (ms_step * 1e-3),
+            "term_by_term_ceiling_per_s": peak_terms,
+            "terms_note": "(event, emission pixel, path end) terms with non-zero position response, which the "
+                          "term-by-term form evaluates one by one; the ceiling is that form's (2 FMAs and an exp2 a term)",
+            "measured_rates_per_s": rates,
+        }
     else:
         roof = None
     roof = roof or {
@@ -779,7 +807,7 @@ def main():
                    **({"emission_set": em_info} if emission is not None else {}),
                    "event_tile": tile, "pixel_tile": pixel_tile, "chunk_rows": chunk, "graphs": bool(graphs),
                    "path": "exact FP32" + (", system rows cached after the first iteration" if args.cache_rows
-                                           else "")},
+                                           else ", directional flux" if "terms_covered_per_s" in roof else "")},
         "roofline": roof,
         "one_time_ms": {"create_tables": t_create * 1e3, "event_ingest": t_load * 1e3,
                         "autotune": t_tune * 1e3,
