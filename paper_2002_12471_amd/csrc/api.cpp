@@ -42,7 +42,7 @@ struct lmosem_ctx {
     float *fws = nullptr;          // workspace of one realisation
     size_t fws_floats = 0;
     int64_t flux_bytes = 0;
-    bool lazy_table = false;       // the path table is filled for the first row cache only
+    bool lazy_table = false;       // the path table is filled for the first row cache or set that wants it
     // HIP graphs: one captured iteration per prepared set, replayed on an
     // internal stream ordered after the caller's stream by events
     bool graphs = true;
@@ -270,19 +270,64 @@ std::string cap_msg(const lmosem_ctx *c, const char *what, int64_t more) {
            " device bytes, above its cap of " + std::to_string(c->mem_cap) + " (lmosem_set_memory_cap)";
 }
 
-// Supports whose every list-mode call runs through the flux stages: from 512
-// pixels the path table that the term-by-term kernels read takes more time to
-// fill (6.4 ms and 2 GB on 1436 pixels) than they save on small event sets.
+// Supports whose calls on events of one sub-iteration (forward, backprojection,
+// subset update) all run through the flux stages: from 512 pixels the path
+// table that the term-by-term kernels read takes more time to fill (6.4 ms and
+// 2 GB on 1436 pixels) than they save on few events.
 constexpr int kFluxAlways = 512;
 
 bool flux_always(const lmosem_ctx *c) { return c->flux_fits && c->g.n_p >= kFluxAlways; }
 
-// The terms from which a sub-iteration runs faster through the flux stages
-// than term by term (8.6e12 terms/s and about 20 us of launches): the
-// stages' own time hardly depends on the events, 110 us on a support of 156
-// pixels.  Without scatter they always do (the term-by-term kernels visit
-// every path end all the same).
+// The terms from which such a call runs faster through the flux stages than
+// term by term (8.6e12 terms/s and about 20 us of launches): the stages' own
+// time hardly depends on the events, 110 us on a support of 156 pixels.
+// Without scatter they always do (the term-by-term kernels visit every path
+// end all the same).
 int64_t flux_from(const lmosem_ctx *c) { return flux_always(c) || !c->g.scatter ? -1 : 800'000'000; }
+
+// The workspace of its own that plan_flux gives a set of max_slots angles and
+// realisations in a sub-iteration (0: it uses the context's).
+size_t flux_set_floats(const lmosem_ctx *c, const EvSet &v, int max_list, int max_slots) {
+    const size_t budget = (size_t)std::max(v.max_rows, 1) * c->g.n_qpad;
+    const size_t need = flux_ws_floats(c->g, c->fg, v.n_real, max_slots);
+    if (need > budget && budget <= c->fws_floats) return 0;
+    const size_t floats = std::min(need, budget);
+    return flux_group(c->g, c->fg, floats, v.n_real, max_list) < 1 ? 0 : floats;
+}
+
+// Whether a set that iterates is faster through the flux stages, by what a
+// sub-iteration of its largest subset takes either way, in us.  Term by term
+// the events count: 9 terms/ps over whole waves of emission pixels, the rows
+// written and read once, and the walk along a tile's path ends where there are
+// too few tiles to hide it.  The flux stages pay by map, angles, realisations
+// and workspace groups, and little by event.  Measured per sub-iteration, flux
+// | term by term (us): 1436 pixels, 15 angles: 2.5k events 114 | 125; 120
+// angles: 3k 524 | 459, 20k 483 | 717; 2832 pixels, 2.5k 233 | 349; 5736
+// pixels, 8 angles: 188 events 520 | 502, 1250 395 | 620; 564 pixels, 12.5k 67
+// | 79; 356 pixels, 12.5k 58 | 50; 156 pixels, 50k 74 | 70, 200k 141 | 201.
+// A call that loads its set for itself (sub_iters sub-iterations) also fills
+// the path table, and walks the path ends in tiles that nobody tuned: 10
+// iterations of 1k events took 13.9 ms term by term and 12.7 ms through the
+// stages on 1436 pixels, 101 and 84 ms on 5736.  The table is counted whether
+// the context holds it yet or not, so that a repeated call gives the same bits;
+// where the stages win by it alone, later calls could have been shorter (2
+// iterations of 1k events on 120 angles: 1.26 ms, 1.16 beside a table that took
+// 6.4).
+bool flux_faster(const lmosem_ctx *c, const EvSet &v, int64_t sub_iters) {
+    const Geo &g = c->g;
+    if (!g.scatter) return true;
+    const int n_list = (g.n_angles + g.n_subsets - 1) / g.n_subsets;
+    const size_t own = flux_set_floats(c, v, n_list, n_list * v.n_real);
+    const int grp = std::max(1, flux_group(g, c->fg, own ? own : c->fws_floats, v.n_real, n_list));
+    const double groups = (v.n_real + grp - 1) / grp, n_p = g.n_p, rows = v.max_rows;
+    const double terms = (double)*std::max_element(v.terms_sub.begin(), v.terms_sub.end());
+    double direct = 20 + terms * g.n_qpad / g.n_q / 9e6 + (sub_iters ? 0.105 : 0.07) * v.max_ranks + rows * g.n_qpad * 1e-6;
+    if (sub_iters && c->lazy_table)   // at 310 GB/s
+        direct += 8.0 * g.n_angles * g.n_rpad * g.n_qpad / 3.1e5 / (double)sub_iters;
+    const double flux = (45 + 0.055 * v.max_ranks) * groups + 3e-4 * rows +
+                        v.n_real * (1.05e-7 * n_list * n_p * c->fg.N * c->fg.K + 6e-6 * n_p * n_p);
+    return flux < direct;
+}
 
 // The angle lists, slots and event records of a flux set: all angles of each
 // subset, or (one given subset) the angles that have events; and the set's own
@@ -338,19 +383,17 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
                         v.fblk, c->st);
     if (e != hipSuccess) return alloc_err(c, "event records", e);
     if (!kept && v.n_real == 1) return LMOSEM_OK;
-    const size_t budget = (size_t)std::max(v.max_rows, 1) * g.n_qpad;
-    const size_t need = flux_ws_floats(g, c->fg, v.n_real, max_slots);
-    if (need > budget && budget <= c->fws_floats) return LMOSEM_OK;
-    const size_t floats = std::min(need, budget);
-    if (flux_group(g, c->fg, floats, v.n_real, max_list) < 1) return LMOSEM_OK;
+    const size_t floats = flux_set_floats(c, v, max_list, max_slots);
+    if (floats == 0) return LMOSEM_OK;
     e = dev_take(v.arena, &s->fws, sizeof(float) * floats);
     if (e != hipSuccess) return alloc_err(c, "workspace", e);
     s->fws_floats = floats;
     return LMOSEM_OK;
 }
 
+// sub_iters: of a call that iterates on its set (0: one sub-iteration)
 lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batch *batch, int force_subset,
-                       lmosem_evset **out, bool kept = false) {
+                       lmosem_evset **out, bool kept = false, int64_t sub_iters = 0) {
     lmosem_status st = LMOSEM_OK;
     if (c->surrogate && !c->net) return set_err(c, LMOSEM_ESTATE, "scatter_model 2 needs a network (lmosem_set_surrogate)");
     if (!check_arrays(c, ev, st)) return st;
@@ -386,7 +429,13 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
         free_set(s);
         return e == hipErrorOutOfMemory ? set_err(c, LMOSEM_ENOMEM, why) : set_err(c, LMOSEM_EDEVICE, why);
     }
-    s->flux = c->flux && *std::max_element(s->s.terms_sub.begin(), s->s.terms_sub.end()) > flux_from(c);
+    s->flux = c->flux && (kept || sub_iters > 0 ? flux_faster(c, s->s, sub_iters)
+                                                : s->s.terms_sub[std::max(force_subset, 0)] > flux_from(c));
+    if (c->flux && !s->flux && !c->t.T) {   // the path table, held since the first list-mode call
+        e = build_path_table(c->g, c->t, c->st);
+        if (e != hipSuccess && e != hipErrorOutOfMemory) { free_set(s); return dev_err(c, "path table", e); }
+        if (e != hipSuccess) { (void)hipGetLastError(); s->flux = true; }
+    }
     lmosem_status ws = s->flux ? plan_flux(c, s, force_subset, kept) : LMOSEM_OK;
     if (ws == LMOSEM_OK) ws = alloc_workspace(c, s);
     if (ws != LMOSEM_OK) { free_set(s); return ws; }
@@ -699,9 +748,10 @@ lmosem_status ensure_paths(lmosem_ctx *c) {
     const auto t0 = std::chrono::steady_clock::now();
     std::string err;
     int64_t bytes = 0;
-    // where every list-mode call runs through the flux stages, the path table's
-    // bytes are held (a table that the device has no room for is refused) but
-    // filled only for the first row cache
+    // where every call on one sub-iteration runs through the flux stages, the
+    // path table's bytes are held (a table that the device has no room for is
+    // refused) but filled only for the first row cache or set that iterates
+    // term by term
     c->lazy_table = flux_always(c);
     if (c->lazy_table) {
         size_t room = 0, total = 0;
@@ -924,7 +974,7 @@ lmosem_status lmosem_reconstruct(lmosem_ctx *c, const lmosem_events *ev, const l
         if (bad) return set_err(c, LMOSEM_ERANGE, "initial image negative or not finite on the support");
     }
     lmosem_evset *s = nullptr;
-    lmosem_status st = load_set(c, ev, batch, -1, &s);
+    lmosem_status st = load_set(c, ev, batch, -1, &s, false, (int64_t)n_iters * c->g.n_subsets);
     if (st != LMOSEM_OK) return st;
     e = launch_gather_image(g, c->t, init_dev, s->s.n_real, 0, s->f, 1, c->st);
     if (e != hipSuccess) { free_set(s); return dev_err(c, "init", e); }

@@ -379,10 +379,12 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
     CK(hipStreamSynchronize(st), "tile plan");
     set.terms_sub.assign(g.n_subsets, 0);
     set.useful_sub.assign(g.n_subsets, 0);
+    set.max_ranks = 0;
     for (int i = 0; i < g.n_subsets; ++i)
         for (int t = set.tile_off[i]; t < set.tile_off[i + 1]; ++t) {
             set.terms_sub[i] += terms[t];
             set.useful_sub[i] += useful[t];
+            set.max_ranks = std::max(set.max_ranks, (int)(terms[t] / ((int64_t)tiles[t].n * g.n_q)));
         }
     cleanup();
 #undef CK

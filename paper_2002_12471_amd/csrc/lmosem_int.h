@@ -83,8 +83,8 @@ struct Tables {
 
 // ---- table build (tables.hip) ----
 // build_base at create; build_paths before the first list-mode use (or, where
-// the flux stages serve every list-mode call, build_path_table before the
-// first one that wants rows)
+// the flux stages serve the calls on one sub-iteration, build_path_table
+// before the first set that wants rows or runs term by term)
 hipError_t build_path_table(const Geo &g, Tables &t, hipStream_t st);
 hipError_t build_base(const Geo &g, Tables &t, hipStream_t st, std::string &err, int64_t &bytes);
 hipError_t build_paths(const Geo &g, Tables &t, bool store_paths, bool store_band, hipStream_t st,
@@ -386,6 +386,7 @@ struct EvSet {
     std::vector<int64_t> terms_sub;         // per subset: terms evaluated
     std::vector<int64_t> useful_sub;        // per subset: terms with K > 0
     int max_rows = 0, max_chunks = 0;
+    int max_ranks = 0;                      // most path ends that a tile's events reach
 };
 
 }  // namespace lmo

@@ -156,3 +156,38 @@ def test_primary_batch_with_fewer_events_than_slots(dev):
     finally:
         ctx.close()
     assert batch.any()
+
+
+# 560 support pixels, where the path table is filled on demand: few events per
+# realisation go term by term (the first two), many through the flux stages
+@pytest.mark.parametrize("per_real,n_real", [(60, 1), (150, 5), (200_000, 1)])
+def test_iterated_sets_by_size_equal_cached_rows(dev, per_real, n_real):
+    L = _lib()
+    g = synth.Geometry(32, 32, 0.4, 32, 0.4, 16, n_subsets=2)
+    X, Y = synth.phantoms.pixel_centres(32, 32, 0.4)
+    mu = np.where((X / 5.6) ** 2 + (Y / 5.1) ** 2 <= 1.0, 0.15, 0.0).astype(np.float32)
+    assert (mu > 0).sum() >= 512
+    J = per_real * n_real
+    ev = synth.generate_events(g, (mu > 0).astype(np.float32), mu, J, 9)
+    evd = L.events_to_device({k: ev[k] for k in ("angle", "u_bin", "energy")}, dev)
+    offs = list(range(0, J + 1, per_real)) if n_real > 1 else None
+    img = torch.as_tensor((mu > 0).astype(np.float32), device=dev).expand(n_real, -1, -1).contiguous().clone()
+    rows = img.clone()
+    ctx = L.Context(g.as_dict(), torch.as_tensor(mu, device=dev))
+    try:
+        evs = L.lmosem_events_load(ctx.handle, evd, offs)
+        try:
+            L.lmosem_iterate(ctx.handle, evs, 2, img, n_real=n_real)
+            L.lmosem_cache_rows(ctx.handle, evs, True)
+            L.lmosem_iterate(ctx.handle, evs, 2, rows, n_real=n_real)
+        finally:
+            L.lmosem_events_free(evs)
+        rec = ctx.reconstruct(evd, 2, batch_offsets=offs).reshape(img.shape)
+        again = ctx.reconstruct(evd, 2, batch_offsets=offs).reshape(img.shape)
+    finally:
+        ctx.close()
+    on = np.broadcast_to(mu > 0, img.shape)
+    a = rows.cpu().numpy().astype(np.float64)[on]
+    for b in (img.cpu().numpy()[on], rec.cpu().numpy()[on]):
+        assert np.max(np.abs(b - a) / np.maximum(a, 1e-3 * a.max())) <= 1e-4
+    assert torch.equal(rec, again)
