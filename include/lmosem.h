@@ -117,17 +117,21 @@ typedef struct {
 typedef struct {
     int64_t n_support;          /* pixels with mu > 0 (path ends and scatter points) */
     int64_t skipped_events;     /* events whose model mean was <= 1e-30, since create */
-    int64_t inner_terms;        /* (event, emission pixel, path end) terms evaluated by
-                                   the forward projection, since create */
+    int64_t inner_terms;        /* (event, emission pixel, path end) terms of the sums that
+                                   the forward projection formed, since create (through
+                                   directional flux they are not evaluated one by one) */
     int64_t useful_terms;       /* of those, terms with a non-zero position response */
     double table_ms;            /* time of the table builds so far (lmosem_create, and
-                                   the path tables at the first list-mode call) */
-    int64_t table_bytes;        /* device bytes held by the tables built so far */
+                                   the path tables at the first list-mode call; not the
+                                   path table of a large map, filled when a set first
+                                   runs term by term or keeps its rows) */
+    int64_t table_bytes;        /* device bytes held by the tables built so far (and, from
+                                   the first list-mode call, by that path table) */
     int32_t event_tile;         /* events per forward-projection tile */
     int32_t n_emission;         /* emission pixels (the estimated image), <= n_support */
     /* kernel times from HIP events on the context's stream, recorded only
        while timing is enabled (lmosem_set_timing) */
-    int64_t forward_launches;
+    int64_t forward_launches;   /* (through directional flux: stages of a sub-iteration) */
     double forward_ms;          /* summed over forward-projection launches */
     int64_t backproject_launches;
     double backproject_ms;
@@ -238,7 +242,11 @@ lmosem_status lmosem_reconstruct(lmosem_ctx *ctx, const lmosem_events *ev,
 /* Prepared event sets: validate once, sort by (subset, realisation, angle,
  * position) and plan the forward-projection tiles, so that repeated
  * iterations pay nothing for ingest.  The set keeps device copies and is
- * tied to its context; free it before the context. */
+ * tied to its context; free it before the context.  Sets (and
+ * lmosem_reconstruct) run through directional flux or term by term,
+ * whichever is shorter for their events, map and realisations: the results
+ * agree to about 1e-6, but one realisation in a batch and alone need not
+ * agree bit for bit. */
 lmosem_status lmosem_events_load(lmosem_ctx *ctx, const lmosem_events *ev,
                                  const lmosem_batch *batch, lmosem_evset **out);
 void lmosem_events_free(lmosem_evset *set);
@@ -271,7 +279,8 @@ lmosem_status lmosem_set_pixel_tile(lmosem_ctx *ctx, int32_t pixels);
  * scratch image), and one whole iteration launched kernel by kernel against one
  * replayed as a HIP graph (iterations estimated above 50 ms are replayed
  * without that comparison); re-plans the set with the fastest choices and
- * returns them (outputs may be NULL).  With LMOSEM_TUNE_CACHE=<file> in the
+ * returns them (outputs may be NULL).  A set that runs through directional
+ * flux has only the replay to choose.  With LMOSEM_TUNE_CACHE=<file> in the
  * environment the choice is looked up in / appended to that file, keyed by
  * support and emission-set sizes, angles, subsets, realisations and subset size.  Results do
  * not depend on the choice beyond FP32 summation order.  Synchronises. */
