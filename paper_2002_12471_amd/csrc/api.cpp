@@ -81,6 +81,7 @@ struct lmosem_evset {
     float *col = nullptr;     // surrogate: per-sub-iteration event column features [max_rows][4] + ranks [max_rows][2]
     uint16_t *X = nullptr;    // surrogate: network inputs [pair_cap][8], bf16
     bool flux = false;        // iterates through directional flux unless its rows are cached
+    bool fused = false;       // term by term in one kernel (launch_forward_back) unless its rows are cached
     bool tuned = false;       // autotuned; a later row cache tunes its own kernels too
     float *fws = nullptr;     // flux workspace of the set (null: the context's)
     size_t fws_floats = 0;
@@ -216,7 +217,7 @@ int64_t set_device_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
     const int64_t n_tiles = std::max<int64_t>(v.tile_off.empty() ? 1 : v.tile_off.back(), 1);
     const int64_t n_chunks = std::max<int64_t>(v.chunk_off.empty() ? 1 : v.chunk_off.back(), 1);
     int64_t b = 20 * n + (int64_t)sizeof(Tile) * n_tiles + (int64_t)sizeof(Chunk) * n_chunks +
-                8 * (int64_t)g.n_subsets * (v.n_real + 1);
+                12 * (int64_t)g.n_subsets * (v.n_real + 1);
     b += 8 * rows + 4 * (int64_t)v.n_real * g.n_qpad + 8 * (int64_t)v.n_real;
     if (s->H) b += 4 * rows * g.n_qpad;
     if (s->pmean) b += 4 * rows * std::max<int64_t>((int64_t)s->pmean_groups, forward_groups(g));
@@ -436,6 +437,7 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
         if (e != hipSuccess && e != hipErrorOutOfMemory) { free_set(s); return dev_err(c, "path table", e); }
         if (e != hipSuccess) { (void)hipGetLastError(); s->flux = true; }
     }
+    s->fused = !c->surrogate && c->pixel_waves == 0 && c->g.n_qpad <= kFuseMax;
     lmosem_status ws = s->flux ? plan_flux(c, s, force_subset, kept) : LMOSEM_OK;
     if (ws == LMOSEM_OK) ws = alloc_workspace(c, s);
     if (ws != LMOSEM_OK) { free_set(s); return ws; }
@@ -557,6 +559,20 @@ hipError_t forward_rows(lmosem_ctx *c, lmosem_evset *s, int i, float *H, hipStre
 
 int mean_groups(const lmosem_ctx *c, const lmosem_evset *s) { return c->surrogate ? 1 : forward_groups(set_geo(c, s)); }
 
+// subset i in one kernel and its update; the tiles' backprojections (no more
+// than its rows) lie in the rows' place
+hipError_t forward_back(lmosem_ctx *c, lmosem_evset *s, int i, hipStream_t st, const KernelEvents *ke) {
+    const EvSet &v = s->s;
+    return launch_forward_back(v.ev_tile, c->g, c->t, v.tiles + v.tile_off[i], v.tile_off[i + 1] - v.tile_off[i], v.u, v.e,
+                               v.efac, s->f, s->H, s->mean, s->inv, c->skipped_dev, v.row_off[i], st, ke);
+}
+
+hipError_t update_tiles(lmosem_ctx *c, lmosem_evset *s, int i, hipStream_t st) {
+    const EvSet &v = s->s;
+    return launch_update_tiles(c->g, v.trange + (size_t)i * (v.n_real + 1), v.n_real, s->H,
+                               c->t.sens + (size_t)i * c->g.n_qpad, s->f, st);
+}
+
 // One sub-iteration of Eq. 7 on all realisations of a prepared set: the
 // system rows are computed (and kept when the set caches them) or, once
 // cached, read back for the means.
@@ -568,12 +584,21 @@ hipError_t subiteration(lmosem_ctx *c, lmosem_evset *s, int i, bool first, bool 
     const int n_chunks = v.chunk_off[i + 1] - v.chunk_off[i];
     const bool cached = s->Hc && s->rows_valid;
     if (s->flux && !s->Hc) return flux_subset(c, s, i, first, true, true, c->t.sens + (size_t)i * g.n_qpad, want_ll, st);
-    const int groups = cached ? 1 : mean_groups(c, s);
-    float *H = s->Hc ? s->Hc + (size_t)v.row_off[i] * g.n_qpad : s->H;
     const float *sens = c->t.sens + (size_t)i * g.n_qpad;
-    const int *crange = v.crange + (size_t)i * (v.n_real + 1);
     const int *rrange = v.rrange + (size_t)i * (v.n_real + 1);
     hipError_t e;
+    if (s->fused && !s->Hc) {
+        // (tiles' backprojections in place of their rows)
+        if (n_tiles > 0 && (e = timed_kernel(c, 0, [&](const KernelEvents *ke) {
+                                return forward_back(c, s, i, st, ke);
+                            })) != hipSuccess)
+            return e;
+        if (want_ll && (e = launch_loglik(g, rrange, v.n_real, s->mean, s->f, sens, s->ll, st)) != hipSuccess) return e;
+        return timed(c, 2, [&] { return update_tiles(c, s, i, st); }, st);
+    }
+    const int groups = cached ? 1 : mean_groups(c, s);
+    float *H = s->Hc ? s->Hc + (size_t)v.row_off[i] * g.n_qpad : s->H;
+    const int *crange = v.crange + (size_t)i * (v.n_real + 1);
     if (cached) {
         // event means and their inverses straight from the stored rows
         if ((e = timed_kernel(c, 0, [&](const KernelEvents *ke) {
@@ -1453,10 +1478,10 @@ lmosem_status lmosem_cache_rows(lmosem_ctx *c, lmosem_evset *s, int32_t enable) 
     c->set_bytes -= s->bytes;
     s->bytes = set_device_bytes(c, s);
     c->set_bytes += s->bytes;
-    if (s->flux) {
+    if (s->flux || s->fused) {
         // the rows' own kernels: their partial sums, and (for a set that was
         // autotuned) their plan
-        lmosem_status ws = alloc_workspace(c, s, true);
+        lmosem_status ws = s->flux ? alloc_workspace(c, s, true) : LMOSEM_OK;
         if (ws == LMOSEM_OK && s->tuned) ws = lmosem_autotune(c, s, nullptr, nullptr, nullptr);
         if (ws != LMOSEM_OK) {   // the set stays usable without the cache
             hipFree(s->Hc);
@@ -1479,7 +1504,7 @@ std::string tune_key(const lmosem_ctx *c, const lmosem_evset *s) {
     char buf[160];
     snprintf(buf, sizeof buf, "np=%d nq=%d na=%d ns=%d real=%d rows2^%d%s", c->g.n_p, c->g.n_q, c->g.n_angles,
              c->g.n_subsets,
-             s->s.n_real, lg, s->flux && !s->Hc ? " flux" : "");
+             s->s.n_real, lg, s->Hc ? "" : s->flux ? " flux" : s->fused ? " fused" : "");
     return buf;
 }
 
@@ -1553,16 +1578,19 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
     s->tuned = true;
     // a flux set without a row cache has nothing to tune but the replay
     const bool direct = !s->flux || s->Hc;
+    // one kernel instead of three: only its events per tile to choose
+    const bool fused = direct && s->fused && !s->Hc;
     // tune the computing path; a row cache is refilled by the next iteration
     struct Restore {
         lmosem_evset *s;
         float *hc;
-        bool flux;
-        ~Restore() { s->Hc = hc; s->flux = flux; s->rows_valid = false; drop_graphs(s); }
-    } restore{s, s->Hc, s->flux};
+        bool flux, fused;
+        ~Restore() { s->Hc = hc; s->flux = flux; s->fused = fused; s->rows_valid = false; drop_graphs(s); }
+    } restore{s, s->Hc, s->flux, s->fused};
     s->Hc = nullptr;
     s->rows_valid = false;
     s->flux = s->flux && !direct;
+    s->fused = fused;
     int best_ev = v.ev_tile, best_ch = v.chunk_rows, best_graph = -1, best_waves = v.fwd_waves;
     float fwd_ms = 0.0f;   // the fastest forward launch of the largest subset
     hipError_t e = hipSuccess;
@@ -1597,12 +1625,17 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
                 if (e != hipSuccess) break;
                 if ((e = plan_tiles(g, c->t, v, ev, v.chunk_rows, c->st, why)) != hipSuccess) break;
                 for (int w : waves_opts) {
-                    v.fwd_waves = w;
+                    if (fused && w != waves_opts[0]) break;
+                    if (!fused) v.fwd_waves = w;
                     lmosem_status ws = alloc_workspace(c, s);
                     if (ws != LMOSEM_OK) return ws;
                     const Geo gw = set_geo(c, s);
                     float ms = 0.0f;
                     e = time_ms(c, [&] {
+                        if (fused) {
+                            const hipError_t r = forward_back(c, s, big, c->st, nullptr);
+                            return r == hipSuccess ? update_tiles(c, s, big, c->st) : r;
+                        }
                         return launch_forward(ev, gw, c->t, v.tiles + v.tile_off[big],
                                               v.tile_off[big + 1] - v.tile_off[big], v.u, v.e, v.efac, s->f, s->H,
                                               s->pmean, v.row_off[big], rows, c->st);
@@ -1611,7 +1644,7 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
                     sweep_ms += 4.0f * ms;   // warm-up and timed runs
                     if (sweep == 0) cand_ms.push_back(ms);
                     else cand_ms[ci] = std::min(cand_ms[ci], ms);
-                    if (cand_ms[ci] < best) { best = cand_ms[ci]; best_ev = ev; best_waves = w; }
+                    if (cand_ms[ci] < best) { best = cand_ms[ci]; best_ev = ev; best_waves = fused ? v.fwd_waves : w; }
                     ++ci;
                 }
             }
@@ -1620,7 +1653,7 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
         fwd_ms = best < 3.4e38f ? best : 0.0f;
         best = 3.4e38f;
         for (int ch : {64, 128, 256, 512, 1024, 2048, 4096}) {
-            if (e != hipSuccess || !direct) break;
+            if (e != hipSuccess || !direct || fused) break;
             if ((e = plan_tiles(g, c->t, v, best_ev, ch, c->st, why)) != hipSuccess) break;
             lmosem_status ws = alloc_workspace(c, s);
             if (ws != LMOSEM_OK) return ws;

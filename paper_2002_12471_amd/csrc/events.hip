@@ -311,6 +311,7 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
     dev_give(set.arena, set.plan);
     set.plan = nullptr;
     set.tiles = nullptr; set.chunks = nullptr; set.crange = nullptr; set.rrange = nullptr;
+    set.trange = nullptr;
     set.ev_tile = ev_tile;
     set.chunk_rows = chunk_rows;
     const int n_real = set.n_real;
@@ -318,7 +319,7 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
     const int EV = ev_tile, CH = chunk_rows;
     std::vector<Tile> tiles;
     std::vector<Chunk> chunks;
-    std::vector<int> crange, rrange;
+    std::vector<int> crange, rrange, trange;
     set.row_off.assign(g.n_subsets + 1, 0);
     set.tile_off.assign(g.n_subsets + 1, 0);
     set.chunk_off.assign(g.n_subsets + 1, 0);
@@ -332,6 +333,7 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
         for (int r = 0; r < n_real; ++r) {
             crange.push_back((int)chunks.size() - set.chunk_off[i]);
             rrange.push_back((int)(pos - set.row_off[i]));
+            trange.push_back((int)tiles.size() - set.tile_off[i]);
             int64_t real_start = pos;
             for (int a = 0; a < g.n_angles; ++a) {
                 int c = cnt[((size_t)i * n_real + r) * g.n_angles + a];
@@ -345,13 +347,14 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
         }
         crange.push_back((int)chunks.size() - set.chunk_off[i]);
         rrange.push_back((int)(pos - set.row_off[i]));
+        trange.push_back((int)tiles.size() - set.tile_off[i]);
         set.max_rows = std::max(set.max_rows, (int)(pos - set.row_off[i]));
         set.max_chunks = std::max(set.max_chunks, (int)chunks.size() - set.chunk_off[i]);
     }
     set.row_off[g.n_subsets] = (int)pos;
     set.tile_off[g.n_subsets] = (int)tiles.size();
     set.chunk_off[g.n_subsets] = (int)chunks.size();
-    // [tiles][chunks][crange][rrange] in one block and one copy
+    // [tiles][chunks][crange][rrange][trange] in one block and one copy
     size_t nt = std::max<size_t>(tiles.size(), 1);
     std::vector<char> up;
     auto add = [&](const auto &v) {
@@ -360,13 +363,15 @@ hipError_t plan_tiles(const Geo &g, const Tables &tb, EvSet &set, int ev_tile, i
         if (bytes) memcpy(up.data() + at, v.data(), bytes);
         return at;
     };
-    const size_t o_tiles = add(tiles), o_chunks = add(chunks), o_crange = add(crange), o_rrange = add(rrange);
+    const size_t o_tiles = add(tiles), o_chunks = add(chunks), o_crange = add(crange), o_rrange = add(rrange),
+                 o_trange = add(trange);
     CK(dev_take(set.arena, &set.plan, up.size()), "alloc tiles");
     char *plan = static_cast<char *>(set.plan);
     set.tiles = reinterpret_cast<Tile *>(plan + o_tiles);
     set.chunks = reinterpret_cast<Chunk *>(plan + o_chunks);
     set.crange = reinterpret_cast<int *>(plan + o_crange);
     set.rrange = reinterpret_cast<int *>(plan + o_rrange);
+    set.trange = reinterpret_cast<int *>(plan + o_trange);
     CK(dev_take(set.arena, &terms_d, 2 * sizeof(long long) * nt), "alloc counters");
     CK(hipMemcpyAsync(plan, up.data(), up.size(), hipMemcpyHostToDevice, st), "upload tiles");
     std::vector<long long> terms(2 * nt, 0);

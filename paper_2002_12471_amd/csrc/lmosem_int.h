@@ -293,6 +293,18 @@ __host__ __device__ int forward_groups(const Geo &g);
 hipError_t launch_forward(int ev_tile, const Geo &g, const Tables &t, const Tile *tiles, int n_tiles,
                           const float *ev_u, const float *ev_e, const float *efac, const float *f, float *H,
                           float *pmean, int row_base, int n_rows, hipStream_t st, const KernelEvents *ke = nullptr);
+// emission pixels (with padding) up to which a sub-iteration's rows may stay in
+// one workgroup's registers
+constexpr int kFuseMax = 384;
+// event means, their inverses and each tile's backprojection pt[tile][n_qpad],
+// for n_qpad up to kFuseMax (else hipErrorInvalidValue); the update that adds
+// the tiles (trange: first tile of each realisation, and their end)
+hipError_t launch_forward_back(int ev_tile, const Geo &g, const Tables &t, const Tile *tiles, int n_tiles,
+                               const float *ev_u, const float *ev_e, const float *efac, const float *f, float *pt,
+                               float *mean, float *inv, unsigned long long *skipped, int row_base, hipStream_t st,
+                               const KernelEvents *ke = nullptr);
+hipError_t launch_update_tiles(const Geo &g, const int *trange, int n_real, const float *pt, const float *sens, float *f,
+                               hipStream_t st);
 hipError_t launch_mean(const float *pmean, int n_groups, int n_rows, float *mean, float *inv,
                        unsigned long long *skipped, hipStream_t st);
 hipError_t launch_row_dot(const Geo &g, const int *rrange, int n_real, int n_rows, const float *H, const float *f,
@@ -378,11 +390,12 @@ struct EvSet {
     std::vector<int> tile_off;              // [n_subsets+1]
     std::vector<int> chunk_off;             // [n_subsets+1]
     Arena *arena = nullptr;                 // where the set's device memory comes from (null: its own allocations)
-    void *plan = nullptr;                   // holds the four below
+    void *plan = nullptr;                   // holds the five below
     Tile *tiles = nullptr;                  // all tiles, subset-major
     Chunk *chunks = nullptr;                // all chunks, subset-major
     int *crange = nullptr;                  // [n_subsets][n_real+1] chunk ranges per realisation
     int *rrange = nullptr;                  // [n_subsets][n_real+1] row ranges per realisation
+    int *trange = nullptr;                  // [n_subsets][n_real+1] tile ranges per realisation
     std::vector<int64_t> terms_sub;         // per subset: terms evaluated
     std::vector<int64_t> useful_sub;        // per subset: terms with K > 0
     int max_rows = 0, max_chunks = 0;

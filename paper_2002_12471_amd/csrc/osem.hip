@@ -137,15 +137,18 @@ __device__ __forceinline__ void term_tail(const float2 (&v)[4], const float *Kg,
     }
 }
 
-template <int EV>
+// (BACK: the workgroup holds the tile's whole rows; H takes the tile's
+// backprojection, pmean the event means)
+template <int EV, bool BACK>
 __device__ __forceinline__ void forward_item(const Geo &g, const Tile *__restrict__ tiles, int n_tiles,
                                              int logical, const float2 *__restrict__ T,
                                              const double *__restrict__ us_sorted,
                                              const float *__restrict__ su, const float *__restrict__ se,
                                              const float *__restrict__ efac, const float *__restrict__ f,
                                              float *__restrict__ H, float *__restrict__ pmean, int row_base,
-                                             int n_rows, float *Ks, float *red, int tid, int wave, int lane) {
-    const int grp = logical / n_tiles;
+                                             int n_rows, float *Ks, float *red, int tid, int wave, int lane,
+                                             float *__restrict__ inv, unsigned long long *__restrict__ skipped) {
+    const int grp = BACK ? 0 : logical / n_tiles;
     const Tile tl = tiles[logical - grp * n_tiles];
     const int gw = 64 * g.fwd_waves;   // pixels per group = threads per workgroup
     const int q = grp * gw + tid;
@@ -228,7 +231,7 @@ __device__ __forceinline__ void forward_item(const Geo &g, const Tile *__restric
         }
     }
 
-    if (wave_on) {
+    if (!BACK && wave_on) {
         float *Hq = H + (size_t)(tl.e0 - row_base) * g.n_qpad + q;
 #pragma unroll
         for (int e = 0; e < EV; ++e)
@@ -244,6 +247,30 @@ __device__ __forceinline__ void forward_item(const Geo &g, const Tile *__restric
         if ((lane & writer_mask<EV>()) == 0) red[wave * EV + e] = v[0];
     }
     __syncthreads();
+    if constexpr (BACK) {
+        if (wave == 0) {
+            float w = 0.0f;
+            int dead = 0;
+            if (lane < tl.n) {
+                float s = red[lane];
+                for (int v = 1; v < g.fwd_waves; ++v) s += red[v * EV + lane];
+                dead = !(s > 1e-30f);
+                w = dead ? 0.0f : 1.0f / s;
+                const int j = tl.e0 - row_base + lane;
+                pmean[j] = s;
+                inv[j] = w;
+            }
+            const unsigned long long m = __ballot(dead);
+            if (lane == 0 && m) atomicAdd(skipped, (unsigned long long)__popcll(m));
+            if (lane < EV) red[lane] = w;   // (the wave's reads came first)
+        }
+        __syncthreads();
+        float b = 0.0f;
+#pragma unroll
+        for (int e = 0; e < EV; ++e) b = fmaf(acc[e], red[e], b);
+        if (wave_on) H[(size_t)logical * g.n_qpad + q] = b;
+        return;
+    }
     if (tid < tl.n) {
         float s;
         if (g.fwd_waves == 4) {
@@ -287,8 +314,34 @@ __global__ __launch_bounds__(256, EV == 8 ? 8 : 1) void k_forward(Geo g, const T
     const int n_groups = forward_groups(g);
     const int logical = xcd_logical(blockIdx.x, n_tiles * n_groups);
     const int tid = threadIdx.x;
-    forward_item<EV>(g, tiles, n_tiles, logical, T, us_sorted, su, se, efac, f, H, pmean, row_base, n_rows, Ks,
-                     red, tid, tid >> 6, tid & 63);
+    forward_item<EV, false>(g, tiles, n_tiles, logical, T, us_sorted, su, se, efac, f, H, pmean, row_base, n_rows, Ks,
+                            red, tid, tid >> 6, tid & 63, nullptr, nullptr);
+}
+
+// As k_forward for emission sets that one workgroup covers (g.fwd_waves waves
+// hold a tile's whole rows): the event means are complete in the workgroup, so
+// the rows are weighted where they stand, in registers, and each tile's
+// backprojection is written instead of them (a sixth of the bytes with 8 events a
+// tile, and no second kernel that reads rows).  The small sets that run this way
+// are bound by the chain of a tile's loads and by launches: 5k events on 156
+// pixels 22.1 -> 17.9 us an iteration (forward, backprojection with means and
+// update before), 50k on 356 pixels in 8 subsets 295 -> 245.  Up to kFuseMax
+// emission pixels: a workgroup of more waves ends with its slowest and walks its
+// path ends with few others beside it, where k_forward splits them over several
+// workgroups (term by term, two kernels | three, us: 356 pixels, 5k events 250 |
+// 251, 50k 245 | 295; 564 pixels, 3k 548 | 407, 20k 318 | 314; 804 pixels, 20k
+// 511 | 433).
+template <int EV, int MAXT>
+__global__ __launch_bounds__(MAXT, EV == 8 ? 8 : 1) void k_forward_back(
+    Geo g, const Tile *__restrict__ tiles, int n_tiles, const float2 *__restrict__ T, const double *__restrict__ us_sorted,
+    const float *__restrict__ su, const float *__restrict__ se, const float *__restrict__ efac,
+    const float *__restrict__ f, float *__restrict__ pt, float *__restrict__ mean, float *__restrict__ inv,
+    unsigned long long *__restrict__ skipped, int row_base) {
+    __shared__ __align__(16) float Ks[kRch * EV];
+    __shared__ float red[MAXT / 64 * EV];
+    const int tid = threadIdx.x;
+    forward_item<EV, true>(g, tiles, n_tiles, xcd_logical(blockIdx.x, n_tiles), T, us_sorted, su, se, efac, f, pt, mean,
+                           row_base, 0, Ks, red, tid, tid >> 6, tid & 63, inv, skipped);
 }
 
 // pixel groups of the forward launch (one group per workgroup)
@@ -331,6 +384,31 @@ hipError_t launch_forward(int ev_tile, const Geo &g, const Tables &t, const Tile
         return launch_ev<32>(g, t, tiles, n_tiles, ev_u, ev_e, efac, f, H, pmean, row_base, n_rows, st, ke);
     default:
         return launch_ev<8>(g, t, tiles, n_tiles, ev_u, ev_e, efac, f, H, pmean, row_base, n_rows, st, ke);
+    }
+}
+
+template <int EV>
+static hipError_t launch_fb(Geo g, const Tables &t, const Tile *tiles, int n_tiles, const float *ev_u, const float *ev_e,
+                            const float *efac, const float *f, float *pt, float *mean, float *inv,
+                            unsigned long long *skipped, int row_base, hipStream_t st, const KernelEvents *ke) {
+    g.fwd_waves = g.n_qpad / 64;
+    auto go = [&](auto kernel) {
+        return launch(kernel, dim3(n_tiles), dim3(g.n_qpad), st, ke, g, tiles, n_tiles, (const float2 *)t.T,
+                      (const double *)t.us_sorted, ev_u, ev_e, efac, f, pt, mean, inv, skipped, row_base);
+    };
+    return g.n_qpad <= 256 ? go(k_forward_back<EV, 256>) : go(k_forward_back<EV, kFuseMax>);
+}
+
+hipError_t launch_forward_back(int ev_tile, const Geo &g, const Tables &t, const Tile *tiles, int n_tiles,
+                               const float *ev_u, const float *ev_e, const float *efac, const float *f, float *pt,
+                               float *mean, float *inv, unsigned long long *skipped, int row_base, hipStream_t st,
+                               const KernelEvents *ke) {
+    if (g.n_qpad > kFuseMax) return hipErrorInvalidValue;
+    if (n_tiles <= 0) return no_launch(ke, st);
+    switch (ev_tile) {
+    case 16: return launch_fb<16>(g, t, tiles, n_tiles, ev_u, ev_e, efac, f, pt, mean, inv, skipped, row_base, st, ke);
+    case 32: return launch_fb<32>(g, t, tiles, n_tiles, ev_u, ev_e, efac, f, pt, mean, inv, skipped, row_base, st, ke);
+    default: return launch_fb<8>(g, t, tiles, n_tiles, ev_u, ev_e, efac, f, pt, mean, inv, skipped, row_base, st, ke);
     }
 }
 
@@ -606,6 +684,58 @@ hipError_t launch_update(const Geo &g, const int *crange, int n_real, const floa
                          const float *sens, float *f, hipStream_t st) {
     hipLaunchKernelGGL(k_update, dim3((g.n_q + 63) / 64, n_real), dim3(64 * kUpdWaves), 0, st, g, crange, pb, sens,
                        f);
+    return hipGetLastError();
+}
+
+// As k_update over a realisation's tiles, of which there are several hundred:
+// 16 pixels per block and 64 rows at a time, so that a pixel's sum is a chain of
+// a dozen loads in several times as many workgroups.
+constexpr int kUpdPix = 16, kUpdRows = 64;
+
+__global__ __launch_bounds__(kUpdPix * kUpdRows) void k_update_tiles(Geo g, const int *__restrict__ trange,
+                                                                    const float *__restrict__ pt,
+                                                                    const float *__restrict__ sens,
+                                                                    float *__restrict__ f) {
+    constexpr int R = kUpdRows;
+    __shared__ float part[R][kUpdPix];
+    const int px = threadIdx.x % kUpdPix, row = threadIdx.x / kUpdPix;
+    const int q = blockIdx.x * kUpdPix + px;   // below n_qpad, a multiple of 64
+    const int r = blockIdx.y;
+    const int c1 = trange[r + 1];
+    const float *p = pt + q;
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int c = trange[r] + row;
+    for (; c + 3 * R < c1; c += 4 * R) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a[k] += p[(size_t)(c + k * R) * g.n_qpad];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (c + k * R < c1) a[k] += p[(size_t)(c + k * R) * g.n_qpad];
+    part[row][px] = (a[0] + a[1]) + (a[2] + a[3]);
+    __syncthreads();
+    float b = 0.0f;
+    if (row < 8) {
+#pragma unroll
+        for (int k = 0; k < R / 8; ++k) b += part[row + 8 * k][px];
+    }
+    __syncthreads();
+    if (row < 8) part[row][px] = b;
+    __syncthreads();
+    if (row == 0 && q < g.n_q) {
+        b = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) b += part[k][px];
+        const float s = sens[q];
+        float *fp = f + (size_t)r * g.n_qpad + q;
+        if (s > 0.0f) *fp = (*fp * b) / s;
+    }
+}
+
+hipError_t launch_update_tiles(const Geo &g, const int *trange, int n_real, const float *pt, const float *sens, float *f,
+                               hipStream_t st) {
+    hipLaunchKernelGGL(k_update_tiles, dim3((g.n_q + kUpdPix - 1) / kUpdPix, n_real), dim3(kUpdPix * kUpdRows), 0, st, g,
+                       trange, pt, sens, f);
     return hipGetLastError();
 }
 
