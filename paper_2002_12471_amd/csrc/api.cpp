@@ -306,15 +306,13 @@ size_t flux_set_floats(const lmosem_ctx *c, const EvSet &v, int max_list, int ma
 // angles: 3k 524 | 459, 20k 483 | 717; 2832 pixels, 2.5k 233 | 349; 5736
 // pixels, 8 angles: 188 events 520 | 502, 1250 395 | 620; 564 pixels, 12.5k 67
 // | 79; 356 pixels, 12.5k 58 | 50; 156 pixels, 50k 74 | 70, 200k 141 | 201.
-// A call that loads its set for itself (sub_iters sub-iterations) also fills
-// the path table, and walks the path ends in tiles that nobody tuned: 10
-// iterations of 1k events took 13.9 ms term by term and 12.7 ms through the
-// stages on 1436 pixels, 101 and 84 ms on 5736.  The table is counted whether
-// the context holds it yet or not, so that a repeated call gives the same bits;
-// where the stages win by it alone, later calls could have been shorter (2
-// iterations of 1k events on 120 angles: 1.26 ms, 1.16 beside a table that took
-// 6.4).
-bool flux_faster(const lmosem_ctx *c, const EvSet &v, int64_t sub_iters) {
+// A call that loads its set for itself walks the path ends in tiles that nobody
+// tuned (10 iterations of 1k events: 13.9 ms term by term and 12.7 through the
+// stages on 1436 pixels, 101 and 84 on 5736).  What the path table takes to fill
+// is not counted: a context's first such call pays for it (2 ms on 804 pixels, 6.4
+// on 1436), every later one gains (10 iterations of 20k events on 804 pixels 6.0
+// ms, 7.6 through the stages).
+bool flux_faster(const lmosem_ctx *c, const EvSet &v, bool tuned, bool fused) {
     const Geo &g = c->g;
     if (!g.scatter) return true;
     const int n_list = (g.n_angles + g.n_subsets - 1) / g.n_subsets;
@@ -322,9 +320,9 @@ bool flux_faster(const lmosem_ctx *c, const EvSet &v, int64_t sub_iters) {
     const int grp = std::max(1, flux_group(g, c->fg, own ? own : c->fws_floats, v.n_real, n_list));
     const double groups = (v.n_real + grp - 1) / grp, n_p = g.n_p, rows = v.max_rows;
     const double terms = (double)*std::max_element(v.terms_sub.begin(), v.terms_sub.end());
-    double direct = 20 + terms * g.n_qpad / g.n_q / 9e6 + (sub_iters ? 0.105 : 0.07) * v.max_ranks + rows * g.n_qpad * 1e-6;
-    if (sub_iters && c->lazy_table)   // at 310 GB/s
-        direct += 8.0 * g.n_angles * g.n_rpad * g.n_qpad / 3.1e5 / (double)sub_iters;
+    // (in one kernel fewer launches, and no rows)
+    const double direct = terms * g.n_qpad / g.n_q / 9e6 + (tuned ? 0.07 : 0.105) * v.max_ranks +
+                          (fused ? 14 : 20 + rows * g.n_qpad * 1e-6);
     const double flux = (45 + 0.055 * v.max_ranks) * groups + 3e-4 * rows +
                         v.n_real * (1.05e-7 * n_list * n_p * c->fg.N * c->fg.K + 6e-6 * n_p * n_p);
     return flux < direct;
@@ -392,9 +390,9 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
     return LMOSEM_OK;
 }
 
-// sub_iters: of a call that iterates on its set (0: one sub-iteration)
+// iterates: the call goes through the set's subsets
 lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batch *batch, int force_subset,
-                       lmosem_evset **out, bool kept = false, int64_t sub_iters = 0) {
+                       lmosem_evset **out, bool kept = false, bool iterates = false) {
     lmosem_status st = LMOSEM_OK;
     if (c->surrogate && !c->net) return set_err(c, LMOSEM_ESTATE, "scatter_model 2 needs a network (lmosem_set_surrogate)");
     if (!check_arrays(c, ev, st)) return st;
@@ -430,14 +428,14 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
         free_set(s);
         return e == hipErrorOutOfMemory ? set_err(c, LMOSEM_ENOMEM, why) : set_err(c, LMOSEM_EDEVICE, why);
     }
-    s->flux = c->flux && (kept || sub_iters > 0 ? flux_faster(c, s->s, sub_iters)
-                                                : s->s.terms_sub[std::max(force_subset, 0)] > flux_from(c));
+    s->fused = !c->surrogate && c->pixel_waves == 0 && c->g.n_qpad <= kFuseMax;
+    s->flux = c->flux && (kept || iterates ? flux_faster(c, s->s, kept, s->fused)
+                                           : s->s.terms_sub[std::max(force_subset, 0)] > flux_from(c));
     if (c->flux && !s->flux && !c->t.T) {   // the path table, held since the first list-mode call
         e = build_path_table(c->g, c->t, c->st);
         if (e != hipSuccess && e != hipErrorOutOfMemory) { free_set(s); return dev_err(c, "path table", e); }
         if (e != hipSuccess) { (void)hipGetLastError(); s->flux = true; }
     }
-    s->fused = !c->surrogate && c->pixel_waves == 0 && c->g.n_qpad <= kFuseMax;
     lmosem_status ws = s->flux ? plan_flux(c, s, force_subset, kept) : LMOSEM_OK;
     if (ws == LMOSEM_OK) ws = alloc_workspace(c, s);
     if (ws != LMOSEM_OK) { free_set(s); return ws; }
@@ -999,7 +997,7 @@ lmosem_status lmosem_reconstruct(lmosem_ctx *c, const lmosem_events *ev, const l
         if (bad) return set_err(c, LMOSEM_ERANGE, "initial image negative or not finite on the support");
     }
     lmosem_evset *s = nullptr;
-    lmosem_status st = load_set(c, ev, batch, -1, &s, false, (int64_t)n_iters * c->g.n_subsets);
+    lmosem_status st = load_set(c, ev, batch, -1, &s, false, true);
     if (st != LMOSEM_OK) return st;
     e = launch_gather_image(g, c->t, init_dev, s->s.n_real, 0, s->f, 1, c->st);
     if (e != hipSuccess) { free_set(s); return dev_err(c, "init", e); }
