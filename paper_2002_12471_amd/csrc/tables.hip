@@ -154,41 +154,48 @@ __device__ inline float2 path_code(const Geo &g, PathW p, double log2_gnorm) {
 }
 
 // Path table and per-angle sensitivities.  One thread per (angle, emission
-// pixel q); it walks the path ends in rank order.
+// pixel q, part of the path ends); it walks its `per` ends in rank order, each a
+// chain of some hundred FP64 operations, so small maps are bound by that chain (156
+// pixels, 16 angles: 324 us with one part, 24 with 18) and large ones by FP64
+// issue (1436 pixels, 120 angles: 6.4 ms with the sensitivities in one part, 5.9 in
+// three, 4.4 without them; 2 GB written).
+template <bool SENS>
 __global__ void k_path_table(Geo g, const int *__restrict__ p_pix, const double *__restrict__ cs,
                              const double *__restrict__ L, const double *__restrict__ Bt,
                              const int *__restrict__ s_sorted, const double *__restrict__ D_sorted,
-                             float2 *__restrict__ T, double *__restrict__ sens_a, float *__restrict__ prim) {
+                             float2 *__restrict__ T, int per, double *__restrict__ sens_a, float *__restrict__ prim) {
     int q = blockIdx.x * blockDim.x + threadIdx.x;
     int a = blockIdx.y;
     if (q >= g.n_qpad) return;
+    const int r0 = blockIdx.z * per, r1 = min(r0 + per, g.n_p);
+    if (SENS) sens_a += (size_t)blockIdx.z * g.n_angles * g.n_qpad;
     // T is null when only the sensitivity and the primary weights are wanted
     float2 *Ta = T ? T + (size_t)a * g.n_rpad * g.n_qpad + q : nullptr;
-    if (Ta)
+    if (Ta && blockIdx.z == 0)
         for (int r = g.n_p; r < g.n_rpad; ++r) Ta[(size_t)r * g.n_qpad] = make_float2(kNegHuge, 0.0f);
     if (q >= g.n_q) {
         if (Ta)
-            for (int r = 0; r < g.n_p; ++r) Ta[(size_t)r * g.n_qpad] = make_float2(kNegHuge, 0.0f);
-        sens_a[(size_t)a * g.n_qpad + q] = 0.0;
+            for (int r = r0; r < r1; ++r) Ta[(size_t)r * g.n_qpad] = make_float2(kNegHuge, 0.0f);
+        if (SENS) sens_a[(size_t)a * g.n_qpad + q] = 0.0;
         return;
     }
     const double nx = cs[2 * a], ny = cs[2 * a + 1];
     const double log2_gnorm = -log2(sqrt(2.0 * M_PI) * g.sig_e);
     const double s2 = M_SQRT2 * g.sig_e;
     double sens = 0.0;
-    for (int r = 0; r < g.n_p; ++r) {
+    for (int r = r0; r < r1; ++r) {
         const size_t o = (size_t)a * g.n_p + r;
         const int s = s_sorted[o];
         const PathW pw = path_weight(g, p_pix, L, Bt, nx, ny, a, q, s);
         const float2 code = path_code(g, pw, log2_gnorm);
-        if (pw.w > 0.0) {
+        if (SENS && pw.w > 0.0) {
             const double win = 0.5 * (erf((g.win_hi - pw.ep) / s2) - erf((g.win_lo - pw.ep) / s2));
             sens += pw.w * D_sorted[o] * win;
         }
-        if (s == q) prim[(size_t)a * g.n_p + q] = code.x;
+        if (SENS && s == q) prim[(size_t)a * g.n_p + q] = code.x;
         if (Ta) Ta[(size_t)r * g.n_qpad] = code;
     }
-    sens_a[(size_t)a * g.n_qpad + q] = sens;
+    if (SENS) sens_a[(size_t)a * g.n_qpad + q] = sens;
 }
 
 // Near-field band of emission pixel q at angle a: the path ends whose detector
@@ -237,19 +244,30 @@ __global__ void k_band_table(Geo g, int band_w, const int *__restrict__ p_pix, c
     }
 }
 
-// sens[i][q] = T sum_{a mod N_s == i} sens_a[a][q]; sens_all = sum over subsets.
-__global__ void k_sens_reduce(Geo g, const double *__restrict__ sens_a, float *__restrict__ sens,
-                              float *__restrict__ sens_all) {
-    int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= g.n_qpad) return;
-    double tot = 0.0;
-    for (int i = 0; i < g.n_subsets; ++i) {
-        double s = 0.0;
-        for (int a = i; a < g.n_angles; a += g.n_subsets) s += sens_a[(size_t)a * g.n_qpad + q];
-        sens[(size_t)i * g.n_qpad + q] = (float)(g.acq_time * s);
-        tot += s;
+// sens[i][q] = T sum_{a mod N_s == i} sens_a[.][a][q] over angles and parts;
+// sens_all the same over all angles.  (16 waves a pixel block: a thread's chain of
+// loads stays at some twenty.)
+constexpr int kSensRows = 16;
+
+__global__ __launch_bounds__(64 * kSensRows) void k_sens_reduce(Geo g, int n_parts, const double *__restrict__ sens_a,
+                                                               float *__restrict__ sens, float *__restrict__ sens_all) {
+    __shared__ double part[kSensRows][64];
+    const int lane = threadIdx.x & 63, row = threadIdx.x >> 6, i = blockIdx.y;
+    const int q = blockIdx.x * 64 + lane;   // n_qpad is a multiple of 64
+    const bool all = i == g.n_subsets;
+    const int a0 = all ? 0 : i, step = all ? 1 : g.n_subsets;
+    const int n = (g.n_angles - a0 + step - 1) / step * n_parts;
+    double s = 0.0;
+#pragma unroll 4
+    for (int k = row; k < n; k += kSensRows) {
+        const int a = a0 + k / n_parts * step, p = k % n_parts;
+        s += sens_a[((size_t)p * g.n_angles + a) * g.n_qpad + q];
     }
-    sens_all[q] = (float)(g.acq_time * tot);
+    part[row][lane] = s;
+    __syncthreads();
+    if (row) return;
+    for (int k = 1; k < kSensRows; ++k) s += part[k][lane];
+    (all ? sens_all : sens + (size_t)i * g.n_qpad)[q] = (float)(g.acq_time * s);
 }
 
 // Geometry every context needs at once: line integrals, scatter-point
@@ -293,21 +311,24 @@ hipError_t build_base(const Geo &g, Tables &t, hipStream_t st, std::string &err,
     return hipSuccess;
 }
 
+// path ends a thread walks: enough parts for eight waves on every SIMD, none
+// shorter than eight ends
+static int path_part(const Geo &g) {
+    const int64_t waves = (int64_t)(g.n_qpad / 64) * g.n_angles;
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(g.n_p / 8, (8192 + waves - 1) / waves));
+    return (g.n_p + parts - 1) / parts;
+}
+
 // The path table alone, for contexts whose sensitivities came without it.
 hipError_t build_path_table(const Geo &g, Tables &t, hipStream_t st) {
-    double *sens_a = nullptr;
-    float *prim = nullptr;
+    const int per = path_part(g);
     hipError_t e = hipMalloc(&t.T, sizeof(float2) * (size_t)g.n_angles * g.n_rpad * g.n_qpad);
-    if (e == hipSuccess) e = hipMalloc(&sens_a, sizeof(double) * g.n_angles * g.n_qpad);
-    if (e == hipSuccess) e = hipMalloc(&prim, sizeof(float) * g.n_angles * g.n_p);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_path_table, dim3((g.n_qpad + 63) / 64, g.n_angles), dim3(64), 0, st, g, t.p_pix, t.cs, t.Ld,
-                           t.Bt, t.s_sorted, t.D_sorted, t.T, sens_a, prim);
+        hipLaunchKernelGGL(k_path_table<false>, dim3(g.n_qpad / 64, g.n_angles, (g.n_p + per - 1) / per), dim3(64), 0, st, g,
+                           t.p_pix, t.cs, t.Ld, t.Bt, t.s_sorted, t.D_sorted, t.T, per, (double *)nullptr, (float *)nullptr);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    hipFree(sens_a);
-    hipFree(prim);
     if (e != hipSuccess) { hipFree(t.T); t.T = nullptr; }
     return e;
 }
@@ -321,6 +342,7 @@ hipError_t build_paths(const Geo &g, Tables &t, bool store_paths, bool store_ban
     double *sens_a = nullptr;
     int *band_len = nullptr;
     size_t nT = (size_t)g.n_angles * g.n_rpad * g.n_qpad;
+    const int per = path_part(g), n_parts = (g.n_p + per - 1) / per;
     auto fail = [&](const char *what, hipError_t code) {
         char buf[256];
         snprintf(buf, sizeof buf, "%s: %s", what, hipGetErrorString(code));
@@ -329,15 +351,15 @@ hipError_t build_paths(const Geo &g, Tables &t, bool store_paths, bool store_ban
         return code;
     };
 #define CK(call, what) do { e = (call); if (e != hipSuccess) return fail(what, e); } while (0)
-    CK(hipMalloc(&sens_a, sizeof(double) * g.n_angles * g.n_qpad), "alloc sens_a");
+    CK(hipMalloc(&sens_a, sizeof(double) * n_parts * g.n_angles * g.n_qpad), "alloc sens_a");
     if (store_paths) CK(hipMalloc(&t.T, sizeof(float2) * nT), "alloc path table");
     CK(hipMalloc(&t.prim, sizeof(float) * g.n_angles * g.n_p), "alloc primary weights");
     CK(hipMalloc(&t.sens, sizeof(float) * g.n_subsets * g.n_qpad), "alloc sens");
     CK(hipMalloc(&t.sens_all, sizeof(float) * g.n_qpad), "alloc sens_all");
     bytes += (int64_t)((store_paths ? sizeof(float2) * nT : 0) + sizeof(float) * g.n_angles * g.n_p +
                        sizeof(float) * (g.n_subsets + 1) * g.n_qpad);
-    hipLaunchKernelGGL(k_path_table, dim3((g.n_qpad + 63) / 64, g.n_angles), dim3(64), 0, st, g,
-                       t.p_pix, t.cs, t.Ld, t.Bt, t.s_sorted, t.D_sorted, t.T, sens_a, t.prim);
+    hipLaunchKernelGGL(k_path_table<true>, dim3(g.n_qpad / 64, g.n_angles, n_parts), dim3(64), 0, st, g,
+                       t.p_pix, t.cs, t.Ld, t.Bt, t.s_sorted, t.D_sorted, t.T, per, sens_a, t.prim);
     CK(hipGetLastError(), "path table");
     if (store_band && g.scatter) {
         CK(hipMalloc(&t.band_lo, sizeof(int) * g.n_angles * g.n_p), "alloc band ranges");
@@ -359,8 +381,8 @@ hipError_t build_paths(const Geo &g, Tables &t, bool store_paths, bool store_ban
         CK(hipGetLastError(), "near-field table");
         bytes += (int64_t)(sizeof(float2) * nb + sizeof(int) * g.n_angles * g.n_p);
     }
-    hipLaunchKernelGGL(k_sens_reduce, dim3((g.n_qpad + 255) / 256), dim3(256), 0, st, g, sens_a,
-                       t.sens, t.sens_all);
+    hipLaunchKernelGGL(k_sens_reduce, dim3(g.n_qpad / 64, g.n_subsets + 1), dim3(64 * kSensRows), 0, st, g, n_parts,
+                       sens_a, t.sens, t.sens_all);
     CK(hipGetLastError(), "sensitivity");
     CK(hipStreamSynchronize(st), "table build");
     hipFree(sens_a); hipFree(band_len);
