@@ -769,7 +769,8 @@ def main():
         roof = None
     roof = roof or {
         "bound": "alu",
-        "kernel": "k_forward (forward projection)",
+        "kernel": "k_forward (forward projection)" if ks["backproject_launches"] else
+                  "k_forward_back (forward projection, means and backprojection)",
         "achieved": achieved_terms * FLOPS_PER_TERM / 1e12,
         "peak": peak_terms * FLOPS_PER_TERM / 1e12,
         "unit": "TFLOP/s",
