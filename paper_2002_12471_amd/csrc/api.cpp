@@ -273,8 +273,8 @@ std::string cap_msg(const lmosem_ctx *c, const char *what, int64_t more) {
 
 // Supports whose calls on events of one sub-iteration (forward, backprojection,
 // subset update) all run through the flux stages: from 512 pixels the path
-// table that the term-by-term kernels read takes more time to fill (4.4 ms and
-// 2 GB on 1436 pixels) than they save on few events.
+// table that the term-by-term kernels read takes more time to fill (0.8 ms and
+// 2 GB on 1436 pixels, 19 ms and 32 GB on 5736) than they save on few events.
 constexpr int kFluxAlways = 512;
 
 bool flux_always(const lmosem_ctx *c) { return c->flux_fits && c->g.n_p >= kFluxAlways; }
@@ -309,8 +309,8 @@ size_t flux_set_floats(const lmosem_ctx *c, const EvSet &v, int max_list, int ma
 // A call that loads its set for itself walks the path ends in tiles that nobody
 // tuned (10 iterations of 1k events: 13.9 ms term by term and 12.7 through the
 // stages on 1436 pixels, 101 and 84 on 5736).  What the path table takes to fill
-// is not counted: a context's first such call pays for it (1.3 ms on 804 pixels, 4.4
-// on 1436), every later one gains (10 iterations of 20k events on 804 pixels 6.0
+// is not counted: a context's first such call pays for it (0.8 ms on
+// 1436 pixels), every later one gains (10 iterations of 20k events on 804 pixels 6.0
 // ms, 7.6 through the stages).
 bool flux_faster(const lmosem_ctx *c, const EvSet &v, bool tuned, bool fused) {
     const Geo &g = c->g;

@@ -158,7 +158,7 @@ __device__ inline float2 path_code(const Geo &g, PathW p, double log2_gnorm) {
 // chain of some hundred FP64 operations, so small maps are bound by that chain (156
 // pixels, 16 angles: 324 us with one part, 24 with 18) and large ones by FP64
 // issue (1436 pixels, 120 angles: 6.4 ms with the sensitivities in one part, 5.9 in
-// three, 4.4 without them; 2 GB written).
+// three).
 template <bool SENS>
 __global__ void k_path_table(Geo g, const int *__restrict__ p_pix, const double *__restrict__ cs,
                              const double *__restrict__ L, const double *__restrict__ Bt,
@@ -319,16 +319,103 @@ static int path_part(const Geo &g) {
     return (g.n_p + parts - 1) / parts;
 }
 
+// What of a scattered path's code depends on the angle and its pixel offset
+// alone (offset index (dj + ny - 1) (2 nx - 1) + di + nx - 1): the code's alpha
+// without the scatter point's factor and attenuation, and the attenuation ratio
+// in bits; beta.
+__global__ __launch_bounds__(256) void k_table_terms(Geo g, const double *__restrict__ cs, int a0,
+                                                     double2 *__restrict__ tab, float *__restrict__ beta) {
+    const int w = 2 * g.nx - 1, n = w * (2 * g.ny - 1);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, a = a0 + blockIdx.y;
+    if (i >= n) return;
+    const int di = i % w - (g.nx - 1), dj = i / w - (g.ny - 1);
+    double2 t = make_double2(0.0, 0.0);
+    float b = 0.0f;
+    if (di != 0 || dj != 0) {
+        const Flight fl = flight(g, di, dj, cs[2 * a], cs[2 * a + 1]);
+        const float2 code = path_code(g, PathW{1.0, fl.ep}, -log2(sqrt(2.0 * M_PI) * g.sig_e));
+        // (path_code's sum before it is rounded)
+        const double ec = fl.ep - g.e_c, bd = 2.0 * g.c2 * ec;
+        b = code.y;
+        t.x = log2(fl.psi / g.psi_bar) - log2(sqrt(2.0 * M_PI) * g.sig_e) - g.c2 * ec * ec + (bd - (double)b) * ec;
+        t.y = fl.rho * M_LOG2E;
+    }
+    tab[(size_t)blockIdx.y * n + i] = t;
+    beta[(size_t)blockIdx.y * n + i] = b;
+}
+
+__global__ __launch_bounds__(256) void k_log2(const double *__restrict__ x, size_t n, double *__restrict__ y) {
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) y[i] = x[i] > 0.0 ? log2(x[i]) : (double)kNegHuge;
+}
+
+// The path table from those terms: two additions a path, so its loads and its
+// 8 bytes written bound it: 1436 pixels, 120 angles 4.4 -> 0.83 ms with the
+// terms (2.5 TB/s), 5736 pixels 56 -> 18.9 ms (31.7 GB), 564 pixels 0.61 -> 0.12.  An XCD takes a run of
+// angles, whose terms then stay in its L2.
+__global__ __launch_bounds__(64) void k_path_table_terms(Geo g, const int *__restrict__ p_pix, const double *__restrict__ L,
+                                                         const double *__restrict__ lB, const int *__restrict__ s_sorted,
+                                                         const double2 *__restrict__ tab, const float *__restrict__ beta,
+                                                         int a0, int per, int n_parts, float2 *__restrict__ T) {
+    const int item = xcd_logical(blockIdx.x, gridDim.x), n_qb = g.n_qpad / 64;
+    const int al = item / (n_qb * n_parts), rest = item - al * n_qb * n_parts, part = rest / n_qb;
+    const int a = a0 + al, q = (rest - part * n_qb) * 64 + threadIdx.x;
+    const int r0 = part * per, r1 = min(r0 + per, g.n_p);
+    float2 *Ta = T + (size_t)a * g.n_rpad * g.n_qpad + q;
+    const float2 none = make_float2(kNegHuge, 0.0f);
+    if (part == 0)
+        for (int r = g.n_p; r < g.n_rpad; ++r) Ta[(size_t)r * g.n_qpad] = none;
+    const bool on = q < g.n_q;
+    const int qc = min(q, g.n_q - 1), pq = p_pix[qc], w = 2 * g.nx - 1, n = w * (2 * g.ny - 1);
+    const size_t from = (size_t)al * n + (g.ny - 1 - pq / g.nx) * w + (g.nx - 1 - pq % g.nx);
+    const float2 own = path_code(g, PathW{exp(-L[(size_t)a * g.n_p + qc]), g.e0}, -log2(sqrt(2.0 * M_PI) * g.sig_e));
+#pragma unroll 4
+    for (int r = r0; r < r1; ++r) {
+        const int s = s_sorted[(size_t)a * g.n_p + r], ps = p_pix[s];
+        const size_t i = from + ps / g.nx * w + ps % g.nx;
+        const double lb = lB[(size_t)s * g.n_p + qc];
+        const double2 t = tab[i];
+        float2 code = make_float2((float)(lb + (t.x - t.y * L[(size_t)a * g.n_p + s])), beta[i]);
+        if (!(lb > (double)kNegHuge)) code = none;
+        if (s == qc) code = own;
+        Ta[(size_t)r * g.n_qpad] = on ? code : none;
+    }
+}
+
 // The path table alone, for contexts whose sensitivities came without it.
 hipError_t build_path_table(const Geo &g, Tables &t, hipStream_t st) {
-    const int per = path_part(g);
+    const int per = path_part(g), n_parts = (g.n_p + per - 1) / per;
     hipError_t e = hipMalloc(&t.T, sizeof(float2) * (size_t)g.n_angles * g.n_rpad * g.n_qpad);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_path_table<false>, dim3(g.n_qpad / 64, g.n_angles, (g.n_p + per - 1) / per), dim3(64), 0, st, g,
-                           t.p_pix, t.cs, t.Ld, t.Bt, t.s_sorted, t.D_sorted, t.T, per, (double *)nullptr, (float *)nullptr);
+    if (e != hipSuccess) { t.T = nullptr; return e; }
+    // terms of as many angles as 64 MB hold; without room for them beside the
+    // table every path's code is evaluated by itself
+    const size_t n_off = (size_t)(2 * g.nx - 1) * (2 * g.ny - 1), per_a = n_off * (sizeof(double2) + sizeof(float));
+    const int n_a = (int)std::min<size_t>(g.n_angles, std::max<size_t>(1, (size_t(64) << 20) / per_a));
+    const size_t n_b = (size_t)g.n_p * g.n_p;
+    char *mem = nullptr;
+    if (g.scatter && hipMalloc(&mem, n_b * sizeof(double) + 16 + per_a * n_a) == hipSuccess) {
+        double *lB = reinterpret_cast<double *>(mem);
+        double2 *tab = reinterpret_cast<double2 *>(mem + ((n_b * sizeof(double) + 15) & ~size_t(15)));
+        float *beta = reinterpret_cast<float *>(tab + n_off * n_a);
+        hipLaunchKernelGGL(k_log2, dim3((unsigned)((n_b + 255) / 256)), dim3(256), 0, st, t.Bt, n_b, lB);
+        e = hipGetLastError();
+        for (int a0 = 0; a0 < g.n_angles && e == hipSuccess; a0 += n_a) {
+            const int n = std::min(n_a, g.n_angles - a0);
+            hipLaunchKernelGGL(k_table_terms, dim3((unsigned)((n_off + 255) / 256), n), dim3(256), 0, st, g, t.cs, a0, tab,
+                               beta);
+            hipLaunchKernelGGL(k_path_table_terms, dim3((unsigned)(g.n_qpad / 64 * n_parts * n)), dim3(64), 0, st, g,
+                               t.p_pix, t.Ld, lB, t.s_sorted, tab, beta, a0, per, n_parts, t.T);
+            e = hipGetLastError();
+        }
+    } else {
+        (void)hipGetLastError();
+        hipLaunchKernelGGL(k_path_table<false>, dim3(g.n_qpad / 64, g.n_angles, n_parts), dim3(64), 0, st, g, t.p_pix, t.cs,
+                           t.Ld, t.Bt, t.s_sorted, t.D_sorted, t.T, per, (double *)nullptr, (float *)nullptr);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    const hipError_t done = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = done;
+    hipFree(mem);
     if (e != hipSuccess) { hipFree(t.T); t.T = nullptr; }
     return e;
 }
