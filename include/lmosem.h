@@ -280,9 +280,12 @@ lmosem_status lmosem_set_pixel_tile(lmosem_ctx *ctx, int32_t pixels);
  * replayed as a HIP graph (iterations estimated above 50 ms are replayed
  * without that comparison); re-plans the set with the fastest choices and
  * returns them (outputs may be NULL).  A set that runs through directional
- * flux has only the replay to choose.  With LMOSEM_TUNE_CACHE=<file> in the
+ * flux has only the replay to choose; one of at most 384 emission pixels is also
+ * timed in a single kernel (rows, means and backprojection of an event tile in
+ * one workgroup, of the whole emission set's width) for the three tiles.  With LMOSEM_TUNE_CACHE=<file> in the
  * environment the choice is looked up in / appended to that file, keyed by
- * support and emission-set sizes, angles, subsets, realisations and subset size.  Results do
+ * support and emission-set sizes, angles, subsets, realisations and subset size
+ * (and the route: " flux", " fused" for the single kernel).  Results do
  * not depend on the choice beyond FP32 summation order.  Synchronises. */
 lmosem_status lmosem_autotune(lmosem_ctx *ctx, lmosem_evset *set, int32_t *event_tile,
                               int32_t *chunk_rows, int32_t *use_graphs);

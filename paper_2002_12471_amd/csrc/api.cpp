@@ -296,6 +296,12 @@ size_t flux_set_floats(const lmosem_ctx *c, const EvSet &v, int max_list, int ma
     return flux_group(c->g, c->fg, floats, v.n_real, max_list) < 1 ? 0 : floats;
 }
 
+// Whether sets may run term by term in one kernel.  Sets that nobody tunes do (10
+// iterations with ingest, three kernels | one, ms: 5k events on 156 pixels 0.96 |
+// 0.59, 52 realisations of 2k in 4 subsets 3.4 | 2.0; 5 iterations of 50k on 356
+// pixels 1.8 | 1.4); the autotuner measures both.
+bool can_fuse(const lmosem_ctx *c) { return !c->surrogate && c->pixel_waves == 0 && c->g.n_qpad <= kFuseMax; }
+
 // Whether a set that iterates is faster through the flux stages, by what a
 // sub-iteration of its largest subset takes either way, in us.  Term by term
 // the events count: 9 terms/ps over whole waves of emission pixels, the rows
@@ -428,7 +434,7 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
         free_set(s);
         return e == hipErrorOutOfMemory ? set_err(c, LMOSEM_ENOMEM, why) : set_err(c, LMOSEM_EDEVICE, why);
     }
-    s->fused = !c->surrogate && c->pixel_waves == 0 && c->g.n_qpad <= kFuseMax;
+    s->fused = can_fuse(c);
     s->flux = c->flux && (kept || iterates ? flux_faster(c, s->s, kept, s->fused)
                                            : s->s.terms_sub[std::max(force_subset, 0)] > flux_from(c));
     if (c->flux && !s->flux && !c->t.T) {   // the path table, held since the first list-mode call
@@ -1502,7 +1508,7 @@ std::string tune_key(const lmosem_ctx *c, const lmosem_evset *s) {
     char buf[160];
     snprintf(buf, sizeof buf, "np=%d nq=%d na=%d ns=%d real=%d rows2^%d%s", c->g.n_p, c->g.n_q, c->g.n_angles,
              c->g.n_subsets,
-             s->s.n_real, lg, s->Hc ? "" : s->flux ? " flux" : s->fused ? " fused" : "");
+             s->s.n_real, lg, s->flux && !s->Hc ? " flux" : "");
     return buf;
 }
 
@@ -1576,8 +1582,9 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
     s->tuned = true;
     // a flux set without a row cache has nothing to tune but the replay
     const bool direct = !s->flux || s->Hc;
-    // one kernel instead of three: only its events per tile to choose
-    const bool fused = direct && s->fused && !s->Hc;
+    // term by term also in one kernel; a plan of it is stored under a key of its own
+    const bool both = direct && !s->Hc && can_fuse(c);
+    const std::string fused_key = key + " fused";
     // tune the computing path; a row cache is refilled by the next iteration
     struct Restore {
         lmosem_evset *s;
@@ -1588,11 +1595,17 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
     s->Hc = nullptr;
     s->rows_valid = false;
     s->flux = s->flux && !direct;
-    s->fused = fused;
+    s->fused = false;
     int best_ev = v.ev_tile, best_ch = v.chunk_rows, best_graph = -1, best_waves = v.fwd_waves;
     float fwd_ms = 0.0f;   // the fastest forward launch of the largest subset
+    // the fastest single kernel with its update, and its events per tile
+    float one_kernel = 3.4e38f;
+    int one_ev = best_ev;
     hipError_t e = hipSuccess;
-    if (tune_lookup(key, best_ev, best_ch, best_graph, best_waves)) {
+    if (both && tune_lookup(fused_key, best_ev, best_ch, best_graph, best_waves)) {
+        s->fused = true;
+        v.fwd_waves = best_waves;
+    } else if (tune_lookup(key, best_ev, best_ch, best_graph, best_waves)) {
         v.fwd_waves = best_waves;
     } else {
         best_graph = -1;
@@ -1615,6 +1628,10 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
         // candidates timed last
         float best = 3.4e38f;
         std::vector<float> cand_ms;
+        // (the single kernel counts dead events: the count is taken back)
+        unsigned long long *kept = reinterpret_cast<unsigned long long *>(s->ll);
+        if (both) e = hipMemcpyAsync(kept, c->skipped_dev, sizeof(*kept), hipMemcpyDeviceToDevice, c->st);
+        if (both && e == hipSuccess) e = launch_fill(s->f, (size_t)v.n_real * g.n_qpad, 1.0f, c->st);
         float sweep_ms = 0.0f;
         for (int sweep = 0; sweep < 2 && !c->surrogate && direct && e == hipSuccess; ++sweep) {
             if (sweep == 1 && sweep_ms >= 300.0f) break;
@@ -1622,18 +1639,23 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
             for (int ev : {8, 16, 32}) {
                 if (e != hipSuccess) break;
                 if ((e = plan_tiles(g, c->t, v, ev, v.chunk_rows, c->st, why)) != hipSuccess) break;
+                if (both) {
+                    float ms = 0.0f;
+                    e = time_ms(c, [&] {
+                        const hipError_t r = forward_back(c, s, big, c->st, nullptr);
+                        return r == hipSuccess ? update_tiles(c, s, big, c->st) : r;
+                    }, ms);
+                    if (e != hipSuccess) break;
+                    sweep_ms += 4.0f * ms;
+                    if (ms < one_kernel) { one_kernel = ms; one_ev = ev; }
+                }
                 for (int w : waves_opts) {
-                    if (fused && w != waves_opts[0]) break;
-                    if (!fused) v.fwd_waves = w;
+                    v.fwd_waves = w;
                     lmosem_status ws = alloc_workspace(c, s);
                     if (ws != LMOSEM_OK) return ws;
                     const Geo gw = set_geo(c, s);
                     float ms = 0.0f;
                     e = time_ms(c, [&] {
-                        if (fused) {
-                            const hipError_t r = forward_back(c, s, big, c->st, nullptr);
-                            return r == hipSuccess ? update_tiles(c, s, big, c->st) : r;
-                        }
                         return launch_forward(ev, gw, c->t, v.tiles + v.tile_off[big],
                                               v.tile_off[big + 1] - v.tile_off[big], v.u, v.e, v.efac, s->f, s->H,
                                               s->pmean, v.row_off[big], rows, c->st);
@@ -1642,7 +1664,7 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
                     sweep_ms += 4.0f * ms;   // warm-up and timed runs
                     if (sweep == 0) cand_ms.push_back(ms);
                     else cand_ms[ci] = std::min(cand_ms[ci], ms);
-                    if (cand_ms[ci] < best) { best = cand_ms[ci]; best_ev = ev; best_waves = fused ? v.fwd_waves : w; }
+                    if (cand_ms[ci] < best) { best = cand_ms[ci]; best_ev = ev; best_waves = w; }
                     ++ci;
                 }
             }
@@ -1651,7 +1673,8 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
         fwd_ms = best < 3.4e38f ? best : 0.0f;
         best = 3.4e38f;
         for (int ch : {64, 128, 256, 512, 1024, 2048, 4096}) {
-            if (e != hipSuccess || !direct || fused) break;
+            // (no chunks to choose where one kernel takes no longer than the rows alone)
+            if (e != hipSuccess || !direct || one_kernel <= fwd_ms) break;
             if ((e = plan_tiles(g, c->t, v, best_ev, ch, c->st, why)) != hipSuccess) break;
             lmosem_status ws = alloc_workspace(c, s);
             if (ws != LMOSEM_OK) return ws;
@@ -1672,7 +1695,12 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
             }, ms);
             if (e == hipSuccess && ms < best) { best = ms; best_ch = ch; }
         }
+        // (best: the chunks' five backprojections and updates)
+        if (both && e == hipSuccess && (one_kernel <= fwd_ms || one_kernel <= fwd_ms + 0.2f * best)) s->fused = true;
+        if (s->fused) best_ev = one_ev;
+        if (both && e == hipSuccess) e = hipMemcpyAsync(c->skipped_dev, kept, sizeof(*kept), hipMemcpyDeviceToDevice, c->st);
     }
+    if (both) restore.fused = s->fused;   // the choice stays
     if (e == hipSuccess) e = plan_tiles(g, c->t, v, best_ev, best_ch, c->st, why);
     if (e != hipSuccess) return dev_err(c, "autotune", e);
     lmosem_status ws = alloc_workspace(c, s);
@@ -1684,7 +1712,7 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
     // iterations)
     if (best_graph < 0 && fwd_ms * g.n_subsets > 50.0f) {
         best_graph = 1;
-        tune_store(key, best_ev, best_ch, best_graph, v.fwd_waves);
+        tune_store(s->fused ? fused_key : key, best_ev, best_ch, best_graph, v.fwd_waves);
     }
     if (best_graph < 0) {
         // one full iteration launched directly versus replayed as a graph
@@ -1698,7 +1726,7 @@ lmosem_status lmosem_autotune(lmosem_ctx *c, lmosem_evset *s, int32_t *event_til
         if (e == hipSuccess) e = time_ms(c, [&] { return one_iteration(c, s, false); }, ms_graph);
         if (e != hipSuccess) return dev_err(c, "autotune", e);
         best_graph = ms_graph < ms_direct ? 1 : 0;
-        tune_store(key, best_ev, best_ch, best_graph, v.fwd_waves);
+        tune_store(s->fused ? fused_key : key, best_ev, best_ch, best_graph, v.fwd_waves);
     }
     s->use_graph = best_graph;
     if (event_tile) *event_tile = best_ev;

@@ -52,3 +52,38 @@ def test_iterations_match_oracle(n, tile):
         err = np.abs(got[r] - ref) / np.maximum(ref, 1e-3 * ref.max())
         assert err.max() <= 1e-4, (r, err.max())
         np.testing.assert_allclose(ll[r], ll_ref, rtol=1e-5)
+
+
+def test_stored_plans_of_both_forms(tmp_path, monkeypatch):
+    """A stored plan names its form by its key: with and without " fused" the
+    autotuner takes the line as it stands, and both forms' iterations agree."""
+    from paper_2002_12471_amd import lmosem as L
+    dev = torch.device("cuda:0")
+    w = synth.workload("tiny")
+    act, mu = synth.phantom(w)
+    evd = L.events_to_device(synth.workload_events(w, n_events=1500), dev)
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("LMOSEM_TUNE_CACHE", str(cache))
+    ctx = L.Context(w.geom.as_dict(), torch.as_tensor(mu, device=dev))
+    out = {}
+    try:
+        for suffix in (None, "", " fused"):
+            if suffix is not None:
+                cache.write_text(f"{key}{suffix}|16 512 0 1\n")
+            evs = L.lmosem_events_load(ctx.handle, evd)
+            try:
+                plan = L.lmosem_autotune(ctx.handle, evs)
+                if suffix is None:
+                    key = cache.read_text().splitlines()[-1].split("|")[0].removesuffix(" fused")
+                else:
+                    assert plan == (16, 512, 0)
+                img = torch.as_tensor((mu > 0).astype(np.float32), device=dev).contiguous()
+                L.lmosem_iterate(ctx.handle, evs, 3, img)
+                out[suffix] = img.cpu().numpy()
+            finally:
+                L.lmosem_events_free(evs)
+    finally:
+        ctx.close()
+    on = mu > 0
+    for a in (out[""], out[" fused"]):
+        assert np.max(np.abs(a - out[None])[on] / np.maximum(out[None][on], 1e-3 * out[None].max())) <= 1e-4
