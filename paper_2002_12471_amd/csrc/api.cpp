@@ -91,6 +91,7 @@ struct lmosem_evset {
     int *lists = nullptr;
     std::vector<int> lists_host;   // what lists was copied from
     std::vector<int> list_off, slot_off, n_list, slot_rows, slot_blk;
+    int n_long = 1;                // the longest list
     int lists_rows = 0, lists_blk = 0;   // where rows and blocks begin in lists
     size_t pb_chunks = 0;     // chunk rows allocated in pb
     size_t pmean_groups = 0;  // pixel groups allocated in pmean
@@ -347,7 +348,8 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
     s->n_list.assign(g.n_subsets, 0);
     s->slot_rows.clear();
     s->slot_blk.clear();
-    int max_slots = 1, max_list = 1, row = 0, blk = 0;
+    int max_slots = 1, row = 0, blk = 0;
+    s->n_long = 1;
     for (int i = 0; i < g.n_subsets; ++i) {
         s->list_off[i] = (int)angles.size();
         s->slot_off[i] = (int)s->slot_rows.size();
@@ -357,7 +359,7 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
                 angles.push_back(a);
         if ((int)angles.size() == s->list_off[i]) angles.push_back(0);   // no events: one angle, nothing in it
         const int k = s->n_list[i] = (int)angles.size() - s->list_off[i];
-        max_list = std::max(max_list, k);
+        s->n_long = std::max(s->n_long, k);
         max_slots = std::max(max_slots, k * v.n_real);
         for (int r = 0; r < v.n_real; ++r)
             for (int l = 0; l < k; ++l) {
@@ -388,7 +390,7 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
                         v.fblk, c->st);
     if (e != hipSuccess) return alloc_err(c, "event records", e);
     if (!kept && v.n_real == 1) return LMOSEM_OK;
-    const size_t floats = flux_set_floats(c, v, max_list, max_slots);
+    const size_t floats = flux_set_floats(c, v, s->n_long, max_slots);
     if (floats == 0) return LMOSEM_OK;
     e = dev_take(v.arena, &s->fws, sizeof(float) * floats);
     if (e != hipSuccess) return alloc_err(c, "workspace", e);
@@ -516,6 +518,7 @@ hipError_t flux_subset(lmosem_ctx *c, lmosem_evset *s, int i, bool first, bool m
     p.ws_floats = s->fws ? s->fws_floats : c->fws_floats;
     p.alist = s->lists + s->list_off[i];
     p.n_list = s->n_list[i];
+    p.n_long = s->n_long;
     p.n_real = v.n_real;
     p.slot_rows = s->slot_rows.data() + s->slot_off[i];
     p.blk_host = s->slot_blk.data() + s->slot_off[i];

@@ -1619,7 +1619,9 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
     const FluxGeo &fg = *p.fg;   // (without the fits: kernel arguments)
     const FluxTables &ft = *p.ft;
     const bool sc = fg.N > 0;
-    const int grp = flux_group(g, fg, p.ws_floats, p.n_real, p.n_list), n_rows = flux_rows(fg);
+    // one group size for every subset of a set, also where their lists differ in
+    // length: the box copy that one sub-iteration leaves has the next one's form
+    const int grp = flux_group(g, fg, p.ws_floats, p.n_real, p.n_long), n_rows = flux_rows(fg);
     const int ca = flux_angles(g, fg, p.n_list);
     if (grp < 1) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
@@ -1631,7 +1633,8 @@ hipError_t flux_run(const FluxRun &p, bool adjoint, const FluxStage &stage) {
         if (p.means && sc) {
             e = stage(0, [&] {
                 // the box copy of the estimate: the previous sub-iteration's
-                // update left it, unless the workspace served others since
+                // update left it, unless the workspace served other sets or
+                // other realisations of this one since
                 if (p.box || grp < p.n_real)
                     hipLaunchKernelGGL(k_flux_box, dim3((g.n_p + 255) / 256, nr), dim3(256), 0, p.st, g, fg, ft, f, w.fbox);
                 hipLaunchKernelGGL(k_flux_spread, dim3(fg.n_blk, fg.N / kSec, nr), dim3(64 * kPairWaves), 0, p.st, g, fg, ft, ft.beg,

@@ -228,6 +228,7 @@ struct FluxRun {
     size_t ws_floats;
     const int *alist;          // device: angles of the list
     int n_list, n_real;
+    int n_long;                // the longest list of the set's subsets: one group size for all of them
     const int *slot_rows;      // host [n_real * n_list + 1]: first row of each slot, counted over the set
     const int *blk_host;       // host [n_real * n_list + 1]: first block of each slot, counted over the set
     const int *blk_beg;        // the same on the device
@@ -240,7 +241,7 @@ struct FluxRun {
     int ev_cap = 0;
     int blk_rows(int b) const;
     bool means;                // form the event means (else inv holds the backprojection's weights); inv is in record order
-    bool box;                  // the estimate is new to the workspace
+    bool box;                  // the estimate is new to the workspace (no sub-iteration of its set ran there just before)
     float *f;                  // [n_real][n_qpad]
     float *mean, *inv;
     unsigned long long *skipped;

@@ -176,7 +176,7 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
         FluxBlock *fblk = reinterpret_cast<FluxBlock *>(b + at_blk);
         FluxEvent *fev = reinterpret_cast<FluxEvent *>(b + at);
         flux->alist = d;
-        flux->n_list = nl;
+        flux->n_list = flux->n_long = nl;
         flux->n_real = 1;
         flux->slot_rows = lists.data() + nl;
         flux->blk_host = lists.data() + 2 * nl + 1;
