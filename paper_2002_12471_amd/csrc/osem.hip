@@ -26,6 +26,7 @@
 #include <algorithm>
 
 #include "lmosem_int.h"
+#include "paths.h"
 
 namespace lmo {
 
@@ -283,18 +284,10 @@ __device__ __forceinline__ void forward_item(const Geo &g, const Tile *__restric
     }
 }
 
-// Map the dispatch index to a logical (pixel group, tile) item so that each
-// XCD (workgroups are dealt to the 8 XCDs round-robin) runs one contiguous run
-// of items: consecutive tiles of one angle and pixel group then share that
-// XCD's L2 copy of the path-table slice they read.  (A persistent kernel that
-// drained per-XCD work queues was measured slower than this hardware-
-// scheduled grid on this workload.)
-__device__ inline int xcd_logical(int p, int n) {
-    constexpr int kXcd = 8;
-    const int x = p % kXcd, k = p / kXcd;
-    const int m = n / kXcd, rem = n % kXcd;
-    return x * m + min(x, rem) + k;
-}
+// Items are (pixel group, tile), in the order of xcd_logical: consecutive tiles
+// of one angle and pixel group then share their XCD's L2 copy of the path-table
+// slice they read.  (A persistent kernel that drained per-XCD work queues was
+// measured slower than this hardware-scheduled grid on this workload.)
 
 // (the 8-event kernel fits 64 VGPRs without spilling: eight waves per SIMD,
 // measured 1-2 % faster than the seven its unbounded allocation allows; the

@@ -141,16 +141,22 @@ __global__ __launch_bounds__(256) void k_rank(Geo g, const int *__restrict__ p_p
     D_sorted[o] = detector_mass(g, u);
 }
 
-// (alpha, beta) code of a path weight; zero weight never contributes
-__device__ inline float2 path_code(const Geo &g, PathW p, double log2_gnorm) {
-    if (!(p.w > 0.0)) return make_float2(kNegHuge, 0.0f);
-    const double ec = p.ep - g.e_c;
+// what of a path's code its end energy gives: (alpha without log2 of its weight, beta)
+__device__ inline double2 end_code(const Geo &g, double ep, double log2_gnorm) {
+    const double ec = ep - g.e_c;
     // beta's rounding is taken up by alpha at the path's own end energy, where
     // its events are (the primary paths share one beta, whose rounding would
     // otherwise shift every photopeak mean by 1.9e-7 the same way)
     const double b = 2.0 * g.c2 * ec;
     const float beta = (float)b;
-    return make_float2((float)(log2(p.w) + log2_gnorm - g.c2 * ec * ec + (b - (double)beta) * ec), beta);
+    return make_double2(log2_gnorm - g.c2 * ec * ec + (b - (double)beta) * ec, (double)beta);
+}
+
+// (alpha, beta) code of a path weight; zero weight never contributes
+__device__ inline float2 path_code(const Geo &g, PathW p, double log2_gnorm) {
+    if (!(p.w > 0.0)) return make_float2(kNegHuge, 0.0f);
+    const double2 c = end_code(g, p.ep, log2_gnorm);
+    return make_float2((float)(log2(p.w) + c.x), (float)c.y);
 }
 
 // Path table and per-angle sensitivities.  One thread per (angle, emission
@@ -333,11 +339,9 @@ __global__ __launch_bounds__(256) void k_table_terms(Geo g, const double *__rest
     float b = 0.0f;
     if (di != 0 || dj != 0) {
         const Flight fl = flight(g, di, dj, cs[2 * a], cs[2 * a + 1]);
-        const float2 code = path_code(g, PathW{1.0, fl.ep}, -log2(sqrt(2.0 * M_PI) * g.sig_e));
-        // (path_code's sum before it is rounded)
-        const double ec = fl.ep - g.e_c, bd = 2.0 * g.c2 * ec;
-        b = code.y;
-        t.x = log2(fl.psi / g.psi_bar) - log2(sqrt(2.0 * M_PI) * g.sig_e) - g.c2 * ec * ec + (bd - (double)b) * ec;
+        const double2 code = end_code(g, fl.ep, -log2(sqrt(2.0 * M_PI) * g.sig_e));
+        b = (float)code.y;
+        t.x = log2(fl.psi / g.psi_bar) + code.x;
         t.y = fl.rho * M_LOG2E;
     }
     tab[(size_t)blockIdx.y * n + i] = t;
