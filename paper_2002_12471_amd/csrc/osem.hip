@@ -690,6 +690,7 @@ __global__ __launch_bounds__(kUpdPix * kUpdRows) void k_update_tiles(Geo g, cons
                                                                     const float *__restrict__ sens,
                                                                     float *__restrict__ f) {
     constexpr int R = kUpdRows;
+    static_assert(R == 64, "summed eight by eight");
     __shared__ float part[R][kUpdPix];
     const int px = threadIdx.x % kUpdPix, row = threadIdx.x / kUpdPix;
     const int q = blockIdx.x * kUpdPix + px;   // below n_qpad, a multiple of 64
@@ -707,18 +708,19 @@ __global__ __launch_bounds__(kUpdPix * kUpdRows) void k_update_tiles(Geo g, cons
         if (c + k * R < c1) a[k] += p[(size_t)(c + k * R) * g.n_qpad];
     part[row][px] = (a[0] + a[1]) + (a[2] + a[3]);
     __syncthreads();
-    float b = 0.0f;
+    float v[8], b = 0.0f;   // (in pairs: a rounding per doubling)
     if (row < 8) {
 #pragma unroll
-        for (int k = 0; k < R / 8; ++k) b += part[row + 8 * k][px];
+        for (int k = 0; k < R / 8; ++k) v[k] = part[row + 8 * k][px];
+        b = pair_sum(v);
     }
     __syncthreads();
     if (row < 8) part[row][px] = b;
     __syncthreads();
     if (row == 0 && q < g.n_q) {
-        b = 0.0f;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) b += part[k][px];
+        for (int k = 0; k < 8; ++k) v[k] = part[k][px];
+        b = pair_sum(v);
         const float s = sens[q];
         float *fp = f + (size_t)r * g.n_qpad + q;
         if (s > 0.0f) *fp = (*fp * b) / s;

@@ -19,6 +19,16 @@ __device__ __forceinline__ int xcd_logical(int p, int n) {
     return x * m + min(x, rem) + p / 8;
 }
 
+// sum of n values, a power of two, in pairs: log2(n) roundings instead of n
+template <int n>
+__device__ __forceinline__ float pair_sum(float (&v)[n]) {
+#pragma unroll
+    for (int h = n / 2; h; h >>= 1)
+#pragma unroll
+        for (int k = 0; k < h; ++k) v[k] += v[k + h];
+    return v[0];
+}
+
 // Klein-Nishina total cross-section in units of r_e^2.
 __device__ __host__ inline double kn_total(double e) {
     double k = e / kMeC2;
