@@ -22,12 +22,13 @@
 // exact for eight exponents b at Chebyshev points of the range met (and not
 // for powers of x, whose remainder grows far out in the tails): for the
 // energies after dividing out a Gaussian about the middle of the end
-// energies, which leaves pure exponentials.  With the node spacings of
-// flux_geometry one path's relative error is at most 4.5e-7 in energy at
-// any distance from its end energy, and in direction 1e-7 within three
-// widths of the energy response, 2e-6 within six, 5e-5 within eight
-// (evaluated over the whole range of directions and energies, 90-175 keV),
-// alternating in sign from path to path.
+// energies, which leaves pure exponentials.  One path's relative error is at
+// most 4.5e-7 in energy at any distance from its end energy; in direction
+// flux_geometry evaluates it for the response, the Klein-Nishina factor and the
+// attenuation at hand and takes as many nodes as keep it within 2e-7 up to
+// three widths of the energy response, 1e-6 up to six and 1e-5 anywhere in the
+// window, alternating in sign from path to path (FP32 leaves 1e-6 of one
+// path's code term by term).
 //
 // Work per sub-iteration: n_p^2 pair visits (twice), angles x n_p x N x K
 // multiply-adds on the matrix cores (twice), and eight multiply-adds per
@@ -1337,6 +1338,65 @@ static void fit_exponentials(double b, FluxFit &fit) {
         for (int m = 0; m < kTap; ++m) fit.v[i][m] = (double)A[i][kTap + m];
 }
 
+// Whether eight nodes of N hold the direction interpolation of every path, and
+// with which exponents: one path's relative error half way between two nodes,
+// over the directions, without attenuation and with e^-16 of it, at end energies
+// off by 0, 3 and 6 widths of the response and at the window's ends, against
+// what kDirectionErr allows for the distance.  The spacing that the response's
+// steepest slope needs is only where the search starts: wide responses are
+// bound by the curvature of E'(phi) and of the Klein-Nishina factor (at 25 %
+// of 159 keV the slope alone asks for 48 nodes, which leave 1.4e-4 within three
+// widths; 144 are taken, 6e-8).  The exponents fill 0.6 to all of the slope's range: fewer
+// of it favour the near tails, which carry the sums.  Some 40 us a context.
+constexpr double kDirectionErr[3] = {2e-7, 1e-6, 1e-5};   // up to 3 widths, 6 widths, anywhere
+constexpr double kLongest = 16.0;
+
+static bool fit_directions(const Geo &g, double slope, int N, FluxFit &best) {
+    constexpr int kDirs = 24, kShares = 3;
+    const double share[kShares] = {0.6, 0.8, 1.0};
+    FluxFit fit[kShares];
+    double w[kShares][kTap], score[kShares] = {0.0, 0.0, 0.0};
+    for (int c = 0; c < kShares; ++c) {
+        fit_exponentials(share[c] * slope * 2.0 * M_PI / N, fit[c]);
+        for (int i = 0; i < kTap; ++i) {
+            w[c][i] = 0.0;
+            for (int m = 0; m < kTap; ++m) w[c][i] += fit[c].v[i][m] * exp(0.5 * fit[c].b[m]);
+        }
+    }
+    const double c2 = 0.5 / (g.sig_e * g.sig_e);
+    struct Path { double ep, log_psi, rho; };
+    auto path = [&](double node) {
+        const double c = cos(2.0 * M_PI * node / N), t = 1.0 + g.kappa * (1.0 - c), P = 1.0 / t;
+        return Path{g.e0 * P, log(P * P * (P + t - 1.0 + c * c)), kn_total(g.e0 * P) / g.sigma_kn_e0};
+    };
+    for (int d = 0; d < kDirs; ++d) {
+        const int n = (int)lround(d * (0.5 * N) / (kDirs - 1) - 0.5);   // intervals from 0 to pi, both ends' included
+        const Path at = path(n + 0.5);
+        Path x[kTap];
+        for (int i = 0; i < kTap; ++i) x[i] = path(n + i - 3);
+        const double far[7] = {0.0, -3.0 * g.sig_e, 3.0 * g.sig_e, -6.0 * g.sig_e, 6.0 * g.sig_e, g.win_lo - at.ep,
+                               g.win_hi - at.ep};
+        for (int k = 0; k < 7; ++k) {
+            const double e = at.ep + far[k];
+            if (k < 5 && (e < g.win_lo || e > g.win_hi)) continue;
+            const double widths = fabs(far[k]) / g.sig_e;
+            const double allowed = kDirectionErr[widths < 3.001 ? 0 : widths < 6.001 ? 1 : 2];
+            for (double L : {0.0, kLongest}) {
+                double err[kShares] = {-1.0, -1.0, -1.0};
+                for (int i = 0; i < kTap; ++i) {
+                    const double r = exp(x[i].log_psi - at.log_psi - (x[i].rho - at.rho) * L -
+                                         c2 * ((e - x[i].ep) * (e - x[i].ep) - far[k] * far[k]));
+                    for (int c = 0; c < kShares; ++c) err[c] += w[c][i] * r;
+                }
+                for (int c = 0; c < kShares; ++c) score[c] = std::max(score[c], fabs(err[c]) / allowed);
+            }
+        }
+    }
+    const int c = (int)(std::min_element(score, score + kShares) - score);
+    best = fit[c];
+    return score[c] <= 1.0;
+}
+
 bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order) {
     int x0 = g.nx, x1 = -1, y0 = g.ny, y1 = -1;
     for (int pix : p_pix) {
@@ -1370,8 +1430,8 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
         slope = std::max(slope, far * ep * ep * g.kappa * sin(ph) / g.e0);
     }
     slope /= g.sig_e * g.sig_e;
-    // direction nodes: slope x spacing at most 0.79, a multiple of 48 (whole
-    // matrix tiles, an even number of sectors)
+    // direction nodes: slope x spacing at most 0.79 and what the error asks for, a
+    // multiple of 48 (whole matrix tiles, an even number of sectors)
     const double n = std::max(2.0 * M_PI * slope / 0.79, 48.0);
     // energy nodes: largest exponent x spacing at most 0.70, eight nodes more
     // than intervals, a multiple of 16
@@ -1380,11 +1440,10 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
     const double k = (g.win_hi - g.win_lo) * b_e / 0.70 + 8.0;
     if (!(n <= kFluxMaxN) || !(k <= kFluxMaxK)) return false;
     fg.N = (int)ceil(n / 48.0) * 48;
+    while (!fit_directions(g, slope, fg.N, fg.direction))
+        if ((fg.N += 48) > kFluxMaxN) return false;
     fg.K = std::max(32, (int)ceil(k / 16.0) * 16);
     fg.h = (g.win_hi - g.win_lo) / (fg.K - 8);
-    // (the directions' exponents fill 0.6 of the range: the near tails,
-    // which carry the sums, at some cost in the far ones)
-    fit_exponentials(0.6 * slope * 2.0 * M_PI / fg.N, fg.direction);
     fit_exponentials(b_e * fg.h, fg.energy);
     return (int64_t)g.n_angles * fg.N * fg.K <= kFluxMaxG;
 }

@@ -1,0 +1,203 @@
+"""How close the directional-flux stages come to FP64, away from one energy
+response as well: from a narrow one that needs many direction and energy nodes
+to a wide one whose nodes follow the curvature of the end energy, at 159 and
+511 keV; compact sources, emission sets, odd grids, unequal subset lists, empty
+angles and realisations.  Every test asserts that the stages ran.
+
+Tolerances, over events whose mean is at least 1e-8 of the largest: one path's
+direction error is at most 2e-7 within three widths of the response, 1e-6 within
+six and 1e-5 beyond, its energy error 4.5e-7, alternating from path to path, and
+FP32 leaves about 3e-7 rms: 6e-7 rms and 1e-5 at most for every set of events
+(events whose only path ends lie within a hundredth of the position response's
+cut, where its own relative error grows to 5e-6, included).  Sums over events
+are held to 5e-6."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+import oracle as O  # noqa: E402
+import synth  # noqa: E402
+
+# energy, FWHM, window (keV): at 15 to 30 % of 159 keV and 25 % of 511 keV the
+# response's slope alone would take too few nodes; at 10 keV N = 816, K = 144
+RESPONSES = {
+    "10%": (159.0, 15.9, (90.0, 175.0)),
+    "15%": (159.0, 23.85, (90.0, 175.0)),
+    "20%": (159.0, 31.8, (90.0, 175.0)),
+    "25%": (159.0, 39.75, (90.0, 175.0)),
+    "30%": (159.0, 47.7, (90.0, 175.0)),
+    "511": (511.0, 127.75, (300.0, 600.0)),
+    "many": (159.0, 10.0, (120.0, 175.0)),
+}
+N, DX, NA = 33, 0.39, 17   # 560 support pixels and more: such calls all take the stages
+
+
+def _lib():
+    from paper_2002_12471_amd import lmosem as L
+    return L
+
+
+def _map():
+    X, Y = synth.phantoms.pixel_centres(N, N, DX)
+    mu = np.where((X / 5.6) ** 2 + (Y / 5.1) ** 2 <= 1.0, 0.15, 0.0).astype(np.float32)
+    assert (mu > 0).sum() >= 512
+    return X, Y, mu
+
+
+def _geom(response, ns=1):
+    e0, fwhm, win = RESPONSES[response]
+    return synth.Geometry(N, N, DX, 64, 0.2, NA, e0_kev=e0, fwhm_e_kev=fwhm, win_lo_kev=win[0], win_hi_kev=win[1], n_subsets=ns)
+
+
+def _spread_events(response, n, seed):
+    """Events anywhere in the window and on the object, some angles without."""
+    rng = np.random.default_rng(seed)
+    _, _, win = RESPONSES[response]
+    return {"angle": rng.choice([a for a in range(NA) if a % 6 != 5], n).astype(np.int32),
+            "u_bin": rng.uniform(10.0, 54.0, n).astype(np.float32),
+            "energy": rng.uniform(win[0], win[1], n).astype(np.float32)}
+
+
+def _stages(ctx, call):
+    """call's result and the forward launches it made (two or more a
+    sub-iteration through the stages, one term by term)."""
+    L = _lib()
+    L.lmosem_set_timing(ctx.handle, True)
+    before = ctx.stats()["forward_launches"]
+    out = call()
+    torch.cuda.synchronize()
+    n = ctx.stats()["forward_launches"] - before
+    L.lmosem_set_timing(ctx.handle, False)
+    return out, n
+
+
+@pytest.mark.parametrize("source", ["uniform", "compact", "pixel"])
+@pytest.mark.parametrize("response", list(RESPONSES))
+def test_means_against_oracle(response, source):
+    L, dev = _lib(), torch.device("cuda:0")
+    X, Y, mu = _map()
+    img = np.zeros((N, N), np.float32)
+    if source == "pixel":
+        img[21, 20] = 1.0
+    else:
+        img[(mu > 0) & (np.hypot(X - 2.0, Y - 1.5) < (99.0 if source == "uniform" else 0.8))] = 1.0
+    g = _geom(response)
+    ev = _spread_events(response, 500, 3)
+    m = O.OracleModel(g.as_dict(), mu)
+    q = np.flatnonzero(img.ravel()).astype(np.int32)
+    ref = m.system_matrix(ev, q) @ img.ravel()[q].astype(np.float64)
+    ctx = L.Context(g.as_dict(), torch.as_tensor(mu, device=dev))
+    try:
+        got, n = _stages(ctx, lambda: ctx.forward(L.events_to_device(ev, dev), torch.as_tensor(img, device=dev)))
+    finally:
+        ctx.close()
+    assert n == 2
+    live = ref > 1e-8 * ref.max()
+    rel = np.abs(got.cpu().numpy().astype(np.float64) - ref)[live] / ref[live]
+    print(response, source, live.sum(), "rms %.1e max %.1e" % (np.sqrt(np.mean(rel ** 2)), rel.max()), flush=True)
+    assert live.sum() >= 200
+    assert np.sqrt(np.mean(rel ** 2)) <= 6e-7 and rel.max() <= 1e-5
+
+
+@pytest.mark.parametrize("response", ["many", "10%", "30%"])
+def test_masked_means_and_adjoint_against_oracle(response):
+    """An emission set of a few pixels: pairs without an emission pixel carry nothing."""
+    L, dev = _lib(), torch.device("cuda:0")
+    X, Y, mu = _map()
+    mask = (mu > 0) & (np.hypot(X - 1.0, Y + 0.8) < 1.4)
+    img = np.where(mask, 1.0 + 0.3 * X, 0.0).astype(np.float32)
+    g = _geom(response)
+    ev = _spread_events(response, 500, 4)
+    m = O.OracleModel(g.as_dict(), mu)
+    q = np.flatnonzero(mask.ravel()).astype(np.int32)
+    H = m.system_matrix(ev, q)
+    ref = H @ img.ravel()[q].astype(np.float64)
+    w = np.random.default_rng(6).uniform(0.5, 1.5, 500).astype(np.float32)
+    ctx = L.Context(g.as_dict(), torch.as_tensor(mu, device=dev),
+                    emission=torch.as_tensor(mask.astype(np.float32), device=dev))
+    try:
+        evd = L.events_to_device(ev, dev)
+        got, n = _stages(ctx, lambda: ctx.forward(evd, torch.as_tensor(img, device=dev)))
+        back = ctx.backproject(evd, torch.as_tensor(w, device=dev)).cpu().numpy().ravel()
+    finally:
+        ctx.close()
+    assert n == 2
+    live = ref > 1e-8 * ref.max()
+    rel = np.abs(got.cpu().numpy().astype(np.float64) - ref)[live] / ref[live]
+    bref = H.T @ w.astype(np.float64)
+    err = np.abs(back[q] - bref) / bref
+    print(response, "means rms %.1e max %.1e, adjoint %.1e" % (np.sqrt(np.mean(rel ** 2)), rel.max(), err.max()), flush=True)
+    assert live.sum() >= 200
+    assert np.sqrt(np.mean(rel ** 2)) <= 6e-7 and rel.max() <= 1e-5
+    assert err.max() <= 5e-6 and np.all(np.delete(back, q) == 0)
+
+
+@pytest.mark.parametrize("response", ["many", "30%"])
+def test_batch_with_unequal_lists_equals_single_runs_and_rows(response):
+    """17 angles in 3 subsets (6, 6 and 5), three realisations, one of them
+    empty: each its own run bit for bit, and the rows that a row cache keeps."""
+    L, dev = _lib(), torch.device("cuda:0")
+    _, _, mu = _map()
+    g = _geom(response, ns=3)
+    ev = synth.generate_events(g, (mu > 0).astype(np.float32), mu, 240_000, 8)
+    keep = ev["angle"] % 6 != 5
+    ev = {k: ev[k][keep] for k in ("angle", "u_bin", "energy")}
+    J = len(ev["angle"])
+    a, b = {k: v[:J // 2] for k, v in ev.items()}, {k: v[J // 2:] for k, v in ev.items()}
+    ctx = L.Context(g.as_dict(), torch.as_tensor(mu, device=dev))
+    try:
+        def iterate(e, offs=None, rows=False):
+            R = 1 if offs is None else len(offs) - 1
+            evs = L.lmosem_events_load(ctx.handle, L.events_to_device(e, dev), offs)
+            try:
+                if rows:
+                    L.lmosem_cache_rows(ctx.handle, evs, True)
+                img = torch.as_tensor((mu > 0).astype(np.float32), device=dev).expand(R, -1, -1).contiguous().clone()
+                _, n = _stages(ctx, lambda: L.lmosem_iterate(ctx.handle, evs, 2, img, n_real=R))
+            finally:
+                L.lmosem_events_free(evs)
+            assert n == 6 if rows else n >= 12, n
+            return img.cpu().numpy()
+        offs = [0, J // 2, J // 2, J]
+        batch, rows = iterate(ev, offs), iterate(ev, offs, rows=True)
+        assert np.array_equal(batch[0], iterate(a)[0]) and np.array_equal(batch[2], iterate(b)[0])
+    finally:
+        ctx.close()
+    assert not batch[1].any() and not rows[1].any()
+    on = mu > 0
+    for r in (0, 2):
+        x, y = rows[r][on].astype(np.float64), batch[r][on]
+        assert np.max(np.abs(y - x) / np.maximum(x, 1e-3 * x.max())) <= 5e-6
+
+
+def test_image_error_no_larger_than_term_by_term():
+    """All 200,000 events of the 64x64 brain in 8 subsets: after one iteration
+    the stages' image is no further from the stored FP64 iterate than the
+    image of the rows formed term by term."""
+    import os
+    L, dev = _lib(), torch.device("cuda:0")
+    w = synth.workload("brain64")
+    gold = np.load(os.path.join(os.path.dirname(__file__), "golden", "brain64_full_os.npz"))
+    _, mu = synth.phantom(w)
+    ev = synth.workload_events(w)
+    ctx = L.Context(w.geom.as_dict(), torch.as_tensor(mu, device=dev))
+    err = {}
+    try:
+        evs = L.lmosem_events_load(ctx.handle, L.events_to_device(ev, dev))
+        try:
+            for rows in (False, True):
+                L.lmosem_cache_rows(ctx.handle, evs, rows)
+                img = torch.as_tensor((mu > 0).astype(np.float32), device=dev).contiguous()
+                _, n = _stages(ctx, lambda: L.lmosem_iterate(ctx.handle, evs, 1, img))
+                assert (n == 8) == rows
+                x = img.cpu().numpy().ravel()[gold["support"]].astype(np.float64)
+                err[rows] = np.linalg.norm(x - gold["images"][0]) / np.linalg.norm(gold["images"][0])
+        finally:
+            L.lmosem_events_free(evs)
+    finally:
+        ctx.close()
+    print("stages %.2e rows %.2e" % (err[False], err[True]), flush=True)
+    assert err[False] <= err[True]
