@@ -333,7 +333,10 @@ lmosem_status lmosem_set_graphs(lmosem_ctx *ctx, int32_t enable);
  * from HBM (the event means, then the backprojection of Eq. 7) instead of
  * recomputing every path term.  Results equal the recomputing path up to
  * FP32 summation order.  Autotuning the set, or enabling again after
- * disabling, recomputes the rows at the next iteration.  Errors: ENOMEM (the
+ * disabling, recomputes the rows at the next iteration.  A set that iterates
+ * through directional flux also gets the rows, partial means and partial
+ * backprojections of one sub-iteration that the rows' kernels work with, and
+ * the context its path table if that is not filled yet.  Errors: ENOMEM (the
  * set stays usable without the cache), EINVAL. */
 lmosem_status lmosem_cache_rows(lmosem_ctx *ctx, lmosem_evset *set, int32_t enable);
 

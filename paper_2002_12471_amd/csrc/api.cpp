@@ -196,6 +196,13 @@ void drop_graphs(lmosem_evset *s) {
         if (x) { hipGraphExecDestroy(x); x = nullptr; }
 }
 
+// what a set works with term by term
+void free_rows(lmosem_evset *s) {
+    for (void *p : {(void *)s->H, (void *)s->pmean, (void *)s->pb}) dev_give(s->s.arena, p);
+    s->H = s->pmean = s->pb = nullptr;
+    s->pmean_groups = s->pb_chunks = 0;
+}
+
 void free_set(lmosem_evset *s) {
     if (!s) return;
     if (s->s.ctx) s->s.ctx->set_bytes -= s->bytes;
@@ -209,27 +216,40 @@ void free_set(lmosem_evset *s) {
     delete s;
 }
 
+// device bytes of what a set works with term by term: rows, their partial means
+// and the chunks' backprojections
+int64_t row_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
+    const Geo g = set_geo(c, s);
+    const int64_t rows = std::max(s->s.max_rows, 1), chunks = std::max(s->s.max_chunks, 1);
+    return 4 * rows * g.n_qpad + 4 * rows * std::max<int64_t>((int64_t)s->pmean_groups, forward_groups(g)) +
+           4 * std::max<int64_t>(chunks, (int64_t)s->pb_chunks) * g.n_qpad;
+}
+
 // Device bytes a set holds with its current plan and workspace.
 int64_t set_device_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
     const Geo g = set_geo(c, s);
     const EvSet &v = s->s;
-    const int64_t n = std::max<int64_t>(v.n, 1), rows = std::max(v.max_rows, 1);
-    const int64_t chunks = std::max<int64_t>((int64_t)s->pb_chunks, 1);
+    const int64_t n = std::max<int64_t>(v.n, 1);
     const int64_t n_tiles = std::max<int64_t>(v.tile_off.empty() ? 1 : v.tile_off.back(), 1);
     const int64_t n_chunks = std::max<int64_t>(v.chunk_off.empty() ? 1 : v.chunk_off.back(), 1);
     int64_t b = 20 * n + (int64_t)sizeof(Tile) * n_tiles + (int64_t)sizeof(Chunk) * n_chunks +
                 12 * (int64_t)g.n_subsets * (v.n_real + 1);
-    b += 8 * rows + 4 * (int64_t)v.n_real * g.n_qpad + 8 * (int64_t)v.n_real;
-    if (s->H) b += 4 * rows * g.n_qpad;
-    if (s->pmean) b += 4 * rows * std::max<int64_t>((int64_t)s->pmean_groups, forward_groups(g));
-    if (s->pb) b += 4 * chunks * g.n_qpad;
+    b += 8 * (int64_t)std::max(v.max_rows, 1) + 4 * (int64_t)v.n_real * g.n_qpad + 8 * (int64_t)v.n_real;
+    if (s->H) b += row_bytes(c, s);
     if (s->flux)
         b += (int64_t)sizeof(FluxEvent) * n + 4 * (int64_t)s->fws_floats +
              (int64_t)sizeof(FluxBlock) * (s->slot_blk.empty() ? 0 : s->slot_blk.back()) +
              4 * (int64_t)(2 * s->slot_rows.size() + g.n_angles + s->n_list.size());
-    if (c->surrogate) b += 24 * rows + 8 * 2 * kPairCap;
+    if (c->surrogate) b += 24 * (int64_t)std::max(v.max_rows, 1) + 8 * 2 * kPairCap;
     if (s->Hc) b += 4 * n * g.n_qpad;
     return b;
+}
+
+// count the set as it now is
+void account(lmosem_ctx *c, lmosem_evset *s) {
+    c->set_bytes -= s->bytes;
+    s->bytes = set_device_bytes(c, s);
+    c->set_bytes += s->bytes;
 }
 
 // (Re)allocate the per-set workspace for the current tile plan.
@@ -257,9 +277,7 @@ lmosem_status alloc_workspace(lmosem_ctx *c, lmosem_evset *s, bool for_rows = fa
         AL(s->X, sizeof(uint16_t) * 8 * (size_t)kPairCap);
     }
 #undef AL
-    c->set_bytes -= s->bytes;
-    s->bytes = set_device_bytes(c, s);
-    c->set_bytes += s->bytes;
+    account(c, s);
     return LMOSEM_OK;
 }
 
@@ -1462,15 +1480,15 @@ lmosem_status lmosem_cache_rows(lmosem_ctx *c, lmosem_evset *s, int32_t enable) 
     if (!enable) {
         hipFree(s->Hc);
         s->Hc = nullptr;
-        c->set_bytes -= s->bytes;
-        s->bytes = set_device_bytes(c, s);
-        c->set_bytes += s->bytes;
+        account(c, s);
         return LMOSEM_OK;
     }
     if (s->Hc) return LMOSEM_OK;
     const size_t n = (size_t)std::max<int64_t>(s->s.n, 1) * c->g.n_qpad;
-    if (over_cap(c, (int64_t)(sizeof(float) * n)))
-        return set_err(c, LMOSEM_ENOMEM, cap_msg(c, "the row cache", (int64_t)(sizeof(float) * n)));
+    // with the cache, and for a flux set with what its rows' kernels work with
+    const bool bare = s->flux && !s->H;
+    const int64_t more = (int64_t)(sizeof(float) * n) + (bare ? row_bytes(c, s) : 0);
+    if (over_cap(c, more)) return set_err(c, LMOSEM_ENOMEM, cap_msg(c, "the row cache", more));
     hipError_t e = hipSuccess;
     if (!c->t.T && !c->surrogate) {   // the rows' path table, held since the first list-mode call
         e = build_path_table(c->g, c->t, c->st);
@@ -1482,9 +1500,7 @@ lmosem_status lmosem_cache_rows(lmosem_ctx *c, lmosem_evset *s, int32_t enable) 
         (void)hipGetLastError();
         return set_err(c, LMOSEM_ENOMEM, "row cache: " + std::to_string(sizeof(float) * n) + " bytes not available");
     }
-    c->set_bytes -= s->bytes;
-    s->bytes = set_device_bytes(c, s);
-    c->set_bytes += s->bytes;
+    account(c, s);
     if (s->flux || s->fused) {
         // the rows' own kernels: their partial sums, and (for a set that was
         // autotuned) their plan
@@ -1493,8 +1509,11 @@ lmosem_status lmosem_cache_rows(lmosem_ctx *c, lmosem_evset *s, int32_t enable) 
         if (ws != LMOSEM_OK) {   // the set stays usable without the cache
             hipFree(s->Hc);
             s->Hc = nullptr;
+            if (bare) free_rows(s);
+            account(c, s);
             return ws;
         }
+        account(c, s);   // (the plan's chunks)
     }
     // zero padding columns (the learned-scatter rows never write them)
     e = launch_fill(s->Hc, n, 0.0f, c->st);
