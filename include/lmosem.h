@@ -125,8 +125,9 @@ typedef struct {
                                    the path tables at the first list-mode call; not the
                                    path table of a large map, filled when a set first
                                    runs term by term or keeps its rows) */
-    int64_t table_bytes;        /* device bytes held by the tables built so far (and, from
-                                   the first list-mode call, by that path table) */
+    int64_t table_bytes;        /* device bytes held by the tables built so far (from the
+                                   first list-mode call with that path table's, and once
+                                   it is filled with the flux tables' beside it) */
     int32_t event_tile;         /* events per forward-projection tile */
     int32_t n_emission;         /* emission pixels (the estimated image), <= n_support */
     /* kernel times from HIP events on the context's stream, recorded only
@@ -296,7 +297,11 @@ lmosem_status lmosem_autotune(lmosem_ctx *ctx, lmosem_evset *set, int32_t *event
  * LMOSEM_ENOMEM and leaves the context usable: the path tables are refused
  * before they are allocated (for scatter_model 2, whose near-field band's
  * width is known only once built, they are freed again), an event set after
- * its sort is planned, a row cache before it is allocated.  Memory a call
+ * its sort is planned, a row cache before it is allocated.  The tables of
+ * directional flux never make a call fail: they are built only where they fit
+ * beside the path table (until that is filled they lie within the bytes counted
+ * for it), and are given up, with the sets that iterate through them going on
+ * term by term, for a set or a row cache that fits without them.  Memory a call
  * uses only while it runs is not counted; without a cap a context keeps up to
  * 128 MB of it for its next call, until it is destroyed or given a cap.
  * Errors: EINVAL (bytes < 0). */

@@ -41,7 +41,9 @@ struct lmosem_ctx {
     std::vector<int> flux_order;   // the flux order's support indices
     float *fws = nullptr;          // workspace of one realisation
     size_t fws_floats = 0;
-    int64_t flux_bytes = 0;
+    int64_t flux_bytes = 0;        // what they take, and how much of it table_bytes counts: none that
+    int64_t flux_counted = 0;      // lies within the bytes counted for a path table not yet filled
+    std::vector<lmosem_evset *> sets;   // its live prepared sets
     bool lazy_table = false;       // the path table is filled for the first row cache or set that wants it
     // HIP graphs: one captured iteration per prepared set, replayed on an
     // internal stream ordered after the caller's stream by events
@@ -205,7 +207,11 @@ void free_rows(lmosem_evset *s) {
 
 void free_set(lmosem_evset *s) {
     if (!s) return;
-    if (s->s.ctx) s->s.ctx->set_bytes -= s->bytes;
+    if (s->s.ctx) {
+        s->s.ctx->set_bytes -= s->bytes;
+        auto &live = s->s.ctx->sets;
+        live.erase(std::remove(live.begin(), live.end(), s), live.end());
+    }
     drop_graphs(s);
     for (void *p : {(void *)s->s.u, (void *)s->s.e, (void *)s->s.efac, (void *)s->s.orig, (void *)s->s.ang, s->s.plan,
                     (void *)s->H, (void *)s->Hc, (void *)s->pmean, (void *)s->mean, (void *)s->inv, (void *)s->pb,
@@ -225,8 +231,9 @@ int64_t row_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
            4 * std::max<int64_t>(chunks, (int64_t)s->pb_chunks) * g.n_qpad;
 }
 
-// Device bytes a set holds with its current plan and workspace.
-int64_t set_device_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
+// Device bytes a set holds with its current plan and workspace (stages: its
+// records and workspace for the flux stages; rows: what it works with term by term).
+int64_t set_device_bytes(const lmosem_ctx *c, const lmosem_evset *s, bool stages, bool rows) {
     const Geo g = set_geo(c, s);
     const EvSet &v = s->s;
     const int64_t n = std::max<int64_t>(v.n, 1);
@@ -235,8 +242,8 @@ int64_t set_device_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
     int64_t b = 20 * n + (int64_t)sizeof(Tile) * n_tiles + (int64_t)sizeof(Chunk) * n_chunks +
                 12 * (int64_t)g.n_subsets * (v.n_real + 1);
     b += 8 * (int64_t)std::max(v.max_rows, 1) + 4 * (int64_t)v.n_real * g.n_qpad + 8 * (int64_t)v.n_real;
-    if (s->H) b += row_bytes(c, s);
-    if (s->flux)
+    if (rows) b += row_bytes(c, s);
+    if (stages)
         b += (int64_t)sizeof(FluxEvent) * n + 4 * (int64_t)s->fws_floats +
              (int64_t)sizeof(FluxBlock) * (s->slot_blk.empty() ? 0 : s->slot_blk.back()) +
              4 * (int64_t)(2 * s->slot_rows.size() + g.n_angles + s->n_list.size());
@@ -248,7 +255,7 @@ int64_t set_device_bytes(const lmosem_ctx *c, const lmosem_evset *s) {
 // count the set as it now is
 void account(lmosem_ctx *c, lmosem_evset *s) {
     c->set_bytes -= s->bytes;
-    s->bytes = set_device_bytes(c, s);
+    s->bytes = set_device_bytes(c, s, s->flux, s->H != nullptr);
     c->set_bytes += s->bytes;
 }
 
@@ -357,7 +364,8 @@ bool flux_faster(const lmosem_ctx *c, const EvSet &v, bool tuned, bool fused) {
 // subset, or (one given subset) the angles that have events; and the set's own
 // workspace, for sets that are kept or hold several realisations: what a whole
 // sub-iteration needs, as far as that takes no more than its system rows would.
-lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool kept) {
+// On the host only: plan_flux allocates and fills.
+void plan_lists(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool kept) {
     const Geo &g = c->g;
     EvSet &v = s->s;
     std::vector<int> angles;
@@ -398,22 +406,117 @@ lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset, bool k
     up.insert(up.end(), s->slot_rows.begin(), s->slot_rows.end());
     up.insert(up.end(), s->slot_blk.begin(), s->slot_blk.end());
     up.insert(up.end(), s->slot_off.begin(), s->slot_off.end());
+    s->fws_floats = kept || v.n_real > 1 ? flux_set_floats(c, v, s->n_long, max_slots) : 0;
+}
+
+lmosem_status plan_flux(lmosem_ctx *c, lmosem_evset *s, int force_subset) {
+    EvSet &v = s->s;
+    const int n_slots = (int)s->slot_rows.size() - 1, blk = s->slot_blk.back();
+    const std::vector<int> &up = s->lists_host;
     hipError_t e = dev_take(v.arena, &s->lists, sizeof(int) * up.size());
     if (e == hipSuccess) e = dev_take(v.arena, &v.fev, sizeof(FluxEvent) * (size_t)std::max<int64_t>(v.n, 1));
     if (e == hipSuccess) e = dev_take(v.arena, &v.fblk, sizeof(FluxBlock) * (size_t)std::max(blk, 1));
     if (e == hipSuccess) e = hipMemcpyAsync(s->lists, up.data(), sizeof(int) * up.size(), hipMemcpyHostToDevice, c->st);
     if (e == hipSuccess)
-        e = flux_events(g, c->fg, 0, blk, 0, s->lists + s->lists_rows, s->lists + s->lists_blk, n_slots,
+        e = flux_events(c->g, c->fg, 0, blk, 0, s->lists + s->lists_rows, s->lists + s->lists_blk, n_slots,
                         force_subset >= 0 ? nullptr : s->lists + s->lists_blk + n_slots + 1, v.ang, v.u, v.e, c->t, v.fev,
                         v.fblk, c->st);
     if (e != hipSuccess) return alloc_err(c, "event records", e);
-    if (!kept && v.n_real == 1) return LMOSEM_OK;
-    const size_t floats = flux_set_floats(c, v, s->n_long, max_slots);
-    if (floats == 0) return LMOSEM_OK;
-    e = dev_take(v.arena, &s->fws, sizeof(float) * floats);
-    if (e != hipSuccess) return alloc_err(c, "workspace", e);
-    s->fws_floats = floats;
+    if (s->fws_floats == 0) return LMOSEM_OK;
+    e = dev_take(v.arena, &s->fws, sizeof(float) * s->fws_floats);
+    return e == hipSuccess ? LMOSEM_OK : alloc_err(c, "workspace", e);
+}
+
+void free_paths(lmosem_ctx *c) {
+    hipFree(c->t.T); hipFree(c->t.prim); hipFree(c->t.sens); hipFree(c->t.sens_all);
+    hipFree(c->t.band); hipFree(c->t.band_lo);
+    c->t.T = nullptr; c->t.prim = nullptr; c->t.sens = nullptr; c->t.sens_all = nullptr;
+    c->t.band = nullptr; c->t.band_lo = nullptr;
+}
+
+void drop_flux(lmosem_ctx *c) {
+    if (!c->flux) return;
+    c->flux = false;
+    c->table_bytes -= c->flux_counted;
+    free_flux(c->ft);
+    hipFree(c->fws);
+    c->fws = nullptr;
+    c->fws_floats = 0;
+    c->flux_bytes = c->flux_counted = 0;
+}
+
+// what filling the path table adds to the bytes counted: its own are, and the
+// flux tables lay within them
+int64_t fill_bytes(const lmosem_ctx *c) { return c->t.T ? 0 : c->flux_bytes - c->flux_counted; }
+
+hipError_t fill_table(lmosem_ctx *c) {
+    const hipError_t e = build_path_table(c->g, c->t, c->st);
+    if (e == hipSuccess) {
+        c->table_bytes += c->flux_bytes - c->flux_counted;
+        c->flux_counted = c->flux_bytes;
+    }
+    return e;
+}
+
+// The bytes counted if the context gave up the flux stages: its live sets term
+// by term, the path table filled, no flux tables.
+int64_t bytes_without_stages(const lmosem_ctx *c) {
+    int64_t b = c->table_bytes - c->flux_counted + c->set_bytes;
+    for (const lmosem_evset *s : c->sets)
+        if (s->flux) b += set_device_bytes(c, s, false, true) - s->bytes;
+    return b;
+}
+
+// Give them up, for a set or a row cache that the memory cap has no room for
+// beside them.  Without device memory for the rows nothing changes.
+lmosem_status give_up_stages(lmosem_ctx *c) {
+    if (!c->t.T) {
+        const hipError_t e = fill_table(c);
+        if (e != hipSuccess) return alloc_err(c, "path table", e);
+    }
+    std::vector<lmosem_evset *> bare;
+    for (lmosem_evset *s : c->sets)
+        if (s->flux && !s->H) {
+            bare.push_back(s);
+            const lmosem_status ws = alloc_workspace(c, s, true);
+            if (ws == LMOSEM_OK) continue;
+            for (lmosem_evset *b : bare) {
+                free_rows(b);
+                account(c, b);
+            }
+            return ws;
+        }
+    const hipError_t e = hipStreamSynchronize(c->st);   // (replays end before the stream)
+    if (e != hipSuccess) return dev_err(c, "flux stages", e);
+    for (lmosem_evset *s : c->sets) {
+        if (!s->flux) continue;
+        drop_graphs(s);
+        hipFree(s->s.fev); hipFree(s->s.fblk); hipFree(s->lists); hipFree(s->fws);
+        s->s.fev = nullptr; s->s.fblk = nullptr; s->lists = nullptr; s->fws = nullptr;
+        s->fws_floats = 0;
+        s->flux = false;
+        account(c, s);
+    }
+    drop_flux(c);
     return LMOSEM_OK;
+}
+
+// The route of a set about to be allocated, under a memory cap: the one it is
+// faster on (s->flux) or, where that does not fit, the other, and at last
+// without the stages.  false: the set does not fit.
+bool admit(lmosem_ctx *c, lmosem_evset *s, int64_t &more, lmosem_status &st) {
+    const int64_t stages = set_device_bytes(c, s, true, false), rows = set_device_bytes(c, s, false, true) + fill_bytes(c);
+    st = LMOSEM_OK;
+    more = s->flux ? stages : rows;
+    if (!over_cap(c, more)) return true;
+    if (!over_cap(c, s->flux ? rows : stages)) {
+        s->flux = !s->flux;
+        return true;
+    }
+    if (bytes_without_stages(c) + set_device_bytes(c, s, false, true) > c->mem_cap) return false;
+    st = give_up_stages(c);
+    s->flux = false;
+    return st == LMOSEM_OK;
 }
 
 // iterates: the call goes through the set's subsets
@@ -457,12 +560,24 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
     s->fused = can_fuse(c);
     s->flux = c->flux && (kept || iterates ? flux_faster(c, s->s, kept, s->fused)
                                            : s->s.terms_sub[std::max(force_subset, 0)] > flux_from(c));
-    if (c->flux && !s->flux && !c->t.T) {   // the path table, held since the first list-mode call
-        e = build_path_table(c->g, c->t, c->st);
-        if (e != hipSuccess && e != hipErrorOutOfMemory) { free_set(s); return dev_err(c, "path table", e); }
-        if (e != hipSuccess) { (void)hipGetLastError(); s->flux = true; }
+    if (s->flux || (c->flux && c->mem_cap > 0)) plan_lists(c, s, force_subset, kept);
+    int64_t more = 0;
+    if (c->flux && c->mem_cap > 0 && !admit(c, s, more, st)) {
+        if (st == LMOSEM_OK) st = set_err(c, LMOSEM_ENOMEM, cap_msg(c, "the event set", more));
+        free_set(s);
+        return st;
     }
-    lmosem_status ws = s->flux ? plan_flux(c, s, force_subset, kept) : LMOSEM_OK;
+    if (c->flux && !s->flux && !c->t.T) {   // the path table, counted since the first list-mode call
+        e = fill_table(c);
+        if (e != hipSuccess && e != hipErrorOutOfMemory) { free_set(s); return dev_err(c, "path table", e); }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            s->flux = true;
+            plan_lists(c, s, force_subset, kept);
+        }
+    }
+    if (!s->flux) s->fws_floats = 0;
+    lmosem_status ws = s->flux ? plan_flux(c, s, force_subset) : LMOSEM_OK;
     if (ws == LMOSEM_OK) ws = alloc_workspace(c, s);
     if (ws != LMOSEM_OK) { free_set(s); return ws; }
     if (over_cap(c, 0)) {
@@ -470,6 +585,7 @@ lmosem_status load_set(lmosem_ctx *c, const lmosem_events *ev, const lmosem_batc
         free_set(s);
         return set_err(c, LMOSEM_ENOMEM, msg);
     }
+    if (kept) c->sets.push_back(s);
     *out = s;
     return LMOSEM_OK;
 }
@@ -742,46 +858,27 @@ lmosem_status iterate_set(lmosem_ctx *c, lmosem_evset *s, int n_iters, double *l
         if ((c)->poisoned) return LMOSEM_ESTATE;                              \
     } while (0)
 
-void free_paths(lmosem_ctx *c) {
-    hipFree(c->t.T); hipFree(c->t.prim); hipFree(c->t.sens); hipFree(c->t.sens_all);
-    hipFree(c->t.band); hipFree(c->t.band_lo);
-    c->t.T = nullptr; c->t.prim = nullptr; c->t.sens = nullptr; c->t.sens_all = nullptr;
-    c->t.band = nullptr; c->t.band_lo = nullptr;
-}
-
-void drop_flux(lmosem_ctx *c) {
-    if (!c->flux) return;
-    c->flux = false;
-    c->table_bytes -= c->flux_bytes;
-    free_flux(c->ft);
-    hipFree(c->fws);
-    c->fws = nullptr;
-    c->fws_floats = 0;
-    c->flux_bytes = 0;
-}
-
 // the flux stages' tables and workspace, beside tables of `others` bytes still
-// to come; without room for them (in memory or under the cap) the context runs
-// term by term
-lmosem_status ensure_flux(lmosem_ctx *c, int64_t others) {
-    int64_t fb = 0;
-    hipError_t e = build_flux(c->g, c->fg, c->flux_order, c->t, c->ft, c->lazy_table, c->st, fb);
-    if (e == hipSuccess) {
-        // one realisation and a chunk of angles
-        c->fws_floats = flux_ws_floats(c->g, c->fg, 1, flux_angles(c->g, c->fg, c->g.n_angles));
-        fb += (int64_t)(sizeof(float) * c->fws_floats);
-        e = over_cap(c, fb + others) ? hipErrorOutOfMemory : hipMalloc(&c->fws, sizeof(float) * c->fws_floats);
-    }
+// to come (`table` of them for a path table that is not filled yet); without
+// room for them (in memory or under the cap) the context runs term by term
+lmosem_status ensure_flux(lmosem_ctx *c, int64_t others, int64_t table) {
+    // one realisation and a chunk of angles
+    const size_t floats = flux_ws_floats(c->g, c->fg, 1, flux_angles(c->g, c->fg, c->g.n_angles));
+    int64_t fb = (int64_t)(sizeof(float) * floats);
+    const int64_t room = c->mem_cap > 0 ? c->mem_cap - c->table_bytes - c->set_bytes - (others - table) - fb : kNoLimit;
+    hipError_t e = build_flux(c->g, c->fg, c->flux_order, c->t, c->ft, c->lazy_table, room, c->st, fb);
+    if (e == hipSuccess) e = hipMalloc(&c->fws, sizeof(float) * floats);
     if (e != hipSuccess && e != hipErrorOutOfMemory) return dev_err(c, "flux tables", e);
     if (e == hipSuccess) {
         c->flux = true;
+        c->fws_floats = floats;
         c->flux_bytes = fb;
-        c->table_bytes += fb;
+        c->flux_counted = std::max<int64_t>(0, fb - table);
+        c->table_bytes += c->flux_counted;
     } else {
         (void)hipGetLastError();
         free_flux(c->ft);
         c->fws = nullptr;
-        c->fws_floats = 0;
     }
     return LMOSEM_OK;
 }
@@ -792,16 +889,17 @@ lmosem_status ensure_paths(lmosem_ctx *c) {
     if (c->paths_ready) return LMOSEM_OK;
     const Geo &g = c->g;
     // the exact path's tables have a known size: refused before any allocation
-    const int64_t predicted = (c->surrogate ? 0 : (int64_t)sizeof(float2) * g.n_angles * g.n_rpad * g.n_qpad) +
+    const int64_t table = c->surrogate ? 0 : (int64_t)sizeof(float2) * g.n_angles * g.n_rpad * g.n_qpad;
+    const int64_t predicted = table +
                               4 * (int64_t)g.n_angles * g.n_p + 4 * (int64_t)(g.n_subsets + 1) * g.n_qpad;
     if (over_cap(c, predicted)) return set_err(c, LMOSEM_ENOMEM, cap_msg(c, "the path tables", predicted));
     const auto t0 = std::chrono::steady_clock::now();
     std::string err;
     int64_t bytes = 0;
     // where every call on one sub-iteration runs through the flux stages, the
-    // path table's bytes are held (a table that the device has no room for is
-    // refused) but filled only for the first row cache or set that iterates
-    // term by term
+    // path table's bytes are counted (a table that the device has no room for is
+    // refused) but it is filled only for the first row cache or set that
+    // iterates term by term; the flux tables lie within them until then
     c->lazy_table = flux_always(c);
     if (c->lazy_table) {
         size_t room = 0, total = 0;
@@ -813,7 +911,7 @@ lmosem_status ensure_paths(lmosem_ctx *c) {
         if (e != hipSuccess) { free_paths(c); return alloc_err(c, "path tables", e); }
     }
     if (c->flux_fits) {
-        const lmosem_status fs = ensure_flux(c, predicted);
+        const lmosem_status fs = ensure_flux(c, predicted, c->lazy_table ? table : 0);
         if (fs != LMOSEM_OK) return fs;
     }
     if (c->lazy_table && c->flux) {
@@ -1486,12 +1584,17 @@ lmosem_status lmosem_cache_rows(lmosem_ctx *c, lmosem_evset *s, int32_t enable) 
     if (s->Hc) return LMOSEM_OK;
     const size_t n = (size_t)std::max<int64_t>(s->s.n, 1) * c->g.n_qpad;
     // with the cache, and for a flux set with what its rows' kernels work with
+    const int64_t more = (int64_t)(sizeof(float) * n) + fill_bytes(c) + (s->flux && !s->H ? row_bytes(c, s) : 0);
+    if (over_cap(c, more)) {
+        if (!c->flux || bytes_without_stages(c) + (int64_t)(sizeof(float) * n) > c->mem_cap)
+            return set_err(c, LMOSEM_ENOMEM, cap_msg(c, "the row cache", more));
+        const lmosem_status gs = give_up_stages(c);
+        if (gs != LMOSEM_OK) return gs;
+    }
     const bool bare = s->flux && !s->H;
-    const int64_t more = (int64_t)(sizeof(float) * n) + (bare ? row_bytes(c, s) : 0);
-    if (over_cap(c, more)) return set_err(c, LMOSEM_ENOMEM, cap_msg(c, "the row cache", more));
     hipError_t e = hipSuccess;
-    if (!c->t.T && !c->surrogate) {   // the rows' path table, held since the first list-mode call
-        e = build_path_table(c->g, c->t, c->st);
+    if (!c->t.T && !c->surrogate) {   // the rows' path table, counted since the first list-mode call
+        e = fill_table(c);
         if (e != hipSuccess) return alloc_err(c, "path table", e);
     }
     e = hipMalloc(&s->Hc, sizeof(float) * n);

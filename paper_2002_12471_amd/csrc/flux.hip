@@ -1468,9 +1468,10 @@ struct Slab {
 };
 
 template <class F>
-hipError_t place(void *&mem, int64_t &held, F &&arrays) {
+hipError_t place(void *&mem, int64_t &held, int64_t room, F &&arrays) {
     Slab s;
     arrays(s);
+    if (held + (int64_t)s.used > room) return hipErrorOutOfMemory;
     const hipError_t e = hipMalloc(&mem, s.used);
     if (e != hipSuccess) { mem = nullptr; return e; }
     held += (int64_t)s.used;
@@ -1482,7 +1483,7 @@ hipError_t place(void *&mem, int64_t &held, F &&arrays) {
 }  // namespace
 
 hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> &order, const Tables &t, FluxTables &ft,
-                      bool sens, hipStream_t st, int64_t &bytes) {
+                      bool sens, int64_t room, hipStream_t st, int64_t &bytes) {
     const FluxGeo &fg = fm;
     hipError_t e = hipSuccess;
     int *cnt = nullptr, *pos = nullptr;
@@ -1508,7 +1509,7 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     size_t tmp_bytes = 0;
     if (g.scatter && (e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, ft.beg, ft.beg, nbin + 1, st)) != hipSuccess)
         return done(e);
-    e = place(ft.mem[0], held, [&](Slab &s) {
+    e = place(ft.mem[0], held, room, [&](Slab &s) {
         s.add(ft.sup, g.n_p);
         s.add(ft.box, g.n_p);
         s.add(ft.mu_s, g.n_p);
@@ -1524,7 +1525,7 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
         s.add(ft.beg, (size_t)nbin + 1);
     });
     if (e == hipSuccess)
-        e = place(scratch[0], own, [&](Slab &s) {
+        e = place(scratch[0], own, kNoLimit, [&](Slab &s) {
             s.add(pos, g.n_p);
             if (!g.scatter) return;
             s.add(cnt, fg.N);
@@ -1554,13 +1555,13 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     int total = 0;
     if ((e = hipMemcpyAsync(&total, ft.beg + nbin, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return done(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return done(e);
-    e = place(ft.mem[1], held, [&](Slab &s) {
+    e = place(ft.mem[1], held, room, [&](Slab &s) {
         s.add(ft.rec_off, total);
         s.add(ft.rec_n, total);
         s.add(ft.rec_w, (size_t)total * kTap);
         s.add(ft.sym, (size_t)total * 64);
     });
-    if (e == hipSuccess) e = place(scratch[1], own, [&](Slab &s) { s.add(w64, (size_t)total * kTap); });
+    if (e == hipSuccess) e = place(scratch[1], own, kNoLimit, [&](Slab &s) { s.add(w64, (size_t)total * kTap); });
     if (e != hipSuccess) return done(e);
     hipLaunchKernelGGL(k_flux_pairs<1>, grid, dim3(64), 0, st, g, fg, fm.direction, ft.sup, t.p_pix, q_of_pix, t.mu, t.Bt, cnt, off,
                        cap, ft.beg, ft.rec_off, ft.rec_n, ft.rec_w, w64, ft.sym);

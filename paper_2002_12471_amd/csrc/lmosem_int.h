@@ -256,9 +256,11 @@ using FluxStage = std::function<hipError_t(int, const std::function<hipError_t()
 
 // false: outside the nodes' limits; order: the flux order
 bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order);
-// sens: also the sensitivities, into t.sens and t.sens_all
+// sens: also the sensitivities, into t.sens and t.sens_all; room: bytes that the
+// tables may take (hipErrorOutOfMemory before an allocation past it)
+constexpr int64_t kNoLimit = INT64_MAX;
 hipError_t build_flux(const Geo &g, const FluxModel &fg, const std::vector<int> &order, const Tables &t, FluxTables &ft,
-                      bool sens, hipStream_t st, int64_t &bytes);
+                      bool sens, int64_t room, hipStream_t st, int64_t &bytes);
 void free_flux(FluxTables &ft);
 int flux_angles(const Geo &g, const FluxGeo &fg, int n_list);
 size_t flux_ws_floats(const Geo &g, const FluxGeo &fg, int n_real, int n_slots);
