@@ -996,6 +996,13 @@ lmosem_status lmosem_create_emission(const lmosem_config *cfg, const float *mu_d
     g.n_p = (int)p_pix.size();
     g.n_q = n_q;
     g.n_qpad = (g.n_q + 63) / 64 * 64;
+    int x1 = 0, y1 = 0;
+    g.box_x = g.nx; g.box_y = g.ny;
+    for (int p : p_pix) {
+        g.box_x = std::min(g.box_x, p % g.nx); x1 = std::max(x1, p % g.nx + 1);
+        g.box_y = std::min(g.box_y, p / g.nx); y1 = std::max(y1, p / g.nx + 1);
+    }
+    g.box_w = x1 - g.box_x; g.box_h = y1 - g.box_y;
     // forward workgroups of 4 waves (fewer for an emission set of up to 192
     // pixels, whose single workgroup would otherwise carry idle waves)
     g.fwd_waves = std::min(4, g.n_qpad / 64);

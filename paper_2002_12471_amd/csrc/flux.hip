@@ -1398,13 +1398,8 @@ static bool fit_directions(const Geo &g, double slope, int N, FluxFit &best) {
 }
 
 bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order) {
-    int x0 = g.nx, x1 = -1, y0 = g.ny, y1 = -1;
-    for (int pix : p_pix) {
-        const int i = pix % g.nx, j = pix / g.nx;
-        x0 = std::min(x0, i); x1 = std::max(x1, i);
-        y0 = std::min(y0, j); y1 = std::max(y1, j);
-    }
-    fg.x0 = x0; fg.y0 = y0; fg.W = x1 - x0 + 1; fg.Hh = y1 - y0 + 1;
+    const int x0 = g.box_x, y0 = g.box_y;
+    fg.x0 = x0; fg.y0 = y0; fg.W = g.box_w; fg.Hh = g.box_h;
     fg.nb = fg.W * fg.Hh;
     // the flux order: strips of kStrip columns, row by row within a strip
     std::vector<int> at((size_t)fg.nb, -1);

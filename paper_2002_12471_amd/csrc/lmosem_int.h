@@ -25,6 +25,7 @@ struct Geo {
     int n_qpad;       // n_q rounded up to a multiple of 64 (row stride of H and the table)
     int n_rpad;       // rank rows per angle in the path table: n_p + kRankPad
     int fwd_waves;    // waves (64 emission pixels each) per forward-projection workgroup
+    int box_x, box_y, box_w, box_h;   // the support's bounding box, in pixels
     int n_angles, n_bins, n_subsets, scatter;
     double dx, bin_cm, half_len;
     double e0, kappa, sig_e, sig_u, win_lo, win_hi;
