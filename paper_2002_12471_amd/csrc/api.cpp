@@ -860,7 +860,8 @@ lmosem_status iterate_set(lmosem_ctx *c, lmosem_evset *s, int n_iters, double *l
 
 // the flux stages' tables and workspace, beside tables of `others` bytes still
 // to come (`table` of them for a path table that is not filled yet); without
-// room for them (in memory or under the cap) the context runs term by term
+// room for them (in memory or under the cap), or on a support too thin for them,
+// the context runs term by term
 lmosem_status ensure_flux(lmosem_ctx *c, int64_t others, int64_t table) {
     // one realisation and a chunk of angles
     const size_t floats = flux_ws_floats(c->g, c->fg, 1, flux_angles(c->g, c->fg, c->g.n_angles));
@@ -868,7 +869,7 @@ lmosem_status ensure_flux(lmosem_ctx *c, int64_t others, int64_t table) {
     const int64_t room = c->mem_cap > 0 ? c->mem_cap - c->table_bytes - c->set_bytes - (others - table) - fb : kNoLimit;
     hipError_t e = build_flux(c->g, c->fg, c->flux_order, c->t, c->ft, c->lazy_table, room, c->st, fb);
     if (e == hipSuccess) e = hipMalloc(&c->fws, sizeof(float) * floats);
-    if (e != hipSuccess && e != hipErrorOutOfMemory) return dev_err(c, "flux tables", e);
+    if (e != hipSuccess && e != hipErrorOutOfMemory && e != hipErrorNotSupported) return dev_err(c, "flux tables", e);
     if (e == hipSuccess) {
         c->flux = true;
         c->fws_floats = floats;

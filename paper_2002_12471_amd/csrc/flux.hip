@@ -1397,6 +1397,18 @@ static bool fit_directions(const Geo &g, double slope, int N, FluxFit &best) {
     return score[c] <= 1.0;
 }
 
+// Pixels spread thinly over a box share few flights: a pair record then serves
+// one or two lanes of its 64, and tables and pair stages cost more than the
+// sums that they replace.  Refused are supports with more than kThinBox offsets a
+// pixel (less than a 32nd of the box filled), before any work, and those whose
+// records have more than kThinRecords times as many rows as there are pairs
+// (solid shapes 1.2 to 2.5).  With the stages | without, us: 600 pixels spread over
+// 200x203 (43 times), new map 5378 | 1504, forward of 500 events 317 | 153, of 25k
+// 422 | 308; 2000 (25 times) 16411 | 9105, 856 | 405, 894 | 1050; but a ring of 724
+// (11 times) 232 | 259, 25k events 279 | 780, 40 disks of 17 (10 times) 218 | 283,
+// 275 | 811.
+constexpr int kThinBox = 128, kThinRecords = 16;
+
 bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order) {
     const int x0 = g.box_x, y0 = g.box_y;
     fg.x0 = x0; fg.y0 = y0; fg.W = g.box_w; fg.Hh = g.box_h;
@@ -1416,6 +1428,7 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
     fg.N = fg.K = 0;
     fg.h = 1.0;
     if (!g.scatter) return true;
+    if ((int64_t)(2 * fg.W - 1) * (2 * fg.Hh - 1) > (int64_t)kThinBox * g.n_p) return false;
     // the steepest logarithmic slope over directions and window energies
     auto end_energy = [&](double ph) { return g.e0 / (1.0 + g.kappa * (1.0 - cos(ph))); };
     double slope = 0.0;
@@ -1550,6 +1563,7 @@ hipError_t build_flux(const Geo &g, const FluxModel &fm, const std::vector<int> 
     int total = 0;
     if ((e = hipMemcpyAsync(&total, ft.beg + nbin, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return done(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return done(e);
+    if ((int64_t)total * 64 > (int64_t)kThinRecords * fg.np64 * fg.np64) return done(hipErrorNotSupported);
     e = place(ft.mem[1], held, room, [&](Slab &s) {
         s.add(ft.rec_off, total);
         s.add(ft.rec_n, total);

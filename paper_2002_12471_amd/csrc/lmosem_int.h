@@ -255,10 +255,11 @@ struct FluxRun {
 // wraps the launches of one stage (0 means, 1 backprojection, 2 update)
 using FluxStage = std::function<hipError_t(int, const std::function<hipError_t()> &)>;
 
-// false: outside the nodes' limits; order: the flux order
+// false: outside the nodes' limits, or a support too thin; order: the flux order
 bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order);
 // sens: also the sensitivities, into t.sens and t.sens_all; room: bytes that the
 // tables may take (hipErrorOutOfMemory before an allocation past it)
+// (hipErrorNotSupported: a support whose pixels share too few flights)
 constexpr int64_t kNoLimit = INT64_MAX;
 hipError_t build_flux(const Geo &g, const FluxModel &fg, const std::vector<int> &order, const Tables &t, FluxTables &ft,
                       bool sens, int64_t room, hipStream_t st, int64_t &bytes);
