@@ -1346,16 +1346,16 @@ static void fit_exponentials(double b, FluxFit &fit) {
 // steepest slope needs is only where the search starts: wide responses are
 // bound by the curvature of E'(phi) and of the Klein-Nishina factor (at 25 %
 // of 159 keV the slope alone asks for 48 nodes, which leave 1.4e-4 within three
-// widths; 144 are taken, 6e-8).  The exponents fill 0.6 to all of the slope's range: fewer
-// of it favour the near tails, which carry the sums.  Some 40 us a context.
+// widths; 144 are taken, 6e-8).  The exponents fill 0.6 or 0.8 of the slope's range:
+// the near tails carry the sums.
 constexpr double kDirectionErr[3] = {2e-7, 1e-6, 1e-5};   // up to 3 widths, 6 widths, anywhere
 constexpr double kLongest = 16.0;
 
 static bool fit_directions(const Geo &g, double slope, int N, FluxFit &best) {
-    constexpr int kDirs = 24, kShares = 3;
-    const double share[kShares] = {0.6, 0.8, 1.0};
+    constexpr int kDirs = 16, kShares = 2, kFar = 7;
+    const double share[kShares] = {0.6, 0.8};
     FluxFit fit[kShares];
-    double w[kShares][kTap], score[kShares] = {0.0, 0.0, 0.0};
+    double w[kShares][kTap], score[kShares] = {0.0, 0.0};
     for (int c = 0; c < kShares; ++c) {
         fit_exponentials(share[c] * slope * 2.0 * M_PI / N, fit[c]);
         for (int i = 0; i < kTap; ++i) {
@@ -1364,32 +1364,41 @@ static bool fit_directions(const Geo &g, double slope, int N, FluxFit &best) {
         }
     }
     const double c2 = 0.5 / (g.sig_e * g.sig_e);
-    struct Path { double ep, log_psi, rho; };
+    struct Path { double ep, psi, rho; };
     auto path = [&](double node) {
         const double c = cos(2.0 * M_PI * node / N), t = 1.0 + g.kappa * (1.0 - c), P = 1.0 / t;
-        return Path{g.e0 * P, log(P * P * (P + t - 1.0 + c * c)), kn_total(g.e0 * P) / g.sigma_kn_e0};
+        return Path{g.e0 * P, P * P * (P + t - 1.0 + c * c), kn_total(g.e0 * P) / g.sigma_kn_e0};
     };
     for (int d = 0; d < kDirs; ++d) {
         const int n = (int)lround(d * (0.5 * N) / (kDirs - 1) - 0.5);   // intervals from 0 to pi, both ends' included
         const Path at = path(n + 0.5);
-        Path x[kTap];
-        for (int i = 0; i < kTap; ++i) x[i] = path(n + i - 3);
-        const double far[7] = {0.0, -3.0 * g.sig_e, 3.0 * g.sig_e, -6.0 * g.sig_e, 6.0 * g.sig_e, g.win_lo - at.ep,
-                               g.win_hi - at.ep};
-        for (int k = 0; k < 7; ++k) {
+        // the nodes' values over the exact one: without the energy response, at
+        // either attenuation, and the energy response
+        double f[2][kTap], ep[kTap];
+        for (int i = 0; i < kTap; ++i) {
+            const Path x = path(n + i - 3);
+            ep[i] = x.ep;
+            f[0][i] = x.psi / at.psi;
+            f[1][i] = f[0][i] * exp((at.rho - x.rho) * kLongest);
+        }
+        const double far[kFar] = {0.0, -3.0 * g.sig_e, 3.0 * g.sig_e, -6.0 * g.sig_e, 6.0 * g.sig_e, g.win_lo - at.ep,
+                                  g.win_hi - at.ep};
+        for (int k = 0; k < kFar; ++k) {
             const double e = at.ep + far[k];
-            if (k < 5 && (e < g.win_lo || e > g.win_hi)) continue;
+            if (k < kFar - 2 && (e < g.win_lo || e > g.win_hi)) continue;
             const double widths = fabs(far[k]) / g.sig_e;
             const double allowed = kDirectionErr[widths < 3.001 ? 0 : widths < 6.001 ? 1 : 2];
-            for (double L : {0.0, kLongest}) {
-                double err[kShares] = {-1.0, -1.0, -1.0};
-                for (int i = 0; i < kTap; ++i) {
-                    const double r = exp(x[i].log_psi - at.log_psi - (x[i].rho - at.rho) * L -
-                                         c2 * ((e - x[i].ep) * (e - x[i].ep) - far[k] * far[k]));
-                    for (int c = 0; c < kShares; ++c) err[c] += w[c][i] * r;
+            double err[kShares][2];
+            for (int c = 0; c < kShares; ++c) err[c][0] = err[c][1] = -1.0;
+            for (int i = 0; i < kTap; ++i) {
+                const double r = exp(c2 * (far[k] * far[k] - (e - ep[i]) * (e - ep[i])));
+                for (int c = 0; c < kShares; ++c) {
+                    err[c][0] += w[c][i] * f[0][i] * r;
+                    err[c][1] += w[c][i] * f[1][i] * r;
                 }
-                for (int c = 0; c < kShares; ++c) score[c] = std::max(score[c], fabs(err[c]) / allowed);
             }
+            for (int c = 0; c < kShares; ++c)
+                score[c] = std::max(score[c], std::max(fabs(err[c][0]), fabs(err[c][1])) / allowed);
         }
     }
     const int c = (int)(std::min_element(score, score + kShares) - score);
@@ -1432,15 +1441,15 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
     // the steepest logarithmic slope over directions and window energies
     auto end_energy = [&](double ph) { return g.e0 / (1.0 + g.kappa * (1.0 - cos(ph))); };
     double slope = 0.0;
-    for (int i = 0; i < 2048; ++i) {
-        const double ph = M_PI * i / 2048, ep = end_energy(ph);
+    for (int i = 0; i < 128; ++i) {
+        const double ph = M_PI * i / 128, ep = end_energy(ph);
         const double far = std::max(fabs(g.win_lo - ep), fabs(g.win_hi - ep));
         slope = std::max(slope, far * ep * ep * g.kappa * sin(ph) / g.e0);
     }
     slope /= g.sig_e * g.sig_e;
-    // direction nodes: slope x spacing at most 0.79 and what the error asks for, a
+    // direction nodes: slope x spacing at most 0.70 and what the error asks for, a
     // multiple of 48 (whole matrix tiles, an even number of sectors)
-    const double n = std::max(2.0 * M_PI * slope / 0.79, 48.0);
+    const double n = std::max(2.0 * M_PI * slope / 0.70, 48.0);
     // energy nodes: largest exponent x spacing at most 0.70, eight nodes more
     // than intervals, a multiple of 16
     fg.e_mid = 0.5 * (g.e0 + end_energy(M_PI));
