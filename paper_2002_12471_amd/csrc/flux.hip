@@ -26,9 +26,11 @@
 // most 4.5e-7 in energy at any distance from its end energy; in direction
 // flux_geometry evaluates it for the response, the Klein-Nishina factor and the
 // attenuation at hand and takes as many nodes as keep it within 2e-7 up to
-// three widths of the energy response, 1e-6 up to six and 1e-5 anywhere in the
-// window, alternating in sign from path to path (FP32 leaves 1e-6 of one
-// path's code term by term).
+// three widths of the energy response, 2e-6 up to six and 6e-5 anywhere in the
+// window, alternating in sign from path to path (term by term FP32 leaves up to
+// 1e-6 of one path's code).  Against FP64, events whose mean is at least 1e-8 of
+// the largest have 1.2 to 2e-7 rms, uniform and compact sources alike, and 2e-7
+// term by term.
 //
 // Work per sub-iteration: n_p^2 pair visits (twice), angles x n_p x N x K
 // multiply-adds on the matrix cores (twice), and eight multiply-adds per
@@ -1340,20 +1342,20 @@ static void fit_exponentials(double b, FluxFit &fit) {
 
 // Whether eight nodes of N hold the direction interpolation of every path, and
 // with which exponents: one path's relative error half way between two nodes,
-// over the directions, without attenuation and with e^-16 of it, at end energies
+// over the directions, without attenuation and with e^-8 of it, at end energies
 // off by 0, 3 and 6 widths of the response and at the window's ends, against
 // what kDirectionErr allows for the distance.  The spacing that the response's
 // steepest slope needs is only where the search starts: wide responses are
 // bound by the curvature of E'(phi) and of the Klein-Nishina factor (at 25 %
 // of 159 keV the slope alone asks for 48 nodes, which leave 1.4e-4 within three
-// widths; 144 are taken, 6e-8).  The exponents fill 0.6 or 0.8 of the slope's range:
+// widths; 144 are taken, 6e-8).  The exponents fill 0.6 or 0.7 of the slope's range:
 // the near tails carry the sums.
-constexpr double kDirectionErr[3] = {2e-7, 1e-6, 1e-5};   // up to 3 widths, 6 widths, anywhere
-constexpr double kLongest = 16.0;
+constexpr double kDirectionErr[3] = {2e-7, 2e-6, 6e-5};   // up to 3 widths, 6 widths, anywhere
+constexpr double kLongest = 8.0;
 
 static bool fit_directions(const Geo &g, double slope, int N, FluxFit &best) {
     constexpr int kDirs = 16, kShares = 2, kFar = 7;
-    const double share[kShares] = {0.6, 0.8};
+    const double share[kShares] = {0.6, 0.7};
     FluxFit fit[kShares];
     double w[kShares][kTap], score[kShares] = {0.0, 0.0};
     for (int c = 0; c < kShares; ++c) {
@@ -1447,9 +1449,9 @@ bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, s
         slope = std::max(slope, far * ep * ep * g.kappa * sin(ph) / g.e0);
     }
     slope /= g.sig_e * g.sig_e;
-    // direction nodes: slope x spacing at most 0.70 and what the error asks for, a
+    // direction nodes: slope x spacing at most 0.79 and what the error asks for, a
     // multiple of 48 (whole matrix tiles, an even number of sectors)
-    const double n = std::max(2.0 * M_PI * slope / 0.70, 48.0);
+    const double n = std::max(2.0 * M_PI * slope / 0.79, 48.0);
     // energy nodes: largest exponent x spacing at most 0.70, eight nodes more
     // than intervals, a multiple of 16
     fg.e_mid = 0.5 * (g.e0 + end_energy(M_PI));

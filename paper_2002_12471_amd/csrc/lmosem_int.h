@@ -158,7 +158,7 @@ hipError_t forward_noalloc(const Geo &g, const Tables &t, const lmosem_events &e
                            int64_t &useful, struct FluxRun *flux, int64_t flux_from);
 
 // ---- sub-iterations through directional flux (flux.hip) ----
-constexpr int kFluxMaxN = 1152;            // direction nodes
+constexpr int kFluxMaxN = 960;             // direction nodes
 constexpr int kFluxMaxK = 192;             // energy nodes (48 KB of LDS in the adjoint)
 constexpr int64_t kFluxMaxG = 1 << 27;     // entries of the energy-response table (512 MB)
 

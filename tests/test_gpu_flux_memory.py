@@ -112,7 +112,10 @@ def test_stages_give_way_to_a_row_cache():
     cat = synth.workload_events(w, n_events=2 * J)
     parts = [L.events_to_device({k: v[i::2].copy() for k, v in cat.items() if k in ("angle", "u_bin", "energy")}, dev)
              for i in range(2)]
-    cache, rows = 4 * J * 1472, 4 * 8000 * 1472   # the cache, and one sub-iteration's rows (about)
+    # beside the cache: some 110 MB with the stages (one set's rows, and the flux
+    # tables beside a filled path table), 50 MB without (two sets' rows for their
+    # stages' workspaces)
+    cache, more = 4 * J * 1472, 82 << 20
     start = torch.as_tensor((mu > 0).astype(np.float32), device=dev).contiguous()
     try:
         ctx.sensitivity(-1)
@@ -121,7 +124,7 @@ def test_stages_give_way_to_a_row_cache():
             before = start.clone()
             assert _stages(L, ctx, sets[1], before) >= 16
             held = L.lmosem_memory_held(ctx.handle)
-            cap = held + cache + rows + (8 << 20)
+            cap = held + cache + more
             L.lmosem_set_memory_cap(ctx.handle, cap)
             L.lmosem_cache_rows(ctx.handle, sets[0], True)
             assert held < L.lmosem_memory_held(ctx.handle) <= cap

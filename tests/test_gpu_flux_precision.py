@@ -4,10 +4,10 @@ to a wide one whose nodes follow the curvature of the end energy, at 159 and
 511 keV; compact sources, emission sets, odd grids, unequal subset lists, empty
 angles and realisations.  Every test asserts that the stages ran.
 
-Tolerances, over events whose mean is at least 1e-8 of the largest: one path's
-direction error is at most 2e-7 within three widths of the response, 1e-6 within
-six and 1e-5 beyond, its energy error 4.5e-7, alternating from path to path, and
-FP32 leaves about 3e-7 rms: 6e-7 rms and 1e-5 at most for every set of events
+Tolerances, over events whose mean is at least 1e-8 of the largest (six widths
+off a path's end energy): one path's direction error is at most 2e-7 within three
+widths of the response and 2e-6 within six, its energy error 4.5e-7, alternating
+from path to path, and FP32 leaves about 3e-7 rms: 6e-7 rms and 1e-5 at most for every set of events
 (events whose only path ends lie within a hundredth of the position response's
 cut, where its own relative error grows to 5e-6, included).  Sums over events
 are held to 5e-6."""
@@ -22,7 +22,7 @@ import oracle as O  # noqa: E402
 import synth  # noqa: E402
 
 # energy, FWHM, window (keV): at 15 to 30 % of 159 keV and 25 % of 511 keV the
-# response's slope alone would take too few nodes; at 10 keV N = 816, K = 144
+# response's slope alone would take too few nodes; at 10 keV N = 720, K = 144
 RESPONSES = {
     "10%": (159.0, 15.9, (90.0, 175.0)),
     "15%": (159.0, 23.85, (90.0, 175.0)),
