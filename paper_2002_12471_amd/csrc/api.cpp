@@ -997,13 +997,12 @@ lmosem_status lmosem_create_emission(const lmosem_config *cfg, const float *mu_d
     g.n_p = (int)p_pix.size();
     g.n_q = n_q;
     g.n_qpad = (g.n_q + 63) / 64 * 64;
-    int x1 = 0, y1 = 0;
-    g.box_x = g.nx; g.box_y = g.ny;
+    int x0 = g.nx, x1 = 0, y0 = g.ny, y1 = 0;
     for (int p : p_pix) {
-        g.box_x = std::min(g.box_x, p % g.nx); x1 = std::max(x1, p % g.nx + 1);
-        g.box_y = std::min(g.box_y, p / g.nx); y1 = std::max(y1, p / g.nx + 1);
+        x0 = std::min(x0, p % g.nx); x1 = std::max(x1, p % g.nx + 1);
+        y0 = std::min(y0, p / g.nx); y1 = std::max(y1, p / g.nx + 1);
     }
-    g.box_w = x1 - g.box_x; g.box_h = y1 - g.box_y;
+    c->t.box = {x0, y0, x1 - x0, y1 - y0};
     // forward workgroups of 4 waves (fewer for an emission set of up to 192
     // pixels, whose single workgroup would otherwise carry idle waves)
     g.fwd_waves = std::min(4, g.n_qpad / 64);
@@ -1023,7 +1022,7 @@ lmosem_status lmosem_create_emission(const lmosem_config *cfg, const float *mu_d
     g.e_c = std::round(0.5 * (g.win_lo + g.win_hi) * 64.0) / 64.0;
     g.c2 = 1.0 / (2.0 * g.sig_e * g.sig_e * log(2.0));
     g.acq_time = cfg->acq_time;
-    c->flux_fits = !c->surrogate && flux_geometry(g, p_pix, c->fg, c->flux_order);
+    c->flux_fits = !c->surrogate && flux_geometry(g, c->t.box, p_pix, c->fg, c->flux_order);
 
     std::vector<double> cs(2 * g.n_angles);
     for (int a = 0; a < g.n_angles; ++a) {

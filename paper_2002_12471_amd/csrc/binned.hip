@@ -76,11 +76,12 @@ __global__ __launch_bounds__(256) void k_binned_rows(Geo g, const int *__restric
 // factor, attenuation ratio, mass of the energy response over each energy bin)
 // depends on the pixel offset q -> s alone: it is evaluated once per (angle,
 // offset), four times the area of the support's bounding box of them, instead of
-// once per path, n_p n_q of them (whichever are fewer: offset_pairs).  A path then costs one exponential and 24 bytes from the L2, which
-// bound it: 6.06 ms -> 1.04 ms for 120 angles x 1436 x 1436 paths.  What depends
+// once per path, n_p n_q of them (whichever are fewer: offset_pairs).  A path then
+// costs one exponential and 24 bytes from the L2, which bound it: 6.06 ms ->
+// 1.04 ms for 120 angles x 1436 x 1436 paths.  What depends
 // on the rank only comes precomputed as well (k_rank_terms), read as scalars.
 template <int W>
-__global__ void k_rank_terms(Geo g, const int *__restrict__ p_pix, const double *__restrict__ Ld,
+__global__ void k_rank_terms(Geo g, Box box, const int *__restrict__ p_pix, const double *__restrict__ Ld,
                              const int *__restrict__ s_sorted, const double *__restrict__ us_sorted, int n_pos,
                              int *__restrict__ rb0, int *__restrict__ roff, double *__restrict__ rL,
                              double *__restrict__ rpm) {
@@ -92,7 +93,7 @@ __global__ void k_rank_terms(Geo g, const int *__restrict__ p_pix, const double 
     const int b0 = min(max((int)floor((us - 3.0 * g.sig_u + g.half_len) / width), 0), n_pos - 1);
     rb0[o] = b0;
     const int s = s_sorted[o];
-    roff[o] = offset_to(g, p_pix, s);
+    roff[o] = offset_to(g, box, p_pix, s);
     rL[o] = Ld[(size_t)a * g.n_p + s];
     for (int i = 0; i < W; ++i) {
         const int b = b0 + i;
@@ -104,14 +105,14 @@ __global__ void k_rank_terms(Geo g, const int *__restrict__ p_pix, const double 
 // tab[angle - a0][1 + n_e][entry]: attenuation ratio, and Klein-Nishina factor
 // times the energy-bin masses of a flight along the entry's offset (0 for no
 // offset: the primary path, which the rows weigh by themselves)
-__global__ __launch_bounds__(256) void k_direction_terms(Geo g, const int *__restrict__ p_pix,
+__global__ __launch_bounds__(256) void k_direction_terms(Geo g, Box box, const int *__restrict__ p_pix,
                                                          const double *__restrict__ cs, int a0,
                                                          const double *__restrict__ edges, int n_e,
                                                          double *__restrict__ tab) {
-    const int n = n_offsets(g);
+    const int n = n_offsets(g, box);
     const int i = blockIdx.x * blockDim.x + threadIdx.x, a = a0 + blockIdx.y;
     if (i >= n) return;
-    const int2 d = offset_at(g, p_pix, i);
+    const int2 d = offset_at(g, box, p_pix, i);
     double *out = tab + (size_t)blockIdx.y * (1 + n_e) * n + i;
     if (d.x == 0 && d.y == 0) {
         for (int k = 0; k < 1 + n_e; ++k) out[(size_t)k * n] = 0.0;
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(256) void k_direction_terms(Geo g, const int *__res
 // direction terms then stay in its L2.  The loads of
 // the next kAhead ranks are on their way while the current ones are used.
 template <int W, int KMAX>
-__global__ __launch_bounds__(64) void k_binned_rows_all(Geo g, const int *__restrict__ p_pix,
+__global__ __launch_bounds__(64) void k_binned_rows_all(Geo g, Box box, const int *__restrict__ p_pix,
                                                         const double *__restrict__ Ld, const double *__restrict__ Bt,
                                                         const int *__restrict__ s_sorted, const int *__restrict__ rb0,
                                                         const int *__restrict__ roff, const double *__restrict__ rL,
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(64) void k_binned_rows_all(Geo g, const int *__rest
     const int q = qb * 64 + threadIdx.x;   // n_qpad is a multiple of 64
     const bool active = q < g.n_q;
     const int qc = min(q, g.n_q - 1);
-    const int n_off = n_offsets(g), from = offset_from(g, p_pix, qc);
+    const int n_off = n_offsets(g, box), from = offset_from(g, box, p_pix, qc);
     const double *ta = g.scatter ? tab + (size_t)al * (1 + n_e) * n_off : nullptr;
     // the primary path
     const double w0 = active ? exp(-Ld[(size_t)a * g.n_p + qc]) : 0.0;
@@ -274,14 +275,14 @@ template <int W, int KMAX>
 hipError_t launch_rows_all(const Geo &g, const Tables &t, int n_pos, const double *edges_dev, int n_e,
                            const int *angle_row0_dev, const RowScratch &w, float *H, hipStream_t st) {
     hipLaunchKernelGGL(k_rank_terms<W>, dim3((unsigned)((g.n_p + 255) / 256), (unsigned)g.n_angles), dim3(256), 0, st,
-                       g, t.p_pix, t.Ld, t.s_sorted, t.us_sorted, n_pos, w.rb0, w.roff, w.rL, w.rpm);
-    const int n_off = n_offsets(g);
+                       g, t.box, t.p_pix, t.Ld, t.s_sorted, t.us_sorted, n_pos, w.rb0, w.roff, w.rL, w.rpm);
+    const int n_off = n_offsets(g, t.box);
     for (int a0 = 0; a0 < g.n_angles; a0 += w.n_a) {
         const int n_a = std::min(w.n_a, g.n_angles - a0);
         if (g.scatter)
             hipLaunchKernelGGL(k_direction_terms, dim3((unsigned)((n_off + 255) / 256), (unsigned)n_a), dim3(256), 0, st, g,
-                               t.p_pix, t.cs, a0, edges_dev, n_e, w.tab);
-        hipLaunchKernelGGL((k_binned_rows_all<W, KMAX>), dim3((unsigned)(g.n_qpad / 64 * n_a)), dim3(64), 0, st, g, t.p_pix,
+                               t.box, t.p_pix, t.cs, a0, edges_dev, n_e, w.tab);
+        hipLaunchKernelGGL((k_binned_rows_all<W, KMAX>), dim3((unsigned)(g.n_qpad / 64 * n_a)), dim3(64), 0, st, g, t.box, t.p_pix,
                            t.Ld, t.Bt, t.s_sorted, w.rb0, w.roff, w.rL, w.rpm, n_pos, edges_dev, n_e, w.tab, a0, n_a,
                            angle_row0_dev, H);
     }
@@ -304,7 +305,7 @@ hipError_t launch_binned_rows_all(const Geo &g, const Tables &t, int n_pos, cons
     const size_t na_np = (size_t)g.n_angles * g.n_p;
     // direction terms of as many angles as 64 MB hold (all of them for supports
     // within 128 x 128: the chip is full with a few tens of angles)
-    const size_t per = (size_t)n_offsets(g) * (1 + n_e) * sizeof(double);
+    const size_t per = (size_t)n_offsets(g, t.box) * (1 + n_e) * sizeof(double);
     w.n_a = g.scatter ? (int)std::min<size_t>(g.n_angles, std::max<size_t>(1, (size_t(64) << 20) / per)) : g.n_angles;
     hipError_t e = dev_take(arena, &w.rb0, sizeof(int) * na_np);
     if (e == hipSuccess) e = dev_take(arena, &w.roff, sizeof(int) * na_np);

@@ -1420,9 +1420,9 @@ static bool fit_directions(const Geo &g, double slope, int N, FluxFit &best) {
 // 275 | 811.
 constexpr int kThinBox = 128, kThinRecords = 16;
 
-bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order) {
-    const int x0 = g.box_x, y0 = g.box_y;
-    fg.x0 = x0; fg.y0 = y0; fg.W = g.box_w; fg.Hh = g.box_h;
+bool flux_geometry(const Geo &g, const Box &box, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order) {
+    const int x0 = box.x, y0 = box.y;
+    fg.x0 = x0; fg.y0 = y0; fg.W = box.w; fg.Hh = box.h;
     fg.nb = fg.W * fg.Hh;
     // the flux order: strips of kStrip columns, row by row within a strip
     std::vector<int> at((size_t)fg.nb, -1);

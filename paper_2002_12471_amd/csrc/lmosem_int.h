@@ -25,7 +25,6 @@ struct Geo {
     int n_qpad;       // n_q rounded up to a multiple of 64 (row stride of H and the table)
     int n_rpad;       // rank rows per angle in the path table: n_p + kRankPad
     int fwd_waves;    // waves (64 emission pixels each) per forward-projection workgroup
-    int box_x, box_y, box_w, box_h;   // the support's bounding box, in pixels
     int n_angles, n_bins, n_subsets, scatter;
     double dx, bin_cm, half_len;
     double e0, kappa, sig_e, sig_u, win_lo, win_hi;
@@ -56,8 +55,15 @@ struct Chunk {
     int pad;
 };
 
+// The support's bounding box, in pixels (apart from Geo, which every kernel takes:
+// 16 bytes more of it cost the short ones 0.1 us a launch).
+struct Box {
+    int x, y, w, h;
+};
+
 // Device tables of one context.
 struct Tables {
+    Box box{};
     int *p_pix = nullptr;        // [n_p] support pixel index
     float *mu = nullptr;         // [n_pix]
     double *cs = nullptr;        // [n_angles][2] cos, sin of theta_a
@@ -256,7 +262,7 @@ struct FluxRun {
 using FluxStage = std::function<hipError_t(int, const std::function<hipError_t()> &)>;
 
 // false: outside the nodes' limits, or a support too thin; order: the flux order
-bool flux_geometry(const Geo &g, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order);
+bool flux_geometry(const Geo &g, const Box &box, const std::vector<int> &p_pix, FluxModel &fg, std::vector<int> &order);
 // sens: also the sensitivities, into t.sens and t.sens_all; room: bytes that the
 // tables may take (hipErrorOutOfMemory before an allocation past it)
 // (hipErrorNotSupported: a support whose pixels share too few flights)

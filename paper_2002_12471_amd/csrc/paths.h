@@ -55,28 +55,28 @@ __device__ inline Flight flight(const Geo &g, int di, int dj, double nx, double 
 // q -> s that the support's bounding box allows, or, where the support has fewer
 // pairs than its box has offsets (a few pixels far apart), an entry per pair
 // (s, q): never more flights than paths.  Entry offset_from(q) + offset_to(s).
-__host__ __device__ inline bool offset_pairs(const Geo &g) {
-    return (int64_t)g.n_p * g.n_q < (int64_t)(2 * g.box_w - 1) * (2 * g.box_h - 1);
+__host__ __device__ inline bool offset_pairs(const Geo &g, const Box &b) {
+    return (int64_t)g.n_p * g.n_q < (int64_t)(2 * b.w - 1) * (2 * b.h - 1);
 }
-__host__ __device__ inline int n_offsets(const Geo &g) {
-    return offset_pairs(g) ? g.n_p * g.n_q : (2 * g.box_w - 1) * (2 * g.box_h - 1);
+__host__ __device__ inline int n_offsets(const Geo &g, const Box &b) {
+    return offset_pairs(g, b) ? g.n_p * g.n_q : (2 * b.w - 1) * (2 * b.h - 1);
 }
-__device__ inline int offset_from(const Geo &g, const int *__restrict__ p_pix, int q) {
-    const int i = p_pix[q] % g.nx - g.box_x, j = p_pix[q] / g.nx - g.box_y;
-    return offset_pairs(g) ? q : (g.box_h - 1 - j) * (2 * g.box_w - 1) + g.box_w - 1 - i;
+__device__ inline int offset_from(const Geo &g, const Box &b, const int *__restrict__ p_pix, int q) {
+    const int i = p_pix[q] % g.nx - b.x, j = p_pix[q] / g.nx - b.y;
+    return offset_pairs(g, b) ? q : (b.h - 1 - j) * (2 * b.w - 1) + b.w - 1 - i;
 }
-__device__ inline int offset_to(const Geo &g, const int *__restrict__ p_pix, int s) {
-    const int i = p_pix[s] % g.nx - g.box_x, j = p_pix[s] / g.nx - g.box_y;
-    return offset_pairs(g) ? s * g.n_q : j * (2 * g.box_w - 1) + i;
+__device__ inline int offset_to(const Geo &g, const Box &b, const int *__restrict__ p_pix, int s) {
+    const int i = p_pix[s] % g.nx - b.x, j = p_pix[s] / g.nx - b.y;
+    return offset_pairs(g, b) ? s * g.n_q : j * (2 * b.w - 1) + i;
 }
 // the offset (di, dj) of an entry
-__device__ inline int2 offset_at(const Geo &g, const int *__restrict__ p_pix, int entry) {
-    if (offset_pairs(g)) {
+__device__ inline int2 offset_at(const Geo &g, const Box &b, const int *__restrict__ p_pix, int entry) {
+    if (offset_pairs(g, b)) {
         const int ps = p_pix[entry / g.n_q], pq = p_pix[entry % g.n_q];
         return make_int2(ps % g.nx - pq % g.nx, ps / g.nx - pq / g.nx);
     }
-    const int w = 2 * g.box_w - 1;
-    return make_int2(entry % w - (g.box_w - 1), entry / w - (g.box_h - 1));
+    const int w = 2 * b.w - 1;
+    return make_int2(entry % w - (b.w - 1), entry / w - (b.h - 1));
 }
 
 // Weight w and end energy E' of the path from emission pixel q through path

@@ -329,12 +329,12 @@ static int path_part(const Geo &g) {
 // alone (an entry per offset_from + offset_to): the code's alpha
 // without the scatter point's factor and attenuation, and the attenuation ratio
 // in bits; beta.
-__global__ __launch_bounds__(256) void k_table_terms(Geo g, const int *__restrict__ p_pix, const double *__restrict__ cs,
+__global__ __launch_bounds__(256) void k_table_terms(Geo g, Box box, const int *__restrict__ p_pix, const double *__restrict__ cs,
                                                      int a0, double2 *__restrict__ tab, float *__restrict__ beta) {
-    const int n = n_offsets(g);
+    const int n = n_offsets(g, box);
     const int i = blockIdx.x * blockDim.x + threadIdx.x, a = a0 + blockIdx.y;
     if (i >= n) return;
-    const int2 d = offset_at(g, p_pix, i);
+    const int2 d = offset_at(g, box, p_pix, i);
     double2 t = make_double2(0.0, 0.0);
     float b = 0.0f;
     if (d.x != 0 || d.y != 0) {
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256) void k_log2(const double *__restrict__ x, size
 // 8 bytes written bound it: 1436 pixels, 120 angles 4.4 -> 0.83 ms with the
 // terms (2.5 TB/s), 5736 pixels 56 -> 18.9 ms (31.7 GB), 564 pixels 0.61 -> 0.12.  An XCD takes a run of
 // angles, whose terms then stay in its L2.
-__global__ __launch_bounds__(64) void k_path_table_terms(Geo g, const int *__restrict__ p_pix, const double *__restrict__ L,
+__global__ __launch_bounds__(64) void k_path_table_terms(Geo g, Box box, const int *__restrict__ p_pix, const double *__restrict__ L,
                                                          const double *__restrict__ lB, const int *__restrict__ s_sorted,
                                                          const double2 *__restrict__ tab, const float *__restrict__ beta,
                                                          int a0, int per, int n_parts, float2 *__restrict__ T) {
@@ -371,12 +371,12 @@ __global__ __launch_bounds__(64) void k_path_table_terms(Geo g, const int *__res
         for (int r = g.n_p; r < g.n_rpad; ++r) Ta[(size_t)r * g.n_qpad] = none;
     const bool on = q < g.n_q;
     const int qc = min(q, g.n_q - 1);
-    const size_t from = (size_t)al * n_offsets(g) + offset_from(g, p_pix, qc);
+    const size_t from = (size_t)al * n_offsets(g, box) + offset_from(g, box, p_pix, qc);
     const float2 own = path_code(g, PathW{exp(-L[(size_t)a * g.n_p + qc]), g.e0}, -log2(sqrt(2.0 * M_PI) * g.sig_e));
 #pragma unroll 4
     for (int r = r0; r < r1; ++r) {
         const int s = s_sorted[(size_t)a * g.n_p + r];
-        const size_t i = from + offset_to(g, p_pix, s);
+        const size_t i = from + offset_to(g, box, p_pix, s);
         const double lb = lB[(size_t)s * g.n_p + qc];
         const double2 t = tab[i];
         float2 code = make_float2((float)(lb + (t.x - t.y * L[(size_t)a * g.n_p + s])), beta[i]);
@@ -393,7 +393,7 @@ hipError_t build_path_table(const Geo &g, Tables &t, hipStream_t st) {
     if (e != hipSuccess) { t.T = nullptr; return e; }
     // terms of as many angles as 64 MB hold; without room for them beside the
     // table every path's code is evaluated by itself
-    const size_t n_off = n_offsets(g), per_a = n_off * (sizeof(double2) + sizeof(float));
+    const size_t n_off = n_offsets(g, t.box), per_a = n_off * (sizeof(double2) + sizeof(float));
     const int n_a = (int)std::min<size_t>(g.n_angles, std::max<size_t>(1, (size_t(64) << 20) / per_a));
     const size_t n_b = (size_t)g.n_p * g.n_p;
     char *mem = nullptr;
@@ -405,10 +405,10 @@ hipError_t build_path_table(const Geo &g, Tables &t, hipStream_t st) {
         e = hipGetLastError();
         for (int a0 = 0; a0 < g.n_angles && e == hipSuccess; a0 += n_a) {
             const int n = std::min(n_a, g.n_angles - a0);
-            hipLaunchKernelGGL(k_table_terms, dim3((unsigned)((n_off + 255) / 256), n), dim3(256), 0, st, g, t.p_pix,
-                               t.cs, a0, tab, beta);
+            hipLaunchKernelGGL(k_table_terms, dim3((unsigned)((n_off + 255) / 256), n), dim3(256), 0, st, g, t.box,
+                               t.p_pix, t.cs, a0, tab, beta);
             hipLaunchKernelGGL(k_path_table_terms, dim3((unsigned)(g.n_qpad / 64 * n_parts * n)), dim3(64), 0, st, g,
-                               t.p_pix, t.Ld, lB, t.s_sorted, tab, beta, a0, per, n_parts, t.T);
+                               t.box, t.p_pix, t.Ld, lB, t.s_sorted, tab, beta, a0, per, n_parts, t.T);
             e = hipGetLastError();
         }
     } else {
