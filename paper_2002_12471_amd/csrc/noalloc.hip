@@ -2,13 +2,14 @@
 //
 // Every buffer of the call -- the estimate on the emission set, the sorted
 // events, the tile plan, the event means and, in turn, the sort's keys and
-// temporary storage and then the system rows of one chunk of tiles -- is
-// carved from one file-scope device array.  The array lives as long as the
-// process on every GPU the library runs on; each call overwrites it (the
-// counters that must start at zero are cleared), so calls that overlap on
-// one GPU race, whatever their contexts.  The forward projection runs as in
-// lmosem_forward, chunk by chunk of whole tiles, so each event's mean is the
-// same sum in the same order.
+// temporary storage and then the system rows of one chunk of tiles, or the
+// flux stages' event records of one run of blocks -- is carved from one
+// file-scope device array; the stages' workspace is the context's.  The array
+// lives as long as the process on every GPU the library runs on; each call
+// overwrites it (the counters that must start at zero are cleared), so calls
+// that overlap on one GPU race, whatever their contexts.  The forward projection takes the
+// route that lmosem_forward takes, chunk by chunk of whole tiles or run by run
+// of whole blocks, so each event's mean is the same sum in the same order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

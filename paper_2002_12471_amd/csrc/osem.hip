@@ -314,8 +314,8 @@ __global__ __launch_bounds__(256, EV == 8 ? 8 : 1) void k_forward(Geo g, const T
 // As k_forward for emission sets that one workgroup covers (g.fwd_waves waves
 // hold a tile's whole rows): the event means are complete in the workgroup, so
 // the rows are weighted where they stand, in registers, and each tile's
-// backprojection is written instead of them (a sixth of the bytes with 8 events a
-// tile, and no second kernel that reads rows).  The small sets that run this way
+// backprojection is written instead of them (an eighth of the bytes with 8 events
+// a tile, and no second kernel that reads rows).  The small sets that run this way
 // are bound by the chain of a tile's loads and by launches: 5k events on 156
 // pixels 22.1 -> 17.9 us an iteration (forward, backprojection with means and
 // update before), 50k on 356 pixels in 8 subsets 295 -> 245.  Up to kFuseMax
